@@ -163,6 +163,9 @@ int launch_attn_bwd(const AttnArgs& a, hipStream_t stream);
 int launch_attn_bwd_generic(const AttnArgs& a, hipStream_t stream);
 bool attn_mfma_supported(const AttnArgs& a);
 int launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t stream);
+int attn_bwd_mfma_d64(const AttnArgs& a, hipStream_t stream);
+int attn_fwd_mfma_d64(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, int max_seqlen,
+                      const int* cu_seqlens, const int* prefix, int seq_begin, int Hq, int Hkv, hipStream_t stream);
 static constexpr int kMaxPrefixSeqs = 4096;  // sequences per batch when prefixes are shared
 double attn_pairs(int n_seqs, const int* cu_host, const int* prefix_host);
 // forward: writes O [T,Hq*D] and LSE [T,Hq] for the query rows of sequences seq_begin .. n_seqs-1 (keys and
