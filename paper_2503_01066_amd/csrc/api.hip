@@ -640,13 +640,8 @@ double attn_pairs(int n_seqs, const int* cu_host, const int* prefix_host) {
 
 int launch_attn_bwd(const AttnArgs& a, hipStream_t stream) {
     TraceScope ts(kTraceAttnBwd, 10.0 * a.D * a.Hq * attn_pairs(a.n_seqs, a.cu_seqlens_host, a.prefix_host), 0.0, stream);
-    if (attn_mfma_supported(a)) return launch_attn_bwd_mfma(a, stream);  // delta and RoPE backward fused
-    ALCH_TRY(launch_attn_delta(a.dtype, a.dO, a.O, a.delta, a.T, a.Hq, a.D, stream));
-    ALCH_TRY(launch_attn_bwd_generic(a, stream));
-    if (a.rope_base > 0.f)
-        ALCH_TRY(launch_rope(a.dtype, a.dQ, a.ld_dqkv, a.T, a.Hq + a.Hkv, a.D, a.positions, a.cu_seqlens, a.n_seqs,
-                             a.rope_base, -1.f, stream));
-    return ALCH_OK;
+    // both form delta and apply the RoPE backward to dQ and dK themselves
+    return attn_mfma_supported(a) ? launch_attn_bwd_mfma(a, stream) : launch_attn_bwd_generic(a, stream);
 }
 
 }  // namespace alch

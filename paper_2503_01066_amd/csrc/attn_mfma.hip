@@ -23,7 +23,7 @@ int launch_attn_fwd(alch_dtype dt, const void* Q, const void* K, const void* V, 
         return D == 128 ? attn_fwd_mfma<128>(Q, K, V, O, LSE, n_seqs, max_seqlen, cu_seqlens, prefix, seq_begin, Hq, Hkv, stream)
                         : attn_fwd_mfma_d64(Q, K, V, O, LSE, n_seqs, max_seqlen, cu_seqlens, prefix, seq_begin, Hq, Hkv, stream);
     }
-    return launch_attn_fwd_generic(dt, Q, K, V, O, LSE, T, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream);
+    return launch_attn_fwd_generic(dt, Q, K, V, O, LSE, T, n_seqs, max_seqlen, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream);
 }
 
 }  // namespace alch

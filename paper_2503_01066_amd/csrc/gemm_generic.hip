@@ -1,18 +1,31 @@
-// Plain tiled GEMM in fp32 arithmetic for the fp32 storage type and for bf16 problems whose
-// shapes or alignments the matrix-core kernel does not take.  Same contract as the
-// matrix-core kernel (segments, split outputs, accumulate); correctness first.
+// GEMM in fp32 arithmetic for the fp32 storage type and for bf16 problems whose shapes or alignments the bf16
+// matrix-core kernel does not take.  Same contract as that kernel (operand pairs, split outputs, accumulate).
+//
+// The multiply-adds run on the fp32 form of the matrix instruction (v_mfma_f32_32x32x2_f32: fp32 operands and
+// accumulation, 157 TFLOP/s on this chip, twice the unpacked vector rate), in two kernels chosen by the number of
+// output tiles:
+//   k_gemm_f32_slices  one 32x32 tile per work-group of 4, 8 or 16 wavefronts that each take a slice of the
+//                      contraction, operands straight from memory into registers, the slices' sums folded through LDS in
+//                      a fixed order.  A problem of a few hundred rows has few tiles and a long serial contraction: what
+//                      bounds it is the latency of that chain, so it is cut (256 x 256 x 2048: 445 -> 13 us).
+//   k_gemm_f32_tiled   128x128 tiles staged through LDS, for problems with enough of them to fill the compute units
+//                      (4096 x 4096 x 2048: 95 - 103 TFLOP/s; vector multiply-adds on 64x64 tiles: 50).
 #include <algorithm>
 #include "kernels.h"
-#include <hip/hip_bf16.h>
 
 namespace alch {
 
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+
 struct GenericGemmParams {
-    int M, N, n_seg, n_out, accumulate, a_kmajor, b_kmajor;
+    int M, N, n_seg, n_out, accumulate, a_kmajor, b_kmajor, tiles_n;
     const void* A[kMaxGemmSegs];
     const void* B[kMaxGemmSegs];
     int K[kMaxGemmSegs];
     long long lda[kMaxGemmSegs], ldb[kMaxGemmSegs];
+    int a_vec[kMaxGemmSegs], b_vec[kMaxGemmSegs];  // base and stride allow loads of four elements
     void* C[3];
     int m_begin[3];
     long long ldc[3];
@@ -21,88 +34,235 @@ struct GenericGemmParams {
     const void* U;
     long long ldgu;
     void* act_out;
-    const uint8_t* row_mask;
 };
 
 template <typename T> __device__ __forceinline__ float ld(const T* p) { return (float)*p; }
 template <typename T> __device__ __forceinline__ void st(T* p, float v) { *p = (T)v; }
+__device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 ld4(const __bf16* p) {
+    const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
+    return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
 
+// One element of the product -> the output.
 template <typename T>
-__global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmParams p) {
-    constexpr int TM = 64, TN = 64, TK = 16;
-    __shared__ float As[TK][TM + 1];
-    __shared__ float Bs[TK][TN + 1];
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4] = {};
+__device__ __forceinline__ void store_element(const GenericGemmParams& p, int m, int n, float acc) {
+    if (m >= p.M || n >= p.N) return;
+    int oseg = 0;
+    for (int s = 1; s < p.n_out; ++s)
+        if (m >= p.m_begin[s]) oseg = s;
+    T* C = static_cast<T*>(p.C[oseg]);
+    const long long ldc = p.ldc[oseg];
+    if (p.epilogue == kEpiSwigluBwd) {
+        const float g = ld(static_cast<const T*>(p.G) + (long long)m * p.ldgu + n);
+        const float u = ld(static_cast<const T*>(p.U) + (long long)m * p.ldgu + n);
+        const float d = (float)(T)acc;
+        const float sg = 1.f / (1.f + expf(-g));
+        st(C + (long long)m * ldc + n, d * u * sg * (1.f + g * (1.f - sg)));
+        st(C + (long long)m * ldc + p.N + n, d * g * sg);
+        if (p.act_out) st(static_cast<T*>(p.act_out) + (long long)m * p.N + n, g * sg * u);
+    } else {
+        T* dst = C + (long long)(m - p.m_begin[oseg]) * ldc + n;
+        st(dst, p.accumulate ? acc + ld(dst) : acc);
+    }
+}
+
+// Elements (idx, k .. k+3) of an operand, zero from k_end on.  idx lies inside the operand.  whole: k + 4 <= k_end
+// for every lane (uniform, so that the usual case has no per-element branches).
+template <typename T>
+__device__ __forceinline__ f32x4 operand4(const T* base, long long ld_, bool kmajor, bool vec, bool whole, int idx, int k, int k_end) {
+    const T* q = kmajor ? base + (long long)idx * ld_ + k : base + (long long)k * ld_ + idx;
+    const long long step = kmajor ? 1 : ld_;
+    if (whole) {
+        if (kmajor && vec) return ld4(q);
+        return f32x4{ld(q), ld(q + step), ld(q + 2 * step), ld(q + 3 * step)};
+    }
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (k + i < k_end) v[i] = ld(q + i * step);
+    return v;
+}
+
+// kTile 32: v_mfma_f32_32x32x2_f32, kTile 16: v_mfma_f32_16x16x4_f32.  A lane gives one (row, k) element of A and one
+// (k, column) element of B, k = lane / kTile.  Which k meet in an instruction is free as long as A and B agree: with
+// kParts = 64 / kTile, part h of the wavefront holds k0 + 4h .. k0 + 4h + 3 of a chunk of 4 kParts, and instruction i
+// multiplies k0 + i, k0 + 4 + i, ...
+template <int kTile> struct F32Tile;
+template <> struct F32Tile<32> {
+    typedef f32x16 Acc;
+    static __device__ __forceinline__ Acc mac(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ int row(int e, int lane) { return 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); }
+};
+template <> struct F32Tile<16> {
+    typedef f32x4 Acc;
+    static __device__ __forceinline__ Acc mac(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    static __device__ __forceinline__ int row(int e, int lane) { return 4 * (lane >> 4) + e; }
+};
+
+template <typename T, int kTile, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_slices(GenericGemmParams p) {
+    constexpr int kElems = kTile * kTile / 64, kChunk = 256 / kTile;
+    __shared__ float red[kWaves][kElems][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = lane / kTile;
+    const int m0 = (int)(blockIdx.x / p.tiles_n) * kTile, n0 = (int)(blockIdx.x % p.tiles_n) * kTile;
+    const int m = min(m0 + lane % kTile, p.M - 1), n = min(n0 + lane % kTile, p.N - 1);
+    const bool ak = p.a_kmajor, bk = p.b_kmajor;
+    typename F32Tile<kTile>::Acc acc;
+#pragma unroll
+    for (int e = 0; e < kElems; ++e) acc[e] = 0.f;
+    constexpr int kBatch = 4;  // chunks requested together; the next batch is on its way during the current one
     for (int s = 0; s < p.n_seg; ++s) {
         const T* A = static_cast<const T*>(p.A[s]);
         const T* B = static_cast<const T*>(p.B[s]);
         const long long lda = p.lda[s], ldb = p.ldb[s];
-        const int K = p.K[s];
-        for (int k0 = 0; k0 < K; k0 += TK) {
-            for (int e = threadIdx.x; e < TM * TK; e += 256) {
-                int mm, kk;
-                if (p.a_kmajor) { mm = e / TK; kk = e % TK; } else { kk = e / TM; mm = e % TM; }
-                const int m = m0 + mm, k = k0 + kk;
-                float v = 0.f;
-                if (m < p.M && k < K && !(p.row_mask && p.row_mask[m] == 0))
-                    v = ld(p.a_kmajor ? A + (long long)m * lda + k : A + (long long)k * lda + m);
-                As[kk][mm] = v;
+        const bool av = p.a_vec[s], bv = p.b_vec[s];
+        const int chunks = (p.K[s] + kChunk - 1) / kChunk;
+        const int lo = wave * chunks / kWaves, hi = (wave + 1) * chunks / kWaves;
+        const int k_end = min(p.K[s], hi * kChunk);
+        auto load = [&](int c, f32x4 (&a)[kBatch], f32x4 (&b)[kBatch]) {
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) {
+                const int k = (c + q) * kChunk + 4 * part;
+                const bool whole = (c + q + 1) * kChunk <= k_end;
+                a[q] = operand4(A, lda, ak, av, whole, m, k, k_end);
+                b[q] = operand4(B, ldb, bk, bv, whole, n, k, k_end);
             }
-            for (int e = threadIdx.x; e < TN * TK; e += 256) {
-                int nn, kk;
-                if (p.b_kmajor) { nn = e / TK; kk = e % TK; } else { kk = e / TN; nn = e % TN; }
-                const int n = n0 + nn, k = k0 + kk;
-                float v = 0.f;
-                if (n < p.N && k < K) v = ld(p.b_kmajor ? B + (long long)n * ldb + k : B + (long long)k * ldb + n);
-                Bs[kk][nn] = v;
-            }
-            __syncthreads();
+        };
+        f32x4 a0[kBatch], b0[kBatch];
+        load(lo, a0, b0);
+        for (int c = lo; c < hi; c += kBatch) {
+            f32x4 a1[kBatch], b1[kBatch];
+            load(c + kBatch, a1, b1);
 #pragma unroll
-            for (int kk = 0; kk < TK; ++kk) {
-                float a[4], b[4];
+            for (int q = 0; q < kBatch; ++q)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
+                for (int i = 0; i < 4; ++i) acc = F32Tile<kTile>::mac(a0[q][i], b0[q][i], acc);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-            }
-            __syncthreads();
+            for (int q = 0; q < kBatch; ++q) { a0[q] = a1[q]; b0[q] = b1[q]; }
         }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty + 16 * i;
-        if (m >= p.M) continue;
-        int oseg = 0;
-        for (int s = 1; s < p.n_out; ++s)
-            if (m >= p.m_begin[s]) oseg = s;
-        T* C = static_cast<T*>(p.C[oseg]);
-        const long long ldc = p.ldc[oseg];
-        const int mr = m - p.m_begin[oseg];
+    for (int e = 0; e < kElems; ++e) red[wave][e][lane] = acc[e];
+    __syncthreads();
+    for (int q = threadIdx.x; q < kElems * 64; q += kWaves * 64) {
+        const int e = q >> 6, l = q & 63;
+        float v = red[0][e][l];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx + 16 * j;
-            if (n >= p.N) continue;
-            if (p.epilogue == kEpiSwigluBwd) {
-                const float g = ld(static_cast<const T*>(p.G) + (long long)m * p.ldgu + n);
-                const float u = ld(static_cast<const T*>(p.U) + (long long)m * p.ldgu + n);
-                const float d = (float)(T)acc[i][j];
-                const float sg = 1.f / (1.f + expf(-g));
-                st(C + (long long)m * ldc + n, d * u * sg * (1.f + g * (1.f - sg)));
-                st(C + (long long)m * ldc + p.N + n, d * g * sg);
-                if (p.act_out) st(static_cast<T*>(p.act_out) + (long long)m * p.N + n, g * sg * u);
-            } else {
-                T* dst = C + (long long)mr * ldc + n;
-                float v = acc[i][j];
-                if (p.accumulate) v += ld(dst);
-                st(dst, v);
+        for (int w = 1; w < kWaves; ++w) v += red[w][e][l];
+        store_element<T>(p, m0 + F32Tile<kTile>::row(e, l), n0 + l % kTile, v);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_gemm_f32_tiled(GenericGemmParams p) {
+    constexpr int TB = 128, TK = 32, kLd = TB + 4;
+    __shared__ __attribute__((aligned(16))) float As[2][TK][kLd];
+    __shared__ __attribute__((aligned(16))) float Bs[2][TK][kLd];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    const int m0 = (int)(blockIdx.x / p.tiles_n) * TB, n0 = (int)(blockIdx.x % p.tiles_n) * TB;
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    // this thread's 16 elements of an operand tile: k-major: row tid/2, k (tid&1)*16 ..+15; else k tid/16 and 16 further,
+    // columns (tid&15)*8 ..+7
+    const int kr = threadIdx.x >> 1, kk = (threadIdx.x & 1) * 16, mk = threadIdx.x >> 4, mc = (threadIdx.x & 15) * 8;
+    auto load = [&](const T* P, long long ld_, bool kmajor, bool vec, int r0, int r_end, int k0, int K, f32x4 (&v)[4]) {
+        const bool inside = kmajor ? k0 + TK <= K : k0 + TK <= K && r0 + TB <= r_end;
+        const int r = min(r0 + kr, r_end - 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = k0 + mk + 16 * (i >> 1), c = r0 + mc + 4 * (i & 1);
+            if (kmajor) v[i] = operand4(P, ld_, true, vec, inside, r, k0 + kk + 4 * i, K);
+            else if (inside || k < K) v[i] = operand4(P, ld_, true, vec, inside, k, c, r_end);  // four columns of a row of k
+            else v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    auto store = [&](float (&S)[TK][kLd], bool kmajor, const f32x4 (&v)[4]) {
+        if (kmajor) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) S[kk + i][kr] = v[i >> 2][i & 3];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(&S[mk + 16 * (i >> 1)][mc + 4 * (i & 1)]) = v[i];
+        }
+    };
+    for (int s = 0; s < p.n_seg; ++s) {
+        const T* A = static_cast<const T*>(p.A[s]);
+        const T* B = static_cast<const T*>(p.B[s]);
+        const int K = p.K[s], nk = (K + TK - 1) / TK;
+        f32x4 a[4], b[4];
+        load(A, p.lda[s], p.a_kmajor, p.a_vec[s], m0, p.M, 0, K, a);
+        load(B, p.ldb[s], p.b_kmajor, p.b_vec[s], n0, p.N, 0, K, b);
+        __syncthreads();  // (the previous pair's last stage has been read)
+        for (int t = 0; t < nk; ++t) {
+            store(As[t & 1], p.a_kmajor, a);
+            store(Bs[t & 1], p.b_kmajor, b);
+            __syncthreads();  // one barrier per stage: stage t+1 goes to the other half of the buffers
+            if (t + 1 < nk) {
+                load(A, p.lda[s], p.a_kmajor, p.a_vec[s], m0, p.M, (t + 1) * TK, K, a);
+                load(B, p.ldb[s], p.b_kmajor, p.b_vec[s], n0, p.N, (t + 1) * TK, K, b);
+            }
+#pragma unroll
+            for (int k = 0; k < TK; k += 2) {
+                float fa[2], fb[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    fa[i] = As[t & 1][k + half][wm + i * 32 + (lane & 31)];
+                    fb[i] = Bs[t & 1][k + half][wn + i * 32 + (lane & 31)];
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
             }
         }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                store_element<T>(p, m0 + wm + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3), n0 + wn + j * 32 + (lane & 31), acc[i][j][e]);
+}
+
+// From this many 128x128 tiles on the tiled kernel is the faster one (K 1024, three layouts, slices against tiled:
+// 128 tiles 101 / 87 / 106 against 135 / 148 / 110 us, 182 tiles 143 / 123 / 150 against 137 / 150 / 110 us,
+// 256 tiles 190 / 163 / 202 against 138 / 151 / 112 us).
+static constexpr int kTiledFrom = 160;
+// Below this many 32x32 tiles the slices kernel takes 16x16 ones: four times as many work-groups share the reads
+// (256 x 256 x 2048, 64 tiles of 32x32: 24 against 12.4 us; 192 tiles, K 256: equal; 512^3, 256 tiles: 10.6 against 13.7 us).
+static constexpr int kWideFrom = 128;
+
+template <typename T, int kTile>
+static void gemm_slices_t(GenericGemmParams& p, int k_total, hipStream_t stream) {
+    p.tiles_n = ceil_div(p.N, kTile);
+    const int grid = ceil_div(p.M, kTile) * p.tiles_n;
+    // slices of at least 64 k
+    if (k_total >= 1024) k_gemm_f32_slices<T, kTile, 16><<<grid, 1024, 0, stream>>>(p);
+    else if (k_total >= 512) k_gemm_f32_slices<T, kTile, 8><<<grid, 512, 0, stream>>>(p);
+    else k_gemm_f32_slices<T, kTile, 4><<<grid, 256, 0, stream>>>(p);
+}
+
+template <typename T>
+static void gemm_generic_t(GenericGemmParams& p, hipStream_t stream) {
+    int k_total = 0;
+    for (int s = 0; s < p.n_seg; ++s) k_total += p.K[s];
+    const long long tiles128 = (long long)ceil_div(p.M, 128) * ceil_div(p.N, 128);
+    const long long tiles32 = (long long)ceil_div(p.M, 32) * ceil_div(p.N, 32);
+    if (tiles128 >= kTiledFrom) {
+        p.tiles_n = ceil_div(p.N, 128);
+        k_gemm_f32_tiled<T><<<(int)tiles128, 256, 0, stream>>>(p);
+    } else if (tiles32 >= kWideFrom) {
+        gemm_slices_t<T, 32>(p, k_total, stream);
+    } else {
+        gemm_slices_t<T, 16>(p, k_total, stream);
     }
 }
 
@@ -110,6 +270,8 @@ int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
     GenericGemmParams p;
     p.M = d.M; p.N = d.N; p.n_seg = d.n_seg; p.n_out = d.n_out; p.accumulate = d.accumulate;
     p.a_kmajor = d.a_kmajor; p.b_kmajor = d.b_kmajor;
+    const size_t E = dtype_size(d.dtype);
+    auto vec_ok = [&](const void* q, long long ld_) { return reinterpret_cast<uintptr_t>(q) % (4 * E) == 0 && ld_ % 4 == 0; };
     for (int s = 0; s < kMaxGemmSegs; ++s) {
         const bool on = s < d.n_seg;
         p.A[s] = on ? d.seg[s].A : nullptr;
@@ -117,6 +279,8 @@ int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
         p.K[s] = on ? d.seg[s].K : 0;
         p.lda[s] = on ? d.seg[s].lda : 0;
         p.ldb[s] = on ? d.seg[s].ldb : 0;
+        p.a_vec[s] = on && vec_ok(d.seg[s].A, d.seg[s].lda);
+        p.b_vec[s] = on && vec_ok(d.seg[s].B, d.seg[s].ldb);
     }
     for (int s = 0; s < kMaxGemmOuts; ++s) {
         const bool oo = s < d.n_out;
@@ -125,12 +289,8 @@ int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
         p.ldc[s] = oo ? d.out[s].ldc : 0;
     }
     p.epilogue = d.epilogue; p.G = d.G; p.U = d.U; p.ldgu = d.ldgu; p.act_out = d.act_out;
-    p.row_mask = d.row_mask;
-    dim3 grid(ceil_div(d.N, 64), ceil_div(d.M, 64));
-    if (d.dtype == ALCH_BF16)
-        k_gemm_generic<__bf16><<<grid, 256, 0, stream>>>(p);
-    else
-        k_gemm_generic<float><<<grid, 256, 0, stream>>>(p);
+    if (d.dtype == ALCH_BF16) gemm_generic_t<__bf16>(p, stream);
+    else gemm_generic_t<float>(p, stream);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
@@ -142,7 +302,7 @@ int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
 // output one after the other (sum in fp32 inside a band, one rounding to the storage type per band).
 // Returns true when the product was launched that way (rc holds the status).
 static bool launch_gemm_in_bands(const GemmDesc& d, hipStream_t stream, int& rc) {
-    if (d.dtype != ALCH_BF16 || d.m_dev || d.k_dev || d.row_mask || d.n_out != 1 || d.out[0].m_begin != 0) return false;
+    if (d.dtype != ALCH_BF16 || d.m_dev || d.k_dev || d.n_out != 1 || d.out[0].m_begin != 0) return false;
     const long long kLimit = (1LL << 31) - 1;
     const bool rows = d.a_kmajor;                        // bands over M
     const bool contr = !d.a_kmajor && !d.b_kmajor;       // bands over K (single operand pair)

@@ -644,7 +644,6 @@ __global__ __launch_bounds__(256) void k_gemm_split_finish(MfmaGemmParams p, int
 bool gemm_mfma_supported(const GemmDesc& d) {
     if (d.dtype != ALCH_BF16 || d.M <= 0 || d.N <= 0 || d.n_seg < 1 || d.n_seg > kMaxGemmSegs || d.n_out < 1 || d.n_out > 3)
         return false;
-    if (d.row_mask) return false;
     for (int s = 0; s < d.n_seg; ++s) {
         const GemmSeg& g = d.seg[s];
         if (g.K <= 0 || !aligned16(g.A) || !aligned16(g.B) || g.lda % 8 || g.ldb % 8) return false;

@@ -51,7 +51,6 @@ struct GemmDesc {
     const void* U = nullptr;
     long long ldgu = 0;
     void* act_out = nullptr;
-    const uint8_t* row_mask = nullptr;  // optional: rows of A whose mask byte is 0 count as zero (A k-major only)
     // optional device-resident sizes (matrix-core kernel only): effective M = min(*m_dev, M); effective K of
     // every operand pair = min(*k_dev, K).  Rows / contraction steps beyond them are neither read nor written.
     const int* m_dev = nullptr;
@@ -88,20 +87,12 @@ int launch_rank_of_kept(const int* index, const int* n_rows, int* inv, int T, hi
 int launch_scatter_rows(const void* src, const int* inv, void* out, int T, size_t row_bytes, hipStream_t stream);
 // Act = silu(G) * U
 int launch_swiglu_act(alch_dtype dt, const void* G, const void* U, void* Act, long long n, hipStream_t stream);
-// dGU[:, 0:F] = dAct*U*silu'(G), dGU[:, F:2F] = dAct*silu(G); optionally Act = silu(G)*U
-int launch_swiglu_bwd(alch_dtype dt, const void* dAct, const void* G, const void* U, void* dGU, void* Act,
-                      int T, int F, hipStream_t stream);
-// delta[t,h] = sum_d dO[t,h,d] * O[t,h,d]   (fp32 out)
-int launch_attn_delta(alch_dtype dt, const void* dO, const void* O, float* delta, int T, int Hq, int D,
-                      hipStream_t stream);
 // In-place rotary rotation of x [T, n_heads, D] (row stride ld elements) by sign * angle.
 int launch_rope(alch_dtype dt, void* x, long long ld, int T, int n_heads, int D, const int* positions,
                 const int* cu_seqlens, int n_seqs, float base, float sign, hipStream_t stream);
 // out = a with rows zeroed where mask == 0 (mask may be NULL: plain copy)
 int launch_masked_copy(alch_dtype dt, const void* a, const uint8_t* mask, void* out, int T, int width,
                        hipStream_t stream);
-// y = a + b
-int launch_add(alch_dtype dt, const void* a, const void* b, void* y, long long n, hipStream_t stream);
 
 // ---- low-rank adapters ---------------------------------------------------------------------
 static constexpr int kLoraSlot = 64;       // columns of one zero-padded rank slot (rank <= 64)
@@ -171,7 +162,7 @@ double attn_pairs(int n_seqs, const int* cu_host, const int* prefix_host);
 // forward: writes O [T,Hq*D] and LSE [T,Hq] for the query rows of sequences seq_begin .. n_seqs-1 (keys and
 // values of a prefix sequence are read wherever it lies); prefix / prefix_host as in AttnArgs
 int launch_attn_fwd_generic(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int T,
-                            int n_seqs, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
+                            int n_seqs, int max_seqlen, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
                             int seq_begin, int Hq, int Hkv, int D, hipStream_t stream);
 int launch_attn_fwd(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int T,
                     int n_seqs, int max_seqlen, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,

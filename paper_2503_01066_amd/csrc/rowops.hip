@@ -1,6 +1,5 @@
 // Row-wise and elementwise kernels of the decoder-layer backward pass (RMSNorm forward and
-// backward with the residual add, SwiGLU activation and its gradient, the softmax-gradient
-// row term, rotary embedding).  All arithmetic in fp32; storage type T is float or bf16.
+// backward with the residual add, SwiGLU activation, rotary embedding).  All arithmetic in fp32; storage type T is float or bf16.
 // These are HBM-bound: one pass over each operand, 16-byte accesses where alignment allows.
 #include "kernels.h"
 
@@ -504,63 +503,6 @@ int launch_swiglu_act(alch_dtype dt, const void* G, const void* U, void* Act, lo
     return ALCH_OK;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_swiglu_bwd(const T* __restrict__ dAct, const T* __restrict__ G,
-                                                    const T* __restrict__ U, T* __restrict__ dGU,
-                                                    T* __restrict__ Act, int Trows, int F) {
-    const long long n = (long long)Trows * F;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-        const long long t = i / F;
-        const int f = (int)(i - t * F);
-        const float g = ldf(G + i), u = ldf(U + i), d = ldf(dAct + i);
-        const float sg = 1.f / (1.f + __expf(-g));
-        stf(dGU + t * 2 * F + f, d * u * sg * (1.f + g * (1.f - sg)));
-        stf(dGU + t * 2 * F + F + f, d * g * sg);
-        if (Act) stf(Act + i, g * sg * u);
-    }
-}
-
-int launch_swiglu_bwd(alch_dtype dt, const void* dAct, const void* G, const void* U, void* dGU, void* Act, int T,
-                      int F, hipStream_t stream) {
-    const long long n = (long long)T * F;
-    if (n <= 0) return ALCH_OK;
-    const int grid = (int)((n + 255) / 256 < 256 * 16 ? (n + 255) / 256 : 256 * 16);
-    if (dt == ALCH_BF16)
-        k_swiglu_bwd<__bf16><<<grid, 256, 0, stream>>>((const __bf16*)dAct, (const __bf16*)G, (const __bf16*)U,
-                                                       (__bf16*)dGU, (__bf16*)Act, T, F);
-    else
-        k_swiglu_bwd<float><<<grid, 256, 0, stream>>>((const float*)dAct, (const float*)G, (const float*)U,
-                                                      (float*)dGU, (float*)Act, T, F);
-    ALCH_HIP_TRY(hipGetLastError());
-    return ALCH_OK;
-}
-
-// ---- delta[t,h] = sum_d dO*O : one wave per (t,h)
-template <typename T>
-__global__ __launch_bounds__(256) void k_attn_delta(const T* __restrict__ dO, const T* __restrict__ O,
-                                                    float* __restrict__ delta, long long n_rows, int D) {
-    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= n_rows) return;
-    const int lane = threadIdx.x & 63;
-    float s = 0.f;
-    for (int d = lane; d < D; d += 64) s += ldf(dO + row * D + d) * ldf(O + row * D + d);
-    s = wave_sum(s);
-    if (lane == 0) delta[row] = s;
-}
-
-int launch_attn_delta(alch_dtype dt, const void* dO, const void* O, float* delta, int T, int Hq, int D,
-                      hipStream_t stream) {
-    const long long n = (long long)T * Hq;
-    if (n <= 0) return ALCH_OK;
-    const int grid = (int)((n + 3) / 4);
-    if (dt == ALCH_BF16)
-        k_attn_delta<__bf16><<<grid, 256, 0, stream>>>((const __bf16*)dO, (const __bf16*)O, delta, n, D);
-    else
-        k_attn_delta<float><<<grid, 256, 0, stream>>>((const float*)dO, (const float*)O, delta, n, D);
-    ALCH_HIP_TRY(hipGetLastError());
-    return ALCH_OK;
-}
-
 // ---- rotary embedding in place: pairs (i, i + D/2), angle = pos * base^(-2i/D), rotation by sign*angle
 template <typename T>
 __global__ __launch_bounds__(256) void k_rope(T* __restrict__ x, long long ld, int Trows, int n_heads, int D,
@@ -665,7 +607,7 @@ int launch_rope(alch_dtype dt, void* x, long long ld, int T, int n_heads, int D,
     return ALCH_OK;
 }
 
-// ---- masked copy / add
+// ---- masked copy
 template <typename T>
 __global__ __launch_bounds__(256) void k_masked_copy(const T* __restrict__ a, const uint8_t* __restrict__ mask,
                                                      T* __restrict__ out, int Trows, int width) {
@@ -703,24 +645,6 @@ int launch_masked_copy(alch_dtype dt, const void* a, const uint8_t* mask, void* 
         k_masked_copy<__bf16><<<grid, 256, 0, stream>>>((const __bf16*)a, mask, (__bf16*)out, T, width);
     else
         k_masked_copy<float><<<grid, 256, 0, stream>>>((const float*)a, mask, (float*)out, T, width);
-    ALCH_HIP_TRY(hipGetLastError());
-    return ALCH_OK;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_add(const T* __restrict__ a, const T* __restrict__ b, T* __restrict__ y,
-                                             long long n) {
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256)
-        stf(y + i, ldf(a + i) + ldf(b + i));
-}
-
-int launch_add(alch_dtype dt, const void* a, const void* b, void* y, long long n, hipStream_t stream) {
-    if (n <= 0) return ALCH_OK;
-    const int grid = (int)((n + 255) / 256 < 256 * 16 ? (n + 255) / 256 : 256 * 16);
-    if (dt == ALCH_BF16)
-        k_add<__bf16><<<grid, 256, 0, stream>>>((const __bf16*)a, (const __bf16*)b, (__bf16*)y, n);
-    else
-        k_add<float><<<grid, 256, 0, stream>>>((const float*)a, (const float*)b, (float*)y, n);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
