@@ -12,7 +12,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "lib", "libalch.so")
-SOURCES = ["api.hip", "pack.hip", "gemm_mfma.hip", "gemm_generic.hip", "rowops.hip", "attn_generic.hip",
+SOURCES = ["api.hip", "pack.hip", "gemm_mfma.hip", "gemm_pair.hip", "gemm_generic.hip", "rowops.hip", "attn_generic.hip",
            "attn_mfma.hip", "attn_mfma_d64.hip", "lmhead.hip", "lora.hip", "dpo.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-inline-asm", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

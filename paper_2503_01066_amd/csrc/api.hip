@@ -286,7 +286,8 @@ static int check_wgrads(const alch_wgrads* g) {
 static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b, const alch_saved& sv_in,
                                   const alch_weights& w, const void* dY, const uint8_t* loss_mask, void* dX,
                                   const alch_wgrads* wg, const LayerBwdPlan& p, hipStream_t st,
-                                  const alch_lora* lo = nullptr, const alch_lora_grads* lg = nullptr) {
+                                  const alch_lora* lo = nullptr, const alch_lora_grads* lg = nullptr,
+                                  bool keep_parts = false) {
     const alch_dtype dt = s.dtype;
     const size_t E = dtype_size(dt);
     const int T = b.total_tokens, H = s.hidden, F = s.ffn, D = s.head_dim;
@@ -296,6 +297,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         GemmDesc d = gemm(t, M, N, a_k, b_k);
         d.split_ws = p.gemm_ws;
         d.split_ws_bytes = kGemmSplitWsBytes;
+        d.keep_parts = keep_parts;
         return d;
     };
 
@@ -952,11 +954,15 @@ static int stack_backward_impl(const alch_layer_shape* shape, int32_t n_layers, 
     const size_t E = dtype_size(dt);
     const int T = batch->total_tokens, H = s.hidden;
     const int acc = wgrads ? (wgrads[0].accumulate != 0) : 0;
-    // scratch of split products in the head: the layers' workspace, idle until the walk starts
+    // scratch of split products in the head: the layers' workspace, idle until the walk starts.
+    // keep_parts: a chain of bf16 tensors over several layers turns a sum taken in another order, one last bit here and
+    // there, into another rounding of nearly every element (0.5 % in the 2-norm after two layers).  The gradients of a
+    // stack therefore do not depend on which of the two contraction kernels is the faster one for a product.
     auto gemm_ws = [&](alch_dtype t, int M, int N, bool a_k, bool b_k) {
         GemmDesc d = gemm(t, M, N, a_k, b_k);
         d.split_ws = p.layer_ws;
         d.split_ws_bytes = p.layer_ws_bytes;
+        d.keep_parts = true;
         return d;
     };
 
@@ -1092,7 +1098,7 @@ static int stack_backward_impl(const alch_layer_shape* shape, int32_t n_layers, 
         const uint8_t* top_mask = (compact_head && l == n_layers - 1) ? p.h_counted : nullptr;
         ALCH_TRY(layer_backward_enqueue(s, *batch, saved[l], weights[l], cur, top_mask, out,
                                         wgrads ? &wgrads[l] : nullptr, lp, st, lora ? &lora[l] : nullptr,
-                                        lora_grads ? &lora_grads[l] : nullptr));
+                                        lora_grads ? &lora_grads[l] : nullptr, true));
         cur = out;
     }
     return ALCH_OK;
@@ -1200,6 +1206,7 @@ static int layer_forward_impl(const alch_layer_shape* shape, const alch_batch* b
         GemmDesc d = gemm(t, M, N, a_k, b_k);
         d.split_ws = p.gemm_ws;
         d.split_ws_bytes = kGemmSplitWsBytes;
+        d.keep_parts = seq_begin > 0;  // the response leg of a stack's forward (see stack_backward_impl)
         return d;
     };
     // the computed rows of every [total_tokens, width] tensor

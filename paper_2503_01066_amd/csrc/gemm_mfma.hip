@@ -28,119 +28,15 @@
 //     share a tile, each taking 1/s of the contraction and leaving an fp32 partial tile in a scratch
 //     buffer; k_gemm_split_finish adds the s partials in a fixed order and writes the output
 //     (deterministic, no atomics).
-#include "kernels.h"
+#include "gemm_mfma_common.h"
 
 namespace alch {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-#define ALCH_LDS(p) ((__attribute__((address_space(3))) void*)(p))
-
-static constexpr int BM = 256, BN = 256, BK = 32;
+static constexpr int BM = 256, BN = 256;
 static constexpr int kStages = 5;                        // 5 x 32 KB = the whole 160 KB LDS
 static constexpr int kOperandStageBytes = 256 * BK * 2;  // 16 KB per operand per stage
 static constexpr int kLoadsPerTile = 8;                  // direct-to-LDS instructions per wave per k-tile (A + B)
-static constexpr uint32_t kOobOffset = 0x80000000u;      // >= any num_records we set
-static constexpr uint32_t kMaxRecords = 0x80000000u;
 static constexpr int kGroupM = 4;                        // tile rows per raster band
-
-struct MfmaGemmParams {
-    int M, N, n_seg, n_out, accumulate, tiles_m, tiles_n;
-    // optional device-resident sizes (row compaction decided on the device): the effective M, or the
-    // effective K of every operand pair, is min(*ptr, host value)
-    const int* m_dev;
-    const int* k_dev;
-    const __bf16* A[kMaxGemmSegs];
-    const __bf16* B[kMaxGemmSegs];
-    int K[kMaxGemmSegs];
-    long long lda[kMaxGemmSegs], ldb[kMaxGemmSegs];
-    __bf16* C[3];
-    int m_begin[3];
-    long long ldc[3];
-    int epilogue;
-    const __bf16* G;
-    const __bf16* U;
-    long long ldgu;
-    __bf16* act_out;
-    // Tiles q < q_end of every XCD's share are computed whole by the plain instantiation.  The kSplit
-    // instantiation computes the tiles q_end .. of the share, split_s work-groups per tile, partial tiles
-    // [tile of the split round][part][256][256] fp32 in split_ws.
-    int q_end;
-    float* split_ws;
-    int split_s, split_per;  // parts per tile; k-tiles per part (counted over all operand pairs in order)
-};
-
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-
-// Buffer resource over [p, p + bytes_left): raw (stride 0), 32-bit data format, so that every
-// access at or beyond bytes_left reads as zero.  All parts are forced into scalar registers.
-__device__ __forceinline__ i32x4 make_rsrc(const void* p, long long bytes_left) {
-    const uint32_t n = bytes_left <= 0 ? 0u : (bytes_left > (long long)kMaxRecords ? kMaxRecords : (uint32_t)bytes_left);
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    i32x4 r;
-    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
-    r[2] = __builtin_amdgcn_readfirstlane((int)n);
-    r[3] = 0x00020000;
-    return r;
-}
-
-// 16 bytes per lane from buffer `r` at byte offset `voff` straight into LDS at
-// lds_addr + lane*16.  Written as assembly so that the compiler does not order later LDS
-// reads of the other pipeline stage behind it; completion is awaited with vmcnt.
-__device__ __forceinline__ void dma16(i32x4 r, uint32_t lds_addr, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(r)
-                 : "memory", "m0");
-}
-
-// Per-lane byte offsets (relative to the tile origin) of the 4 direct-to-LDS loads a wave
-// issues for one operand tile.  LDS slot s (16-byte units) = (wave*4 + j)*64 + lane.
-//   k-major tile [256 rows][32 k]: slot = row*4 + (c ^ ((row>>2)&3)), c = 16-byte chunk in the row
-//   mn-major tile [32 k][256 cols]: slot = k*32 + (c ^ (4*(k&3)))
-template <bool KMAJOR>
-__device__ __forceinline__ void tile_offsets(uint32_t (&voff)[4], int wave, int lane, long long ld, int valid) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int s = (wave * 4 + j) * 64 + lane;
-        if (KMAJOR) {
-            const int row = s >> 2, c = (s & 3) ^ ((row >> 2) & 3);
-            voff[j] = row < valid ? (uint32_t)((row * ld + c * 8) * 2) : kOobOffset;
-        } else {
-            const int k = s >> 5, c = (s & 31) ^ (4 * (k & 3));
-            voff[j] = c * 8 < valid ? (uint32_t)((k * ld + c * 8) * 2) : kOobOffset;
-        }
-    }
-}
-
-__device__ __forceinline__ void issue_tile(i32x4 r, uint32_t stage_addr, int wave, const uint32_t (&voff)[4]) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dma16(r, stage_addr + (uint32_t)(wave * 4 + j) * 1024u, voff[j]);
-}
-
-// Fragment (8 consecutive-k bf16 per lane for one 32-wide block of rows/cols) from an LDS tile.
-template <bool KMAJOR>
-__device__ __forceinline__ bf16x8 read_frag(const char* stage, int idx0 /*first row/col of the 32-block*/, int kk, int lane) {
-    if (KMAJOR) {
-        const int row = idx0 + (lane & 31);
-        const int c = (kk * 2 + (lane >> 5)) ^ ((row >> 2) & 3);
-        return *reinterpret_cast<const bf16x8*>(stage + row * 64 + c * 16);
-    } else {
-        const int g = lane >> 4, i = lane & 15;
-        const int col = idx0 + (g & 1) * 16 + 4 * (i & 3);
-        const int krow = kk * 16 + 8 * (g >> 1) + (i >> 2);  // + 4 for the second half
-        const int chunk = col >> 3, sub = (col & 7) * 2;
-        const char* p0 = stage + krow * 512 + ((chunk ^ (4 * (krow & 3))) << 4) + sub;
-        const char* p1 = p0 + 4 * 512;  // krow + 4 has the same (krow & 3)
-        bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(p0));
-        bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(p1));
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    }
-}
 
 // ---- k-major A staged 64 k wide ---------------------------------------------------------------
 // A k-major tile fetched 32 k at a time takes 64 bytes of every row: each 128-byte line then crosses the
@@ -173,25 +69,6 @@ struct Frags {
     bf16x8 a[4], b[4];
 };
 
-template <bool AK, bool BKM>
-__device__ __forceinline__ void read_frags(Frags& f, const char* sa, const char* sb, int wm, int wn, int kk, int lane) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f.a[i] = read_frag<AK>(sa, wm * 128 + i * 32, kk, lane);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f.b[i] = read_frag<BKM>(sb, wn * 128 + i * 32, kk, lane);
-}
-
-__device__ __forceinline__ void mfma_block(const Frags& f, f32x16 (&acc)[4][4]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
-}
-
-__device__ __forceinline__ float bf2f(__bf16 v) { return (float)v; }
-
-template <int I> struct IntC { static constexpr int value = I; };
 template <typename F> __device__ __forceinline__ void static_for4(F&& f) {
     f(IntC<0>{});
     f(IntC<1>{});
@@ -666,6 +543,68 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     return true;
 }
 
+// How the 256x256 kernel walks a product: tiles q < q_end of every XCD's share whole, the rest in `parts` parts of
+// `per` k-tiles each.
+struct BigPlan { int q_end, parts, per; };
+static BigPlan big_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes) {
+    const int per_xcd = ceil_div(ceil_div(p.M, BM) * ceil_div(p.N, BN), 8), wgx = n_cu / 8;
+    const int full_q = per_xcd / wgx * wgx, rem = per_xcd - full_q;
+    BigPlan b{per_xcd, 1, 0};
+    int nk_total = 0;
+    for (int s = 0; s < p.n_seg; ++s) nk_total += ceil_div(p.K[s], BK);
+    // Split of the last round (see the header): host-known sizes and a contraction long enough that every part
+    // still runs the pipeline for a while (the finish kernel carries the SwiGLU-gradient epilogue if there is one).  A
+    // product with tiles for at most half of the compute units (a short batch) has no other round: every tile is split.
+    if (ws_bytes > 0 && !p.m_dev && !p.k_dev && rem > 0 && 2 * rem <= wgx) {
+        int s = wgx / rem < 16 ? wgx / rem : 16;
+        if (s > nk_total / 16) s = nk_total / 16;
+        if (s > 1 && (size_t)8 * rem * s * BM * BN * sizeof(float) <= ws_bytes) {
+            b.q_end = full_q;
+            b.parts = s;
+            b.per = ceil_div(nk_total, s);
+            if (a_kmajor) b.per += b.per & 1;  // parts start on a 64-k boundary: whole 128-byte lines of A
+        }
+    }
+    return b;
+}
+
+// Which of the two matrix-core kernels takes a product: the one whose estimated time is shorter.  Both estimates count
+// rounds of tiles over the compute units of an XCD: so many us for each k of the contraction and for what a tile costs
+// besides, with the last round on its own.  The constants are fits to measured products of 128 .. 8192 rows,
+// K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 %:
+//   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round; a last round that is cut along K adds its two kernels
+//   128x256 tiles, two per compute unit:   0.0265 K + 2 us a round (0.0255 K + 3 weight gradient, 0.0276 K + 6 forward);
+//                                          with one per compute unit, half of that
+// The second one reads 1.5 times as much from L2 per multiply-add, which the long K pays for (8192 x 4096 x 28672: 1388
+// against 1574 us), and has no idle start and end of tile, nor as coarse a last round (4096 x 14336 x 487: 86 against
+// 60 us; 6144 x 4096 x 1024: 82 against 49; 487 x 4096 x 4096: 47 against 31; 6001 x 4096 x 6144: 262 against 239 us).
+static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, bool a_kmajor, bool b_kmajor, int n_cu, bool can_split,
+                           bool keep_parts) {
+    if (p.m_dev || p.k_dev) return false;  // sizes that only the device knows
+    double K = 0;
+    for (int s = 0; s < p.n_seg; ++s) K += p.K[s];
+    const int cus = n_cu / 8;  // compute units of an XCD
+    const double swiglu_split = p.epilogue == kEpiSwigluBwd ? 15.0 : 0.0;  // its finish kernel also moves G, U, dG, dU, Act
+
+    const int tiles = ceil_div(ceil_div(p.M, BM) * ceil_div(p.N, BN), 8);
+    const double big_k = b_kmajor ? 0.0238 : 0.0232, big_fixed = 11.0;
+    double big = tiles / cus * (big_k * K + big_fixed);
+    if (tiles % cus) big += b.parts > 1 ? big_k * K / b.parts + 33.0 + swiglu_split : 0.9 * big_k * K + big_fixed;
+
+    const int tiles2 = keep_parts ? 2 * tiles : ceil_div(ceil_div(p.M, BM / 2) * ceil_div(p.N, BN), 8), rem2 = tiles2 % (2 * cus);
+    const double pair_k = b_kmajor ? 0.0276 : a_kmajor ? 0.0265 : 0.0255, pair_fixed = b_kmajor ? 6.0 : a_kmajor ? 2.0 : 3.0;
+    double pair = tiles2 / (2 * cus) * (pair_k * K + pair_fixed);
+    if (rem2 > 0) {
+        int s = 1;
+        if (keep_parts) s = b.parts;
+        else if (can_split && rem2 <= cus) s = std::min(std::min(cus / rem2, 16), (int)(K / (16 * BK)));
+        if (s > 1) pair += (rem2 * s > cus ? pair_k * K / s + 27.0 : 0.52 * pair_k * K / s + 17.0) + swiglu_split;
+        else if (rem2 <= cus) pair += 0.52 * pair_k * K + 4.0;
+        else pair += 0.9 * pair_k * K + pair_fixed;
+    }
+    return pair < big;
+}
+
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     MfmaGemmParams p;
     p.M = d.M;
@@ -704,29 +643,21 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
         ALCH_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
         n_cu = v > 8 ? v / 8 * 8 : 8;
     }
-    const int grid = ceil_div(nt, 8) * 8 < n_cu ? ceil_div(nt, 8) * 8 : n_cu;
-    // Split of the last round (see the header): host-known sizes and a contraction long enough that every part
-    // still runs the pipeline for a while (the finish kernel carries the SwiGLU-gradient epilogue if there is one).  A product with tiles for at most half of the compute
-    // units (a short batch) has no other round: every tile is split.
-    const int per_xcd = ceil_div(nt, 8), wgx = n_cu / 8;
-    const int full_q = per_xcd / wgx * wgx, rem = per_xcd - full_q;
-    p.q_end = per_xcd;
-    p.split_ws = nullptr;
-    p.split_s = 1;
-    p.split_per = 0;
-    int nk_total = 0;
-    for (int s = 0; s < d.n_seg; ++s) nk_total += ceil_div(d.seg[s].K, BK);
-    if (d.split_ws && aligned16(d.split_ws) && !d.m_dev && !d.k_dev && rem > 0 && 2 * rem <= wgx) {
-        int s = wgx / rem < 16 ? wgx / rem : 16;
-        if (s > nk_total / 16) s = nk_total / 16;
-        if (s > 1 && (size_t)8 * rem * s * BM * BN * sizeof(float) <= d.split_ws_bytes) {
-            p.q_end = full_q;
-            p.split_ws = static_cast<float*>(d.split_ws);
-            p.split_s = s;
-            p.split_per = ceil_div(nk_total, s);
-            if (d.a_kmajor) p.split_per += p.split_per & 1;  // parts start on a 64-k boundary: whole 128-byte lines of A
-        }
+    float* split_ws = aligned16(d.split_ws) ? static_cast<float*>(d.split_ws) : nullptr;
+    const BigPlan plan = big_plan(p, d.a_kmajor, n_cu, split_ws ? d.split_ws_bytes : 0);
+    if (pair_is_better(p, plan, d.a_kmajor, d.b_kmajor, n_cu, split_ws != nullptr, d.keep_parts)) {
+        // (a 256x256 tile is two tiles of the other kernel, numbered in the same order)
+        if (d.keep_parts)
+            return launch_gemm_pair(p, d.a_kmajor, d.b_kmajor, 2 * p.tiles_m, 2 * ceil_div(nt, 8), 2 * plan.q_end, plan.parts, plan.per,
+                                    split_ws, stream);
+        return launch_gemm_pair(p, d.a_kmajor, d.b_kmajor, n_cu, split_ws, d.split_ws_bytes, stream);
     }
+    const int grid = ceil_div(nt, 8) * 8 < n_cu ? ceil_div(nt, 8) * 8 : n_cu;
+    const int per_xcd = ceil_div(nt, 8), rem = per_xcd - plan.q_end;
+    p.q_end = plan.q_end;
+    p.split_ws = plan.parts > 1 ? split_ws : nullptr;
+    p.split_s = plan.parts;
+    p.split_per = plan.per;
     const int grid_split = 8 * rem * p.split_s;
     if (d.a_kmajor && d.b_kmajor) {
         if (p.q_end > 0) k_gemm_mfma<true, true><<<grid, 256, 0, stream>>>(p);

@@ -1,0 +1,135 @@
+// Pieces shared by the bf16 matrix-core GEMM kernels (gemm_mfma.hip, gemm_pair.hip).
+#pragma once
+#include <algorithm>
+#include "kernels.h"
+
+namespace alch {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+#define ALCH_LDS(p) ((__attribute__((address_space(3))) void*)(p))
+
+static constexpr int BK = 32;
+static constexpr uint32_t kOobOffset = 0x80000000u;      // >= any num_records we set
+static constexpr uint32_t kMaxRecords = 0x80000000u;
+
+struct MfmaGemmParams {
+    int M, N, n_seg, n_out, accumulate, tiles_m, tiles_n;
+    // optional device-resident sizes (row compaction decided on the device): the effective M, or the
+    // effective K of every operand pair, is min(*ptr, host value)
+    const int* m_dev;
+    const int* k_dev;
+    const __bf16* A[kMaxGemmSegs];
+    const __bf16* B[kMaxGemmSegs];
+    int K[kMaxGemmSegs];
+    long long lda[kMaxGemmSegs], ldb[kMaxGemmSegs];
+    __bf16* C[3];
+    int m_begin[3];
+    long long ldc[3];
+    int epilogue;
+    const __bf16* G;
+    const __bf16* U;
+    long long ldgu;
+    __bf16* act_out;
+    // Tiles q < q_end of every XCD's share are computed whole by the plain instantiation.  The kSplit
+    // instantiation computes the tiles q_end .. of the share, split_s work-groups per tile, partial tiles
+    // [tile of the split round][part][256][256] fp32 in split_ws.
+    int q_end;
+    float* split_ws;
+    int split_s, split_per;  // parts per tile; k-tiles per part (counted over all operand pairs in order)
+    int per_xcd;             // k_gemm_pair: tiles of an XCD's share (unless the row count lives on the device)
+};
+
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+
+// Buffer resource over [p, p + bytes_left): raw (stride 0), 32-bit data format, so that every
+// access at or beyond bytes_left reads as zero.  All parts are forced into scalar registers.
+__device__ __forceinline__ i32x4 make_rsrc(const void* p, long long bytes_left) {
+    const uint32_t n = bytes_left <= 0 ? 0u : (bytes_left > (long long)kMaxRecords ? kMaxRecords : (uint32_t)bytes_left);
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    i32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
+    r[2] = __builtin_amdgcn_readfirstlane((int)n);
+    r[3] = 0x00020000;
+    return r;
+}
+
+// 16 bytes per lane from buffer `r` at byte offset `voff` straight into LDS at
+// lds_addr + lane*16.  Written as assembly so that the compiler does not order later LDS
+// reads of the other pipeline stage behind it; completion is awaited with vmcnt.
+__device__ __forceinline__ void dma16(i32x4 r, uint32_t lds_addr, uint32_t voff) {
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(voff), "s"(r)
+                 : "memory", "m0");
+}
+
+// Per-lane byte offsets (relative to the tile origin) of the 4 direct-to-LDS loads a wave
+// issues for one operand tile.  LDS slot s (16-byte units) = (wave*4 + j)*64 + lane.
+//   k-major tile [256 rows][32 k]: slot = row*4 + (c ^ ((row>>2)&3)), c = 16-byte chunk in the row
+//   mn-major tile [32 k][256 cols]: slot = k*32 + (c ^ (4*(k&3)))
+template <bool KMAJOR>
+__device__ __forceinline__ void tile_offsets(uint32_t (&voff)[4], int wave, int lane, long long ld, int valid) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int s = (wave * 4 + j) * 64 + lane;
+        if (KMAJOR) {
+            const int row = s >> 2, c = (s & 3) ^ ((row >> 2) & 3);
+            voff[j] = row < valid ? (uint32_t)((row * ld + c * 8) * 2) : kOobOffset;
+        } else {
+            const int k = s >> 5, c = (s & 31) ^ (4 * (k & 3));
+            voff[j] = c * 8 < valid ? (uint32_t)((k * ld + c * 8) * 2) : kOobOffset;
+        }
+    }
+}
+
+// Fragment (8 consecutive-k bf16 per lane for one 32-wide block of rows/cols) from an LDS tile; kCols = columns of a
+// token-major tile.
+template <bool KMAJOR, int kCols = 256>
+__device__ __forceinline__ bf16x8 read_frag(const char* stage, int idx0 /*first row/col of the 32-block*/, int kk, int lane) {
+    if (KMAJOR) {
+        const int row = idx0 + (lane & 31);
+        const int c = (kk * 2 + (lane >> 5)) ^ ((row >> 2) & 3);
+        return *reinterpret_cast<const bf16x8*>(stage + row * 64 + c * 16);
+    } else {
+        const int g = lane >> 4, i = lane & 15;
+        const int col = idx0 + (g & 1) * 16 + 4 * (i & 3);
+        const int krow = kk * 16 + 8 * (g >> 1) + (i >> 2);  // + 4 for the second half
+        const int chunk = col >> 3, sub = (col & 7) * 2;
+        const char* p0 = stage + krow * (kCols * 2) + ((chunk ^ (4 * (krow & 3))) << 4) + sub;
+        const char* p1 = p0 + 4 * (kCols * 2);  // krow + 4 has the same (krow & 3)
+        bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(p0));
+        bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(p1));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+}
+
+__device__ __forceinline__ float bf2f(__bf16 v) { return (float)v; }
+
+// dAct = d8 rounded to bf16, saved g, u -> dG = dAct U s'(G), dU = dAct silu(G), Act = silu(G) U
+__device__ __forceinline__ void swiglu_gradient(const bf16x8& d8, const bf16x8& g8, const bf16x8& u8, bf16x8& dg8, bf16x8& du8,
+                                                bf16x8& a8) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const float g = bf2f(g8[r]), u = bf2f(u8[r]), d = bf2f(d8[r]);
+        const float sg = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
+        const float silu = g * sg;
+        dg8[r] = (__bf16)(d * u * sg * (1.f + g * (1.f - sg)));
+        du8[r] = (__bf16)(d * silu);
+        a8[r] = (__bf16)(silu * u);
+    }
+}
+
+// The kernel of 128x256 tiles.  p: operands and outputs; split_ws: scratch or null.  The second form is told how many
+// tile rows there are (the last may be empty), how many tiles an XCD has, which of them to cut, and into which parts.
+int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int n_cu, float* split_ws, size_t ws_bytes, hipStream_t stream);
+int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, int per_xcd, int q_end, int parts, int per,
+                     float* split_ws, hipStream_t stream);
+
+template <int I> struct IntC { static constexpr int value = I; };
+
+}  // namespace alch
