@@ -574,6 +574,8 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         a.Q = sv.Q; a.K = sv.K; a.V = sv.V; a.O = sv.O; a.dO = p.dO; a.LSE = sv.LSE; a.delta = p.delta;
         a.dQ = p.dQKV; a.dK = at(p.dQKV, QD, E); a.dV = at(p.dQKV, QD + KD, E); a.ld_dqkv = QKV;
         a.positions = b.positions; a.rope_base = s.rope_base;
+        a.scratch = p.dGU;  // [dG | dU] has had its last reader
+        a.scratch_bytes = (size_t)T * 2 * F * E;
         ALCH_TRY(launch_attn_bwd(a, st));
     }
 

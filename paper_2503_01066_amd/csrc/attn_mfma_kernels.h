@@ -22,6 +22,7 @@
 // of attn_generic.hip before, whose every (row, key) pair costs two six-step lane reductions: 5 sequences, 4099 tokens,
 // 32/8 heads: dQ 7043 -> 53 us, dK/dV 7630 -> 103 us, delta and RoPE backward (29 us) now inside these two.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 #include "kernels.h"
 
@@ -46,6 +47,8 @@ template <int kD> struct AttnTile {
     static constexpr int kLoads = kD / 32;                 // 1 KB direct-to-LDS loads per wavefront and tile
 };
 static constexpr float kLog2e = 1.4426950408889634f;
+static constexpr int kMinPartTiles = 8;  // tiles a part of a key block has at least
+
 
 struct AttnMfmaParams {
     const __bf16 *Q, *K, *V, *O, *dO;
@@ -61,7 +64,26 @@ struct AttnMfmaParams {
     long long ldq, ldk, ldo;  // row strides (elements) of Q/dO, K/V, and of the outputs
     float scale;
     float rope_log2_base;  // > 0: rotate dQ, dK by minus the RoPE angle before they are stored
+    // dK/dV: key blocks of up to n_blocks per sequence; a block whose query stream is longer than part_len tiles is cut
+    // over the query heads of the group into up to max_parts work-groups, which leave fp32 partial sums
+    // [part][T][Hkv][dK | dV] in `partial` (max_parts 1: none is)
+    int T, n_blocks, max_parts, part_len;
+    float* partial;
 };
+
+// Work-groups that share a key block whose query stream has `tiles` tiles per head, and how many heads each takes.
+__device__ __forceinline__ int dkv_parts(const AttnMfmaParams& p, int G, int tiles, int& heads) {
+    const int want = min(p.max_parts, (G * tiles + p.part_len - 1) / p.part_len);
+    heads = (G + max(want, 1) - 1) / max(want, 1);
+    return (G + heads - 1) / heads;
+}
+// 64-query tiles per head of the sequences that name `seq` as their prefix
+__device__ __forceinline__ int prefix_child_tiles(const AttnMfmaParams& p, int seq) {
+    int n = 0;
+    for (int c = seq + 1; c < p.n_seqs; ++c)
+        if (p.prefix[c] == seq) n += (p.cu[c + 1] - p.cu[c] + kTileRows - 1) / kTileRows;
+    return n;
+}
 
 // RoPE backward on one accumulator set: block nb of the lower half holds element d = nb*32 + (lane&31) of a head,
 // block nb + kNB/2 its partner d + kD/2; x'[d] = x[d] cos a + x[d+kD/2] sin a, x'[d+kD/2] = x[d+kD/2] cos a - x[d] sin a
@@ -205,11 +227,21 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     // and heads start first (longest-processing-time-first keeps the last compute units busy).
     const int seq = blockIdx.y, kv = blockIdx.x;
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
-    const int rem = (int)gridDim.z - (int)blockIdx.z, kb = (len + 127) / 128 - rem;
+    const int part = (int)blockIdx.z / p.n_blocks;
+    const int rem = p.n_blocks - ((int)blockIdx.z - part * p.n_blocks), kb = (len + 127) / 128 - rem;
     if (kb < 0) return;
+    // this work-group's query heads h_first .. h_end-1: the group's, or a part of them
+    const int qt0 = (kb * 128) / kTileRows;
+    const int nqt = (len + kTileRows - 1) / kTileRows - qt0;
+    const int G = p.Hq / p.Hkv;
+    int head_tiles = nqt;
+    if constexpr (kPrefix) head_tiles += prefix_child_tiles(p, seq);
+    int part_heads;
+    const int parts = dkv_parts(p, G, head_tiles, part_heads);
+    if (part >= parts) return;
+    const int h_first = kv * G + part * part_heads, h_end = min(h_first + part_heads, kv * G + G);
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int G = p.Hq / p.Hkv;
     const int j0 = kb * 128 + wave * 32;  // this wave's first key (index inside the sequence)
 
     // K, V fragments of the wave's 32 keys stay in registers
@@ -230,13 +262,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     const uint32_t lane_d = frag_d_lane<kD>(lane), lane_r0 = frag_rows_lane<kD>(lane, 0), lane_r1 = frag_rows_lane<kD>(lane, 1);
     uint32_t voff[kLoads];
     tile_voffsets<kD>(voff, p.ldq, wave, lane);
-    const int qt0 = (kb * 128) / kTileRows;
-    const int nqt = (len + kTileRows - 1) / kTileRows - qt0;
-    int n_it = G * nqt;
-    if constexpr (kPrefix) {
-        for (int c = seq + 1; c < p.n_seqs; ++c)
-            if (p.prefix[c] == seq) n_it += G * ((p.cu[c + 1] - p.cu[c] + kTileRows - 1) / kTileRows);
-    }
+    const int n_it = (h_end - h_first) * head_tiles;
     const float sl2 = p.scale * kLog2e;
 
     // The tile stream: for the key block's own sequence and then (kPrefix) every sequence that names it as
@@ -246,7 +272,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     // others, which need none -- rows and keys past the end of the sequence are zero-filled by the loads, so
     // they contribute exactly nothing to rows that are stored.  n_mask iterations take the masked code.
     const int n_diag = kPrefix ? nqt : min(2, nqt);
-    const int n_mask = kPrefix ? n_it : G * n_diag;
+    const int n_mask = kPrefix ? n_it : (h_end - h_first) * n_diag;
     struct Cursor {
         int c, row0, n;         // sequence of the queries, its first row in the batch, its length
         int qt_first, qt_end;   // its tiles that this key block meets in the current pass
@@ -255,8 +281,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     auto advance = [&](Cursor& q) {
         if (++q.qt < q.qt_end) return;
         q.qt = q.qt_first;
-        if (++q.h < kv * G + G) return;
-        q.h = kv * G;
+        if (++q.h < h_end) return;
+        q.h = h_first;
         if constexpr (!kPrefix) {
             if (q.qt_first == qt0 && nqt > n_diag) {  // second pass: the tiles past the diagonal
                 q.qt_first = q.qt = qt0 + n_diag;
@@ -352,7 +378,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
         dma4(d.sc, st + sc_lds, sc_voff);
     };
     // Four LDS stages, tile t in stage t & 3; iteration `it` works on tiles it and it+1 and loads tile it+3.
-    Cursor q_ld{seq, seq_start, len, qt0, qt0 + n_diag, kv * G, qt0};
+    Cursor q_ld{seq, seq_start, len, qt0, qt0 + n_diag, h_first, qt0};
     Meta m_cur = meta_of(q_ld);
     issue_tile(desc_of(q_ld, 0 < n_it), lds0);
     advance(q_ld);
@@ -530,6 +556,21 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
     // accumulator element e of block nb: key row j0 + 8*(e>>2) + 4*half + (e&3), column nb*32 + (lane&31)
+    if (parts > 1) {
+        float* ws = p.partial + (((long long)part * p.T + seq_start) * p.Hkv + kv) * (2 * kD) + (lane & 31);
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int j = j0 + 8 * (e >> 2) + 4 * half + (e & 3);
+                if (j < len) {
+                    float* row = ws + (long long)j * p.Hkv * (2 * kD) + nb * 32;
+                    row[0] = dK[nb][e];
+                    row[kD] = dV[nb][e];
+                }
+            }
+        return;
+    }
     if (p.rope_log2_base > 0.f) rope_backward_rows<kD>(dK, p, seq_start, j0, len, lane);
     __bf16* dKb = p.dK + (long long)seq_start * p.ldo + kv * kD;
     __bf16* dVb = p.dV + (long long)seq_start * p.ldo + kv * kD;
@@ -544,6 +585,58 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
                 dVb[off] = (__bf16)dV[nb][e];
             }
         }
+}
+
+// Sum of the partial dK, dV of the key blocks that were cut (in the order of the parts), RoPE backward, one rounding.
+// blockIdx.z: 32 keys of a sequence; kD / 4 threads to a row, four columns of the lower half of dK and their partners
+// or eight of dV each.
+template <int kD, bool kPrefix>
+__global__ __launch_bounds__(256) void k_dkv_finish(AttnMfmaParams p) {
+    const int seq = blockIdx.y, kv = blockIdx.x;
+    const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
+    const int row0 = (int)blockIdx.z * 32, kb = row0 / 128;
+    if (row0 >= len) return;
+    int tiles = (len + kTileRows - 1) / kTileRows - 2 * kb;
+    if constexpr (kPrefix) tiles += prefix_child_tiles(p, seq);
+    int heads;
+    const int parts = dkv_parts(p, p.Hq / p.Hkv, tiles, heads);
+    if (parts < 2) return;
+    constexpr int kRowThreads = kD / 4;
+    const int c = (int)threadIdx.x % kRowThreads;
+    const bool is_k = c < kRowThreads / 2;
+    // columns c0 .. c0+3 and c1 .. c1+3 of [dK | dV]
+    const int c0 = is_k ? 4 * c : kD + 8 * (c - kRowThreads / 2), c1 = is_k ? c0 + kD / 2 : c0 + 4;
+    const long long pitch = (long long)p.T * p.Hkv * (2 * kD);
+    for (int r = row0 + (int)threadIdx.x / kRowThreads; r < min(row0 + 32, len); r += 256 / kRowThreads) {
+        const float* src = p.partial + ((long long)(seq_start + r) * p.Hkv + kv) * (2 * kD);
+        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+        for (int k = 0; k < parts; ++k) {
+            a += *reinterpret_cast<const f32x4*>(src + k * pitch + c0);
+            b += *reinterpret_cast<const f32x4*>(src + k * pitch + c1);
+        }
+        if (is_k) {
+            if (p.rope_log2_base > 0.f) {
+                const int pos = p.positions ? p.positions[seq_start + r] : r;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float theta = __builtin_amdgcn_exp2f(-(float)(c0 + e) * (2.0f / kD) * p.rope_log2_base);
+                    float sn, cs;
+                    __sincosf((float)pos * theta, &sn, &cs);
+                    const float x = a[e], y = b[e];
+                    a[e] = x * cs + y * sn;
+                    b[e] = y * cs - x * sn;
+                }
+            }
+            a *= p.scale;
+            b *= p.scale;
+        }
+        __bf16* dst = (is_k ? p.dK : p.dV) + (long long)(seq_start + r) * p.ldo + kv * kD - (is_k ? 0 : kD);
+        bf16x4 oa, ob;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { oa[e] = (__bf16)a[e]; ob[e] = (__bf16)b[e]; }
+        *reinterpret_cast<bf16x4*>(dst + c0) = oa;
+        *reinterpret_cast<bf16x4*>(dst + c1) = ob;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -860,9 +953,52 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
     }
 }
 
+// Which key blocks the dK/dV kernel cuts (max_parts 1: none), and the longest sequence.  A compute unit holds one
+// work-group, at about 2 us a tile and 11 us besides, so a launch of few work-groups lasts as long as its longest one:
+// blocks beyond 1.2 even shares of all tiles are cut.  The second kernel and the partial sums take 9 us: at least ten
+// tiles have to come off the longest block.  With more work-groups than compute units by an eighth the dispatcher, which
+// hands them out in a fixed order over the shader engines, fills the chip no better with parts than without.  Measured
+// (dK/dV and the sum of the parts, 32/8 heads of 128): one sequence of 512 tokens 62 -> 39 us, 1024 119 -> 54 us, 2048
+// 230 -> 159 us, 1239 + 1057 + 705 146 -> 113 us, 4 x 1024 153 -> 144 us; not cut: 8 x 512 96 us (cut: 99), 6001 tokens
+// in 7 sequences 166 us (cut: 172 .. 208).  Heads of 64, 5 sequences of 4099 tokens 115 -> 103 us.
+inline int plan_dkv_parts(const AttnArgs& a, AttnMfmaParams& p, int& longest) {
+    p.max_parts = 1;
+    p.part_len = 1 << 30;
+    p.partial = nullptr;
+    const int G = a.Hq / a.Hkv;
+    const size_t part_bytes = (size_t)a.T * a.Hkv * 2 * a.D * sizeof(float);
+    const int* cu = a.cu_seqlens_host;
+    int child[kMaxPrefixSeqs];  // tiles of the sequences that name this one (batches with prefixes have no more sequences)
+    if (a.prefix_host) {
+        std::fill(child, child + a.n_seqs, 0);
+        for (int s = 0; s < a.n_seqs; ++s)
+            if (a.prefix_host[s] >= 0) child[a.prefix_host[s]] += ceil_div(cu[s + 1] - cu[s], kTileRows);
+    }
+    long long total = 0, most = 0, n_blocks = 0;
+    for (int s = 0; s < a.n_seqs; ++s) {
+        const int len = cu[s + 1] - cu[s];
+        if (len == 0) continue;
+        longest = std::max(longest, len);
+        const long long tiles = ceil_div(len, kTileRows), blocks = ceil_div(len, 128), more = a.prefix_host ? child[s] : 0;
+        total += blocks * (tiles + more) - blocks * (blocks - 1);  // sum over its blocks of tiles - 2 kb + more
+        most = std::max(most, tiles + more);
+        n_blocks += blocks;
+    }
+    int n_cu = 0;
+    ALCH_TRY(compute_units(&n_cu));
+    const long long part_len = std::max<long long>(total * G * a.Hkv * 6 / 5 / n_cu, kMinPartTiles);
+    if (!a.scratch || part_bytes == 0 || n_blocks * a.Hkv > n_cu + n_cu / 8 || most * G < part_len + 10) return ALCH_OK;
+    const int max_parts = (int)std::min<size_t>(std::min(G, 8), a.scratch_bytes / part_bytes);
+    if (max_parts < 2 || (long long)p.n_blocks * max_parts > 65535) return ALCH_OK;
+    p.max_parts = max_parts;
+    p.part_len = (int)part_len;
+    p.partial = static_cast<float*>(a.scratch);
+    return ALCH_OK;
+}
+
 template <int kD>
 int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
-    AttnMfmaParams p;
+    AttnMfmaParams p{};
     p.Q = (const __bf16*)a.Q; p.K = (const __bf16*)a.K; p.V = (const __bf16*)a.V; p.dO = (const __bf16*)a.dO;
     p.O = (const __bf16*)a.O; p.LSE = a.LSE; p.delta = a.delta; p.lse2 = a.delta + (size_t)a.T * a.Hq;
     p.positions = a.positions; p.rope_log2_base = a.rope_base > 0.f ? log2f(a.rope_base) : 0.f;
@@ -873,11 +1009,20 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     const int nb = ceil_div(a.max_seqlen, 128);
     if (nb <= 0 || a.n_seqs <= 0) return ALCH_OK;
     if (nb > 65535 || a.n_seqs > 65535) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
+    p.T = a.T;
+    p.n_blocks = nb;
+    int longest = 0;
+    ALCH_TRY(plan_dkv_parts(a, p, longest));
+    const bool cut = p.max_parts > 1;
     k_attn_bwd_dq_mfma<kD><<<dim3(a.Hq, a.n_seqs, nb), 256, 0, stream>>>(p);   // also writes delta
-    if (a.prefix)
-        k_attn_bwd_dkv_mfma<kD, true><<<dim3(a.Hkv, a.n_seqs, nb), 256, 0, stream>>>(p);
-    else
-        k_attn_bwd_dkv_mfma<kD, false><<<dim3(a.Hkv, a.n_seqs, nb), 256, 0, stream>>>(p);
+    const dim3 grid(a.Hkv, a.n_seqs, nb * p.max_parts), grid_finish(a.Hkv, a.n_seqs, ceil_div(longest, 32));
+    if (a.prefix) {
+        k_attn_bwd_dkv_mfma<kD, true><<<grid, 256, 0, stream>>>(p);
+        if (cut) k_dkv_finish<kD, true><<<grid_finish, 256, 0, stream>>>(p);
+    } else {
+        k_attn_bwd_dkv_mfma<kD, false><<<grid, 256, 0, stream>>>(p);
+        if (cut) k_dkv_finish<kD, false><<<grid_finish, 256, 0, stream>>>(p);
+    }
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }

@@ -28,6 +28,7 @@
 //     share a tile, each taking 1/s of the contraction and leaving an fp32 partial tile in a scratch
 //     buffer; k_gemm_split_finish adds the s partials in a fixed order and writes the output
 //     (deterministic, no atomics).
+#include <atomic>
 #include "gemm_mfma_common.h"
 
 namespace alch {
@@ -605,6 +606,20 @@ static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, bool a_kma
     return pair < big;
 }
 
+int compute_units(int* n_cu) {
+    static std::atomic<int> known{0};
+    int n = known.load(std::memory_order_relaxed);
+    if (n == 0) {
+        int dev = 0, v = 0;
+        ALCH_HIP_TRY(hipGetDevice(&dev));
+        ALCH_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
+        n = v > 8 ? v / 8 * 8 : 8;
+        known.store(n, std::memory_order_relaxed);
+    }
+    *n_cu = n;
+    return ALCH_OK;
+}
+
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     MfmaGemmParams p;
     p.M = d.M;
@@ -636,13 +651,8 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     p.ldgu = d.ldgu;
     p.act_out = static_cast<__bf16*>(d.act_out);
     const int nt = p.tiles_m * p.tiles_n;
-    static int n_cu = 0;
-    if (n_cu == 0) {
-        int dev = 0, v = 0;
-        ALCH_HIP_TRY(hipGetDevice(&dev));
-        ALCH_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
-        n_cu = v > 8 ? v / 8 * 8 : 8;
-    }
+    int n_cu = 0;
+    ALCH_TRY(compute_units(&n_cu));
     float* split_ws = aligned16(d.split_ws) ? static_cast<float*>(d.split_ws) : nullptr;
     const BigPlan plan = big_plan(p, d.a_kmajor, n_cu, split_ws ? d.split_ws_bytes : 0);
     if (pair_is_better(p, plan, d.a_kmajor, d.b_kmajor, n_cu, split_ws != nullptr, d.keep_parts)) {

@@ -152,7 +152,12 @@ struct AttnArgs {
     // rope_base > 0: dQ and dK come out already rotated by minus the RoPE angle (RoPE backward)
     const int* positions = nullptr;  // device [T] or null (index inside the sequence)
     float rope_base = 0.f;
+    // optional: fp32 partial sums of dK, dV where the key blocks are too few or too unequal for the chip; 16-byte aligned,
+    // any size (T * Hkv * 2 * D floats for each of up to 8 parts are made use of)
+    void* scratch = nullptr;
+    size_t scratch_bytes = 0;
 };
+int compute_units(int* n_cu);  // of the current device, a multiple of 8
 int launch_attn_bwd(const AttnArgs& a, hipStream_t stream);
 int launch_attn_bwd_generic(const AttnArgs& a, hipStream_t stream);
 bool attn_mfma_supported(const AttnArgs& a);
