@@ -1,10 +1,10 @@
 // Capture/pack: mask scan and row gather (Section 4.1 of the paper: only the tokens of the
 // prefill that are to be trained on are recorded; Section 5: one record per layer).
 //
-// The scan is one single-work-group kernel for batches of up to 262,144 tokens, and beyond that four small
-// kernels over the byte mask (per-block popcount, scan of the block counts, index fill, per-sequence counts)
-// with the block counts in caller-provided scratch; the gather runs one work-group per kept row,
-// moving 16 bytes per lane per access.  Everything is bit-exact and
+// Batches of up to 4096 tokens take one launch for scan and gather.  The scan of longer ones is one kernel for batches
+// of up to 262,144 tokens, and beyond that four small kernels over the byte mask (per-block popcount, scan of the block
+// counts, index fill, per-sequence counts) with the block counts in caller-provided scratch; the gather runs one
+// work-group per kept row, moving 16 bytes per lane per access.  Everything is bit-exact and
 // deterministic: the output order is the ascending token order.
 #include "common.h"
 #include "kernels.h"
@@ -14,6 +14,10 @@ namespace alch {
 static constexpr int kTokPerThread = 16;
 static constexpr int kScanThreads = 256;
 static constexpr int kTokPerBlock = kTokPerThread * kScanThreads;  // 4096
+static constexpr int kSmallRows = 256;  // up to so many rows a call of at most 4096 tokens has a work-group per row and stream
+
+// 0x80 in every byte of w that is not zero
+__device__ __forceinline__ uint32_t nonzero_flags(uint32_t w) { return (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u; }
 
 __device__ __forceinline__ int nonzero_bytes16(const uint8_t* __restrict__ mask, int t0, int T, uint32_t& bits) {
     // bits: bit i set <=> mask[t0+i] != 0 (tokens beyond T count as dropped)
@@ -22,10 +26,8 @@ __device__ __forceinline__ int nonzero_bytes16(const uint8_t* __restrict__ mask,
         uint4 v = *reinterpret_cast<const uint4*>(mask + t0);
         uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                if ((w[i] >> (8 * b)) & 0xffu) bits |= 1u << (4 * i + b);
+        for (int i = 0; i < 4; ++i)  // the flags of four bytes, moved together by one multiplication
+            bits |= ((((nonzero_flags(w[i]) >> 7) * 0x01020408u) >> 24) & 0xfu) << (4 * i);
     } else {
         for (int i = 0; i < kTokPerThread; ++i)
             if (t0 + i < T && mask[t0 + i] != 0) bits |= 1u << i;
@@ -124,65 +126,59 @@ __global__ __launch_bounds__(64) void k_pack_cu(const uint8_t* __restrict__ mask
 }
 
 // ---- the whole scan in one launch, for batches of up to kOneLaunchTokens tokens ------------------------
-// One work-group of 1024 threads; thread i owns the tokens [i * chunk, (i + 1) * chunk) with chunk a multiple
-// of 16 (<= 256): it counts its kept tokens, the block scans the 1024 counts, and the thread writes the indices
-// of its kept tokens; then one thread per sequence boundary forms cu_kept from the scanned counts.  A prefill
-// batch of the paper's sizes (tens of thousands of tokens) is a mask of tens of kilobytes: four launches of the
-// general path cost more than the work.
-static constexpr int kOneLaunchThreads = 1024;
-static constexpr int kOneLaunchTokens = kOneLaunchThreads * 256;
+// One work-group per 4096 tokens.  Each counts all of the mask before its tokens by itself (the masks of a prefill batch
+// are tens of kilobytes, read from L2), so that nothing is handed from one to the next; then it writes the indices of its
+// kept tokens and cu_kept of the sequence boundaries among them.  Bound by latency: the last work-group's loads, four in
+// flight.  70,001 tokens: 22 -> 6 us against one work-group for the whole mask, 32,768: 9.5 -> 8 us.  Every work-group
+// reads what lies before it, so at some length the four launches of the general path are the shorter way.
+static constexpr int kOneLaunchTokens = 1 << 18;
 
-__global__ __launch_bounds__(kOneLaunchThreads) void k_pack_scan_one(const uint8_t* __restrict__ mask, int T, int chunk,
-                                                                      const int* __restrict__ cu_seqlens, int n_bounds,
-                                                                      int* __restrict__ kept_index, int* __restrict__ cu_kept,
-                                                                      int* __restrict__ n_kept_and_status, long long capacity) {
-    __shared__ int prefix[kOneLaunchThreads];            // kept tokens before each thread's chunk
-    __shared__ int wave_sum[kOneLaunchThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t_begin = tid * chunk;
+__global__ __launch_bounds__(kScanThreads) void k_pack_scan(const uint8_t* __restrict__ mask, int T,
+                                                            const int* __restrict__ cu_seqlens, int n_bounds,
+                                                            int* __restrict__ kept_index, int* __restrict__ cu_kept,
+                                                            int* __restrict__ n_kept_and_status, long long capacity) {
+    __shared__ int prefix[kScanThreads];  // kept tokens before each thread's sixteen
+    const int tid = threadIdx.x, block0 = blockIdx.x * kTokPerBlock, t0 = block0 + tid * kTokPerThread;
     int count = 0;
-    for (int t0 = t_begin; t0 < t_begin + chunk && t0 < T; t0 += kTokPerThread) {
-        uint32_t bits;
-        count += nonzero_bytes16(mask, t0, T, bits);
+#pragma unroll 4
+    for (int b = 0; b < (int)blockIdx.x; ++b) {
+        const uint4 v = *reinterpret_cast<const uint4*>(mask + b * kTokPerBlock + tid * kTokPerThread);
+        count += __popc(nonzero_flags(v.x)) + __popc(nonzero_flags(v.y)) + __popc(nonzero_flags(v.z)) + __popc(nonzero_flags(v.w));
     }
-    const int inc = wave_inclusive_scan(count);
-    if (lane == 63) wave_sum[wave] = inc;
-    __syncthreads();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < kOneLaunchThreads / 64; ++w) {
-        const int sw = wave_sum[w];
-        if (w < wave) before += sw;
-        total += sw;
-    }
-    const int ex = before + inc - count;
+    uint32_t bits;
+    const int own = nonzero_bytes16(mask, t0, T, bits);
+    int before, total;
+    block_exclusive_scan(count, before);
+    int ex = before + block_exclusive_scan(own, total);
     prefix[tid] = ex;
-    if (tid == 0) {
-        n_kept_and_status[0] = total;
-        n_kept_and_status[1] = (long long)total > capacity ? 1 : 0;
-    }
-    long long pos = ex;
-    for (int t0 = t_begin; t0 < t_begin + chunk && t0 < T; t0 += kTokPerThread) {
-        uint32_t bits;
-        nonzero_bytes16(mask, t0, T, bits);
-        while (bits) {
-            const int i = __ffs(bits) - 1;
-            bits &= bits - 1;
-            if (pos < capacity) kept_index[pos] = t0 + i;
-            ++pos;
-        }
+    if (tid == 0 && blockIdx.x == gridDim.x - 1) {
+        n_kept_and_status[0] = before + total;
+        n_kept_and_status[1] = (long long)(before + total) > capacity ? 1 : 0;
     }
     __syncthreads();
-    for (int s = tid; s < n_bounds; s += kOneLaunchThreads) {
+    // boundaries among this work-group's tokens; what lies at or behind the end of the last one's is its own too
+    for (int s = tid; s < n_bounds; s += kScanThreads) {
         const int end = cu_seqlens[s];
-        const int owner = end / chunk;  // thread whose chunk holds token `end` (>= 1024 only for end == T at full chunks)
-        int c = owner < kOneLaunchThreads ? prefix[owner] : total;
-        for (int t = owner * chunk; t < end; ++t) c += mask[t] != 0;
+        if (end / kTokPerBlock != (int)blockIdx.x && !(blockIdx.x == gridDim.x - 1 && end >= block0 + kTokPerBlock)) continue;
+        int c = before + total;
+        if (end < block0 + kTokPerBlock) {
+            const int owner = (end - block0) / kTokPerThread;
+            c = prefix[owner];
+            for (int t = block0 + owner * kTokPerThread; t < end; ++t) c += mask[t] != 0;
+        }
         cu_kept[s] = c;
+    }
+    while (bits) {
+        const int i = __ffs(bits) - 1;
+        bits &= bits - 1;
+        if (ex < capacity) kept_index[ex] = t0 + i;
+        ++ex;
     }
 }
 
 // ---- gather ---------------------------------------------------------------------------
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 struct GatherArgs {
     const char* src[kMaxStreamsPerLaunch];
@@ -191,6 +187,27 @@ struct GatherArgs {
     unsigned long long src_stride[kMaxStreamsPerLaunch];
     int n;
 };
+
+// Row t of stream k to row r of its destination, by the whole work-group.
+template <typename V>
+__device__ __forceinline__ void copy_row(const GatherArgs& a, int k, long long t, long long r) {
+    constexpr unsigned long long kStep = 256ull * sizeof(V);
+    const unsigned long long rb = a.row_bytes[k];
+    const char* __restrict__ s = a.src[k] + (unsigned long long)t * a.src_stride[k];
+    char* __restrict__ d = a.dst[k] + (unsigned long long)r * rb;
+    unsigned long long off = (unsigned long long)threadIdx.x * sizeof(V);
+    // two independent accesses in flight per lane; non-temporal both ways (nothing is reused)
+    for (; off + kStep < rb; off += 2 * kStep) {
+        V v0 = __builtin_nontemporal_load(reinterpret_cast<const V*>(s + off));
+        V v1 = __builtin_nontemporal_load(reinterpret_cast<const V*>(s + off + kStep));
+        __builtin_nontemporal_store(v0, reinterpret_cast<V*>(d + off));
+        __builtin_nontemporal_store(v1, reinterpret_cast<V*>(d + off + kStep));
+    }
+    for (; off < rb; off += kStep) {
+        V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(s + off));
+        __builtin_nontemporal_store(v, reinterpret_cast<V*>(d + off));
+    }
+}
 
 // One work-group per kept row (the grid is sized for the most rows the call can produce; work-groups
 // beyond n_kept leave at once).  Letting the hardware dispatcher hand out rows measured faster than a
@@ -201,34 +218,70 @@ __global__ __launch_bounds__(256) void k_pack_gather(GatherArgs a, const int* __
                                                      long long capacity) {
     long long n_rows = n_kept_and_status[0];
     if (n_rows > capacity) n_rows = capacity;
-    constexpr unsigned long long kStep = 256ull * sizeof(V);
-    for (long long r = blockIdx.x; r < n_rows; r += gridDim.x) {
-        const long long t = kept_index[r];
-        for (int k = 0; k < a.n; ++k) {
-            const unsigned long long rb = a.row_bytes[k];
-            const char* __restrict__ s = a.src[k] + (unsigned long long)t * a.src_stride[k];
-            char* __restrict__ d = a.dst[k] + (unsigned long long)r * rb;
-            unsigned long long off = (unsigned long long)threadIdx.x * sizeof(V);
-            // two independent accesses in flight per lane; non-temporal both ways (nothing is reused)
-            for (; off + kStep < rb; off += 2 * kStep) {
-                V v0 = __builtin_nontemporal_load(reinterpret_cast<const V*>(s + off));
-                V v1 = __builtin_nontemporal_load(reinterpret_cast<const V*>(s + off + kStep));
-                __builtin_nontemporal_store(v0, reinterpret_cast<V*>(d + off));
-                __builtin_nontemporal_store(v1, reinterpret_cast<V*>(d + off + kStep));
-            }
-            for (; off < rb; off += kStep) {
-                V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(s + off));
-                __builtin_nontemporal_store(v, reinterpret_cast<V*>(d + off));
-            }
-        }
-    }
+    for (long long r = blockIdx.x; r < n_rows; r += gridDim.x)
+        for (int k = 0; k < a.n; ++k) copy_row<V>(a, k, kept_index[r], r);
 }
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// Scan and gather of a batch of at most 4096 tokens in one launch: every work-group finds its row's token in the mask by
+// itself (a 16-byte load a thread and a block scan, about 1 us), the first one writes the counts.  One prompt of 317
+// tokens, 79 of them kept: bound by launches and by the chain of loads of a row, so blockIdx.y may deal out the streams
+// of a row.
+template <typename V>
+__global__ __launch_bounds__(kScanThreads) void k_pack_small(GatherArgs a, const uint8_t* __restrict__ mask, int T,
+                                                             const int* __restrict__ cu_seqlens, int n_bounds,
+                                                             int* __restrict__ kept_index, int* __restrict__ cu_kept,
+                                                             int* __restrict__ n_kept_and_status, long long capacity) {
+    __shared__ int token;
+    __shared__ int prefix[kScanThreads];
+    uint32_t bits;
+    const int tid = threadIdx.x, c = nonzero_bytes16(mask, tid * kTokPerThread, T, bits);
+    int total;
+    const int ex = block_exclusive_scan(c, total), r = blockIdx.x;
+    if (r >= ex && r < ex + c) {
+        for (int i = ex; i < r; ++i) bits &= bits - 1;
+        token = tid * kTokPerThread + __ffs(bits) - 1;
+        if (blockIdx.y == 0 && r < capacity) kept_index[r] = token;
+    }
+    const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+    if (first) prefix[tid] = ex;
+    __syncthreads();
+    if (first) {
+        if (tid == 0) {
+            n_kept_and_status[0] = total;
+            n_kept_and_status[1] = (long long)total > capacity ? 1 : 0;
+        }
+        for (int s = tid; s < n_bounds; s += kScanThreads) {
+            const int end = cu_seqlens[s], owner = end / kTokPerThread;
+            int n = total;
+            if (owner < kScanThreads) {
+                n = prefix[owner];
+                for (int t = owner * kTokPerThread; t < end; ++t) n += mask[t] != 0;
+            }
+            cu_kept[s] = n;
+        }
+    }
+    if (r >= total || r >= capacity) return;
+    for (int k = blockIdx.y; k < a.n; k += gridDim.y) copy_row<V>(a, k, token, r);
+}
 
 size_t pack_workspace_bytes(int total_tokens) {
     int nblocks = ceil_div(total_tokens > 0 ? total_tokens : 1, kTokPerBlock);
     return round_up((size_t)nblocks * sizeof(int), 256) + 256;
+}
+
+// Streams base .. of a call, at most kMaxStreamsPerLaunch of them; false: some row is not made of aligned 16-byte pieces.
+static bool gather_args(GatherArgs& a, int n_streams, const alch_stream* streams, int base) {
+    a.n = n_streams - base < kMaxStreamsPerLaunch ? n_streams - base : kMaxStreamsPerLaunch;
+    bool vec16 = true;
+    for (int k = 0; k < a.n; ++k) {
+        const alch_stream& s = streams[base + k];
+        a.src[k] = static_cast<const char*>(s.src);
+        a.dst[k] = static_cast<char*>(s.dst);
+        a.row_bytes[k] = s.row_bytes;
+        a.src_stride[k] = s.src_row_stride_bytes;
+        vec16 = vec16 && aligned16(s.src) && aligned16(s.dst) && s.row_bytes % 16 == 0 && s.src_row_stride_bytes % 16 == 0;
+    }
+    return vec16;
 }
 
 int launch_pack(const uint8_t* mask, int T, const int* cu_seqlens, int n_seqs, int n_streams,
@@ -236,18 +289,34 @@ int launch_pack(const uint8_t* mask, int T, const int* cu_seqlens, int n_seqs, i
                 int* n_kept_and_status, void* workspace, hipStream_t stream, bool traced) {
     int* block_offsets = static_cast<int*>(workspace);
     const int nblocks = T > 0 ? ceil_div(T, kTokPerBlock) : 0;
+    const long long max_rows = (long long)T < capacity ? (long long)T : capacity;
+    if (T <= kTokPerBlock && max_rows > 0 && n_streams > 0 && n_streams <= kMaxStreamsPerLaunch) {
+        double row_bytes_rw = 0;
+        for (int k = 0; k < n_streams; ++k) row_bytes_rw += 2.0 * (double)streams[k].row_bytes;
+        TraceScope ts(traced ? kTracePackGather : kTraceRowOps, 0.0, row_bytes_rw, stream);
+        GatherArgs a;
+        const bool vec16 = gather_args(a, n_streams, streams, 0);
+        const dim3 grid((unsigned)max_rows, max_rows <= kSmallRows ? n_streams : 1);
+        if (vec16)
+            k_pack_small<u32x4><<<grid, kScanThreads, 0, stream>>>(a, mask, T, cu_seqlens, n_seqs + 1, kept_index, cu_kept,
+                                                                   n_kept_and_status, capacity);
+        else
+            k_pack_small<unsigned int><<<grid, kScanThreads, 0, stream>>>(a, mask, T, cu_seqlens, n_seqs + 1, kept_index, cu_kept,
+                                                                          n_kept_and_status, capacity);
+        ALCH_HIP_TRY(hipGetLastError());
+        return ALCH_OK;
+    }
     if (T <= kOneLaunchTokens) {
         TraceScope ts(traced ? kTracePackScan : kTraceRowOps, 0.0, (double)T + 4.0 * (n_seqs + 1), stream);
-        const int chunk = (int)round_up((size_t)ceil_div(T > 0 ? T : 1, kOneLaunchThreads), kTokPerThread);
-        k_pack_scan_one<<<1, kOneLaunchThreads, 0, stream>>>(mask, T, chunk, cu_seqlens, n_seqs + 1, kept_index, cu_kept,
-                                                             n_kept_and_status, capacity);
+        k_pack_scan<<<nblocks > 0 ? nblocks : 1, kScanThreads, 0, stream>>>(mask, T, cu_seqlens, n_seqs + 1, kept_index, cu_kept,
+                                                                            n_kept_and_status, capacity);
     } else {
-    TraceScope ts(traced ? kTracePackScan : kTraceRowOps, 0.0, (double)T + 4.0 * (n_seqs + 1), stream);
-    if (nblocks > 0) k_pack_count<<<nblocks, kScanThreads, 0, stream>>>(mask, T, block_offsets);
-    k_pack_scan_blocks<<<1, kScanThreads, 0, stream>>>(block_offsets, nblocks, n_kept_and_status, capacity);
-    if (nblocks > 0) k_pack_fill<<<nblocks, kScanThreads, 0, stream>>>(mask, T, block_offsets, kept_index, capacity);
-    k_pack_cu<<<n_seqs + 1, 64, 0, stream>>>(mask, cu_seqlens, n_seqs + 1, block_offsets, nblocks,
-                                              n_kept_and_status, cu_kept);
+        TraceScope ts(traced ? kTracePackScan : kTraceRowOps, 0.0, (double)T + 4.0 * (n_seqs + 1), stream);
+        k_pack_count<<<nblocks, kScanThreads, 0, stream>>>(mask, T, block_offsets);
+        k_pack_scan_blocks<<<1, kScanThreads, 0, stream>>>(block_offsets, nblocks, n_kept_and_status, capacity);
+        k_pack_fill<<<nblocks, kScanThreads, 0, stream>>>(mask, T, block_offsets, kept_index, capacity);
+        k_pack_cu<<<n_seqs + 1, 64, 0, stream>>>(mask, cu_seqlens, n_seqs + 1, block_offsets, nblocks,
+                                                  n_kept_and_status, cu_kept);
     }
     ALCH_HIP_TRY(hipGetLastError());
     return launch_pack_gather(T, n_streams, streams, capacity, kept_index, n_kept_and_status, stream, traced);
@@ -267,18 +336,7 @@ int launch_pack_gather(int T, int n_streams, const alch_stream* streams, long lo
     int grid = (int)(max_rows < (long long)kGatherGridMax ? max_rows : (long long)kGatherGridMax);
     for (int base = 0; base < n_streams; base += kMaxStreamsPerLaunch) {
         GatherArgs a;
-        a.n = n_streams - base < kMaxStreamsPerLaunch ? n_streams - base : kMaxStreamsPerLaunch;
-        bool vec16 = true;
-        for (int k = 0; k < a.n; ++k) {
-            const alch_stream& s = streams[base + k];
-            a.src[k] = static_cast<const char*>(s.src);
-            a.dst[k] = static_cast<char*>(s.dst);
-            a.row_bytes[k] = s.row_bytes;
-            a.src_stride[k] = s.src_row_stride_bytes;
-            vec16 = vec16 && aligned16(s.src) && aligned16(s.dst) && s.row_bytes % 16 == 0 &&
-                    s.src_row_stride_bytes % 16 == 0;
-        }
-        if (vec16)
+        if (gather_args(a, n_streams, streams, base))
             k_pack_gather<u32x4><<<grid, 256, 0, stream>>>(a, kept_index, n_kept_and_status, capacity);
         else
             k_pack_gather<unsigned int><<<grid, 256, 0, stream>>>(a, kept_index, n_kept_and_status, capacity);
