@@ -579,8 +579,10 @@ static BigPlan big_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t
 // The second one reads 1.5 times as much from L2 per multiply-add, which the long K pays for (8192 x 4096 x 28672: 1388
 // against 1574 us), and has no idle start and end of tile, nor as coarse a last round (4096 x 14336 x 487: 86 against
 // 60 us; 6144 x 4096 x 1024: 82 against 49; 487 x 4096 x 4096: 47 against 31; 6001 x 4096 x 6144: 262 against 239 us).
-static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, bool a_kmajor, bool b_kmajor, int n_cu, bool can_split,
-                           bool keep_parts) {
+// Whole tiles of the second one fill rounds of two work-groups per compute unit, or a last one of at most one each; the
+// tiles cut along K run beside that.  4099 x 2048 x 16384 is 17 tiles for the 32 compute units of an XCD, or 32 whole tiles
+// of half the size and one in 16 parts: 410 -> 290 us.
+static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, const PairPlan& plan, bool a_kmajor, bool b_kmajor, int n_cu) {
     if (p.m_dev || p.k_dev) return false;  // sizes that only the device knows
     double K = 0;
     for (int s = 0; s < p.n_seg; ++s) K += p.K[s];
@@ -592,17 +594,11 @@ static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, bool a_kma
     double big = tiles / cus * (big_k * K + big_fixed);
     if (tiles % cus) big += b.parts > 1 ? big_k * K / b.parts + 33.0 + swiglu_split : 0.9 * big_k * K + big_fixed;
 
-    const int tiles2 = keep_parts ? 2 * tiles : ceil_div(ceil_div(p.M, BM / 2) * ceil_div(p.N, BN), 8), rem2 = tiles2 % (2 * cus);
     const double pair_k = b_kmajor ? 0.0276 : a_kmajor ? 0.0265 : 0.0255, pair_fixed = b_kmajor ? 6.0 : a_kmajor ? 2.0 : 3.0;
-    double pair = tiles2 / (2 * cus) * (pair_k * K + pair_fixed);
-    if (rem2 > 0) {
-        int s = 1;
-        if (keep_parts) s = b.parts;
-        else if (can_split && rem2 <= cus) s = std::min(std::min(cus / rem2, 16), (int)(K / (16 * BK)));
-        if (s > 1) pair += (rem2 * s > cus ? pair_k * K / s + 27.0 : 0.52 * pair_k * K / s + 17.0) + swiglu_split;
-        else if (rem2 <= cus) pair += 0.52 * pair_k * K + 4.0;
-        else pair += 0.9 * pair_k * K + pair_fixed;
-    }
+    double pair = plan.q_end / (2 * cus) * (pair_k * K + pair_fixed);
+    const int rest = plan.q_end % (2 * cus), cut = plan.per_xcd - plan.q_end, s = plan.parts;
+    if (rest > 0) pair += rest <= cus ? 0.52 * pair_k * K + 4.0 : 0.9 * pair_k * K + pair_fixed;
+    if (cut > 0) pair += (cut * s > cus ? pair_k * K / s + 27.0 : 0.52 * pair_k * K / s + 17.0) + swiglu_split;
     return pair < big;
 }
 
@@ -655,13 +651,11 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     ALCH_TRY(compute_units(&n_cu));
     float* split_ws = aligned16(d.split_ws) ? static_cast<float*>(d.split_ws) : nullptr;
     const BigPlan plan = big_plan(p, d.a_kmajor, n_cu, split_ws ? d.split_ws_bytes : 0);
-    if (pair_is_better(p, plan, d.a_kmajor, d.b_kmajor, n_cu, split_ws != nullptr, d.keep_parts)) {
-        // (a 256x256 tile is two tiles of the other kernel, numbered in the same order)
-        if (d.keep_parts)
-            return launch_gemm_pair(p, d.a_kmajor, d.b_kmajor, 2 * p.tiles_m, 2 * ceil_div(nt, 8), 2 * plan.q_end, plan.parts, plan.per,
-                                    split_ws, stream);
-        return launch_gemm_pair(p, d.a_kmajor, d.b_kmajor, n_cu, split_ws, d.split_ws_bytes, stream);
-    }
+    // (a 256x256 tile is two tiles of the other kernel, numbered in the same order)
+    const PairPlan pair = d.keep_parts ? PairPlan{2 * ceil_div(nt, 8), 2 * plan.q_end, plan.parts, plan.per}
+                                       : pair_plan(p, d.a_kmajor, n_cu, split_ws ? d.split_ws_bytes : 0);
+    if (pair_is_better(p, plan, pair, d.a_kmajor, d.b_kmajor, n_cu))
+        return launch_gemm_pair(p, d.a_kmajor, d.b_kmajor, d.keep_parts ? 2 * p.tiles_m : ceil_div(p.M, BM / 2), pair, split_ws, stream);
     const int grid = ceil_div(nt, 8) * 8 < n_cu ? ceil_div(nt, 8) * 8 : n_cu;
     const int per_xcd = ceil_div(nt, 8), rem = per_xcd - plan.q_end;
     p.q_end = plan.q_end;

@@ -124,11 +124,11 @@ __device__ __forceinline__ void swiglu_gradient(const bf16x8& d8, const bf16x8& 
     }
 }
 
-// The kernel of 128x256 tiles.  p: operands and outputs; split_ws: scratch or null.  The second form is told how many
-// tile rows there are (the last may be empty), how many tiles an XCD has, which of them to cut, and into which parts.
-int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int n_cu, float* split_ws, size_t ws_bytes, hipStream_t stream);
-int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, int per_xcd, int q_end, int parts, int per,
-                     float* split_ws, hipStream_t stream);
+// The kernel of 128x256 tiles.  A share of per_xcd tiles per XCD (of tiles_m tile rows, the last may be empty), whole up
+// to q_end, the others in `parts` parts of `per` k-tiles each, with their partial tiles in split_ws.
+struct PairPlan { int per_xcd, q_end, parts, per; };
+PairPlan pair_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes);
+int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream);
 
 template <int I> struct IntC { static constexpr int value = I; };
 

@@ -393,14 +393,14 @@ __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
     }
 }
 
-int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, int per_xcd, int q_end, int parts, int per,
-                     float* split_ws, hipStream_t stream) {
+int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream) {
+    const int per_xcd = plan.per_xcd, q_end = plan.q_end, parts = plan.parts;
     p.tiles_m = tiles_m;
     p.tiles_n = ceil_div(p.N, PN);
     p.per_xcd = per_xcd;
     p.q_end = q_end;
     p.split_s = parts;
-    p.split_per = per;
+    p.split_per = plan.per;
     p.split_ws = split_ws;
     const int grid = 8 * (q_end + (per_xcd - q_end) * parts);
     if (a_kmajor && b_kmajor) k_gemm_pair<true, true><<<grid, 256, 0, stream>>>(p);
@@ -412,23 +412,25 @@ int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m
     return ALCH_OK;
 }
 
-int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int n_cu, float* split_ws, size_t ws_bytes, hipStream_t stream) {
-    const int tiles_m = ceil_div(p.M, PM), per_xcd = ceil_div(tiles_m * ceil_div(p.N, PN), 8), slots = 2 * n_cu / 8;
+// How the tiles of a share run: whole up to q_end, the rest in parts for one work-group per compute unit (a second one
+// would halve the length of the parts again and double the partial tiles: 487 x 4096 x 4096 41 us with 8 parts, 31 us with
+// 4).  Tiles that leave some compute units with two work-groups and the others with one are cut as well, once every
+// compute unit has a whole one: 4099 rows by 2048 are 33 tiles for the 32 units of an XCD.
+PairPlan pair_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes) {
+    const int per_xcd = ceil_div(ceil_div(p.M, PM) * ceil_div(p.N, PN), 8), cus = n_cu / 8;
+    PairPlan plan{per_xcd, per_xcd, 1, 0};
+    if (ws_bytes == 0 || p.m_dev || p.k_dev) return plan;
+    const int rem = per_xcd % cus;
+    if (rem == 0) return plan;
     int nk_total = 0;
     for (int s = 0; s < p.n_seg; ++s) nk_total += ceil_div(p.K[s], BK);
-    const int full_q = per_xcd / slots * slots, rem = per_xcd - full_q;
-    if (split_ws && !p.m_dev && !p.k_dev && rem > 0) {
-        // parts for one work-group per compute unit: a second one would halve the length of the parts again and double
-        // the partial tiles (487 x 4096 x 4096: 41 us with 8 parts, 31 us with 4)
-        int s = std::min(slots / 2 / rem, 16);
-        s = std::min(s, nk_total / 16);
-        if (s > 1 && (size_t)8 * rem * s * PM * PN * sizeof(float) <= ws_bytes) {
-            int per = ceil_div(nk_total, s);
-            if (a_kmajor) per += per & 1;  // parts start on a 64-k boundary: whole 128-byte lines of A
-            return launch_gemm_pair(p, a_kmajor, b_kmajor, tiles_m, per_xcd, full_q, s, per, split_ws, stream);
-        }
-    }
-    return launch_gemm_pair(p, a_kmajor, b_kmajor, tiles_m, per_xcd, per_xcd, 1, 0, split_ws, stream);
+    const int s = std::min(std::min(cus / rem, 16), nk_total / 16);
+    if (s < 2 || (size_t)8 * rem * s * PM * PN * sizeof(float) > ws_bytes) return plan;
+    plan.q_end = per_xcd - rem;
+    plan.parts = s;
+    plan.per = ceil_div(nk_total, s);
+    if (a_kmajor) plan.per += plan.per & 1;  // parts start on a 64-k boundary: whole 128-byte lines of A
+    return plan;
 }
 
 }  // namespace alch

@@ -11,6 +11,28 @@ from test_gpu_gemm import operands
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("M,N,Ks", [(4104, 2048, (1024, 64)), (4104, 2304, (2048,)), (6000, 2048, (1024,))])
+@pytest.mark.parametrize("a_k,b_k", [(True, False), (False, False)])
+def test_whole_tiles_beside_cut_ones(a_k, b_k, M, N, Ks):
+    # a little more than one tile for every compute unit: 33, 38 and 47 tiles for the 32 units of an XCD
+    import paper_2503_01066_amd as A_
+    rng = np.random.default_rng(M + N)
+    terms, ref = [], 0.0
+    for K in Ks:
+        A, B, r = operands(rng, M, N, K, a_k, b_k, "bf16")
+        terms.append((to_dev(A, "bf16"), to_dev(B, "bf16"), K))
+        ref = ref + r
+    ws = torch.empty(A_.lib().alch_gemm_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    outs = []
+    for _ in range(2):
+        C = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        A_.alch_gemm(M, N, terms, a_k, b_k, out=C, workspace=ws)
+        torch.cuda.synchronize()
+        assert rel_err(to_np(C), ref) < 6e-3  # one bf16 rounding of the output
+        outs.append(C)
+    assert torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("a_k,b_k", [(True, False), (False, False), (True, True), (False, True)])
 @pytest.mark.parametrize("M,N,Ks", [(8, 8, (64,)), (128, 256, (64, 128)), (136, 264, (192,)), (120, 520, (1024,)),
                                     (1000, 2048, (704,)),       # 8 x 8 tiles, no part of the contraction long enough to cut
