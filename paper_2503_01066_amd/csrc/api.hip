@@ -313,12 +313,12 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     if (T > 0 && !sv.X2) {
         if (lo && lo->A[ALCH_PROJ_O])
             return fail(ALCH_ERR_UNSUPPORTED, "saved.X2 must be given when the output projection carries an adapter");
-        ALCH_TRY(launch_masked_copy(dt, sv.X, nullptr, p.X2_re, T, H, st));
         GemmDesc d;
         d.M = T; d.N = H; d.a_kmajor = true; d.b_kmajor = true; d.dtype = dt;
         d.seg[d.n_seg++] = GemmSeg{sv.O, w.Wo, QD, QD, QD};
         d.out[d.n_out++] = GemmOut{p.X2_re, 0, H};
         d.accumulate = 1;
+        d.residual = sv.X;
         ALCH_TRY(launch_gemm(d, st));
         sv.X2 = p.X2_re;
     }
@@ -334,16 +334,17 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         const void* Wm[2] = {w.Wg, w.Wu};
         void* om[2] = {p.c_G, p.c_U};
         const void* have[2] = {sv.G, sv.U};
+        GemmDesc d;
+        d.M = T; d.N = 0; d.a_kmajor = true; d.b_kmajor = true; d.dtype = dt;
+        d.m_dev = rows_dev;
+        d.by_cols = true;
         for (int i = 0; i < 2; ++i) {
             if (have[i]) continue;
-            GemmDesc d;
-            d.M = T; d.N = F; d.a_kmajor = true; d.b_kmajor = true; d.dtype = dt;
-            d.m_dev = rows_dev;
-            d.seg[d.n_seg++] = GemmSeg{p.Hn, Wm[i], H, H, H};
-            d.out[d.n_out++] = GemmOut{om[i], 0, F};
-            ALCH_TRY(launch_gemm(d, st));
+            d.out[d.n_out++] = GemmOut{om[i], d.N, F, Wm[i]};
+            d.N += F;
         }
-        return ALCH_OK;
+        d.seg[d.n_seg++] = GemmSeg{p.Hn, d.out[0].B, H, H, H};
+        return launch_gemm(d, st);
     };
     const int acc = wg ? (wg->accumulate != 0) : 0;
     static const alch_wgrads none = {};
@@ -1225,10 +1226,14 @@ static int layer_forward_impl(const alch_layer_shape* shape, const alch_batch* b
     const void* Ws[3] = {w->Wq, w->Wk, w->Wv};
     void* outs[3] = {rQ, rK, rV};
     const int widths[3] = {QD, KD, KD};
-    for (int i = 0; i < 3; ++i) {
-        GemmDesc d = gemm_ws(dt, T, widths[i], true, true);
-        add_seg(d, p.Hn, H, Ws[i], H, H);
-        add_out(d, outs[i], 0, widths[i]);
+    {  // [Q | K | V] in one product
+        GemmDesc d = gemm_ws(dt, T, 0, true, true);
+        d.by_cols = true;
+        for (int i = 0; i < 3; ++i) {
+            d.out[d.n_out++] = GemmOut{outs[i], d.N, widths[i], Ws[i]};
+            d.N += widths[i];
+        }
+        add_seg(d, p.Hn, H, Ws[0], H, H);
         ALCH_TRY(launch_gemm(d, st));
     }
     ALCH_TRY(launch_rope(dt, rQ, QD, T, s.n_q_heads, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, 1.f, st));
@@ -1238,29 +1243,30 @@ static int layer_forward_impl(const alch_layer_shape* shape, const alch_batch* b
                              batch->max_seqlen, batch->cu_seqlens, batch->cu_seqlens_host, batch->seq_prefix,
                              batch->seq_prefix_host, seq_begin, s.n_q_heads, s.n_kv_heads, D, st));
     {  // X2 = X + O Wo^T
-        ALCH_TRY(launch_masked_copy(dt, Xr, nullptr, rX2, T, H, st));
         GemmDesc d = gemm_ws(dt, T, H, true, true);
         add_seg(d, rO, QD, w->Wo, QD, QD);
         add_out(d, rX2, 0, H);
         d.accumulate = 1;
+        d.residual = Xr;
         ALCH_TRY(launch_gemm(d, st));
     }
     ALCH_TRY(launch_rmsnorm_fwd(dt, rX2, w->g2, p.Hn, T, H, s.rms_eps, st));
     const void* Wm[2] = {w->Wg, w->Wu};
     void* om[2] = {rG, rU};
-    for (int i = 0; i < 2; ++i) {
-        GemmDesc d = gemm_ws(dt, T, F, true, true);
-        add_seg(d, p.Hn, H, Wm[i], H, H);
-        add_out(d, om[i], 0, F);
+    {  // [G | U] in one product
+        GemmDesc d = gemm_ws(dt, T, 2 * F, true, true);
+        d.by_cols = true;
+        for (int i = 0; i < 2; ++i) d.out[d.n_out++] = GemmOut{om[i], i * F, F, Wm[i]};
+        add_seg(d, p.Hn, H, w->Wg, H, H);
         ALCH_TRY(launch_gemm(d, st));
     }
     ALCH_TRY(launch_swiglu_act(dt, rG, rU, p.Act, (long long)T * F, st));
     {  // Y = X2 + Act Wd^T
-        ALCH_TRY(launch_masked_copy(dt, rX2, nullptr, Yr, T, H, st));
         GemmDesc d = gemm_ws(dt, T, H, true, true);
         add_seg(d, p.Act, F, w->Wd, F, F);
         add_out(d, Yr, 0, H);
         d.accumulate = 1;
+        d.residual = rX2;
         ALCH_TRY(launch_gemm(d, st));
     }
     return ALCH_OK;

@@ -356,11 +356,29 @@ int launch_gemm(const GemmDesc& d, hipStream_t stream) {
     const double flops = dev_sized ? 0.0 : 2.0 * d.M * d.N * k_total;
     const size_t E = dtype_size(d.dtype);
     const double bytes = dev_sized ? 0.0 : ((double)d.M * k_total + (double)d.N * k_total + (double)d.M * d.N) * E;
-    if (dev_sized && !gemm_mfma_supported(d))
+    if (dev_sized && !d.by_cols && !gemm_mfma_supported(d))
         return fail(ALCH_ERR_UNSUPPORTED, "device-resident sizes need the matrix-core kernel (bf16, aligned, K %% 64 == 0)");
-    if (gemm_mfma_supported(d)) {
+    if (gemm_mfma_supported(d) && (!d.by_cols || gemm_cols_together(d))) {
         TraceScope ts(kTraceGemmMfma, flops, bytes, stream);
         return launch_gemm_mfma(d, stream);
+    }
+    if (d.by_cols) {  // one product per column range
+        for (int o = 0; o < d.n_out; ++o) {
+            GemmDesc r = d;
+            r.by_cols = false;
+            r.N = (o + 1 < d.n_out ? d.out[o + 1].m_begin : d.N) - d.out[o].m_begin;
+            r.seg[0].B = d.out[o].B;
+            r.n_out = 1;
+            r.out[0] = GemmOut{d.out[o].C, 0, d.out[o].ldc};
+            ALCH_TRY(launch_gemm(r, stream));
+        }
+        return ALCH_OK;
+    }
+    if (d.residual) {  // (C is the whole of its rows)
+        ALCH_TRY(launch_masked_copy(d.dtype, d.residual, nullptr, d.out[0].C, d.M, d.N, stream));
+        GemmDesc r = d;
+        r.residual = nullptr;
+        return launch_gemm(r, stream);
     }
     int rc = ALCH_OK;
     if (launch_gemm_in_bands(d, stream, rc)) return rc;

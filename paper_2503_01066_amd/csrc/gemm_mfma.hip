@@ -144,8 +144,9 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
             stepa = (long long)BK * lda * 2;
         }
         if (BKM) {
-            pb = (const char*)(p.B[seg] + (long long)n0 * ldb);
-            endb = (const char*)(p.B[seg] + (long long)(p.N - 1) * ldb + K);
+            const __bf16* B = p.B[p.by_cols ? range_of(p, n0) : seg];
+            pb = (const char*)(B + (long long)n0 * ldb);
+            endb = (const char*)(B + (long long)(p.N - 1) * ldb + K);
             stepb = BK * 2;
         } else {
             pb = (const char*)(p.B[seg] + n0);
@@ -334,14 +335,12 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
     // ---- epilogue.  The MFMAs were issued with the operand roles swapped, so block (i, j) holds
     // the transposed 32x32 result: this lane owns output row m = .. + i*32 + (lane&31) and, in
     // registers 4b..4b+3, the four consecutive columns n = .. + j*32 + 8b + 4*(lane>>5) + 0..3.
-    int oseg = 0;
-#pragma unroll
-    for (int s = 1; s < 3; ++s)
-        if (s < p.n_out && m0 >= p.m_begin[s]) oseg = s;
+    const bool cols = BKM && p.by_cols;
+    const int oseg = range_of(p, cols ? n0 : m0);
     __bf16* __restrict__ C = p.C[oseg];
     const long long ldc = p.ldc[oseg];
-    const int mrel0 = m0 - p.m_begin[oseg];
-    const int m_end = (oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], Mv) : Mv);
+    const int mrel0 = cols ? m0 : m0 - p.m_begin[oseg];
+    const int m_end = (!cols && oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], Mv) : Mv);
     const int half = lane >> 5;
 
     if (!p.accumulate) {
@@ -420,6 +419,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
             constexpr int i = decltype(ic)::value;
             const int ml = wm * 128 + i * 32 + (lane & 31);
             __bf16* row = C + (long long)(mrel0 + ml) * ldc;
+            const __bf16* old_row = BKM && p.residual ? p.residual + (long long)(m0 + ml) * ldc : row;
             const bool row_ok = m0 + ml < m_end;
             bf16x4 old[4][4];
 #pragma unroll
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
                     const int nn = n0 + wn * 128 + j * 32 + 8 * b + 4 * half;
-                    if (row_ok && nn < p.N) old[j][b] = *reinterpret_cast<const bf16x4*>(row + nn);
+                    if (row_ok && nn < p.N) old[j][b] = *reinterpret_cast<const bf16x4*>(old_row + nn);
                 }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -457,14 +457,13 @@ __global__ __launch_bounds__(256) void k_gemm_split_finish(MfmaGemmParams p, int
     const int band = t / band_tiles, in_band = t % band_tiles;
     const int band_rows = min(kGroupM, p.tiles_m - band * kGroupM);
     const int m0 = (band * kGroupM + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
-    int oseg = 0;
-#pragma unroll
-    for (int s = 1; s < 3; ++s)
-        if (s < p.n_out && m0 >= p.m_begin[s]) oseg = s;
+    const bool cols = p.by_cols;
+    const int oseg = range_of(p, cols ? n0 : m0);
     __bf16* __restrict__ C = p.C[oseg];
     const long long ldc = p.ldc[oseg];
-    const int mrel0 = m0 - p.m_begin[oseg];
-    const int m_end = (oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], p.M) : p.M);
+    const int mrel0 = cols ? m0 : m0 - p.m_begin[oseg];
+    const int m_end = (!cols && oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], p.M) : p.M);
+    const __bf16* old_rows = p.residual ? p.residual + (long long)m0 * ldc : C + (long long)mrel0 * ldc;
     const float* ws = p.split_ws + (size_t)blockIdx.x * p.split_s * (BM * BN);
     const int col = 4 * (threadIdx.x & 63), n = n0 + col;
     if (n >= p.N) return;  // (N is a multiple of 8: a thread's four columns are all inside or all outside)
@@ -504,7 +503,7 @@ __global__ __launch_bounds__(256) void k_gemm_split_finish(MfmaGemmParams p, int
         v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (m0 + r < m_end) {
             for (int k = 0; k < p.split_s; ++k) v[i] += *reinterpret_cast<const f32x4*>(ws + (size_t)k * (BM * BN) + r * BN + col);
-            if (p.accumulate) old[i] = *reinterpret_cast<const bf16x4*>(C + (long long)(mrel0 + r) * ldc + n);
+            if (p.accumulate) old[i] = *reinterpret_cast<const bf16x4*>(old_rows + (long long)r * ldc + n);
         }
     }
 #pragma unroll
@@ -536,10 +535,12 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     }
     for (int o = 0; o < d.n_out; ++o) {
         if (d.out[o].ldc % 8 || !aligned16(d.out[o].C)) return false;
-        if (d.out[o].m_begin % BM) return false;
+        if (d.out[o].m_begin % BM) return false;  // (a tile is as wide as it is high)
+        if (d.by_cols && (!aligned16(d.out[o].B) || !d.b_kmajor || d.n_seg != 1 || d.epilogue != kEpiNone)) return false;
         if (o == 0 && d.out[o].m_begin != 0) return false;
         if (o > 0 && d.out[o].m_begin <= d.out[o - 1].m_begin) return false;
     }
+    if (d.residual && (!d.accumulate || !d.b_kmajor || d.n_out != 1 || !aligned16(d.residual))) return false;
     if (d.epilogue == kEpiSwigluBwd && (d.n_out != 1 || d.accumulate || d.ldgu % 8 || (d.act_out && !aligned16(d.act_out)) || !aligned16(d.G) || !aligned16(d.U))) return false;
     return true;
 }
@@ -567,6 +568,25 @@ static BigPlan big_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t
         }
     }
     return b;
+}
+
+// Column ranges run as one product, unless their bits are to stay and a product of one of them, or of all, is cut along
+// the contraction: what is cut depends on the number of tiles.
+bool gemm_cols_together(const GemmDesc& d) {
+    if (!d.keep_parts) return true;
+    int n_cu = 0;
+    if (compute_units(&n_cu) != ALCH_OK) return false;
+    MfmaGemmParams p{};
+    p.M = d.M;
+    p.n_seg = 1;
+    p.K[0] = d.seg[0].K;
+    p.m_dev = d.m_dev;
+    const size_t ws_bytes = aligned16(d.split_ws) && d.split_ws ? d.split_ws_bytes : 0;
+    for (int s = -1; s < d.n_out; ++s) {
+        p.N = s < 0 ? d.N : (s + 1 < d.n_out ? d.out[s + 1].m_begin : d.N) - d.out[s].m_begin;
+        if (big_plan(p, d.a_kmajor, n_cu, ws_bytes).parts > 1) return false;
+    }
+    return true;
 }
 
 // Which of the two matrix-core kernels takes a product: the one whose estimated time is shorter.  Both estimates count
@@ -641,6 +661,14 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
         p.m_begin[s] = oo ? d.out[s].m_begin : 0x7fffffff;
         p.ldc[s] = oo ? d.out[s].ldc : 0;
     }
+    p.by_cols = d.by_cols;
+    p.residual = static_cast<const __bf16*>(d.residual);
+    if (d.by_cols)  // (as numbers: what is indexed lies in the range)
+        for (int s = 0; s < d.n_out; ++s) {
+            p.B[s] = reinterpret_cast<const __bf16*>(reinterpret_cast<uintptr_t>(d.out[s].B) -
+                                                     (uintptr_t)d.out[s].m_begin * (uintptr_t)d.seg[0].ldb * 2);
+            p.C[s] = reinterpret_cast<__bf16*>(reinterpret_cast<uintptr_t>(d.out[s].C) - (uintptr_t)d.out[s].m_begin * 2);
+        }
     p.epilogue = d.epilogue;
     p.G = static_cast<const __bf16*>(d.G);
     p.U = static_cast<const __bf16*>(d.U);

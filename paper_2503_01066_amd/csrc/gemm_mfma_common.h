@@ -29,6 +29,10 @@ struct MfmaGemmParams {
     __bf16* C[3];
     int m_begin[3];
     long long ldc[3];
+    // by_cols: m_begin are columns; C[i] and B[i] (of range i, not of an operand pair) point m_begin[i] columns / rows
+    // before their range, so that they are indexed with columns of the whole product
+    int by_cols;
+    const __bf16* residual;
     int epilogue;
     const __bf16* G;
     const __bf16* U;
@@ -42,6 +46,15 @@ struct MfmaGemmParams {
     int split_s, split_per;  // parts per tile; k-tiles per part (counted over all operand pairs in order)
     int per_xcd;             // k_gemm_pair: tiles of an XCD's share (unless the row count lives on the device)
 };
+
+// output range that row (or column) x of the product belongs to
+__device__ __forceinline__ int range_of(const MfmaGemmParams& p, int x) {
+    int r = 0;
+#pragma unroll
+    for (int s = 1; s < 3; ++s)
+        if (s < p.n_out && x >= p.m_begin[s]) r = s;
+    return r;
+}
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 

@@ -77,8 +77,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
             stepa = (long long)BK * lda * 2;
         }
         if (BKM) {
-            pb = (const char*)(p.B[seg] + (long long)n0 * ldb);
-            endb = (const char*)(p.B[seg] + (long long)(p.N - 1) * ldb + K);
+            const __bf16* B = p.B[p.by_cols ? range_of(p, n0) : seg];
+            pb = (const char*)(B + (long long)n0 * ldb);
+            endb = (const char*)(B + (long long)(p.N - 1) * ldb + K);
             stepb = BK * 2;
         } else {
             pb = (const char*)(p.B[seg] + n0);
@@ -237,18 +238,17 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
                 }
         return;
     }
-    int oseg = 0;
-#pragma unroll
-    for (int s = 1; s < 3; ++s)
-        if (s < p.n_out && m0 >= p.m_begin[s]) oseg = s;
+    const bool cols = BKM && p.by_cols;
+    const int oseg = range_of(p, cols ? n0 : m0);
     __bf16* __restrict__ C = p.C[oseg];
     const long long ldc = p.ldc[oseg];
-    const int mrel0 = m0 - p.m_begin[oseg];
-    const int m_end = (oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], Mv) : Mv);
+    const int mrel0 = cols ? m0 : m0 - p.m_begin[oseg];
+    const int m_end = (!cols && oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], Mv) : Mv);
     char* stage = smem + wave * 16384;
     const int n = n0 + wn * 128 + (lane & 15) * 8;
     __syncthreads();  // every wave's loads have landed and every wave is done reading the pipeline
     if (p.accumulate) {
+        const __bf16* old_rows = BKM && p.residual ? p.residual + (long long)m0 * ldc : C + (long long)mrel0 * ldc;
         // C = round(acc + C), the sum in fp32: 32 rows at a time through LDS as fp32 [32][128], 16-byte pieces XOR-ed with
         // the row, all old values of a pass requested before its first store
 #pragma unroll
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const int ml = wm * 64 + i * 32 + 4 * k + (lane >> 4);
-                if (m0 + ml < m_end && n < p.N) old[k] = *reinterpret_cast<const bf16x8*>(C + (long long)(mrel0 + ml) * ldc + n);
+                if (m0 + ml < m_end && n < p.N) old[k] = *reinterpret_cast<const bf16x8*>(old_rows + (long long)ml * ldc + n);
             }
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
@@ -347,13 +347,12 @@ __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
     const int band = t / band_tiles, in_band = t % band_tiles;
     const int band_rows = min(kPairGroupM, p.tiles_m - band * kPairGroupM);
     const int m0 = (band * kPairGroupM + in_band % band_rows) * PM, n0 = (in_band / band_rows) * PN;
-    int oseg = 0;
-#pragma unroll
-    for (int s = 1; s < 3; ++s)
-        if (s < p.n_out && m0 >= p.m_begin[s]) oseg = s;
+    const bool cols = p.by_cols;
+    const int oseg = range_of(p, cols ? n0 : m0);
     __bf16* __restrict__ C = p.C[oseg];
     const long long ldc = p.ldc[oseg];
-    const int m_end = (oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], p.M) : p.M);
+    const int mrel0 = cols ? m0 : m0 - p.m_begin[oseg];
+    const int m_end = (!cols && oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], p.M) : p.M);
     const float* ws = p.split_ws + (size_t)(xcd * rem + j) * p.split_s * (PM * PN);
     const int col = 8 * (threadIdx.x & 31), n = n0 + col;
     if (n >= p.N) return;  // (N is a multiple of 8)
@@ -381,9 +380,9 @@ __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
             if (p.act_out) *reinterpret_cast<bf16x8*>(p.act_out + (long long)m * p.N + n) = a8;
             continue;
         }
-        __bf16* dst = C + (long long)(m - p.m_begin[oseg]) * ldc + n;
+        __bf16* dst = C + (long long)(mrel0 + r) * ldc + n;
         bf16x8 old;
-        if (p.accumulate) old = *reinterpret_cast<const bf16x8*>(dst);
+        if (p.accumulate) old = *reinterpret_cast<const bf16x8*>(p.residual ? p.residual + (long long)m * ldc + n : dst);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const float v = e < 4 ? lo[e & 3] : hi[e & 3];

@@ -31,8 +31,9 @@ struct GemmSeg {
 };
 struct GemmOut {
     void* C;
-    int m_begin;
+    int m_begin;  // first row of the product that goes to C; of a product cut by columns, the first column
     long long ldc;
+    const void* B = nullptr;  // cut by columns: the right operand's part behind these columns
 };
 enum GemmEpilogue { kEpiNone = 0, kEpiSwigluBwd = 1 };
 struct GemmDesc {
@@ -43,6 +44,10 @@ struct GemmDesc {
     int n_out = 0;
     GemmOut out[kMaxGemmOuts];
     int accumulate = 0;
+    const void* residual = nullptr;  // with accumulate: what is added instead of the old values of C (row stride of C)
+    // out[] are column ranges of the product, each with a right operand of its own (k-major, row stride of seg[0].B), one
+    // operand pair: products with a common left operand in one launch
+    bool by_cols = false;
     alch_dtype dtype = ALCH_BF16;
     // kEpiSwigluBwd: the product is dAct [M, N]; with G, U [M, N] (ld = ldgu) the kernel writes
     // dG to out[0].C[:, 0:N], dU to out[0].C[:, N:2N] and Act = silu(G)*U to act_out [M, N].
@@ -68,6 +73,7 @@ static constexpr size_t kGemmSplitWsBytes = (size_t)64 << 20;
 int launch_gemm(const GemmDesc& d, hipStream_t stream);
 // used by launch_gemm
 bool gemm_mfma_supported(const GemmDesc& d);
+bool gemm_cols_together(const GemmDesc& d);
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream);
 int launch_gemm_generic(const GemmDesc& d, hipStream_t stream);
 
