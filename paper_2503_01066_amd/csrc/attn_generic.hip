@@ -17,7 +17,8 @@
 // memory: the row-major ones 16 bytes per lane along the head, those of the second contraction as whole 128-byte lines.
 // What bounds it at the sizes it serves is latency, so the blocks of one work-group are spread over its wavefronts.
 // A wavefront per row with two lane reductions per (row, key) pair took, 2 sequences x 128 tokens, 4 heads of 64, fp32:
-// dQ 78 us, dK/dV 63 us, plus 9 us for delta and the RoPE backward; with these inside, now 21 and 31 us.
+// dQ 78 us, dK/dV 63 us, plus 9 us for delta and the RoPE backward.  With loads that depend on the head size by a branch,
+// wavefronts adding their sums in turn and a launch for each gradient it was 21 + 31 us, without these 19 us in all.
 #include <initializer_list>
 #include <type_traits>
 
@@ -63,13 +64,14 @@ __device__ __forceinline__ f32x4 head4(const T* row, int d, int D, bool vec) {
     return v;
 }
 
-// acc += A B^T over the head: rows ra (this lane's row of A) and rb (of B), both [*, D].
-template <typename T, int NB>
+// acc += A B^T over the head: rows ra (this lane's row of A) and rb (of B), both [*, D].  kFull: D = NB * 32 and rows that
+// allow loads of four elements, so that no load depends on a condition.
+template <typename T, int NB, bool kFull>
 __device__ __forceinline__ f32x16 rows_product(const T* ra, const T* rb, int D, bool vec, int half, f32x16 acc) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         f32x4 a[4], b[4];
-        const bool whole = vec && nb * 32 + 32 <= D;
+        const bool whole = kFull || (vec && nb * 32 + 32 <= D);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int d = nb * 32 + 8 * c + 4 * half;
@@ -85,31 +87,46 @@ __device__ __forceinline__ f32x16 rows_product(const T* ra, const T* rb, int D, 
 }
 __device__ __forceinline__ int row_of(int e, int half) { return 8 * (e >> 2) + 4 * half + (e & 3); }
 
-// Sums of the wavefronts, added in order into LDS [32 rows][kLd]; value e of block nb of a lane is element
-// (row_of(e), nb*32 + lane&31), or its transpose.
+// Sums of the wavefronts on their way to a row-major block of 32 rows; value e of block nb of a lane is element
+// (row_of(e), nb*32 + lane&31), or its transpose.  Up to 128 columns every wavefront has a block of its own in LDS and the
+// reader adds them in order; beyond that they are added in turn into one.
+template <int NB> struct FoldBuf {
+    static constexpr int kLd = NB * 32 + 1, kBlocks = NB <= 4 ? kWaves : 1, kPitch = kBlk * kLd;
+    float at[kBlocks * kPitch];
+    __device__ __forceinline__ float sum(int i) const {
+        float v = at[i];
+#pragma unroll
+        for (int w = 1; w < kBlocks; ++w) v += at[w * kPitch + i];
+        return v;
+    }
+};
 template <int NB, bool kTransposed>
-__device__ __forceinline__ void fold(float* buf, int ld, const f32x16 (&x)[NB], int wave, int lane, float factor) {
-    for (int w = 0; w < kWaves; ++w) {
-        __syncthreads();
-        if (wave == w) {
+__device__ __forceinline__ void fold(FoldBuf<NB>& buf, const f32x16 (&x)[NB], int wave, int lane, float factor) {
+    constexpr int ld = FoldBuf<NB>::kLd;
+    constexpr bool kOwn = FoldBuf<NB>::kBlocks > 1;
+    __syncthreads();  // (the buffer has been read)
+    for (int w = 0; w < (kOwn ? 1 : kWaves); ++w) {
+        if (kOwn || wave == w) {
+            float* base = buf.at + (kOwn ? wave * FoldBuf<NB>::kPitch : 0);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int r = row_of(e, lane >> 5), c = lane & 31;
-                    float* q = kTransposed ? buf + c * ld + nb * 32 + r : buf + r * ld + nb * 32 + c;
+                    float* q = kTransposed ? base + c * ld + nb * 32 + r : base + r * ld + nb * 32 + c;
                     const float v = x[nb][e] * factor;
-                    *q = w == 0 ? v : *q + v;
+                    *q = kOwn || w == 0 ? v : *q + v;
                 }
         }
+        __syncthreads();
     }
-    __syncthreads();
 }
 
 // LDS [32][ld] -> rows of the output, scaled and, with log2_base > 0, rotated by minus the RoPE angle.
-template <typename T>
-__device__ __forceinline__ void store_rows(const float* buf, int ld, T* out, long long ldo, int rows, int D, float scale,
+template <typename T, int NB>
+__device__ __forceinline__ void store_rows(const FoldBuf<NB>& buf, T* out, long long ldo, int rows, int D, float scale,
                                            float log2_base, const int* positions, int token0, int row0) {
+    constexpr int ld = FoldBuf<NB>::kLd;
     if (log2_base > 0.f) {
         const int hd = D >> 1;
         for (int q = threadIdx.x; q < rows * hd; q += kWaves * 64) {
@@ -117,7 +134,7 @@ __device__ __forceinline__ void store_rows(const float* buf, int ld, T* out, lon
             const int pos = positions ? positions[token0 + r] : row0 + r;
             float sn, cs;
             sincosf((float)pos * exp2f(-2.f * (float)k / (float)D * log2_base), &sn, &cs);
-            const float a = buf[r * ld + k] * scale, b = buf[r * ld + k + hd] * scale;
+            const float a = buf.sum(r * ld + k) * scale, b = buf.sum(r * ld + k + hd) * scale;
             stf(out + (long long)r * ldo + k, a * cs + b * sn);
             stf(out + (long long)r * ldo + k + hd, b * cs - a * sn);
         }
@@ -125,7 +142,7 @@ __device__ __forceinline__ void store_rows(const float* buf, int ld, T* out, lon
     }
     for (int q = threadIdx.x; q < rows * D; q += kWaves * 64) {
         const int r = q / D, k = q - r * D;
-        stf(out + (long long)r * ldo + k, buf[r * ld + k] * scale);
+        stf(out + (long long)r * ldo + k, buf.sum(r * ld + k) * scale);
     }
 }
 
@@ -150,13 +167,12 @@ struct KeyBlocks {
     }
 };
 
-template <typename T, int NB>
+template <typename T, int NB, bool kFull>
 __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<T> p) {
-    constexpr int kLd = NB * 32 + 1;
-    __shared__ float buf[kBlk * kLd];
+    __shared__ FoldBuf<NB> buf;
     __shared__ float ml[2][kWaves][kBlk];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
-    const int seq = p.seq_begin + blockIdx.y, h = (int)blockIdx.x % p.Hq, kv = h / (p.Hq / p.Hkv), D = p.D;
+    const int seq = p.seq_begin + blockIdx.y, h = (int)blockIdx.x % p.Hq, kv = h / (p.Hq / p.Hkv), D = kFull ? NB * 32 : p.D;
     const int i0 = (p.blocks - 1 - (int)blockIdx.x / p.Hq) * kBlk;  // the longest rows first
     const KeyBlocks kb(p.cu, p.prefix, seq, i0);
     if (i0 >= kb.len) return;
@@ -176,7 +192,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<
         f32x16 S;
 #pragma unroll
         for (int e = 0; e < 16; ++e) S[e] = 0.f;
-        S = rows_product<T, NB>(p.K + (row0 + min(j0 + (lane & 31), keys - 1)) * ldk + (long long)kv * D, q, D, p.vec, half, S);
+        S = rows_product<T, NB, kFull>(p.K + (row0 + min(j0 + (lane & 31), keys - 1)) * ldk + (long long)kv * D, q, D, p.vec, half, S);
         float mx = m;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -204,7 +220,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 const int d = nb * 32 + (lane & 31);
-                Ot[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(d < D ? ldf(vr + d) : 0.f, S[e], Ot[nb], 0, 0, 0);
+                Ot[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kFull || d < D ? ldf(vr + d) : 0.f, S[e], Ot[nb], 0, 0, 0);
             }
         }
     }
@@ -215,34 +231,38 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<
     for (int w = 0; w < kWaves; ++w) M = fmaxf(M, ml[0][w][lane & 31]);
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) L += ml[1][w][lane & 31] * expf(ml[0][w][lane & 31] - M);
-    fold<NB, true>(buf, kLd, Ot, wave, lane, expf(m - M) / L);
+    fold<NB, true>(buf, Ot, wave, lane, expf(m - M) / L);
     const int rows = min(kBlk, kb.len - i0);
-    store_rows(buf, kLd, p.Oout + (kb.own0 + i0) * ldq + (long long)h * D, ldq, rows, D, 1.f, 0.f, nullptr, 0, 0);
+    store_rows(buf, p.Oout + (kb.own0 + i0) * ldq + (long long)h * D, ldq, rows, D, 1.f, 0.f, nullptr, 0, 0);
     if (wave == 0 && half == 0 && lane < rows) p.LSE[(long long)(kb.own0 + i0 + lane) * p.Hq + h] = M + logf(L);
 }
 
-template <typename T, int NB>
-__global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dq_plain(AttnPlainParams<T> p) {
-    constexpr int kLd = NB * 32 + 1;
-    __shared__ float buf[kBlk * kLd];
+// delta_i = sum_d dO O of row `off` of either, half of the elements per lane
+template <typename T>
+__device__ __forceinline__ float row_delta(const T* go, const T* o, int D, bool vec, int half) {
+    float del = 0.f;
+    for (int d = 4 * half; d < D; d += 8) {
+        const f32x4 a = head4(go, d, D, vec), b = head4(o, d, D, vec);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) del = __builtin_fmaf(a[c], b[c], del);
+    }
+    return del + __shfl_xor(del, 32, 64);
+}
+
+// dQ of block `block` (heads first, then 32-query blocks); kDelta: also writes delta
+template <typename T, int NB, bool kFull, bool kDelta>
+__device__ __forceinline__ void attn_bwd_dq_block(const AttnPlainParams<T>& p, FoldBuf<NB>& buf, int block) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
-    const int seq = p.seq_begin + blockIdx.y, h = (int)blockIdx.x % p.Hq, kv = h / (p.Hq / p.Hkv), D = p.D;
-    const int i0 = (p.blocks - 1 - (int)blockIdx.x / p.Hq) * kBlk;
+    const int seq = p.seq_begin + blockIdx.y, h = block % p.Hq, kv = h / (p.Hq / p.Hkv), D = kFull ? NB * 32 : p.D;
+    const int i0 = (p.blocks - 1 - block / p.Hq) * kBlk;
     const KeyBlocks kb(p.cu, p.prefix, seq, i0);
     if (i0 >= kb.len) return;
     const long long ldq = (long long)p.Hq * D, ldk = (long long)p.Hkv * D;
     const int i = min(i0 + (lane & 31), kb.len - 1);
     const long long qoff = (kb.own0 + i) * ldq + (long long)h * D, roff = (long long)(kb.own0 + i) * p.Hq + h;
     const T *q = p.Q + qoff, *go = p.dO + qoff, *o = p.O + qoff;
-    // delta_i = sum_d dO O of this lane's query, half of the elements per lane
-    float del = 0.f;
-    for (int d = 4 * half; d < D; d += 8) {
-        const f32x4 a = head4(go, d, D, p.vec), b = head4(o, d, D, p.vec);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) del = __builtin_fmaf(a[c], b[c], del);
-    }
-    del += __shfl_xor(del, 32, 64);
-    if (wave == 0 && half == 0 && i0 + lane < kb.len) p.delta[roff] = del;
+    const float del = row_delta(go, o, D, kFull || p.vec, half);
+    if (kDelta && wave == 0 && half == 0 && i0 + lane < kb.len) p.delta[roff] = del;
     const float lse = p.LSE[roff];
     f32x16 dQ[NB];
 #pragma unroll
@@ -257,8 +277,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dq_plain(AttnPlainPara
         f32x16 S, dP;
 #pragma unroll
         for (int e = 0; e < 16; ++e) S[e] = dP[e] = 0.f;
-        S = rows_product<T, NB>(p.K + koff, q, D, p.vec, half, S);
-        dP = rows_product<T, NB>(p.V + koff, go, D, p.vec, half, dP);
+        S = rows_product<T, NB, kFull>(p.K + koff, q, D, p.vec, half, S);
+        dP = rows_product<T, NB, kFull>(p.V + koff, go, D, p.vec, half, dP);
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             S[e] = j0 + row_of(e, half) <= lim ? expf(S[e] * p.scale - lse) * (dP[e] - del) : 0.f;
@@ -269,22 +289,22 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dq_plain(AttnPlainPara
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 const int d = nb * 32 + (lane & 31);
-                dQ[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(S[e], d < D ? ldf(kr + d) : 0.f, dQ[nb], 0, 0, 0);
+                dQ[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(S[e], kFull || d < D ? ldf(kr + d) : 0.f, dQ[nb], 0, 0, 0);
             }
         }
     }
-    fold<NB, false>(buf, kLd, dQ, wave, lane, 1.f);
-    store_rows(buf, kLd, p.dQ + (kb.own0 + i0) * p.ldo + (long long)h * D, p.ldo, min(kBlk, kb.len - i0), D, p.scale,
+    fold<NB, false>(buf, dQ, wave, lane, 1.f);
+    store_rows(buf, p.dQ + (kb.own0 + i0) * p.ldo + (long long)h * D, p.ldo, min(kBlk, kb.len - i0), D, p.scale,
                p.log2_base, p.positions, kb.own0 + i0, i0);
 }
 
-template <typename T, int NB>
-__global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dkv_plain(AttnPlainParams<T> p) {
-    constexpr int kLd = NB * 32 + 1;
-    __shared__ float buf[kBlk * kLd];
+// dK, dV of block `block` (kv heads first, then 32-key blocks); kDelta: forms delta of the queries it meets by itself
+// instead of reading it
+template <typename T, int NB, bool kFull, bool kDelta>
+__device__ __forceinline__ void attn_bwd_dkv_block(const AttnPlainParams<T>& p, FoldBuf<NB>& buf, int block) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
-    const int seq = p.seq_begin + blockIdx.y, kv = (int)blockIdx.x % p.Hkv, G = p.Hq / p.Hkv, D = p.D;
-    const int own0 = p.cu[seq], len = p.cu[seq + 1] - own0, j0 = (int)blockIdx.x / p.Hkv * kBlk;
+    const int seq = p.seq_begin + blockIdx.y, kv = block % p.Hkv, G = p.Hq / p.Hkv, D = kFull ? NB * 32 : p.D;
+    const int own0 = p.cu[seq], len = p.cu[seq + 1] - own0, j0 = block / p.Hkv * kBlk;
     if (j0 >= len) return;
     const long long ldq = (long long)p.Hq * D, ldk = (long long)p.Hkv * D;
     const int j = min(j0 + (lane & 31), len - 1);  // this lane's key
@@ -304,18 +324,25 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dkv_plain(AttnPlainPar
             for (int h = kv * G; h < (kv + 1) * G; ++h, ++turn) {
                 if (turn % kWaves != wave) continue;
                 const long long qoff = (row0 + min(i0 + (lane & 31), n - 1)) * ldq + (long long)h * D;
+                float lse = 0.f, del = 0.f;  // of this lane's query row
+                if constexpr (kDelta) {
+                    lse = p.LSE[(long long)(row0 + min(i0 + (lane & 31), n - 1)) * p.Hq + h];
+                    del = row_delta(p.dO + qoff, p.O + qoff, D, kFull || p.vec, half);
+                }
                 f32x16 S, dP;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) S[e] = dP[e] = 0.f;
-                S = rows_product<T, NB>(p.Q + qoff, k, D, p.vec, half, S);
-                dP = rows_product<T, NB>(p.dO + qoff, v, D, p.vec, half, dP);
+                S = rows_product<T, NB, kFull>(p.Q + qoff, k, D, p.vec, half, S);
+                dP = rows_product<T, NB, kFull>(p.dO + qoff, v, D, p.vec, half, dP);
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int i = i0 + row_of(e, half);
                     const long long roff = (long long)(row0 + min(i, n - 1)) * p.Hq + h;
                     const bool seen = i < n && (c > seq || i >= j0 + (lane & 31));
-                    S[e] = seen ? expf(S[e] * p.scale - p.LSE[roff]) : 0.f;
-                    dP[e] = S[e] * (dP[e] - p.delta[roff]);
+                    const float le = kDelta ? __shfl(lse, row_of(e, half), 64) : p.LSE[roff];
+                    const float de = kDelta ? __shfl(del, row_of(e, half), 64) : p.delta[roff];
+                    S[e] = seen ? expf(S[e] * p.scale - le) : 0.f;
+                    dP[e] = S[e] * (dP[e] - de);
                 }
                 const T *qh = p.Q + row0 * ldq + (long long)h * D, *gh = p.dO + row0 * ldq + (long long)h * D;
 #pragma unroll
@@ -324,8 +351,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dkv_plain(AttnPlainPar
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         const int d = nb * 32 + (lane & 31);
-                        dV[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(S[e], d < D ? ldf(gh + ro + d) : 0.f, dV[nb], 0, 0, 0);
-                        dK[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dP[e], d < D ? ldf(qh + ro + d) : 0.f, dK[nb], 0, 0, 0);
+                        dV[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(S[e], kFull || d < D ? ldf(gh + ro + d) : 0.f, dV[nb], 0, 0, 0);
+                        dK[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dP[e], kFull || d < D ? ldf(qh + ro + d) : 0.f, dK[nb], 0, 0, 0);
                     }
                 }
             }
@@ -333,10 +360,29 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dkv_plain(AttnPlainPar
     }
     const int rows = min(kBlk, len - j0);
     const long long out = (own0 + j0) * p.ldo + (long long)kv * D;
-    fold<NB, false>(buf, kLd, dK, wave, lane, 1.f);
-    store_rows(buf, kLd, p.dK + out, p.ldo, rows, D, p.scale, p.log2_base, p.positions, own0 + j0, j0);
-    fold<NB, false>(buf, kLd, dV, wave, lane, 1.f);
-    store_rows(buf, kLd, p.dV + out, p.ldo, rows, D, 1.f, 0.f, nullptr, 0, 0);
+    fold<NB, false>(buf, dK, wave, lane, 1.f);
+    store_rows(buf, p.dK + out, p.ldo, rows, D, p.scale, p.log2_base, p.positions, own0 + j0, j0);
+    fold<NB, false>(buf, dV, wave, lane, 1.f);
+    store_rows(buf, p.dV + out, p.ldo, rows, D, 1.f, 0.f, nullptr, 0, 0);
+}
+
+template <typename T, int NB, bool kFull>
+__global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dq_plain(AttnPlainParams<T> p) {
+    __shared__ FoldBuf<NB> buf;
+    attn_bwd_dq_block<T, NB, kFull, true>(p, buf, (int)blockIdx.x);
+}
+template <typename T, int NB, bool kFull>
+__global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dkv_plain(AttnPlainParams<T> p) {
+    __shared__ FoldBuf<NB> buf;
+    attn_bwd_dkv_block<T, NB, kFull, false>(p, buf, (int)blockIdx.x);
+}
+// Both in one launch: key blocks first (they take longer), then query blocks.
+template <typename T, int NB, bool kFull>
+__global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_plain(AttnPlainParams<T> p) {
+    __shared__ FoldBuf<NB> buf;
+    const int key_blocks = p.blocks * p.Hkv;
+    if ((int)blockIdx.x < key_blocks) attn_bwd_dkv_block<T, NB, kFull, true>(p, buf, (int)blockIdx.x);
+    else attn_bwd_dq_block<T, NB, kFull, false>(p, buf, (int)blockIdx.x - key_blocks);
 }
 
 // rows of a head start on a multiple of four elements
@@ -347,13 +393,21 @@ static bool head_rows_vec(int D, std::initializer_list<const void*> ptrs) {
     return ok;
 }
 
-template <typename F>
-static int with_blocks(int D, F&& f) {
+// f(32-column blocks of a head, whether it fills them in rows of aligned groups of four: told apart for the head sizes of
+// the fp32 layers)
+template <typename T, typename F>
+static int with_blocks(int D, bool vec, F&& f) {
     if (D > 256) return fail(ALCH_ERR_UNSUPPORTED, "head_dim %d > 256", D);
-    if (D <= 32) f(std::integral_constant<int, 1>{});
-    else if (D <= 64) f(std::integral_constant<int, 2>{});
-    else if (D <= 128) f(std::integral_constant<int, 4>{});
-    else f(std::integral_constant<int, 8>{});
+    auto g = [&](auto NB) {
+        constexpr int kNB = decltype(NB)::value;
+        if constexpr (std::is_same<T, float>::value && (kNB == 2 || kNB == 4))
+            if (vec && D == kNB * 32) return f(NB, std::true_type{});
+        f(NB, std::false_type{});
+    };
+    if (D <= 32) g(std::integral_constant<int, 1>{});
+    else if (D <= 64) g(std::integral_constant<int, 2>{});
+    else if (D <= 128) g(std::integral_constant<int, 4>{});
+    else g(std::integral_constant<int, 8>{});
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
@@ -380,12 +434,24 @@ static int attn_bwd_generic_t(const AttnArgs& a, hipStream_t stream) {
     p.vec = head_rows_vec<T>(a.D, {a.Q, a.K, a.V, a.O, a.dO});
     p.blocks = ceil_div(a.max_seqlen, kBlk);
     if (p.blocks <= 0 || a.n_seqs <= 0) return ALCH_OK;
-    return with_blocks(a.D, [&](auto NB) {
+    int n_cu = 0;
+    ALCH_TRY(compute_units(&n_cu));
+    return with_blocks<T>(a.D, p.vec, [&](auto NB, auto full) {
+        constexpr int kNB = decltype(NB)::value;
+        constexpr bool kFull = decltype(full)::value;
+        // A batch whose work-groups all find a compute unit is bound by the latency of one: both gradients in one launch,
+        // delta formed where it is needed (2 x 128 tokens, 4 heads of 64: 19 us).  Beyond that the registers of the dK/dV
+        // code would halve the wavefronts of the dQ work-groups.
+        if constexpr (kNB <= 4)
+            if ((long long)p.blocks * (a.Hq + a.Hkv) * a.n_seqs <= n_cu) {
+                k_attn_bwd_plain<T, kNB, kFull><<<dim3(p.blocks * (a.Hq + a.Hkv), a.n_seqs), kWaves * 64, 0, stream>>>(p);
+                return;
+            }
         by_sequences(p, 0, [&](int n) {  // also writes delta, which the second kernel reads for all sequences
-            k_attn_bwd_dq_plain<T, decltype(NB)::value><<<dim3(p.blocks * a.Hq, n), kWaves * 64, 0, stream>>>(p);
+            k_attn_bwd_dq_plain<T, kNB, kFull><<<dim3(p.blocks * a.Hq, n), kWaves * 64, 0, stream>>>(p);
         });
         by_sequences(p, 0, [&](int n) {
-            k_attn_bwd_dkv_plain<T, decltype(NB)::value><<<dim3(p.blocks * a.Hkv, n), kWaves * 64, 0, stream>>>(p);
+            k_attn_bwd_dkv_plain<T, kNB, kFull><<<dim3(p.blocks * a.Hkv, n), kWaves * 64, 0, stream>>>(p);
         });
     });
 }
@@ -404,9 +470,9 @@ static int attn_fwd_generic_t(const void* Q, const void* K, const void* V, void*
     p.scale = 1.f / sqrtf((float)D);
     p.vec = head_rows_vec<T>(D, {Q, K, V});
     p.blocks = ceil_div(max_seqlen, kBlk);
-    return with_blocks(D, [&](auto NB) {
+    return with_blocks<T>(D, p.vec, [&](auto NB, auto full) {
         by_sequences(p, seq_begin, [&](int n) {
-            k_attn_fwd_plain<T, decltype(NB)::value><<<dim3(p.blocks * Hq, n), kWaves * 64, 0, stream>>>(p);
+            k_attn_fwd_plain<T, decltype(NB)::value, decltype(full)::value><<<dim3(p.blocks * Hq, n), kWaves * 64, 0, stream>>>(p);
         });
     });
 }
