@@ -11,6 +11,8 @@
 //   k_gemm_f32_tiled   128x128 tiles staged through LDS, for problems with enough of them to fill the compute units
 //                      (4096 x 4096 x 2048: 95 - 103 TFLOP/s; vector multiply-adds on 64x64 tiles: 50).
 #include <algorithm>
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace alch {
@@ -100,14 +102,19 @@ template <> struct F32Tile<16> {
     static __device__ __forceinline__ int row(int e, int lane) { return 4 * (lane >> 4) + e; }
 };
 
-template <typename T, int kTile, int kWaves>
+// kForm: 0..3 = (a_kmajor, b_kmajor << 1) with contractions of whole chunks and, for a k-major operand, rows that allow
+// loads of four elements: no load then depends on a condition, so that all of a batch are requested before the first is
+// waited for (the eight products of a layer backward of 256 tokens, hidden 256, ffn 1024: 77 us with the conditions, 63 us
+// without); -1 = everything else.
+template <typename T, int kTile, int kWaves, int kForm>
 __global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_slices(GenericGemmParams p) {
     constexpr int kElems = kTile * kTile / 64, kChunk = 256 / kTile;
     __shared__ float red[kWaves][kElems][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = lane / kTile;
     const int m0 = (int)(blockIdx.x / p.tiles_n) * kTile, n0 = (int)(blockIdx.x % p.tiles_n) * kTile;
     const int m = min(m0 + lane % kTile, p.M - 1), n = min(n0 + lane % kTile, p.N - 1);
-    const bool ak = p.a_kmajor, bk = p.b_kmajor;
+    constexpr bool kPlain = kForm >= 0;
+    const bool ak = kPlain ? (kForm & 1) != 0 : p.a_kmajor != 0, bk = kPlain ? (kForm & 2) != 0 : p.b_kmajor != 0;
     typename F32Tile<kTile>::Acc acc;
 #pragma unroll
     for (int e = 0; e < kElems; ++e) acc[e] = 0.f;
@@ -116,15 +123,16 @@ __global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_slices(GenericGemmPara
         const T* A = static_cast<const T*>(p.A[s]);
         const T* B = static_cast<const T*>(p.B[s]);
         const long long lda = p.lda[s], ldb = p.ldb[s];
-        const bool av = p.a_vec[s], bv = p.b_vec[s];
+        const bool av = kPlain || p.a_vec[s], bv = kPlain || p.b_vec[s];
         const int chunks = (p.K[s] + kChunk - 1) / kChunk;
         const int lo = wave * chunks / kWaves, hi = (wave + 1) * chunks / kWaves;
         const int k_end = min(p.K[s], hi * kChunk);
         auto load = [&](int c, f32x4 (&a)[kBatch], f32x4 (&b)[kBatch]) {
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) {
-                const int k = (c + q) * kChunk + 4 * part;
-                const bool whole = (c + q + 1) * kChunk <= k_end;
+                // (past the slice, whose products are left out below: its last chunk again, or the first of all)
+                const int k = (kPlain ? max(min(c + q, hi - 1), 0) : c + q) * kChunk + 4 * part;
+                const bool whole = kPlain || (c + q + 1) * kChunk <= k_end;
                 a[q] = operand4(A, lda, ak, av, whole, m, k, k_end);
                 b[q] = operand4(B, ldb, bk, bv, whole, n, k, k_end);
             }
@@ -136,8 +144,10 @@ __global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_slices(GenericGemmPara
             load(c + kBatch, a1, b1);
 #pragma unroll
             for (int q = 0; q < kBatch; ++q)
+                if (!kPlain || c + q < hi) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc = F32Tile<kTile>::mac(a0[q][i], b0[q][i], acc);
+                    for (int i = 0; i < 4; ++i) acc = F32Tile<kTile>::mac(a0[q][i], b0[q][i], acc);
+                }
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) { a0[q] = a1[q]; b0[q] = b1[q]; }
         }
@@ -240,14 +250,29 @@ static constexpr int kTiledFrom = 160;
 // (256 x 256 x 2048, 64 tiles of 32x32: 24 against 12.4 us; 192 tiles, K 256: equal; 512^3, 256 tiles: 10.6 against 13.7 us).
 static constexpr int kWideFrom = 128;
 
-template <typename T, int kTile>
-static void gemm_slices_t(GenericGemmParams& p, int k_total, hipStream_t stream) {
+template <typename T, int kTile, int kForm>
+static void gemm_slices_form(GenericGemmParams& p, int k_total, hipStream_t stream) {
     p.tiles_n = ceil_div(p.N, kTile);
     const int grid = ceil_div(p.M, kTile) * p.tiles_n;
     // slices of at least 64 k
-    if (k_total >= 1024) k_gemm_f32_slices<T, kTile, 16><<<grid, 1024, 0, stream>>>(p);
-    else if (k_total >= 512) k_gemm_f32_slices<T, kTile, 8><<<grid, 512, 0, stream>>>(p);
-    else k_gemm_f32_slices<T, kTile, 4><<<grid, 256, 0, stream>>>(p);
+    if (k_total >= 1024) k_gemm_f32_slices<T, kTile, 16, kForm><<<grid, 1024, 0, stream>>>(p);
+    else if (k_total >= 512) k_gemm_f32_slices<T, kTile, 8, kForm><<<grid, 512, 0, stream>>>(p);
+    else k_gemm_f32_slices<T, kTile, 4, kForm><<<grid, 256, 0, stream>>>(p);
+}
+template <typename T, int kTile>
+static void gemm_slices_t(GenericGemmParams& p, int k_total, hipStream_t stream) {
+    if constexpr (std::is_same<T, float>::value) {
+        bool plain = true;
+        for (int s = 0; s < p.n_seg; ++s)
+            plain = plain && p.K[s] % (256 / kTile) == 0 && (!p.a_kmajor || p.a_vec[s]) && (!p.b_kmajor || p.b_vec[s]);
+        if (plain) {
+            if (p.a_kmajor && p.b_kmajor) return gemm_slices_form<T, kTile, 3>(p, k_total, stream);
+            if (p.b_kmajor) return gemm_slices_form<T, kTile, 2>(p, k_total, stream);
+            if (p.a_kmajor) return gemm_slices_form<T, kTile, 1>(p, k_total, stream);
+            return gemm_slices_form<T, kTile, 0>(p, k_total, stream);
+        }
+    }
+    gemm_slices_form<T, kTile, -1>(p, k_total, stream);
 }
 
 template <typename T>
