@@ -18,9 +18,14 @@
 // that makes both the row-major and the transposing reads bank-conflict free.
 //
 // Heads of 64 run the same schedule with half as many matrix instructions per score element, so they are bound by the
-// vector port (exponentials and conversions) rather than by the matrix pipes.  They took the wavefront-per-row kernels
-// of attn_generic.hip before, whose every (row, key) pair costs two six-step lane reductions: 5 sequences, 4099 tokens,
-// 32/8 heads: dQ 7043 -> 53 us, dK/dV 7630 -> 103 us, delta and RoPE backward (29 us) now inside these two.
+// vector port (exponentials and conversions) rather than by the matrix pipes.  They took kernels of a wavefront per row
+// before, whose every (row, key) pair costs two six-step lane reductions and which held probabilities and dS in fp32.  That
+// precision is kept: P and dS enter the second contractions as sums of two bf16 numbers each (2^-17 of the value is lost, the
+// results are bf16), the forward's LSE is formed to fp32 rounding and RoPE angles take the accurate sine and cosine.  Against
+// 64 bits (4096 tokens) the errors of O, dQ, dK, dV are those of rounding the exact values to bf16 to four digits (1.61e-3 ..
+// 1.68e-3; P and dS in one bf16 number: 2.06e-3 .. 2.32e-3), that of the LSE 4.6e-8.  5 sequences, 4099 tokens, 32/8 heads:
+// dQ 7043 -> 65 us, dK/dV 7630 -> 131 us and 7 us for the sum of its parts (one bf16 number: 53 and 103 us), delta and RoPE
+// backward (29 us) inside these.  Heads of 128 round P and dS to bf16 once.
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -45,6 +50,7 @@ template <int kD> struct AttnTile {
     static constexpr int kKK = kD / 16;                    // 16-wide steps of a contraction over the head
     static constexpr int kNB = kD / 32;                    // 32-wide column blocks of a head
     static constexpr int kLoads = kD / 32;                 // 1 KB direct-to-LDS loads per wavefront and tile
+    static constexpr bool kTwo = kD == 64;                 // probabilities and dS as two bf16 numbers each (see the head)
 };
 static constexpr float kLog2e = 1.4426950408889634f;
 static constexpr int kMinPartTiles = 8;  // tiles a part of a key block has at least
@@ -85,6 +91,14 @@ __device__ __forceinline__ int prefix_child_tiles(const AttnMfmaParams& p, int s
     return n;
 }
 
+template <int kD> __device__ __forceinline__ float rope_theta(int d, float log2_base) {
+    const float x = -(float)d * (2.0f / kD) * log2_base;
+    return AttnTile<kD>::kTwo ? exp2f(x) : __builtin_amdgcn_exp2f(x);
+}
+template <int kD> __device__ __forceinline__ void rope_sincos(float angle, float& sn, float& cs) {
+    if (AttnTile<kD>::kTwo) sincosf(angle, &sn, &cs);
+    else __sincosf(angle, &sn, &cs);
+}
 // RoPE backward on one accumulator set: block nb of the lower half holds element d = nb*32 + (lane&31) of a head,
 // block nb + kNB/2 its partner d + kD/2; x'[d] = x[d] cos a + x[d+kD/2] sin a, x'[d+kD/2] = x[d+kD/2] cos a - x[d] sin a
 // with a = pos * base^(-2d/kD).
@@ -94,13 +108,13 @@ __device__ __forceinline__ void rope_backward_rows(f32x16 (&x)[AttnTile<kD>::kNB
     const int half = lane >> 5;
 #pragma unroll
     for (int nb = 0; nb < AttnTile<kD>::kNB / 2; ++nb) {
-        const float theta = __builtin_amdgcn_exp2f(-(float)(nb * 32 + (lane & 31)) * (2.0f / kD) * p.rope_log2_base);
+        const float theta = rope_theta<kD>(nb * 32 + (lane & 31), p.rope_log2_base);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int r = row0 + 8 * (e >> 2) + 4 * half + (e & 3);
             const int pos = (p.positions && r < len) ? p.positions[seq_start + r] : r;
             float sn, cs;
-            __sincosf((float)pos * theta, &sn, &cs);
+            rope_sincos<kD>((float)pos * theta, sn, cs);
             const float a = x[nb][e], b = x[nb + AttnTile<kD>::kNB / 2][e];
             x[nb][e] = a * cs + b * sn;
             x[nb + AttnTile<kD>::kNB / 2][e] = b * cs - a * sn;
@@ -193,11 +207,18 @@ __device__ __forceinline__ bf16x8 lds_frag_rows(const char* tile, uint32_t lane_
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-__device__ __forceinline__ bf16x8 pack8(const f32x16& v, int ks) {
-    bf16x8 o;
+// Accumulator elements 8 ks .. 8 ks + 7 as the bf16 operand of the next contraction.  kTwo: as a sum of two bf16 numbers, the
+// rounded value and the rounded rest, which carries 16 bits of the fp32 value at the price of a second matrix instruction.
+template <bool kTwo> struct Operand;
+template <> struct Operand<false> { bf16x8 hi; };
+template <> struct Operand<true> { bf16x8 hi, lo; };
+template <bool kTwo>
+__device__ __forceinline__ void pack8(Operand<kTwo>& o, const f32x16& v, int ks) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (__bf16)v[8 * ks + e];
-    return o;
+    for (int e = 0; e < 8; ++e) {
+        o.hi[e] = (__bf16)v[8 * ks + e];
+        if constexpr (kTwo) o.lo[e] = (__bf16)(v[8 * ks + e] - (float)o.hi[e]);
+    }
 }
 
 // 16-byte global load of an operand fragment held in registers for the whole kernel:
@@ -314,7 +335,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     // buffer descriptors of the tile the next iteration loads.  Beyond the end of the stream the loads are
     // issued with zero extent: they move nothing and keep every wave's count of outstanding loads the same.
     f32x16 S1, dP1;         // raw scores of block 1 of the current tile
-    bf16x8 pf0[2], dsf0[2]; // P, dS of block 0 of the current tile
+    constexpr bool kTwo = AttnTile<kD>::kTwo;
+    Operand<kTwo> pf0[2], dsf0[2]; // P, dS of block 0 of the current tile
     const int jl = j0 + (lane & 31);  // this lane's key
     const unsigned live_own = (unsigned)max(len - jl, 0);
     // P, dS of accumulator elements e0 .. e0+n-1 of one block, in place.  Element e is query row
@@ -411,8 +433,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
         softmax_part(S0, dP0, l, d, m_cur, 0, 0, 16);
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            pf0[ks] = pack8(S0, ks);
-            dsf0[ks] = pack8(dP0, ks);
+            pack8(pf0[ks], S0, ks);
+            pack8(dsf0[ks], dP0, ks);
         }
         load_row_scalars(smem, 1, l1, d1);
     }
@@ -447,7 +469,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
         ld_rdo(0); ld_rq(0); ld_d(0);
         ld_rdo(1); ld_rq(1); ld_d(1);
         f32x16 Sn0, dPn0, Sn1, dPn1;  // scores of the next tile
-        bf16x8 pf1[2], dsf1[2], pfn[2], dsfn[2];
+        Operand<kTwo> pf1[2], dsf1[2], pfn[2], dsfn[2];
         Meta m_n4;
         LoadDesc dsc_next;
         // One element of the softmax gradient in two halves, each pinned where it is written so that it is issued
@@ -475,30 +497,47 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
                 const int ib = g / kHalf, ks = (g / kNB) & 1, nb = g % kNB, kk = g % kHalf;
                 const int e0 = kElems * (g % kHalf), e1 = e0 + kElems / 2, e2 = e0 + kElems;
                 const Frags& f = fr[g % 3];
+                const Operand<kTwo>& pg = ib == 0 ? pf0[ks] : pf1[ks];
+                const Operand<kTwo>& dsg = ib == 0 ? dsf0[ks] : dsf1[ks];
+                auto h1 = [&](int b, int n) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int e = b; e < n; ++e) {
+                        if (ib == 0) sm_h1(S1, l1, m_cur, 1, e); else sm_h1(Sn0, ln, m_nxt, 0, e);
+                    }
+                };
+                auto h2 = [&](int b, int n) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int e = b; e < n; ++e) {
+                        if (ib == 0) sm_h2(S1, dP1, d1, e); else sm_h2(Sn0, dPn0, dn, e);
+                    }
+                };
                 // slot 0
                 if (g + 2 < kGroups) ld_rdo(g + 2);
-#pragma unroll
-                for (int e = e0; e < e1; ++e) {
-                    if (ib == 0) sm_h1(S1, l1, m_cur, 1, e); else sm_h1(Sn0, ln, m_nxt, 0, e);
+                h1(e0, e1);
+                ALCH_SB;
+                dV[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pg.hi, f.rdo, dV[nb], 0, 0, 0);
+                ALCH_SB;
+                if constexpr (kTwo) {
+                    h1(e1, e2);
+                    ALCH_SB;
+                    dV[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pg.lo, f.rdo, dV[nb], 0, 0, 0);
+                    ALCH_SB;
                 }
-                ALCH_SB;
-                dV[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ib == 0 ? pf0[ks] : pf1[ks], f.rdo, dV[nb], 0, 0, 0);
-                ALCH_SB;
                 // slot 1
                 if (g + 2 < kGroups) ld_rq(g + 2);
-#pragma unroll
-                for (int e = e1; e < e2; ++e) {
-                    if (ib == 0) sm_h1(S1, l1, m_cur, 1, e); else sm_h1(Sn0, ln, m_nxt, 0, e);
+                if constexpr (kTwo) h2(e0, e1); else h1(e1, e2);
+                ALCH_SB;
+                dK[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsg.hi, f.rq, dK[nb], 0, 0, 0);
+                ALCH_SB;
+                if constexpr (kTwo) {
+                    h2(e1, e2);
+                    ALCH_SB;
+                    dK[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsg.lo, f.rq, dK[nb], 0, 0, 0);
+                    ALCH_SB;
                 }
-                ALCH_SB;
-                dK[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ib == 0 ? dsf0[ks] : dsf1[ks], f.rq, dK[nb], 0, 0, 0);
-                ALCH_SB;
                 // slot 2
                 if (g + 2 < kGroups) ld_d(g + 2);
-#pragma unroll
-                for (int e = e0; e < e2; ++e) {
-                    if (ib == 0) sm_h2(S1, dP1, d1, e); else sm_h2(Sn0, dPn0, dn, e);
-                }
+                if constexpr (!kTwo) h2(e0, e2);
                 ALCH_SB;
                 if (g == 0) {
 #pragma unroll
@@ -531,10 +570,16 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
                     dsc_next = desc_of(q_ld, it + 4 < n_it);
                     advance(q_ld);
                 }
-                if (g == kHalf / 2 - 1) { pf1[0] = pack8(S1, 0); dsf1[0] = pack8(dP1, 0); asm volatile("" : "+v"(pf1[0]), "+v"(dsf1[0])); }
-                if (g == kHalf - 1) { pf1[1] = pack8(S1, 1); dsf1[1] = pack8(dP1, 1); asm volatile("" : "+v"(pf1[1]), "+v"(dsf1[1])); }
-                if (g == kHalf + kHalf / 2 - 1) { pfn[0] = pack8(Sn0, 0); dsfn[0] = pack8(dPn0, 0); asm volatile("" : "+v"(pfn[0]), "+v"(dsfn[0])); }
-                if (g == kGroups - 1) { pfn[1] = pack8(Sn0, 1); dsfn[1] = pack8(dPn0, 1); asm volatile("" : "+v"(pfn[1]), "+v"(dsfn[1])); }
+                auto pack = [&](Operand<kTwo>& po, Operand<kTwo>& dso, const f32x16& pr, const f32x16& ds, int k) __attribute__((always_inline)) {
+                    pack8(po, pr, k);
+                    pack8(dso, ds, k);
+                    asm volatile("" : "+v"(po.hi), "+v"(dso.hi));
+                    if constexpr (kTwo) asm volatile("" : "+v"(po.lo), "+v"(dso.lo));
+                };
+                if (g == kHalf / 2 - 1) pack(pf1[0], dsf1[0], S1, dP1, 0);
+                if (g == kHalf - 1) pack(pf1[1], dsf1[1], S1, dP1, 1);
+                if (g == kHalf + kHalf / 2 - 1) pack(pfn[0], dsfn[0], Sn0, dPn0, 0);
+                if (g == kGroups - 1) pack(pfn[1], dsfn[1], Sn0, dPn0, 1);
                 ALCH_SB;
                 if (ib == 0) dPn0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.ddo, vf[kk], dPn0, 0, 0, 0);
                 else dPn1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.ddo, vf[kk], dPn1, 0, 0, 0);
@@ -619,9 +664,8 @@ __global__ __launch_bounds__(256) void k_dkv_finish(AttnMfmaParams p) {
                 const int pos = p.positions ? p.positions[seq_start + r] : r;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float theta = __builtin_amdgcn_exp2f(-(float)(c0 + e) * (2.0f / kD) * p.rope_log2_base);
                     float sn, cs;
-                    __sincosf((float)pos * theta, &sn, &cs);
+                    rope_sincos<kD>((float)pos * rope_theta<kD>(c0 + e, p.rope_log2_base), sn, cs);
                     const float x = a[e], y = b[e];
                     a[e] = x * cs + y * sn;
                     b[e] = y * cs - x * sn;
@@ -786,10 +830,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 // left operand dS[i][j]: row i = lane&31 (this lane's query), k <-> key rows of the accumulator
-                const bf16x8 dsf = pack8(dPt, ks);
+                Operand<AttnTile<kD>::kTwo> dsf;
+                pack8(dsf, dPt, ks);
 #pragma unroll
-                for (int nb = 0; nb < kNB; ++nb)
-                    dQ[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf, lds_frag_rows<kD>(bk, lane_r0, lane_r1, ks, nb), dQ[nb], 0, 0, 0);
+                for (int nb = 0; nb < kNB; ++nb) {
+                    const bf16x8 kr = lds_frag_rows<kD>(bk, lane_r0, lane_r1, ks, nb);
+                    dQ[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf.hi, kr, dQ[nb], 0, 0, 0);
+                    if constexpr (AttnTile<kD>::kTwo) dQ[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf.lo, kr, dQ[nb], 0, 0, 0);
+                }
             }
         }
     }
@@ -851,6 +899,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) Ot[n][e] = 0.f;
     float m2 = -INFINITY, l = 0.f;  // running max (log2 domain) and normaliser of this lane's half of the keys
+    float m_raw = -INFINITY;        // heads of 64: the running max of the raw scores (m2 is it, scaled and rounded)
 
     const uint32_t lane_d = frag_d_lane<kD>(lane), lane_r0 = frag_rows_lane<kD>(lane, 0), lane_r1 = frag_rows_lane<kD>(lane, 1);
     uint32_t voff[kLoads];
@@ -894,14 +943,16 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
             for (int kk = 0; kk < kKK; ++kk)
                 St[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_d(tk + jb * 32 * kRowBytes, lane_d, kk), qf[kk], St[jb], 0, 0, 0);
         }
-        // scores in the log2 domain, masked (key j = jt + jb*32 + 8b + 4*half + r must satisfy j <= lim)
+        // scores, masked (key j = jt + jb*32 + 8b + 4*half + r must satisfy j <= lim); heads of 128 take them to the log2
+        // domain here, heads of 64 inside the exponent, where it costs no rounding
+        constexpr bool kTwo = AttnTile<kD>::kTwo;
         const bool need_mask = jt + 63 > (in_pre ? pre_len - 1 : i0);
-        float mx = m2;
+        float mx = kTwo ? m_raw : m2;
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                float sv = St[jb][e] * sl2;
+                float sv = kTwo ? St[jb][e] : St[jb][e] * sl2;
                 if (need_mask) {
                     const int j = jt + jb * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
                     if (j > lim) sv = -INFINITY;
@@ -910,6 +961,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
                 mx = fmaxf(mx, sv);
             }
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // both halves of the wave share the query
+        if (kTwo) {
+            m_raw = mx;
+            mx *= sl2;
+            asm("" : "+v"(mx));  // (the rounded product everywhere: fused into the differences below, each tile would rescale by its rounding)
+        }
         const float alpha = __builtin_amdgcn_exp2f(m2 - mx);  // 0 on the first tile (m2 = -inf), keys 0.. always valid
         m2 = mx;
         float sum = 0.f;
@@ -917,7 +973,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
         for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float pr = __builtin_amdgcn_exp2f(St[jb][e] - mx);
+                const float pr = __builtin_amdgcn_exp2f(kTwo ? __builtin_fmaf(St[jb][e], sl2, -mx) : St[jb][e] - mx);
                 St[jb][e] = pr;
                 sum += pr;
             }
@@ -930,10 +986,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
         for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                const bf16x8 pf = pack8(St[jb], ks);  // right operand P^T: column = this lane's query, k <-> key rows
+                Operand<kTwo> pf;  // right operand P^T: column = this lane's query, k <-> key rows
+                pack8(pf, St[jb], ks);
 #pragma unroll
-                for (int nb = 0; nb < kNB; ++nb)
-                    Ot[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_rows<kD>(tv + jb * 32 * kRowBytes, lane_r0, lane_r1, ks, nb), pf, Ot[nb], 0, 0, 0);
+                for (int nb = 0; nb < kNB; ++nb) {
+                    const bf16x8 vr = lds_frag_rows<kD>(tv + jb * 32 * kRowBytes, lane_r0, lane_r1, ks, nb);
+                    Ot[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr, pf.hi, Ot[nb], 0, 0, 0);
+                    if constexpr (kTwo) Ot[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr, pf.lo, Ot[nb], 0, 0, 0);
+                }
             }
     }
     l += __shfl_xor(l, 32, 64);
@@ -949,7 +1009,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
                 for (int r = 0; r < 4; ++r) o[r] = (__bf16)(Ot[nb][4 * b + r] * inv);
                 *reinterpret_cast<bf16x4*>(orow + nb * 32 + 8 * b + 4 * half) = o;
             }
-        if (half == 0) p.LSE[(long long)(seq_start + i) * p.Hq + h] = (m2 + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+        if (half == 0) {
+            const long long row = (long long)(seq_start + i) * p.Hq + h;
+            if (AttnTile<kD>::kTwo) p.LSE[row] = (float)((double)m2 * 0.6931471805599453 + (double)logf(l));  // (m2 as the exponents had it)
+            else p.LSE[row] = (m2 + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+        }
     }
 }
 
