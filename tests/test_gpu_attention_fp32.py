@@ -26,3 +26,28 @@ def test_gradients(monkeypatch, shape_name, lens):
     compare(first, ref, "f32")
     for k in first:
         assert np.array_equal(first[k], second[k]), k
+
+
+@pytest.mark.parametrize("D,Hkv,lens", [(64, 4, [128, 128]), (64, 4, [300, 1, 723]), (128, 2, [300, 1, 723]), (256, 2, [1024]), (32, 8, [1, 1023])])
+def test_sums_round_no_more_often_than_a_tree(D, Hkv, lens):
+    # Scores are sums of D products of order 1 and lose what their order of addition costs.  With the terms paired (log2 D
+    # roundings each) O was within 1.6e-7 of its norm at 2 x 128 tokens and 2.5e-7 .. 3.3e-7 at 1024, dQ of the short
+    # sequences within 3.6e-7; one sum over the whole head made it 2.0e-7, 2.0e-7 .. 4.4e-7 and 4.3e-7.  The bounds are the
+    # paired sums' errors (of 1024 tokens the smallest).
+    import torch
+    import paper_2503_01066_amd as A
+    from helpers import alch_shape, to_dev, to_np
+    from test_gpu_attention_d64 import attention_fp64, exposed_case, run_exposed
+    cu = synth.ragged_cu(lens)
+    T = int(cu[-1])
+    shp, W, rec, dY = exposed_case(cu, Hkv, D, 10000.0, np.random.default_rng(7), "f32")
+    ref = attention_fp64(shp, cu, rec, dY)
+    O, _ = A.alch_attention_forward(alch_shape(shp, "f32"), A.Batch(cu), *[to_dev(rec[k], "f32") for k in "QKV"])
+    torch.cuda.synchronize()
+    err = np.linalg.norm(to_np(O) - ref["O"]) / np.linalg.norm(ref["O"])
+    assert err <= (1.6e-7 if T == 256 else 2.5e-7), err
+    if T == 256:
+        got = run_exposed(shp, W, rec, ref["LSE"], dY, cu, dtype="f32")
+        for k, bound in (("dQ", 3.65e-7), ("dK", 3.2e-7), ("dV", 2.6e-7)):
+            err = np.linalg.norm(got[k] - ref[k]) / np.linalg.norm(ref[k])
+            assert err <= bound, (k, err)
