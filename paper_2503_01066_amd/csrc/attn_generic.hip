@@ -49,7 +49,8 @@ struct AttnPlainParams {
     const int *cu, *prefix, *positions;
     int n_seqs, seq_begin, blocks, Hq, Hkv, D;  // the grid: (head, block of 32 rows) x sequences from seq_begin on
     long long ldo;          // row stride of dQ, dK, dV
-    float scale, log2_base;  // log2_base > 0: dQ and dK are rotated by minus the RoPE angle
+    float scale, log2_base;
+    int rope;               // dQ and dK are rotated by minus the RoPE angle
     int vec;                // rows allow loads of four elements
 };
 
@@ -136,12 +137,12 @@ __device__ __forceinline__ void fold(FoldBuf<NB>& buf, const f32x16 (&x)[NB], in
     }
 }
 
-// LDS [32][ld] -> rows of the output, scaled and, with log2_base > 0, rotated by minus the RoPE angle.
+// LDS [32][ld] -> rows of the output, scaled and, with `rope`, rotated by minus the RoPE angle.
 template <typename T, int NB>
 __device__ __forceinline__ void store_rows(const FoldBuf<NB>& buf, T* out, long long ldo, int rows, int D, float scale,
-                                           float log2_base, const int* positions, int token0, int row0) {
+                                           bool rope, float log2_base, const int* positions, int token0, int row0) {
     constexpr int ld = FoldBuf<NB>::kLd;
-    if (log2_base > 0.f) {
+    if (rope) {
         const int hd = D >> 1;
         for (int q = threadIdx.x; q < rows * hd; q += kWaves * 64) {
             const int r = q / hd, k = q - r * hd;
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<
     for (int w = 0; w < kWaves; ++w) L += ml[1][w][lane & 31] * expf(ml[0][w][lane & 31] - M);
     fold<NB, true>(buf, Ot, wave, lane, expf(m - M) / L);
     const int rows = min(kBlk, kb.len - i0);
-    store_rows(buf, p.Oout + (kb.own0 + i0) * ldq + (long long)h * D, ldq, rows, D, 1.f, 0.f, nullptr, 0, 0);
+    store_rows(buf, p.Oout + (kb.own0 + i0) * ldq + (long long)h * D, ldq, rows, D, 1.f, false, 0.f, nullptr, 0, 0);
     if (wave == 0 && half == 0 && lane < rows) p.LSE[(long long)(kb.own0 + i0 + lane) * p.Hq + h] = M + logf(L);
 }
 
@@ -304,7 +305,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnPlainParams<T>& p, F
     }
     fold<NB, false>(buf, dQ, wave, lane, 1.f);
     store_rows(buf, p.dQ + (kb.own0 + i0) * p.ldo + (long long)h * D, p.ldo, min(kBlk, kb.len - i0), D, p.scale,
-               p.log2_base, p.positions, kb.own0 + i0, i0);
+               p.rope, p.log2_base, p.positions, kb.own0 + i0, i0);
 }
 
 // dK, dV of block `block` (kv heads first, then 32-key blocks); kDelta: forms delta of the queries it meets by itself
@@ -367,9 +368,9 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnPlainParams<T>& p, 
     const int rows = min(kBlk, len - j0);
     const long long out = (own0 + j0) * p.ldo + (long long)kv * D;
     fold<NB, false>(buf, dK, wave, lane, 1.f);
-    store_rows(buf, p.dK + out, p.ldo, rows, D, p.scale, p.log2_base, p.positions, own0 + j0, j0);
+    store_rows(buf, p.dK + out, p.ldo, rows, D, p.scale, p.rope, p.log2_base, p.positions, own0 + j0, j0);
     fold<NB, false>(buf, dV, wave, lane, 1.f);
-    store_rows(buf, p.dV + out, p.ldo, rows, D, 1.f, 0.f, nullptr, 0, 0);
+    store_rows(buf, p.dV + out, p.ldo, rows, D, 1.f, false, 0.f, nullptr, 0, 0);
 }
 
 template <typename T, int NB, bool kFull>
@@ -436,7 +437,8 @@ static int attn_bwd_generic_t(const AttnArgs& a, hipStream_t stream) {
     p.cu = a.cu_seqlens; p.prefix = a.prefix; p.positions = a.positions;
     p.n_seqs = a.n_seqs; p.Hq = a.Hq; p.Hkv = a.Hkv; p.D = a.D;
     p.scale = 1.f / sqrtf((float)a.D);
-    p.log2_base = a.rope_base > 0.f ? log2f(a.rope_base) : 0.f;
+    p.rope = a.rope_base > 0.f;
+    p.log2_base = p.rope ? log2f(a.rope_base) : 0.f;
     p.vec = head_rows_vec<T>(a.D, {a.Q, a.K, a.V, a.O, a.dO});
     p.blocks = ceil_div(a.max_seqlen, kBlk);
     if (p.blocks <= 0 || a.n_seqs <= 0) return ALCH_OK;

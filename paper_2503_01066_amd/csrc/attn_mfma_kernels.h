@@ -69,7 +69,8 @@ struct AttnMfmaParams {
     int Hq, Hkv;
     long long ldq, ldk, ldo;  // row strides (elements) of Q/dO, K/V, and of the outputs
     float scale;
-    float rope_log2_base;  // > 0: rotate dQ, dK by minus the RoPE angle before they are stored
+    int rope;              // rotate dQ, dK by minus the RoPE angle before they are stored
+    float rope_log2_base;
     // dK/dV: key blocks of up to n_blocks per sequence; a block whose query stream is longer than part_len tiles is cut
     // over the query heads of the group into up to max_parts work-groups, which leave fp32 partial sums
     // [part][T][Hkv][dK | dV] in `partial` (max_parts 1: none is)
@@ -616,7 +617,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
             }
         return;
     }
-    if (p.rope_log2_base > 0.f) rope_backward_rows<kD>(dK, p, seq_start, j0, len, lane);
+    if (p.rope) rope_backward_rows<kD>(dK, p, seq_start, j0, len, lane);
     __bf16* dKb = p.dK + (long long)seq_start * p.ldo + kv * kD;
     __bf16* dVb = p.dV + (long long)seq_start * p.ldo + kv * kD;
 #pragma unroll
@@ -660,7 +661,7 @@ __global__ __launch_bounds__(256) void k_dkv_finish(AttnMfmaParams p) {
             b += *reinterpret_cast<const f32x4*>(src + k * pitch + c1);
         }
         if (is_k) {
-            if (p.rope_log2_base > 0.f) {
+            if (p.rope) {
                 const int pos = p.positions ? p.positions[seq_start + r] : r;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -842,7 +843,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
         }
     }
 
-    if (p.rope_log2_base > 0.f) rope_backward_rows<kD>(dQ, p, seq_start, i0, len, lane);
+    if (p.rope) rope_backward_rows<kD>(dQ, p, seq_start, i0, len, lane);
     __bf16* dQb = p.dQ + (long long)seq_start * p.ldo + h * kD;
 #pragma unroll
     for (int nb = 0; nb < kNB; ++nb)
@@ -1065,7 +1066,7 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     AttnMfmaParams p{};
     p.Q = (const __bf16*)a.Q; p.K = (const __bf16*)a.K; p.V = (const __bf16*)a.V; p.dO = (const __bf16*)a.dO;
     p.O = (const __bf16*)a.O; p.LSE = a.LSE; p.delta = a.delta; p.lse2 = a.delta + (size_t)a.T * a.Hq;
-    p.positions = a.positions; p.rope_log2_base = a.rope_base > 0.f ? log2f(a.rope_base) : 0.f;
+    p.positions = a.positions; p.rope = a.rope_base > 0.f; p.rope_log2_base = p.rope ? log2f(a.rope_base) : 0.f;
     p.dQ = (__bf16*)a.dQ; p.dK = (__bf16*)a.dK; p.dV = (__bf16*)a.dV;
     p.cu = a.cu_seqlens; p.prefix = a.prefix; p.n_seqs = a.n_seqs; p.Hq = a.Hq; p.Hkv = a.Hkv;
     p.ldq = (long long)a.Hq * a.D; p.ldk = (long long)a.Hkv * a.D; p.ldo = a.ld_dqkv;
