@@ -440,8 +440,7 @@ static int attn_bwd_generic_t(const AttnArgs& a, hipStream_t stream) {
     p.rope = a.rope_base > 0.f;
     p.log2_base = p.rope ? log2f(a.rope_base) : 0.f;
     p.vec = head_rows_vec<T>(a.D, {a.Q, a.K, a.V, a.O, a.dO});
-    p.blocks = ceil_div(a.max_seqlen, kBlk);
-    if (p.blocks <= 0 || a.n_seqs <= 0) return ALCH_OK;
+    p.blocks = ceil_div(longest_sequence(a.cu_seqlens_host, 0, a.n_seqs), kBlk);
     int n_cu = 0;
     ALCH_TRY(compute_units(&n_cu));
     return with_blocks<T>(a.D, p.vec, [&](auto NB, auto full) {
@@ -470,14 +469,14 @@ int launch_attn_bwd_generic(const AttnArgs& a, hipStream_t stream) {
 }
 
 template <typename T>
-static int attn_fwd_generic_t(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, int max_seqlen,
-                              const int* cu, const int* prefix, int seq_begin, int Hq, int Hkv, int D, hipStream_t stream) {
+static int attn_fwd_generic_t(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, const int* cu,
+                              const int* cu_host, const int* prefix, int seq_begin, int Hq, int Hkv, int D, hipStream_t stream) {
     AttnPlainParams<T> p = {};
     p.Q = (const T*)Q; p.K = (const T*)K; p.V = (const T*)V; p.Oout = (T*)O; p.LSE = LSE;
     p.cu = cu; p.prefix = prefix; p.n_seqs = n_seqs; p.Hq = Hq; p.Hkv = Hkv; p.D = D;
     p.scale = 1.f / sqrtf((float)D);
     p.vec = head_rows_vec<T>(D, {Q, K, V});
-    p.blocks = ceil_div(max_seqlen, kBlk);
+    p.blocks = ceil_div(longest_sequence(cu_host, seq_begin, n_seqs), kBlk);
     return with_blocks<T>(D, p.vec, [&](auto NB, auto full) {
         by_sequences(p, seq_begin, [&](int n) {
             k_attn_fwd_plain<T, decltype(NB)::value, decltype(full)::value><<<dim3(p.blocks * Hq, n), kWaves * 64, 0, stream>>>(p);
@@ -486,12 +485,12 @@ static int attn_fwd_generic_t(const void* Q, const void* K, const void* V, void*
 }
 
 int launch_attn_fwd_generic(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int T,
-                            int n_seqs, int max_seqlen, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
+                            int n_seqs, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
                             int seq_begin, int Hq, int Hkv, int D, hipStream_t stream) {
-    if (T - cu_seqlens_host[seq_begin] <= 0 || max_seqlen <= 0) return ALCH_OK;
+    if (T - cu_seqlens_host[seq_begin] <= 0) return ALCH_OK;
     return dt == ALCH_BF16
-               ? attn_fwd_generic_t<__bf16>(Q, K, V, O, LSE, n_seqs, max_seqlen, cu_seqlens, prefix, seq_begin, Hq, Hkv, D, stream)
-               : attn_fwd_generic_t<float>(Q, K, V, O, LSE, n_seqs, max_seqlen, cu_seqlens, prefix, seq_begin, Hq, Hkv, D, stream);
+               ? attn_fwd_generic_t<__bf16>(Q, K, V, O, LSE, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream)
+               : attn_fwd_generic_t<float>(Q, K, V, O, LSE, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream);
 }
 
 }  // namespace alch

@@ -9,7 +9,10 @@ bool attn_mfma_supported(const AttnArgs& a) {
 }
 
 int launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
-    return a.D == 128 ? attn_bwd_mfma<128>(a, stream) : attn_bwd_mfma_d64(a, stream);
+    if (a.D == 128) return attn_bwd_mfma<128>(a, stream);
+    AttnArgs b = a;
+    b.max_seqlen = longest_sequence(a.cu_seqlens_host, 0, a.n_seqs);
+    return attn_bwd_mfma_d64(b, stream);
 }
 
 int launch_attn_fwd(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int T,
@@ -21,9 +24,10 @@ int launch_attn_fwd(alch_dtype dt, const void* Q, const void* K, const void* V, 
     TraceScope ts(kTraceAttnFwd, 4.0 * D * Hq * pairs, 0.0, stream);
     if (dt == ALCH_BF16 && (D == 128 || D == 64) && T > 0 && aligned16(Q) && aligned16(K) && aligned16(V) && aligned16(O)) {
         return D == 128 ? attn_fwd_mfma<128>(Q, K, V, O, LSE, n_seqs, max_seqlen, cu_seqlens, prefix, seq_begin, Hq, Hkv, stream)
-                        : attn_fwd_mfma_d64(Q, K, V, O, LSE, n_seqs, max_seqlen, cu_seqlens, prefix, seq_begin, Hq, Hkv, stream);
+                        : attn_fwd_mfma_d64(Q, K, V, O, LSE, n_seqs, longest_sequence(cu_seqlens_host, seq_begin, n_seqs), cu_seqlens,
+                                            prefix, seq_begin, Hq, Hkv, stream);
     }
-    return launch_attn_fwd_generic(dt, Q, K, V, O, LSE, T, n_seqs, max_seqlen, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream);
+    return launch_attn_fwd_generic(dt, Q, K, V, O, LSE, T, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream);
 }
 
 }  // namespace alch

@@ -1071,7 +1071,7 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     p.cu = a.cu_seqlens; p.prefix = a.prefix; p.n_seqs = a.n_seqs; p.Hq = a.Hq; p.Hkv = a.Hkv;
     p.ldq = (long long)a.Hq * a.D; p.ldk = (long long)a.Hkv * a.D; p.ldo = a.ld_dqkv;
     p.scale = 1.0f / sqrtf((float)a.D);
-    const int nb = ceil_div(a.max_seqlen, 128);
+    const int nb = (int)(((long long)a.max_seqlen + 127) / 128);
     if (nb <= 0 || a.n_seqs <= 0) return ALCH_OK;
     if (nb > 65535 || a.n_seqs > 65535) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
     p.T = a.T;
@@ -1100,7 +1100,7 @@ int attn_fwd_mfma(const void* Q, const void* K, const void* V, void* O, float* L
     p.cu = cu_seqlens; p.prefix = prefix; p.seq_begin = seq_begin;
     p.Hq = Hq; p.Hkv = Hkv; p.ldq = (long long)Hq * kD; p.ldk = (long long)Hkv * kD;
     p.scale = 1.0f / sqrtf((float)kD);
-    const int nb = ceil_div(max_seqlen, 128);
+    const int nb = (int)(((long long)max_seqlen + 127) / 128);
     if (nb <= 0 || n_seqs <= 0) return ALCH_OK;
     if (nb > 65535 || n_seqs > 65535) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
     k_attn_fwd_mfma<kD><<<dim3(Hq, n_seqs - seq_begin, nb), 256, 0, stream>>>(p);

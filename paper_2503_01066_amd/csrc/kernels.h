@@ -163,6 +163,13 @@ struct AttnArgs {
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
 };
+// Tokens of the longest of the sequences first .. n_seqs-1.  max_seqlen is only a bound on them, and may be any number that
+// is not below it.
+inline int longest_sequence(const int* cu_host, int first, int n_seqs) {
+    int n = 0;
+    for (int s = first; s < n_seqs; ++s) n = cu_host[s + 1] - cu_host[s] > n ? cu_host[s + 1] - cu_host[s] : n;
+    return n;
+}
 int compute_units(int* n_cu);  // of the current device, a multiple of 8
 int launch_attn_bwd(const AttnArgs& a, hipStream_t stream);
 int launch_attn_bwd_generic(const AttnArgs& a, hipStream_t stream);
@@ -176,7 +183,7 @@ double attn_pairs(int n_seqs, const int* cu_host, const int* prefix_host);
 // forward: writes O [T,Hq*D] and LSE [T,Hq] for the query rows of sequences seq_begin .. n_seqs-1 (keys and
 // values of a prefix sequence are read wherever it lies); prefix / prefix_host as in AttnArgs
 int launch_attn_fwd_generic(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int T,
-                            int n_seqs, int max_seqlen, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
+                            int n_seqs, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
                             int seq_begin, int Hq, int Hkv, int D, hipStream_t stream);
 int launch_attn_fwd(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int T,
                     int n_seqs, int max_seqlen, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
