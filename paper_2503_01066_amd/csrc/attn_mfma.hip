@@ -3,8 +3,14 @@
 
 namespace alch {
 
+// Batches of heads of 64 that the grid of the matrix-core kernels cannot hold run on the fp32-arithmetic ones, which take any.
+// (Heads of 128 are refused there: they have never had another path.)
+static bool head_size_fits(int D, int n_seqs, const int* cu_host) {
+    return D == 128 || (D == 64 && n_seqs <= kMaxGridSeqs && longest_sequence(cu_host, 0, n_seqs) <= kMaxGridBlocks * 128);
+}
+
 bool attn_mfma_supported(const AttnArgs& a) {
-    return a.dtype == ALCH_BF16 && (a.D == 128 || a.D == 64) && a.T > 0 && a.ld_dqkv % 8 == 0 && aligned16(a.Q) && aligned16(a.K) &&
+    return a.dtype == ALCH_BF16 && head_size_fits(a.D, a.n_seqs, a.cu_seqlens_host) && a.T > 0 && a.ld_dqkv % 8 == 0 && aligned16(a.Q) && aligned16(a.K) &&
            aligned16(a.V) && aligned16(a.dO) && aligned16(a.O);
 }
 
@@ -22,7 +28,7 @@ int launch_attn_fwd(alch_dtype dt, const void* Q, const void* K, const void* V, 
     const double pairs = attn_pairs(n_seqs - seq_begin, cu_seqlens_host + seq_begin, nullptr) +
                          (attn_pairs(n_seqs, cu_seqlens_host, prefix_host) - attn_pairs(n_seqs, cu_seqlens_host, nullptr));
     TraceScope ts(kTraceAttnFwd, 4.0 * D * Hq * pairs, 0.0, stream);
-    if (dt == ALCH_BF16 && (D == 128 || D == 64) && T > 0 && aligned16(Q) && aligned16(K) && aligned16(V) && aligned16(O)) {
+    if (dt == ALCH_BF16 && head_size_fits(D, n_seqs, cu_seqlens_host) && T > 0 && aligned16(Q) && aligned16(K) && aligned16(V) && aligned16(O)) {
         return D == 128 ? attn_fwd_mfma<128>(Q, K, V, O, LSE, n_seqs, max_seqlen, cu_seqlens, prefix, seq_begin, Hq, Hkv, stream)
                         : attn_fwd_mfma_d64(Q, K, V, O, LSE, n_seqs, longest_sequence(cu_seqlens_host, seq_begin, n_seqs), cu_seqlens,
                                             prefix, seq_begin, Hq, Hkv, stream);

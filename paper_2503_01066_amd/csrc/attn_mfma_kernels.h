@@ -54,7 +54,7 @@ template <int kD> struct AttnTile {
 };
 static constexpr float kLog2e = 1.4426950408889634f;
 static constexpr int kMinPartTiles = 8;  // tiles a part of a key block has at least
-
+static constexpr int kMaxGridSeqs = 65535, kMaxGridBlocks = 65535;  // of 128 tokens: limits of a grid's second and third dimension
 
 struct AttnMfmaParams {
     const __bf16 *Q, *K, *V, *O, *dO;
@@ -1054,7 +1054,7 @@ inline int plan_dkv_parts(const AttnArgs& a, AttnMfmaParams& p, int& longest) {
     const long long part_len = std::max<long long>(total * G * a.Hkv * 6 / 5 / n_cu, kMinPartTiles);
     if (!a.scratch || part_bytes == 0 || n_blocks * a.Hkv > n_cu + n_cu / 8 || most * G < part_len + 10) return ALCH_OK;
     const int max_parts = (int)std::min<size_t>(std::min(G, 8), a.scratch_bytes / part_bytes);
-    if (max_parts < 2 || (long long)p.n_blocks * max_parts > 65535) return ALCH_OK;
+    if (max_parts < 2 || (long long)p.n_blocks * max_parts > kMaxGridBlocks) return ALCH_OK;
     p.max_parts = max_parts;
     p.part_len = (int)part_len;
     p.partial = static_cast<float*>(a.scratch);
@@ -1073,7 +1073,7 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     p.scale = 1.0f / sqrtf((float)a.D);
     const int nb = (int)(((long long)a.max_seqlen + 127) / 128);
     if (nb <= 0 || a.n_seqs <= 0) return ALCH_OK;
-    if (nb > 65535 || a.n_seqs > 65535) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
+    if (nb > kMaxGridBlocks || a.n_seqs > kMaxGridSeqs) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
     p.T = a.T;
     p.n_blocks = nb;
     int longest = 0;
@@ -1102,7 +1102,7 @@ int attn_fwd_mfma(const void* Q, const void* K, const void* V, void* O, float* L
     p.scale = 1.0f / sqrtf((float)kD);
     const int nb = (int)(((long long)max_seqlen + 127) / 128);
     if (nb <= 0 || n_seqs <= 0) return ALCH_OK;
-    if (nb > 65535 || n_seqs > 65535) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
+    if (nb > kMaxGridBlocks || n_seqs > kMaxGridSeqs) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
     k_attn_fwd_mfma<kD><<<dim3(Hq, n_seqs - seq_begin, nb), 256, 0, stream>>>(p);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;

@@ -104,3 +104,30 @@ def test_heads_of_64_lose_nothing_but_the_rounding_of_their_results(Hkv, lens):
         assert err <= 1.01 * rounding, (k, err / rounding)
     # one fp32 rounding of a number up to |LSE|, and that of the normaliser's sum and logarithm
     assert np.abs(to_np(lse) - ref["LSE"]).max() <= 2.0 ** -24 * np.abs(ref["LSE"]).max() + 2.0 ** -21
+
+
+def test_more_sequences_than_a_grid_holds():
+    # 65,538 sequences, all but two of one token: beyond the 65,535 of the matrix-core kernels' grid, and the same tokens in two
+    # batches that fit it.  Outputs of a token depend on its own sequence alone.
+    import paper_2503_01066_amd as A
+    shp = dict(hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=64, rms_eps=1e-5, rope_base=10000.0)
+    lens = [1] * 32768 + [37] + [1] * 32768 + [70]
+    T, rng = sum(lens), np.random.default_rng(3)
+    W = {k: to_dev(v, "bf16") for k, v in synth.layer_weights(shp, 1, "bf16").items()}
+    rec = {k: to_dev(v, "bf16") for k, v in synth.drawn_record(shp, T, 2, "bf16").items() if k != "LSE"}
+    dY = to_dev(synth.activations(T, 64, 3, "bf16", std=0.01), "bf16")
+    sh, half = alch_shape(shp, "bf16"), 32768 + 37
+
+    def run(lens, rows):
+        batch = A.Batch(synth.ragged_cu(lens))
+        part = {k: v[rows].contiguous() for k, v in rec.items()}
+        O, part["LSE"] = A.alch_attention_forward(sh, batch, part["Q"], part["K"], part["V"])
+        dX = A.alch_layer_backward(sh, batch, part, W, dY[rows].contiguous(), want=())["dX"]
+        torch.cuda.synchronize()
+        return to_np(O), to_np(part["LSE"]), to_np(dX)
+
+    whole = run(lens, slice(0, T))
+    parts = [run(lens[:32769], slice(0, half)), run(lens[32769:], slice(half, T))]
+    for i, tol in enumerate((TOL["bf16"], 1e-5, TOL["bf16"])):
+        assert rel_err(whole[i], np.concatenate([p[i] for p in parts])) <= tol, i
+    assert np.array_equal(whole[0][:32768], to_np(rec["V"])[:32768].repeat(2, 0).reshape(32768, -1))  # one key: O = V
