@@ -22,7 +22,7 @@
 #include <initializer_list>
 #include <type_traits>
 
-#include "kernels.h"
+#include "attn_rows.h"
 
 namespace alch {
 
@@ -137,6 +137,19 @@ __device__ __forceinline__ void fold(FoldBuf<NB>& buf, const f32x16 (&x)[NB], in
     }
 }
 
+// Any sum of the work-group not finite (the wavefronts' flags of not_finite)
+__device__ __forceinline__ bool any_not_finite(float flag) { return __syncthreads_or(!(flag == 0.f)) != 0; }
+// A row formed anew, in place of the sums of the wavefronts
+template <int NB, typename T, int E>
+__device__ __forceinline__ void replace_row(FoldBuf<NB>& buf, int r, const HeadRow<T, E>& x, int D) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int d = (int)(threadIdx.x & 63) + 64 * e;
+        if (d >= D) continue;
+        for (int w = 0; w < FoldBuf<NB>::kBlocks; ++w) buf.at[w * FoldBuf<NB>::kPitch + r * FoldBuf<NB>::kLd + d] = w == 0 ? x.v[e] : 0.f;
+    }
+}
+
 // LDS [32][ld] -> rows of the output, scaled and, with `rope`, rotated by minus the RoPE angle.
 template <typename T, int NB>
 __device__ __forceinline__ void store_rows(const FoldBuf<NB>& buf, T* out, long long ldo, int rows, int D, float scale,
@@ -173,6 +186,7 @@ struct KeyBlocks {
         n_pre = (pre_len + kBlk - 1) / kBlk;
         n = n_pre + min(i0 + kBlk - 1, len - 1) / kBlk + 1;
     }
+    __device__ __forceinline__ SeenKeys seen_by(int i) const { return SeenKeys{pre0, pre_len, own0, pre_len + i + 1}; }
     // first key of block b, keys of its sequence, its first row in the batch
     __device__ __forceinline__ void at(int b, int& j0, int& keys, int& row0) const {
         const bool in_pre = b < n_pre;
@@ -243,8 +257,21 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<
     for (int w = 0; w < kWaves; ++w) M = fmaxf(M, ml[0][w][lane & 31]);
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) L += ml[1][w][lane & 31] * expf(ml[0][w][lane & 31] - M);
-    fold<NB, true>(buf, Ot, wave, lane, expf(m - M) / L);
     const int rows = min(kBlk, kb.len - i0);
+    float flag = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) flag = not_finite(Ot[nb], flag);
+    if (any_not_finite(flag)) {  // formed again from the visible keys alone (attn_rows.h)
+        for (int r = wave; r < rows; r += kWaves) {
+            HeadRow<T, (NB + 1) / 2> o;
+            attn_fwd_row(p.Q + (kb.own0 + i0 + r) * ldq + (long long)h * D, p.K + (long long)kv * D, p.V + (long long)kv * D, ldk,
+                         kb.seen_by(i0 + r), D, p.scale, o);
+            replace_row(buf, r, o, D);
+        }
+        __syncthreads();
+    } else {
+        fold<NB, true>(buf, Ot, wave, lane, expf(m - M) / L);
+    }
     store_rows(buf, p.Oout + (kb.own0 + i0) * ldq + (long long)h * D, ldq, rows, D, 1.f, false, 0.f, nullptr, 0, 0);
     if (wave == 0 && half == 0 && lane < rows) p.LSE[(long long)(kb.own0 + i0 + lane) * p.Hq + h] = M + logf(L);
 }
@@ -303,7 +330,21 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnPlainParams<T>& p, F
             }
         }
     }
-    fold<NB, false>(buf, dQ, wave, lane, 1.f);
+    float flag = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) flag = not_finite(dQ[nb], flag);
+    if (any_not_finite(flag)) {
+        for (int r = wave; r < min(kBlk, kb.len - i0); r += kWaves) {
+            const long long at = (kb.own0 + i0 + r) * ldq + (long long)h * D;
+            HeadRow<T, (NB + 1) / 2> x;
+            attn_dq_row(p.Q + at, p.dO + at, p.O + at, p.K + (long long)kv * D, p.V + (long long)kv * D, ldk, kb.seen_by(i0 + r), D,
+                        p.scale, p.LSE[(long long)(kb.own0 + i0 + r) * p.Hq + h], x);
+            replace_row(buf, r, x, D);
+        }
+        __syncthreads();
+    } else {
+        fold<NB, false>(buf, dQ, wave, lane, 1.f);
+    }
     store_rows(buf, p.dQ + (kb.own0 + i0) * p.ldo + (long long)h * D, p.ldo, min(kBlk, kb.len - i0), D, p.scale,
                p.rope, p.log2_base, p.positions, kb.own0 + i0, i0);
 }
@@ -352,6 +393,37 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnPlainParams<T>& p, 
                     dP[e] = S[e] * (dP[e] - de);
                 }
                 const T *qh = p.Q + row0 * ldq + (long long)h * D, *gh = p.dO + row0 * ldq + (long long)h * D;
+                if constexpr (kFull) {
+                    // the elements of four rows are on their way while those of the four before are multiplied (left to the
+                    // compiler, each load of heads of 128 stood before its use: 870 us for 2000 tokens, 504 us so)
+                    float gb[2][4][NB], qb[2][4][NB];
+                    auto load = [&](int e0, float (&g)[4][NB], float (&q)[4][NB]) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const long long ro = min(i0 + row_of(e0 + e, half), n - 1) * ldq + (lane & 31);
+#pragma unroll
+                            for (int nb = 0; nb < NB; ++nb) {
+                                g[e][nb] = ldf(gh + ro + nb * 32);
+                                q[e][nb] = ldf(qh + ro + nb * 32);
+                            }
+                        }
+                    };
+                    load(0, gb[0], qb[0]);
+#pragma unroll
+                    for (int e0 = 0; e0 < 16; e0 += 4) {
+                        if (e0 + 4 < 16) load(e0 + 4, gb[(e0 / 4 + 1) & 1], qb[(e0 / 4 + 1) & 1]);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int nb = 0; nb < NB; ++nb) {
+                                dV[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(S[e0 + e], gb[(e0 / 4) & 1][e][nb], dV[nb], 0, 0, 0);
+                                dK[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dP[e0 + e], qb[(e0 / 4) & 1][e][nb], dK[nb], 0, 0, 0);
+                            }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    continue;
+                }
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const long long ro = min(i0 + row_of(e, half), n - 1) * ldq;
@@ -367,6 +439,24 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnPlainParams<T>& p, 
     }
     const int rows = min(kBlk, len - j0);
     const long long out = (own0 + j0) * p.ldo + (long long)kv * D;
+    float flag = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) flag = not_finite(dV[nb], not_finite(dK[nb], flag));
+    if (any_not_finite(flag)) {
+        for (int r = wave; r < rows; r += kWaves) {
+            HeadRow<T, (NB + 1) / 2> dk, dv;
+            const long long at = (own0 + j0 + r) * ldk + (long long)kv * D;
+            attn_dkv_row(p.K + at, p.V + at, p.Q, p.dO, p.O, p.LSE, p.Hq, kv * G, (kv + 1) * G, p.cu, p.prefix, p.n_seqs, seq, j0 + r, D,
+                         p.scale, dk, dv);
+            replace_row(buf, r, dk, D);
+#pragma unroll
+            for (int e = 0; e < (NB + 1) / 2; ++e)
+                if (lane + 64 * e < D) stf(p.dV + out + (long long)r * p.ldo + lane + 64 * e, dv.v[e]);
+        }
+        __syncthreads();
+        store_rows(buf, p.dK + out, p.ldo, rows, D, p.scale, p.rope, p.log2_base, p.positions, own0 + j0, j0);
+        return;
+    }
     fold<NB, false>(buf, dK, wave, lane, 1.f);
     store_rows(buf, p.dK + out, p.ldo, rows, D, p.scale, p.rope, p.log2_base, p.positions, own0 + j0, j0);
     fold<NB, false>(buf, dV, wave, lane, 1.f);

@@ -29,7 +29,7 @@
 #pragma once
 #include <algorithm>
 #include <type_traits>
-#include "kernels.h"
+#include "attn_rows.h"
 
 namespace alch {
 
@@ -121,6 +121,17 @@ __device__ __forceinline__ void rope_backward_rows(f32x16 (&x)[AttnTile<kD>::kNB
             x[nb + AttnTile<kD>::kNB / 2][e] = b * cs - a * sn;
         }
     }
+}
+
+// The same for one row of a head of 64, element `lane` per lane
+template <int kD>
+__device__ __forceinline__ float rope_backward_row(float x, const AttnMfmaParams& p, int seq_start, int row, int lane) {
+    if (!p.rope) return x;
+    const int pos = p.positions ? p.positions[seq_start + row] : row;
+    float sn, cs;
+    rope_sincos<kD>((float)pos * rope_theta<kD>(lane & 31, p.rope_log2_base), sn, cs);
+    const float other = __shfl_xor(x, 32, 64);
+    return lane < 32 ? x * cs + other * sn : x * cs - other * sn;
 }
 
 __device__ __forceinline__ i32x4 rsrc_of(const void* p, long long bytes) {
@@ -601,6 +612,28 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
+    if constexpr (kTwo) {
+        float flag = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) flag = not_finite(dV[nb], not_finite(dK[nb], flag));
+        if (__any(!(flag == 0.f))) {  // formed again from the visible pairs alone (attn_rows.h)
+            for (int j = j0; j < min(j0 + 32, len); ++j) {
+                HeadRow<__bf16, 1> dk, dv;
+                attn_dkv_row(Kb + (long long)j * p.ldk, Vb + (long long)j * p.ldk, p.Q, p.dO, p.O, p.LSE, p.Hq, h_first, h_end, p.cu,
+                             kPrefix ? p.prefix : nullptr, p.n_seqs, seq, j, kD, p.scale, dk, dv);
+                if (parts > 1) {
+                    float* row = p.partial + (((long long)part * p.T + seq_start + j) * p.Hkv + kv) * (2 * kD);
+                    row[lane] = dk.v[0];
+                    row[kD + lane] = dv.v[0];
+                } else {
+                    const long long at = (long long)(seq_start + j) * p.ldo + kv * kD + lane;
+                    p.dK[at] = (__bf16)(rope_backward_row<kD>(dk.v[0], p, seq_start, j, lane) * p.scale);
+                    p.dV[at] = (__bf16)dv.v[0];
+                }
+            }
+            return;
+        }
+    }
     // accumulator element e of block nb: key row j0 + 8*(e>>2) + 4*half + (e&3), column nb*32 + (lane&31)
     if (parts > 1) {
         float* ws = p.partial + (((long long)part * p.T + seq_start) * p.Hkv + kv) * (2 * kD) + (lane & 31);
@@ -843,6 +876,21 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
         }
     }
 
+    if constexpr (AttnTile<kD>::kTwo) {
+        float flag = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) flag = not_finite(dQ[nb], flag);
+        if (__any(!(flag == 0.f))) {
+            for (int r = i0; r < min(i0 + 32, len); ++r) {
+                const long long at = (long long)(seq_start + r) * p.ldq + h * kD;
+                HeadRow<__bf16, 1> x;
+                attn_dq_row(p.Q + at, p.dO + at, p.O + at, p.K + kv_off, p.V + kv_off, p.ldk, SeenKeys{pre_start, pre_len, seq_start, pre_len + r + 1},
+                            kD, p.scale, p.LSE[(long long)(seq_start + r) * p.Hq + h], x);
+                p.dQ[(long long)(seq_start + r) * p.ldo + h * kD + lane] = (__bf16)(rope_backward_row<kD>(x.v[0], p, seq_start, r, lane) * p.scale);
+            }
+            return;
+        }
+    }
     if (p.rope) rope_backward_rows<kD>(dQ, p, seq_start, i0, len, lane);
     __bf16* dQb = p.dQ + (long long)seq_start * p.ldo + h * kD;
 #pragma unroll
@@ -900,6 +948,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) Ot[n][e] = 0.f;
     float m2 = -INFINITY, l = 0.f;  // running max (log2 domain) and normaliser of this lane's half of the keys
+    bool rows_again = false;
     float m_raw = -INFINITY;        // heads of 64: the running max of the raw scores (m2 is it, scaled and rounded)
 
     const uint32_t lane_d = frag_d_lane<kD>(lane), lane_r0 = frag_rows_lane<kD>(lane, 0), lane_r1 = frag_rows_lane<kD>(lane, 1);
@@ -998,9 +1047,23 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
             }
     }
     l += __shfl_xor(l, 32, 64);
+    if constexpr (AttnTile<kD>::kTwo) {
+        float flag = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) flag = not_finite(Ot[nb], flag);
+        rows_again = __any(!(flag == 0.f));
+        if (rows_again)
+            for (int r = i0; r < min(i0 + 32, len); ++r) {
+                HeadRow<__bf16, 1> o;
+                attn_fwd_row(Qb + (long long)r * p.ldq, p.K + kv * kD, p.V + kv * kD, p.ldk, SeenKeys{pre_start, pre_len, seq_start, pre_len + r + 1},
+                             kD, p.scale, o);
+                p.O[(long long)(seq_start + r) * p.ldq + h * kD + lane] = (__bf16)o.v[0];
+            }
+    }
     if (i < len) {
         const float inv = 1.f / l;
         __bf16* orow = p.O + (long long)(seq_start + i) * p.ldq + h * kD;
+        if (!rows_again)
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
