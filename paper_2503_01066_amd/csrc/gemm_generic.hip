@@ -102,7 +102,8 @@ template <> struct F32Tile<16> {
     static __device__ __forceinline__ int row(int e, int lane) { return 4 * (lane >> 4) + e; }
 };
 
-// kForm: 0..3 = (a_kmajor, b_kmajor << 1) with contractions of whole chunks and, for a k-major operand, rows that allow
+// kForm: 0..3 = (a_kmajor, b_kmajor << 1) with contractions of whole chunks, one at least (a pair of length zero may have no
+// operands), and, for a k-major operand, rows that allow
 // loads of four elements: no load then depends on a condition, so that all of a batch are requested before the first is
 // waited for (the eight products of a layer backward of 256 tokens, hidden 256, ffn 1024: 77 us with the conditions, 63 us
 // without); -1 = everything else.
@@ -264,7 +265,7 @@ static void gemm_slices_t(GenericGemmParams& p, int k_total, hipStream_t stream)
     if constexpr (std::is_same<T, float>::value) {
         bool plain = true;
         for (int s = 0; s < p.n_seg; ++s)
-            plain = plain && p.K[s] % (256 / kTile) == 0 && (!p.a_kmajor || p.a_vec[s]) && (!p.b_kmajor || p.b_vec[s]);
+            plain = plain && p.K[s] > 0 && p.K[s] % (256 / kTile) == 0 && (!p.a_kmajor || p.a_vec[s]) && (!p.b_kmajor || p.b_vec[s]);
         if (plain) {
             if (p.a_kmajor && p.b_kmajor) return gemm_slices_form<T, kTile, 3>(p, k_total, stream);
             if (p.b_kmajor) return gemm_slices_form<T, kTile, 2>(p, k_total, stream);

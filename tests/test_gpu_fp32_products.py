@@ -29,3 +29,25 @@ def test_products_of_whole_chunks(M, N, Ks, a_k, b_k):
         A_.alch_gemm(M, N, terms, a_k, b_k, out=C, accumulate=acc)
         torch.cuda.synchronize()
         assert rel_err(to_np(C), ref + C0 if acc else ref) < 2e-6
+
+
+@pytest.mark.parametrize("a_k,b_k", [(True, False), (False, False), (True, True), (False, True)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(5, 9, 0), (352, 384, 0), (1537, 1665, 0), (40, 24, 64), (352, 384, 512), (40, 24, 1024)])
+def test_pairs_of_length_zero(a_k, b_k, M, N, K, dtype):
+    # legal with NULL operands, alone (the product is zero) and beside a pair of whole chunks: nothing is read through them
+    import ctypes
+    import paper_2503_01066_amd as A_
+    from paper_2503_01066_amd.binding import CGemmTerm
+    A, B, ref = operands(np.random.default_rng(M + K), M, N, max(K, 1), a_k, b_k, dtype)
+    dA, dB = to_dev(A, dtype), to_dev(B, dtype)
+    empty = CGemmTerm(0, 0, 0, 0 if a_k else M, 0 if b_k else N)
+    terms = [empty] if K == 0 else [empty, CGemmTerm(dA.data_ptr(), dB.data_ptr(), K, dA.stride(0), dB.stride(0)), empty]
+    C0 = synth.quantize(np.random.default_rng(1).standard_normal((M, N)).astype(np.float32), dtype)
+    for acc in (0, 1):
+        C = to_dev(C0, dtype)
+        rc = A_.lib().alch_gemm(0 if dtype == "f32" else 1, M, N, int(a_k), int(b_k), len(terms), (CGemmTerm * len(terms))(*terms),
+                                ctypes.c_void_p(C.data_ptr()), C.stride(0), acc, None)
+        torch.cuda.synchronize()
+        want = (ref if K else 0.0 * ref) + (C0 if acc else 0)
+        assert rc == 0 and rel_err(to_np(C), want) < (2e-6 if dtype == "f32" else 6e-3)
