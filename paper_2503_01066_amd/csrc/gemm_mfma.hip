@@ -623,14 +623,17 @@ static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, const Pair
 }
 
 int compute_units(int* n_cu) {
-    static std::atomic<int> known{0};
-    int n = known.load(std::memory_order_relaxed);
+    static constexpr int kDevices = 64;
+    static std::atomic<int> known[kDevices] = {};  // by device: those of a process need not be alike (partitions)
+    int dev = 0;
+    ALCH_HIP_TRY(hipGetDevice(&dev));
+    const bool kept = dev >= 0 && dev < kDevices;
+    int n = kept ? known[dev].load(std::memory_order_relaxed) : 0;
     if (n == 0) {
-        int dev = 0, v = 0;
-        ALCH_HIP_TRY(hipGetDevice(&dev));
+        int v = 0;
         ALCH_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
         n = v > 8 ? v / 8 * 8 : 8;
-        known.store(n, std::memory_order_relaxed);
+        if (kept) known[dev].store(n, std::memory_order_relaxed);
     }
     *n_cu = n;
     return ALCH_OK;
