@@ -1236,8 +1236,8 @@ static int layer_forward_impl(const alch_layer_shape* shape, const alch_batch* b
         add_seg(d, p.Hn, H, Ws[0], H, H);
         ALCH_TRY(launch_gemm(d, st));
     }
-    ALCH_TRY(launch_rope(dt, rQ, QD, T, s.n_q_heads, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, 1.f, st));
-    ALCH_TRY(launch_rope(dt, rK, KD, T, s.n_kv_heads, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, 1.f, st));
+    ALCH_TRY(launch_rope(dt, rQ, QD, T, s.n_q_heads, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, st));
+    ALCH_TRY(launch_rope(dt, rK, KD, T, s.n_kv_heads, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, st));
     // attention indexes whole-batch rows: the keys and values of a prefix sequence lie before r0
     ALCH_TRY(launch_attn_fwd(dt, rec->Q, rec->K, rec->V, rec->O, rec->LSE, batch->total_tokens, batch->n_seqs,
                              batch->max_seqlen, batch->cu_seqlens, batch->cu_seqlens_host, batch->seq_prefix,

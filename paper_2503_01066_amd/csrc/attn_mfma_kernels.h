@@ -183,13 +183,6 @@ __device__ __forceinline__ void issue_rows_tile(const __bf16* base, long long ld
     for (int j = 0; j < AttnTile<kD>::kLoads; ++j)
         dma16(r, lds_addr + (uint32_t)(wave * AttnTile<kD>::kLoads + j) * 1024u, voff[j]);
 }
-// 64 floats with stride `stride` elements (one per tile row) -> LDS, by one wave
-__device__ __forceinline__ void issue_row_scalars(const float* base, long long stride, int rows_valid, uint32_t lds_addr,
-                                                  int lane) {
-    const i32x4 r = rsrc_of(base, rows_valid > 0 ? ((long long)(rows_valid - 1) * stride + 1) * 4 : 0);
-    dma4(r, lds_addr, (uint32_t)(lane * stride * 4));
-}
-
 // LDS read addresses.  Every fragment address of a [rows][kD] tile is a per-lane constant combined
 // with compile-time terms, so the lane parts are computed once per kernel:
 //   d-fragments (k = d):   byte = row0*kRowBytes + (lane_d ^ (kk << 5)),       lane_d from frag_d_lane()

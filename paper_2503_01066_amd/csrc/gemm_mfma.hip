@@ -388,15 +388,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
                     const bf16x8 d8 = *reinterpret_cast<const bf16x8*>(stage + rl * kRowStride + (((lane & 15) ^ (rl & 15)) << 4));
                     if (m < Mv && n < p.N) {
                         bf16x8 dg8, du8, a8;
-#pragma unroll
-                        for (int r = 0; r < 8; ++r) {
-                            const float g = bf2f(g8[k][r]), u = bf2f(u8[k][r]), d = bf2f(d8[r]);
-                            const float sg = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
-                            const float silu = g * sg;
-                            dg8[r] = (__bf16)(d * u * sg * (1.f + g * (1.f - sg)));
-                            du8[r] = (__bf16)(d * silu);
-                            a8[r] = (__bf16)(silu * u);
-                        }
+                        swiglu_gradient<8>(d8, g8[k], u8[k], dg8, du8, a8);
                         *reinterpret_cast<bf16x8*>(C + (long long)m * ldc + n) = dg8;
                         *reinterpret_cast<bf16x8*>(C + (long long)m * ldc + p.N + n) = du8;
                         if (p.act_out) *reinterpret_cast<bf16x8*>(p.act_out + (long long)m * p.N + n) = a8;
@@ -479,16 +471,10 @@ __global__ __launch_bounds__(256) void k_gemm_split_finish(MfmaGemmParams p, int
             for (int k = 0; k < p.split_s; ++k) v += *reinterpret_cast<const f32x4*>(ws + (size_t)k * (BM * BN) + (r0 + 4 * i) * BN + col);
             const bf16x4 g4 = *reinterpret_cast<const bf16x4*>(p.G + (long long)m * p.ldgu + n);
             const bf16x4 u4 = *reinterpret_cast<const bf16x4*>(p.U + (long long)m * p.ldgu + n);
-            bf16x4 dg4, du4, a4;
+            bf16x4 d4, dg4, du4, a4;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float g = bf2f(g4[e]), u = bf2f(u4[e]), dd = bf2f((__bf16)v[e]);
-                const float sg = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
-                const float silu = g * sg;
-                dg4[e] = (__bf16)(dd * u * sg * (1.f + g * (1.f - sg)));
-                du4[e] = (__bf16)(dd * silu);
-                a4[e] = (__bf16)(silu * u);
-            }
+            for (int e = 0; e < 4; ++e) d4[e] = (__bf16)v[e];
+            swiglu_gradient<4>(d4, g4, u4, dg4, du4, a4);
             *reinterpret_cast<bf16x4*>(C + (long long)m * ldc + n) = dg4;
             *reinterpret_cast<bf16x4*>(C + (long long)m * ldc + p.N + n) = du4;
             if (p.act_out) *reinterpret_cast<bf16x4*>(p.act_out + (long long)m * p.N + n) = a4;

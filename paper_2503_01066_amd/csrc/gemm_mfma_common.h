@@ -14,7 +14,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 static constexpr int BK = 32;
 static constexpr uint32_t kOobOffset = 0x80000000u;      // >= any num_records we set
-static constexpr uint32_t kMaxRecords = 0x80000000u;
 
 struct MfmaGemmParams {
     int M, N, n_seg, n_out, accumulate, tiles_m, tiles_n;
@@ -44,7 +43,7 @@ struct MfmaGemmParams {
     int q_end;
     float* split_ws;
     int split_s, split_per;  // parts per tile; k-tiles per part (counted over all operand pairs in order)
-    int per_xcd;             // k_gemm_pair: tiles of an XCD's share (unless the row count lives on the device)
+    int per_xcd;             // k_gemm_pair: tiles of an XCD's share
 };
 
 // output range that row (or column) x of the product belongs to
@@ -57,19 +56,6 @@ __device__ __forceinline__ int range_of(const MfmaGemmParams& p, int x) {
 }
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
-
-// Buffer resource over [p, p + bytes_left): raw (stride 0), 32-bit data format, so that every
-// access at or beyond bytes_left reads as zero.  All parts are forced into scalar registers.
-__device__ __forceinline__ i32x4 make_rsrc(const void* p, long long bytes_left) {
-    const uint32_t n = bytes_left <= 0 ? 0u : (bytes_left > (long long)kMaxRecords ? kMaxRecords : (uint32_t)bytes_left);
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    i32x4 r;
-    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
-    r[2] = __builtin_amdgcn_readfirstlane((int)n);
-    r[3] = 0x00020000;
-    return r;
-}
 
 // 16 bytes per lane from buffer `r` at byte offset `voff` straight into LDS at
 // lds_addr + lane*16.  Written as assembly so that the compiler does not order later LDS
@@ -123,17 +109,17 @@ __device__ __forceinline__ bf16x8 read_frag(const char* stage, int idx0 /*first 
 
 __device__ __forceinline__ float bf2f(__bf16 v) { return (float)v; }
 
-// dAct = d8 rounded to bf16, saved g, u -> dG = dAct U s'(G), dU = dAct silu(G), Act = silu(G) U
-__device__ __forceinline__ void swiglu_gradient(const bf16x8& d8, const bf16x8& g8, const bf16x8& u8, bf16x8& dg8, bf16x8& du8,
-                                                bf16x8& a8) {
+// dAct = d rounded to bf16, saved g, u -> dG = dAct U s'(G), dU = dAct silu(G), Act = silu(G) U, of kN elements
+template <int kN, typename V>
+__device__ __forceinline__ void swiglu_gradient(const V& dv, const V& gv, const V& uv, V& dg, V& du, V& act) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const float g = bf2f(g8[r]), u = bf2f(u8[r]), d = bf2f(d8[r]);
+    for (int r = 0; r < kN; ++r) {
+        const float g = bf2f(gv[r]), u = bf2f(uv[r]), d = bf2f(dv[r]);
         const float sg = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
         const float silu = g * sg;
-        dg8[r] = (__bf16)(d * u * sg * (1.f + g * (1.f - sg)));
-        du8[r] = (__bf16)(d * silu);
-        a8[r] = (__bf16)(silu * u);
+        dg[r] = (__bf16)(d * u * sg * (1.f + g * (1.f - sg)));
+        du[r] = (__bf16)(d * silu);
+        act[r] = (__bf16)(silu * u);
     }
 }
 

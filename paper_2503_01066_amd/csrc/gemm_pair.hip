@@ -1,5 +1,6 @@
 // bf16 GEMM on the gfx950 matrix cores, two work-groups per compute unit: the kernel for products whose tiles are short
-// or few.  Same contract as k_gemm_mfma (gemm_mfma.hip).
+// or few.  Same contract as k_gemm_mfma (gemm_mfma.hip), but for sizes that
+// only the device knows.
 //
 //   * 128x256 tile per work-group, 4 wavefronts of 64x128 each (128 accumulator registers), at most 256 registers and
 //     80 KB of LDS, so that two work-groups share a compute unit: while one waits for its first loads, writes its tile or
@@ -36,12 +37,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
     const int wm = wave >> 1, wn = wave & 1;
 
     // ---- work-group -> tile (and part of its contraction): every XCD owns per_xcd consecutive tiles
-    const int Mv = p.m_dev ? min(__builtin_amdgcn_readfirstlane(*p.m_dev), p.M) : p.M;
-    const int tiles_m = p.m_dev ? (Mv + PM - 1) / PM : p.tiles_m;
-    const int nt = tiles_m * p.tiles_n, per_xcd = p.m_dev ? (nt + 7) / 8 : p.per_xcd;
+    const int Mv = p.M, tiles_m = p.tiles_m, nt = tiles_m * p.tiles_n, per_xcd = p.per_xcd;
     const int in_xcd = (int)(blockIdx.x / 8);
     const bool whole = in_xcd < p.q_end;
-    const int rem = per_xcd - p.q_end;  // (split products have host-known sizes)
+    const int rem = per_xcd - p.q_end;
     const int q = whole ? in_xcd : p.q_end + (in_xcd - p.q_end) % rem;
     const int ks = whole ? 0 : (in_xcd - p.q_end) / rem;
     const int t = (int)(blockIdx.x % 8) * per_xcd + q;
@@ -63,7 +62,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
     int seg_kt0 = 0;  // k-tiles of the operand pairs before this one
     for (int seg = 0; seg < p.n_seg; ++seg) {
         const long long lda = p.lda[seg], ldb = p.ldb[seg];
-        const int K = p.k_dev ? min(__builtin_amdgcn_readfirstlane(*p.k_dev), p.K[seg]) : p.K[seg];
+        const int K = p.K[seg];
         int nk = (K + BK - 1) / BK;
         const char *pa, *pb, *enda, *endb;
         long long stepa, stepb;
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
                 const bf16x8 d8 = *reinterpret_cast<const bf16x8*>(stage + rl * 256 + (((lane & 15) ^ (rl & 15)) << 4));
                 if (m < Mv && n < p.N) {
                     bf16x8 dg8, du8, a8;
-                    swiglu_gradient(d8, g8[k], u8[k], dg8, du8, a8);
+                    swiglu_gradient<8>(d8, g8[k], u8[k], dg8, du8, a8);
                     *reinterpret_cast<bf16x8*>(C + (long long)m * ldc + n) = dg8;
                     *reinterpret_cast<bf16x8*>(C + (long long)m * ldc + p.N + n) = du8;
                     if (p.act_out) *reinterpret_cast<bf16x8*>(p.act_out + (long long)m * p.N + n) = a8;
@@ -374,7 +373,7 @@ __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = (__bf16)(e < 4 ? lo[e & 3] : hi[e & 3]);
             bf16x8 dg8, du8, a8;
-            swiglu_gradient(o, g8, u8, dg8, du8, a8);
+            swiglu_gradient<8>(o, g8, u8, dg8, du8, a8);
             *reinterpret_cast<bf16x8*>(C + (long long)m * ldc + n) = dg8;
             *reinterpret_cast<bf16x8*>(C + (long long)m * ldc + p.N + n) = du8;
             if (p.act_out) *reinterpret_cast<bf16x8*>(p.act_out + (long long)m * p.N + n) = a8;
@@ -418,7 +417,7 @@ int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m
 PairPlan pair_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes) {
     const int per_xcd = ceil_div(ceil_div(p.M, PM) * ceil_div(p.N, PN), 8), cus = n_cu / 8;
     PairPlan plan{per_xcd, per_xcd, 1, 0};
-    if (ws_bytes == 0 || p.m_dev || p.k_dev) return plan;
+    if (ws_bytes == 0) return plan;
     const int rem = per_xcd % cus;
     if (rem == 0) return plan;
     int nk_total = 0;

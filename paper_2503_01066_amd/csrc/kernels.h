@@ -96,9 +96,9 @@ int launch_rank_of_kept(const int* index, const int* n_rows, int* inv, int T, hi
 int launch_scatter_rows(const void* src, const int* inv, void* out, int T, size_t row_bytes, hipStream_t stream);
 // Act = silu(G) * U
 int launch_swiglu_act(alch_dtype dt, const void* G, const void* U, void* Act, long long n, hipStream_t stream);
-// In-place rotary rotation of x [T, n_heads, D] (row stride ld elements) by sign * angle.
+// In-place rotary rotation of x [T, n_heads, D] (row stride ld elements).
 int launch_rope(alch_dtype dt, void* x, long long ld, int T, int n_heads, int D, const int* positions,
-                const int* cu_seqlens, int n_seqs, float base, float sign, hipStream_t stream);
+                const int* cu_seqlens, int n_seqs, float base, hipStream_t stream);
 // out = a with rows zeroed where mask == 0 (mask may be NULL: plain copy)
 int launch_masked_copy(alch_dtype dt, const void* a, const uint8_t* mask, void* out, int T, int width,
                        hipStream_t stream);

@@ -520,11 +520,11 @@ int launch_swiglu_act(alch_dtype dt, const void* G, const void* U, void* Act, lo
     return ALCH_OK;
 }
 
-// ---- rotary embedding in place: pairs (i, i + D/2), angle = pos * base^(-2i/D), rotation by sign*angle
+// ---- rotary embedding in place: pairs (i, i + D/2), angle = pos * base^(-2i/D), rotation by the angle
 template <typename T>
 __global__ __launch_bounds__(256) void k_rope(T* __restrict__ x, long long ld, int Trows, int n_heads, int D,
                                               const int* __restrict__ positions, const int* __restrict__ cu_seqlens,
-                                              int n_seqs, float log2_base, float sign) {
+                                              int n_seqs, float log2_base) {
     const int half = D >> 1;
     const long long per_row = (long long)n_heads * half;
     const long long n = (long long)Trows * per_row;
@@ -547,7 +547,6 @@ __global__ __launch_bounds__(256) void k_rope(T* __restrict__ x, long long ld, i
         const float theta = exp2f(-2.f * (float)k / (float)D * log2_base);
         float sn, cs;
         sincosf((float)pos * theta, &sn, &cs);
-        sn *= sign;
         T* p = x + t * ld + (long long)h * D + k;
         const float a = ldf(p), b = ldf(p + half);
         stf(p, a * cs - b * sn);
@@ -560,7 +559,7 @@ __global__ __launch_bounds__(256) void k_rope(T* __restrict__ x, long long ld, i
 static constexpr int kHeadLanes = 8;
 __global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ x, long long ld, int Trows, int n_heads, int D,
                                                      const int* __restrict__ positions, const int* __restrict__ cu_seqlens,
-                                                     int n_seqs, float log2_base, float sign) {
+                                                     int n_seqs, float log2_base) {
     const int half = D >> 1, kc = half >> 3;  // 8-pair chunks per head
     const int per_tok = kc * kHeadLanes;
     const long long n = (long long)Trows * per_tok;
@@ -585,7 +584,6 @@ __global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ x, lon
         for (int e = 0; e < 8; ++e) {
             const float theta = exp2f(-2.f * (float)(k0 + e) / (float)D * log2_base);
             sincosf((float)pos * theta, &sn[e], &cs[e]);
-            sn[e] *= sign;
         }
         for (int h = hl; h < n_heads; h += kHeadLanes) {
             __bf16* p = x + t * ld + (long long)h * D + k0;
@@ -604,22 +602,22 @@ __global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ x, lon
 }
 
 int launch_rope(alch_dtype dt, void* x, long long ld, int T, int n_heads, int D, const int* positions,
-                const int* cu_seqlens, int n_seqs, float base, float sign, hipStream_t stream) {
+                const int* cu_seqlens, int n_seqs, float base, hipStream_t stream) {
     const long long n = (long long)T * n_heads * (D / 2);
     if (n <= 0) return ALCH_OK;
     if (dt == ALCH_BF16 && D % 16 == 0 && ld % 8 == 0 && aligned16(x)) {
         const long long nt = (long long)T * (D / 16) * kHeadLanes;
         const int g = (int)((nt + 255) / 256 < 256 * 32 ? (nt + 255) / 256 : 256 * 32);
-        k_rope_bf16x8<<<g, 256, 0, stream>>>((__bf16*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, log2f(base), sign);
+        k_rope_bf16x8<<<g, 256, 0, stream>>>((__bf16*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, log2f(base));
         ALCH_HIP_TRY(hipGetLastError());
         return ALCH_OK;
     }
     const int grid = (int)((n + 255) / 256 < 256 * 16 ? (n + 255) / 256 : 256 * 16);
     const float l2 = log2f(base);
     if (dt == ALCH_BF16)
-        k_rope<__bf16><<<grid, 256, 0, stream>>>((__bf16*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, l2, sign);
+        k_rope<__bf16><<<grid, 256, 0, stream>>>((__bf16*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, l2);
     else
-        k_rope<float><<<grid, 256, 0, stream>>>((float*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, l2, sign);
+        k_rope<float><<<grid, 256, 0, stream>>>((float*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, l2);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
