@@ -47,7 +47,7 @@ struct AttnPlainParams {
     float* delta;
     T *dQ, *dK, *dV, *Oout;
     const int *cu, *prefix, *positions;
-    int n_seqs, seq_begin, blocks, Hq, Hkv, D;  // the grid: (head, block of 32 rows) x sequences from seq_begin on
+    int n_seqs, seq_begin, blocks, short_upto, Hq, Hkv, D;  // the grid: (head, block of 32 rows) x sequences from seq_begin on
     long long ldo;          // row stride of dQ, dK, dV
     float scale, log2_base;
     int rope;               // dQ and dK are rotated by minus the RoPE angle
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<
     const int seq = p.seq_begin + blockIdx.y, h = (int)blockIdx.x % p.Hq, kv = h / (p.Hq / p.Hkv), D = kFull ? NB * 32 : p.D;
     const int i0 = (p.blocks - 1 - (int)blockIdx.x / p.Hq) * kBlk;  // the longest rows first
     const KeyBlocks kb(p.cu, p.prefix, seq, i0);
-    if (i0 >= kb.len) return;
+    if (i0 >= kb.len || kb.len <= p.short_upto) return;
     const long long ldq = (long long)p.Hq * D, ldk = (long long)p.Hkv * D;
     const int i = min(i0 + (lane & 31), kb.len - 1);  // this lane's query
     const T* q = p.Q + (kb.own0 + i) * ldq + (long long)h * D;
@@ -264,8 +264,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_plain(AttnPlainParams<
     if (any_not_finite(flag)) {  // formed again from the visible keys alone (attn_rows.h)
         for (int r = wave; r < rows; r += kWaves) {
             HeadRow<T, (NB + 1) / 2> o;
+            float lse;
             attn_fwd_row(p.Q + (kb.own0 + i0 + r) * ldq + (long long)h * D, p.K + (long long)kv * D, p.V + (long long)kv * D, ldk,
-                         kb.seen_by(i0 + r), D, p.scale, o);
+                         kb.seen_by(i0 + r), D, p.scale, o, lse);
             replace_row(buf, r, o, D);
         }
         __syncthreads();
@@ -296,7 +297,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnPlainParams<T>& p, F
     const int seq = p.seq_begin + blockIdx.y, h = block % p.Hq, kv = h / (p.Hq / p.Hkv), D = kFull ? NB * 32 : p.D;
     const int i0 = (p.blocks - 1 - block / p.Hq) * kBlk;
     const KeyBlocks kb(p.cu, p.prefix, seq, i0);
-    if (i0 >= kb.len) return;
+    if (i0 >= kb.len || kb.len <= p.short_upto) return;
     const long long ldq = (long long)p.Hq * D, ldk = (long long)p.Hkv * D;
     const int i = min(i0 + (lane & 31), kb.len - 1);
     const long long qoff = (kb.own0 + i) * ldq + (long long)h * D, roff = (long long)(kb.own0 + i) * p.Hq + h;
@@ -337,8 +338,9 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnPlainParams<T>& p, F
         for (int r = wave; r < min(kBlk, kb.len - i0); r += kWaves) {
             const long long at = (kb.own0 + i0 + r) * ldq + (long long)h * D;
             HeadRow<T, (NB + 1) / 2> x;
+            float del_again;
             attn_dq_row(p.Q + at, p.dO + at, p.O + at, p.K + (long long)kv * D, p.V + (long long)kv * D, ldk, kb.seen_by(i0 + r), D,
-                        p.scale, p.LSE[(long long)(kb.own0 + i0 + r) * p.Hq + h], x);
+                        p.scale, p.LSE[(long long)(kb.own0 + i0 + r) * p.Hq + h], x, del_again);
             replace_row(buf, r, x, D);
         }
         __syncthreads();
@@ -356,7 +358,7 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnPlainParams<T>& p, 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
     const int seq = p.seq_begin + blockIdx.y, kv = block % p.Hkv, G = p.Hq / p.Hkv, D = kFull ? NB * 32 : p.D;
     const int own0 = p.cu[seq], len = p.cu[seq + 1] - own0, j0 = block / p.Hkv * kBlk;
-    if (j0 >= len) return;
+    if (j0 >= len || len <= p.short_upto) return;
     const long long ldq = (long long)p.Hq * D, ldk = (long long)p.Hkv * D;
     const int j = min(j0 + (lane & 31), len - 1);  // this lane's key
     const T *k = p.K + (own0 + j) * ldk + (long long)kv * D, *v = p.V + (own0 + j) * ldk + (long long)kv * D;
@@ -446,7 +448,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnPlainParams<T>& p, 
         for (int r = wave; r < rows; r += kWaves) {
             HeadRow<T, (NB + 1) / 2> dk, dv;
             const long long at = (own0 + j0 + r) * ldk + (long long)kv * D;
-            attn_dkv_row(p.K + at, p.V + at, p.Q, p.dO, p.O, p.LSE, p.Hq, kv * G, (kv + 1) * G, p.cu, p.prefix, p.n_seqs, seq, j0 + r, D,
+            attn_dkv_row(p.K + at, p.V + at, p.Q, p.dO, p.O, p.LSE, nullptr, p.Hq, kv * G, (kv + 1) * G, p.cu, p.prefix, p.n_seqs, seq,
+                         j0 + r, D,
                          p.scale, dk, dv);
             replace_row(buf, r, dk, D);
 #pragma unroll
@@ -482,6 +485,109 @@ __global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_plain(AttnPlainParams<
     else attn_bwd_dq_block<T, NB, kFull, false>(p, buf, (int)blockIdx.x - key_blocks);
 }
 
+// ---- a row at a time, for sequences of up to short_upto tokens: a wavefront takes one head of one sequence,
+// or every gridDim.z-th row of it
+template <typename T, int E>
+__device__ __forceinline__ void store_row(const HeadRow<T, E>& x, float* tmp, T* out, int D, float scale, bool rope, float log2_base, int pos) {
+    const int lane = threadIdx.x & 63;
+    if (rope)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (lane + 64 * e < D) tmp[lane + 64 * e] = x.v[e];  // (of this wavefront alone)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int d = lane + 64 * e, hd = D >> 1, k = d < hd ? d : d - hd;
+        if (d >= D) continue;
+        float v = x.v[e] * scale;
+        if (rope) {
+            float sn, cs;
+            sincosf((float)pos * exp2f(-2.f * (float)k / (float)D * log2_base), &sn, &cs);
+            const float other = tmp[d < hd ? d + hd : d - hd] * scale;
+            v = d < hd ? v * cs + other * sn : v * cs - other * sn;
+        }
+        stf(out + d, v);
+    }
+}
+
+template <typename T, int E>
+__global__ __launch_bounds__(kWaves * 64) void k_attn_fwd_rows(AttnPlainParams<T> p) {
+    const int seq = p.seq_begin + blockIdx.y, row0 = p.cu[seq], len = p.cu[seq + 1] - row0;
+    const int h = (int)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kv = h / (p.Hq / p.Hkv), lane = threadIdx.x & 63;
+    if (len > p.short_upto || h >= p.Hq) return;
+    const long long ldq = (long long)p.Hq * p.D, ldk = (long long)p.Hkv * p.D, kvo = (long long)kv * p.D;
+    for (int i = blockIdx.z; i < len; i += gridDim.z) {
+        HeadRow<T, E> o;
+        float lse;
+        const long long at = (row0 + i) * ldq + (long long)h * p.D;
+        attn_fwd_row(p.Q + at, p.K + kvo, p.V + kvo, ldk, SeenKeys{0, 0, row0, i + 1}, p.D, p.scale, o, lse);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (lane + 64 * e < p.D) stf(p.Oout + at + lane + 64 * e, o.v[e]);
+        if (lane == 0) p.LSE[(long long)(row0 + i) * p.Hq + h] = lse;
+    }
+}
+
+template <typename T, int E>
+__global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dq_rows(AttnPlainParams<T> p) {  // also writes delta
+    __shared__ float tmp[kWaves][64 * E];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, D = p.D;
+    const int seq = p.seq_begin + blockIdx.y, row0 = p.cu[seq], len = p.cu[seq + 1] - row0, h = (int)blockIdx.x * kWaves + wave;
+    if (len > p.short_upto || h >= p.Hq) return;
+    const long long ldq = (long long)p.Hq * D, ldk = (long long)p.Hkv * D, kvo = (long long)(h / (p.Hq / p.Hkv)) * D;
+    for (int r = blockIdx.z; r < len; r += gridDim.z) {
+        const long long at = (row0 + r) * ldq + (long long)h * D, row = (long long)(row0 + r) * p.Hq + h;
+        HeadRow<T, E> x;
+        float delta;
+        attn_dq_row(p.Q + at, p.dO + at, p.O + at, p.K + kvo, p.V + kvo, ldk, SeenKeys{0, 0, row0, r + 1}, D, p.scale, p.LSE[row], x, delta);
+        if (lane == 0) p.delta[row] = delta;
+        store_row(x, tmp[wave], p.dQ + (row0 + r) * p.ldo + (long long)h * D, D, p.scale, p.rope, p.log2_base, p.positions ? p.positions[row0 + r] : r);
+    }
+}
+template <typename T, int E>
+__global__ __launch_bounds__(kWaves * 64) void k_attn_bwd_dkv_rows(AttnPlainParams<T> p) {
+    __shared__ float tmp[kWaves][64 * E];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, D = p.D, G = p.Hq / p.Hkv;
+    const int seq = p.seq_begin + blockIdx.y, row0 = p.cu[seq], len = p.cu[seq + 1] - row0, kv = (int)blockIdx.x * kWaves + wave;
+    if (len > p.short_upto || kv >= p.Hkv) return;
+    for (int r = blockIdx.z; r < len; r += gridDim.z) {
+        const long long at = ((long long)(row0 + r) * p.Hkv + kv) * D, out = (row0 + r) * p.ldo + (long long)kv * D;
+        HeadRow<T, E> dk, dv;
+        attn_dkv_row(p.K + at, p.V + at, p.Q, p.dO, p.O, p.LSE, p.delta, p.Hq, kv * G, (kv + 1) * G, p.cu, nullptr, p.n_seqs, seq, r, D, p.scale,
+                     dk, dv);
+        store_row(dk, tmp[wave], p.dK + out, D, p.scale, p.rope, p.log2_base, p.positions ? p.positions[row0 + r] : r);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (lane + 64 * e < D) stf(p.dV + out + lane + 64 * e, dv.v[e]);
+    }
+}
+
+// A tile kernel spends a work-group's blocks on every (sequence, head), however short: of sequences of a few tokens it takes
+// less time to form a row at a time.  Up to how many tokens that is so, forward / backward in us, rows against tiles, 8000
+// tokens, 8/2 heads: bf16 heads of 64 (tiles: the matrix-core kernels) 8 tokens 36 / 181 against 40 / 267, 12 tokens 47 / 227
+// against 28 / 211; fp32 64 8 tokens 35 / 258 against 79 / 349, 12 tokens 48 / 293 against 55 / 299; bf16 80 16 tokens 70 /
+// 341 against 175 / 455, 24 tokens 140 / 538 against 143 / 379; fp32 128 16 tokens 59 / 362 against 90 / 428; bf16 160 24
+// tokens 229 / 765 against 453 / 1029.  The rows are a launch (backward: two) more where there are long sequences beside
+// them, so the tiles of the short ones have to be worth it: more than per_cu work-groups for each compute unit (forward of
+// one sequence of 1000 tokens and 256 of 4, 8 heads: fp32 64 83 against 169 us, bf16 64 40 against 30 us and left to the
+// tiles there, 1024 of 4: 51 against 60 us).
+int rows_up_to(int D, int Hq, int per_cu, int first, int n_seqs, const int* cu_host, const int* prefix, ShortRows* rows) {
+    *rows = ShortRows{};
+    if (prefix) return ALCH_OK;
+    const int limit = D > 128 ? 24 : D <= 32 || D == 64 ? 8 : 16;
+    long long n = 0, tokens = 0;
+    for (int s = first; s < n_seqs; ++s) {
+        const int len = cu_host[s + 1] - cu_host[s];
+        if (len > 0 && len <= limit) { ++n; tokens += len; }
+    }
+    int n_cu = 0;
+    ALCH_TRY(compute_units(&n_cu));
+    if (n * Hq >= (long long)per_cu * n_cu) *rows = ShortRows{limit, (int)(tokens / (2 * n)) > 1 ? (int)(tokens / (2 * n)) : 1};
+    return ALCH_OK;
+}
+
+// (forward of 64 sequences of 4 tokens, 8 heads, rows against tiles: bf16 80 12 against 19 us, fp32 64 13 and 13 us)
+static int plain_per_cu(int D) { return D > 64 ? 2 : 4; }
+
 // rows of a head start on a multiple of four elements
 template <typename T>
 static bool head_rows_vec(int D, std::initializer_list<const void*> ptrs) {
@@ -494,7 +600,6 @@ static bool head_rows_vec(int D, std::initializer_list<const void*> ptrs) {
 // the fp32 layers)
 template <typename T, typename F>
 static int with_blocks(int D, bool vec, F&& f) {
-    if (D > 256) return fail(ALCH_ERR_UNSUPPORTED, "head_dim %d > 256", D);
     auto g = [&](auto NB) {
         constexpr int kNB = decltype(NB)::value;
         if constexpr (std::is_same<T, float>::value && (kNB == 2 || kNB == 4))
@@ -519,7 +624,7 @@ static void by_sequences(AttnPlainParams<T>& p, int seq_begin, F&& f) {
 }
 
 template <typename T>
-static int attn_bwd_generic_t(const AttnArgs& a, hipStream_t stream) {
+static AttnPlainParams<T> bwd_params(const AttnArgs& a) {
     AttnPlainParams<T> p = {};
     p.Q = (const T*)a.Q; p.K = (const T*)a.K; p.V = (const T*)a.V; p.O = (const T*)a.O; p.dO = (const T*)a.dO;
     p.LSE = const_cast<float*>(a.LSE); p.delta = a.delta;
@@ -530,7 +635,40 @@ static int attn_bwd_generic_t(const AttnArgs& a, hipStream_t stream) {
     p.rope = a.rope_base > 0.f;
     p.log2_base = p.rope ? log2f(a.rope_base) : 0.f;
     p.vec = head_rows_vec<T>(a.D, {a.Q, a.K, a.V, a.O, a.dO});
-    p.blocks = ceil_div(longest_sequence(a.cu_seqlens_host, 0, a.n_seqs), kBlk);
+    p.short_upto = a.rows.up_to;
+    return p;
+}
+
+// the elements of a head that a lane of a row kernel holds
+template <typename F>
+static int with_row(int D, F&& f) {
+    if (D <= 64) f(std::integral_constant<int, 1>{});
+    else if (D <= 128) f(std::integral_constant<int, 2>{});
+    else f(std::integral_constant<int, 4>{});
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
+}
+
+template <typename T>
+static int attn_bwd_rows_t(const AttnArgs& a, hipStream_t stream) {
+    AttnPlainParams<T> p = bwd_params<T>(a);
+    return with_row(a.D, [&](auto E) {
+        by_sequences(p, 0, [&](int n) {
+            k_attn_bwd_dq_rows<T, decltype(E)::value><<<dim3(ceil_div(a.Hq, kWaves), n, a.rows.step), kWaves * 64, 0, stream>>>(p);
+            k_attn_bwd_dkv_rows<T, decltype(E)::value><<<dim3(ceil_div(a.Hkv, kWaves), n, a.rows.step), kWaves * 64, 0, stream>>>(p);
+        });
+    });
+}
+int launch_attn_bwd_rows(const AttnArgs& a, hipStream_t stream) {
+    return a.dtype == ALCH_BF16 ? attn_bwd_rows_t<__bf16>(a, stream) : attn_bwd_rows_t<float>(a, stream);
+}
+
+template <typename T>
+static int attn_bwd_generic_t(const AttnArgs& a, hipStream_t stream) {
+    AttnPlainParams<T> p = bwd_params<T>(a);
+    const int longest = longest_sequence(a.cu_seqlens_host, 0, a.n_seqs);
+    if (longest <= a.rows.up_to) return ALCH_OK;
+    p.blocks = ceil_div(longest, kBlk);
     int n_cu = 0;
     ALCH_TRY(compute_units(&n_cu));
     return with_blocks<T>(a.D, p.vec, [&](auto NB, auto full) {
@@ -555,18 +693,47 @@ static int attn_bwd_generic_t(const AttnArgs& a, hipStream_t stream) {
 
 int launch_attn_bwd_generic(const AttnArgs& a, hipStream_t stream) {
     if (a.T <= 0) return ALCH_OK;
-    return a.dtype == ALCH_BF16 ? attn_bwd_generic_t<__bf16>(a, stream) : attn_bwd_generic_t<float>(a, stream);
+    if (a.D > 256) return fail(ALCH_ERR_UNSUPPORTED, "head_dim %d > 256", a.D);
+    AttnArgs b = a;
+    ALCH_TRY(rows_up_to(a.D, a.Hq, plain_per_cu(a.D), 0, a.n_seqs, a.cu_seqlens_host, a.prefix, &b.rows));
+    if (b.rows.up_to) ALCH_TRY(launch_attn_bwd_rows(b, stream));
+    return a.dtype == ALCH_BF16 ? attn_bwd_generic_t<__bf16>(b, stream) : attn_bwd_generic_t<float>(b, stream);
 }
 
 template <typename T>
-static int attn_fwd_generic_t(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, const int* cu,
-                              const int* cu_host, const int* prefix, int seq_begin, int Hq, int Hkv, int D, hipStream_t stream) {
+static AttnPlainParams<T> fwd_params(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, const int* cu,
+                                     const int* prefix, int Hq, int Hkv, int D, int short_upto) {
     AttnPlainParams<T> p = {};
     p.Q = (const T*)Q; p.K = (const T*)K; p.V = (const T*)V; p.Oout = (T*)O; p.LSE = LSE;
     p.cu = cu; p.prefix = prefix; p.n_seqs = n_seqs; p.Hq = Hq; p.Hkv = Hkv; p.D = D;
     p.scale = 1.f / sqrtf((float)D);
     p.vec = head_rows_vec<T>(D, {Q, K, V});
-    p.blocks = ceil_div(longest_sequence(cu_host, seq_begin, n_seqs), kBlk);
+    p.short_upto = short_upto;
+    return p;
+}
+
+template <typename T>
+static int attn_fwd_rows_t(AttnPlainParams<T> p, int seq_begin, int step, hipStream_t stream) {
+    return with_row(p.D, [&](auto E) {
+        by_sequences(p, seq_begin, [&](int n) {
+            k_attn_fwd_rows<T, decltype(E)::value><<<dim3(ceil_div(p.Hq, kWaves), n, step), kWaves * 64, 0, stream>>>(p);
+        });
+    });
+}
+int launch_attn_fwd_rows(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, const int* cu_seqlens,
+                         int seq_begin, int Hq, int Hkv, int D, const ShortRows& rows, hipStream_t stream) {
+    return dt == ALCH_BF16
+               ? attn_fwd_rows_t(fwd_params<__bf16>(Q, K, V, O, LSE, n_seqs, cu_seqlens, nullptr, Hq, Hkv, D, rows.up_to), seq_begin, rows.step, stream)
+               : attn_fwd_rows_t(fwd_params<float>(Q, K, V, O, LSE, n_seqs, cu_seqlens, nullptr, Hq, Hkv, D, rows.up_to), seq_begin, rows.step, stream);
+}
+
+template <typename T>
+static int attn_fwd_generic_t(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, const int* cu,
+                              const int* cu_host, const int* prefix, int seq_begin, int Hq, int Hkv, int D, int short_upto, hipStream_t stream) {
+    AttnPlainParams<T> p = fwd_params<T>(Q, K, V, O, LSE, n_seqs, cu, prefix, Hq, Hkv, D, short_upto);
+    const int longest = longest_sequence(cu_host, seq_begin, n_seqs);
+    if (longest <= short_upto) return ALCH_OK;
+    p.blocks = ceil_div(longest, kBlk);
     return with_blocks<T>(D, p.vec, [&](auto NB, auto full) {
         by_sequences(p, seq_begin, [&](int n) {
             k_attn_fwd_plain<T, decltype(NB)::value, decltype(full)::value><<<dim3(p.blocks * Hq, n), kWaves * 64, 0, stream>>>(p);
@@ -578,9 +745,13 @@ int launch_attn_fwd_generic(alch_dtype dt, const void* Q, const void* K, const v
                             int n_seqs, const int* cu_seqlens, const int* cu_seqlens_host, const int* prefix,
                             int seq_begin, int Hq, int Hkv, int D, hipStream_t stream) {
     if (T - cu_seqlens_host[seq_begin] <= 0) return ALCH_OK;
+    if (D > 256) return fail(ALCH_ERR_UNSUPPORTED, "head_dim %d > 256", D);
+    ShortRows rows;
+    ALCH_TRY(rows_up_to(D, Hq, plain_per_cu(D), seq_begin, n_seqs, cu_seqlens_host, prefix, &rows));
+    if (rows.up_to) ALCH_TRY(launch_attn_fwd_rows(dt, Q, K, V, O, LSE, n_seqs, cu_seqlens, seq_begin, Hq, Hkv, D, rows, stream));
     return dt == ALCH_BF16
-               ? attn_fwd_generic_t<__bf16>(Q, K, V, O, LSE, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream)
-               : attn_fwd_generic_t<float>(Q, K, V, O, LSE, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, stream);
+               ? attn_fwd_generic_t<__bf16>(Q, K, V, O, LSE, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, rows.up_to, stream)
+               : attn_fwd_generic_t<float>(Q, K, V, O, LSE, n_seqs, cu_seqlens, cu_seqlens_host, prefix, seq_begin, Hq, Hkv, D, rows.up_to, stream);
 }
 
 }  // namespace alch

@@ -64,7 +64,7 @@ struct AttnMfmaParams {
     __bf16 *dQ, *dK, *dV;
     const int* cu;
     const int* prefix;     // null, or per sequence: -1 / the earlier sequence whose keys it also attends to
-    int n_seqs;
+    int n_seqs, short_upto;  // sequences of up to so many tokens are not these kernels'
     const int* positions;  // RoPE positions per token, or null: index inside the sequence
     int Hq, Hkv;
     long long ldq, ldk, ldo;  // row strides (elements) of Q/dO, K/V, and of the outputs
@@ -253,6 +253,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     // and heads start first (longest-processing-time-first keeps the last compute units busy).
     const int seq = blockIdx.y, kv = blockIdx.x;
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
+    if (len <= p.short_upto) return;
     const int part = (int)blockIdx.z / p.n_blocks;
     const int rem = p.n_blocks - ((int)blockIdx.z - part * p.n_blocks), kb = (len + 127) / 128 - rem;
     if (kb < 0) return;
@@ -612,7 +613,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
         if (__any(!(flag == 0.f))) {  // formed again from the visible pairs alone (attn_rows.h)
             for (int j = j0; j < min(j0 + 32, len); ++j) {
                 HeadRow<__bf16, 1> dk, dv;
-                attn_dkv_row(Kb + (long long)j * p.ldk, Vb + (long long)j * p.ldk, p.Q, p.dO, p.O, p.LSE, p.Hq, h_first, h_end, p.cu,
+                attn_dkv_row(Kb + (long long)j * p.ldk, Vb + (long long)j * p.ldk, p.Q, p.dO, p.O, p.LSE, p.delta, p.Hq, h_first, h_end, p.cu,
                              kPrefix ? p.prefix : nullptr, p.n_seqs, seq, j, kD, p.scale, dk, dv);
                 if (parts > 1) {
                     float* row = p.partial + (((long long)part * p.T + seq_start + j) * p.Hkv + kv) * (2 * kD);
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
     // heaviest (last) query blocks of every sequence and head first: blockIdx.z is the slowest index
     const int qb = (int)gridDim.z - 1 - (int)blockIdx.z;
-    if (qb * 128 >= len) return;
+    if (qb * 128 >= len || len <= p.short_upto) return;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kv = h / (p.Hq / p.Hkv);
@@ -877,8 +878,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
             for (int r = i0; r < min(i0 + 32, len); ++r) {
                 const long long at = (long long)(seq_start + r) * p.ldq + h * kD;
                 HeadRow<__bf16, 1> x;
+                float del_again;
                 attn_dq_row(p.Q + at, p.dO + at, p.O + at, p.K + kv_off, p.V + kv_off, p.ldk, SeenKeys{pre_start, pre_len, seq_start, pre_len + r + 1},
-                            kD, p.scale, p.LSE[(long long)(seq_start + r) * p.Hq + h], x);
+                            kD, p.scale, p.LSE[(long long)(seq_start + r) * p.Hq + h], x, del_again);
                 p.dQ[(long long)(seq_start + r) * p.ldo + h * kD + lane] = (__bf16)(rope_backward_row<kD>(x.v[0], p, seq_start, r, lane) * p.scale);
             }
             return;
@@ -909,6 +911,7 @@ struct AttnFwdParams {
     const int* cu;
     const int* prefix;  // as in the backward
     int seq_begin;      // first sequence whose queries are computed
+    int short_upto;     // as in the backward
     int Hq, Hkv;
     long long ldq, ldk;
     float scale;
@@ -924,7 +927,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
     // heaviest (last) query blocks of every sequence and head first: blockIdx.z is the slowest index
     const int qb = (int)gridDim.z - 1 - (int)blockIdx.z;
-    if (qb * 128 >= len) return;
+    if (qb * 128 >= len || len <= p.short_upto) return;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kv = h / (p.Hq / p.Hkv);
@@ -1048,8 +1051,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
         if (rows_again)
             for (int r = i0; r < min(i0 + 32, len); ++r) {
                 HeadRow<__bf16, 1> o;
+                float lse_again;
                 attn_fwd_row(Qb + (long long)r * p.ldq, p.K + kv * kD, p.V + kv * kD, p.ldk, SeenKeys{pre_start, pre_len, seq_start, pre_len + r + 1},
-                             kD, p.scale, o);
+                             kD, p.scale, o, lse_again);
                 p.O[(long long)(seq_start + r) * p.ldq + h * kD + lane] = (__bf16)o.v[0];
             }
     }
@@ -1132,6 +1136,7 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     if (nb > kMaxGridBlocks || a.n_seqs > kMaxGridSeqs) return fail(ALCH_ERR_UNSUPPORTED, "attention: more than 65535 sequences or 128-token blocks");
     p.T = a.T;
     p.n_blocks = nb;
+    p.short_upto = a.rows.up_to;
     int longest = 0;
     ALCH_TRY(plan_dkv_parts(a, p, longest));
     const bool cut = p.max_parts > 1;
@@ -1150,8 +1155,9 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
 
 template <int kD>
 int attn_fwd_mfma(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, int max_seqlen,
-                  const int* cu_seqlens, const int* prefix, int seq_begin, int Hq, int Hkv, hipStream_t stream) {
+                  const int* cu_seqlens, const int* prefix, int seq_begin, int Hq, int Hkv, int short_upto, hipStream_t stream) {
     AttnFwdParams p;
+    p.short_upto = short_upto;
     p.Q = (const __bf16*)Q; p.K = (const __bf16*)K; p.V = (const __bf16*)V; p.O = (__bf16*)O; p.LSE = LSE;
     p.cu = cu_seqlens; p.prefix = prefix; p.seq_begin = seq_begin;
     p.Hq = Hq; p.Hkv = Hkv; p.ldq = (long long)Hq * kD; p.ldk = (long long)Hkv * kD;

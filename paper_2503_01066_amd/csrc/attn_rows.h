@@ -3,6 +3,7 @@
 // is the same for every finite number, but a NaN or an infinity in a key, a value, a query or an output gradient would reach
 // rows that do not see it (0 * inf).  A tile kernel whose sums are not finite therefore forms its rows again with these, which
 // visit visible pairs only.  Finite batches never come here; rows that are not finite by their own right come out so again.
+// The other use is sequences too short to fill a tile of 32 keys (attn_generic.hip: rows_up_to).
 #pragma once
 #include "kernels.h"
 
@@ -56,7 +57,8 @@ struct SeenKeys {
 
 // K, V: of the kv head
 template <typename T, int E>
-__device__ void attn_fwd_row(const T* q, const T* K, const T* V, long long ldk, const SeenKeys& keys, int D, float scale, HeadRow<T, E>& o) {
+__device__ void attn_fwd_row(const T* q, const T* K, const T* V, long long ldk, const SeenKeys& keys, int D, float scale, HeadRow<T, E>& o,
+                             float& lse) {
     HeadRow<T, E> qr;
     qr.load(q, D);
     o.clear();
@@ -74,17 +76,18 @@ __device__ void attn_fwd_row(const T* q, const T* K, const T* V, long long ldk, 
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) o.v[e] /= l;
+    lse = m + logf(l);
 }
 
 // (without the factor scale of the result)
 template <typename T, int E>
 __device__ void attn_dq_row(const T* q, const T* dO, const T* O, const T* K, const T* V, long long ldk, const SeenKeys& keys, int D,
-                            float scale, float lse, HeadRow<T, E>& dq) {
+                            float scale, float lse, HeadRow<T, E>& dq, float& delta) {
     HeadRow<T, E> qr, g, o;
     qr.load(q, D);
     g.load(dO, D);
     o.load(O, D);
-    const float delta = g.dot(o);
+    delta = g.dot(o);
     dq.clear();
     for (int jj = 0; jj < keys.n; ++jj) {
         const long long at = keys.row(jj) * ldk;
@@ -96,9 +99,9 @@ __device__ void attn_dq_row(const T* q, const T* dO, const T* O, const T* K, con
 }
 
 // Sums over the query heads h_first .. h_end-1 of the rows that see key j of sequence seq: the sequence's own from j on, then
-// all of the sequences that name it as their prefix.  dk without the factor scale.
+// all of the sequences that name it as their prefix.  dk without the factor scale.  delta: of every row, or null (formed here).
 template <typename T, int E>
-__device__ void attn_dkv_row(const T* k, const T* v, const T* Q, const T* dO, const T* O, const float* LSE, int Hq, int h_first, int h_end,
+__device__ void attn_dkv_row(const T* k, const T* v, const T* Q, const T* dO, const T* O, const float* LSE, const float* delta, int Hq, int h_first, int h_end,
                              const int* cu, const int* prefix, int n_seqs, int seq, int j, int D, float scale, HeadRow<T, E>& dk,
                              HeadRow<T, E>& dv) {
     HeadRow<T, E> kr, vr;
@@ -114,10 +117,16 @@ __device__ void attn_dkv_row(const T* k, const T* v, const T* Q, const T* dO, co
                 HeadRow<T, E> q, g, o;
                 q.load(Q + at, D);
                 g.load(dO + at, D);
-                o.load(O + at, D);
+                float del;
+                if (delta) {
+                    del = delta[(long long)i * Hq + h];
+                } else {
+                    o.load(O + at, D);
+                    del = g.dot(o);
+                }
                 const float p = expf(kr.dot(q) * scale - LSE[(long long)i * Hq + h]);
                 dv.add(p, g);
-                dk.add(p * (vr.dot(g) - g.dot(o)), q);
+                dk.add(p * (vr.dot(g) - del), q);
             }
         if (!prefix) break;
     }

@@ -140,6 +140,7 @@ struct LoraPrepParams { LoraPrepJob job[16]; };
 int launch_lora_prep(alch_dtype dt, const LoraPrepParams& p, int n_jobs, hipStream_t stream);
 
 // ---- attention ---------------------------------------------------------------------------
+struct ShortRows { int up_to = 0, step = 1; };  // tokens of the longest such sequence; wavefronts that share the rows of a head
 struct AttnArgs {
     alch_dtype dtype;
     int T, n_seqs, max_seqlen, Hq, Hkv, D;
@@ -162,6 +163,7 @@ struct AttnArgs {
     // any size (T * Hkv * 2 * D floats for each of up to 8 parts are made use of)
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
+    ShortRows rows;  // see rows_up_to
 };
 // Tokens of the longest of the sequences first .. n_seqs-1.  max_seqlen is only a bound on them, and may be any number that
 // is not below it.
@@ -177,7 +179,13 @@ bool attn_mfma_supported(const AttnArgs& a);
 int launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t stream);
 int attn_bwd_mfma_d64(const AttnArgs& a, hipStream_t stream);
 int attn_fwd_mfma_d64(const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, int max_seqlen,
-                      const int* cu_seqlens, const int* prefix, int seq_begin, int Hq, int Hkv, hipStream_t stream);
+                      const int* cu_seqlens, const int* prefix, int seq_begin, int Hq, int Hkv, int short_upto, hipStream_t stream);
+// Sequences too short for the tile kernels, a row at a time: up to how many tokens these take them (0: they take none), and
+// the launches for them.  The tile kernels then leave them out.
+int rows_up_to(int D, int Hq, int per_cu, int first, int n_seqs, const int* cu_host, const int* prefix, ShortRows* rows);
+int launch_attn_bwd_rows(const AttnArgs& a, hipStream_t stream);
+int launch_attn_fwd_rows(alch_dtype dt, const void* Q, const void* K, const void* V, void* O, float* LSE, int n_seqs, const int* cu_seqlens,
+                         int seq_begin, int Hq, int Hkv, int D, const ShortRows& rows, hipStream_t stream);
 static constexpr int kMaxPrefixSeqs = 4096;  // sequences per batch when prefixes are shared
 double attn_pairs(int n_seqs, const int* cu_host, const int* prefix_host);
 // forward: writes O [T,Hq*D] and LSE [T,Hq] for the query rows of sequences seq_begin .. n_seqs-1 (keys and
