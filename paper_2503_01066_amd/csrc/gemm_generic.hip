@@ -9,7 +9,7 @@
 //                      a fixed order.  A problem of a few hundred rows has few tiles and a long serial contraction: what
 //                      bounds it is the latency of that chain, so it is cut (256 x 256 x 2048: 445 -> 13 us).
 //   k_gemm_f32_tiled   128x128 tiles staged through LDS, for problems with enough of them to fill the compute units
-//                      (4096 x 4096 x 2048: 95 - 103 TFLOP/s; vector multiply-adds on 64x64 tiles: 50).
+//                      (4096 x 4096 x 2048: 93 - 107 TFLOP/s; vector multiply-adds on 64x64 tiles: 50).
 #include <algorithm>
 #include <type_traits>
 
@@ -31,6 +31,7 @@ struct GenericGemmParams {
     void* C[3];
     int m_begin[3];
     long long ldc[3];
+    int c_vec[3];  // (as a_vec)
     int epilogue;
     const void* G;
     const void* U;
@@ -44,6 +45,11 @@ __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<
 __device__ __forceinline__ f32x4 ld4(const __bf16* p) {
     const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
     return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+
+__device__ __forceinline__ void st4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ __forceinline__ void st4(__bf16* p, const f32x4& v) {
+    *reinterpret_cast<bf16x4*>(p) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
 }
 
 // One element of the product -> the output.
@@ -234,6 +240,46 @@ __global__ __launch_bounds__(256) void k_gemm_f32_tiled(GenericGemmParams p) {
             }
         }
     }
+    // A tile of one output leaves through LDS as 16-byte (bf16: 8-byte) pieces of whole rows, 64x64 per wavefront, columns
+    // turned by 32 in every other group of four rows so that the two halves of a wavefront write to different banks.  Element
+    // by element the stores were what short contractions took: 4096 x 1312, K 32 28 us, now 14;
+    // 8192 x 8192, K 16 208 us, now 91, K 64 226 us, now 120; 4096 x 4096, K 2048 736 us, now 706.
+    int oseg = 0;
+    for (int s = 1; s < p.n_out; ++s)
+        if (m0 >= p.m_begin[s]) oseg = s;
+    if (p.epilogue == kEpiNone && p.N % 4 == 0 && p.c_vec[oseg] && (oseg + 1 >= p.n_out || m0 + TB <= p.m_begin[oseg + 1])) {
+        __syncthreads();  // (the last stage has been read)
+        float* st = (wave < 2 ? &As[0][0][0] : &Bs[0][0][0]) + (wave & 1) * 4096;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int r = i * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+                    st[r * 64 + ((j * 32 + (lane & 31)) ^ (half * 32))] = acc[i][j][e];
+                }
+        const long long ldc = p.ldc[oseg];
+        const int rows = p.M - (m0 + wm + (lane >> 4));  // of this lane's: row 4 k is inside for 4 k < rows
+        if (n0 + wn + 4 * (lane & 15) >= p.N) return;
+        T* C = static_cast<T*>(p.C[oseg]) + (long long)(m0 - p.m_begin[oseg] + wm + (lane >> 4)) * ldc + n0 + wn + 4 * (lane & 15);
+#pragma unroll
+        for (int q = 0; q < 16; q += 8) {
+            f32x4 old[8];
+            if (p.accumulate)
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (4 * (q + k) < rows) old[k] = ld4(C + (long long)(4 * (q + k)) * ldc);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int r = 4 * (q + k) + (lane >> 4);
+                f32x4 v = *reinterpret_cast<const f32x4*>(st + r * 64 + ((4 * (lane & 15)) ^ ((((q + k) & 1)) * 32)));
+                if (p.accumulate) v += old[k];
+                if (4 * (q + k) < rows) st4(C + (long long)(4 * (q + k)) * ldc, v);
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -244,8 +290,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32_tiled(GenericGemmParams p) {
 }
 
 // From this many 128x128 tiles on the tiled kernel is the faster one (K 1024, three layouts, slices against tiled:
-// 128 tiles 101 / 87 / 106 against 135 / 148 / 110 us, 182 tiles 143 / 123 / 150 against 137 / 150 / 110 us,
-// 256 tiles 190 / 163 / 202 against 138 / 151 / 112 us).
+// 121 tiles 88 / 95 / 103 against 125 / 139 / 99 us, 182 tiles 129 / 141 / 150 against 125 / 138 / 99 us,
+// 256 tiles 174 / 191 / 203 against 126 / 139 / 101 us; K 256: 156 tiles 36 / 36 / 37 against 34 / 37 / 30 us).
 static constexpr int kTiledFrom = 160;
 // Below this many 32x32 tiles the slices kernel takes 16x16 ones: four times as many work-groups share the reads
 // (256 x 256 x 2048, 64 tiles of 32x32: 24 against 12.4 us; 192 tiles, K 256: equal; 512^3, 256 tiles: 10.6 against 13.7 us).
@@ -313,6 +359,7 @@ int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
         p.C[s] = oo ? d.out[s].C : nullptr;
         p.m_begin[s] = oo ? d.out[s].m_begin : 0x7fffffff;
         p.ldc[s] = oo ? d.out[s].ldc : 0;
+        p.c_vec[s] = oo && vec_ok(d.out[s].C, d.out[s].ldc);
     }
     p.epilogue = d.epilogue; p.G = d.G; p.U = d.U; p.ldgu = d.ldgu; p.act_out = d.act_out;
     if (d.dtype == ALCH_BF16) gemm_generic_t<__bf16>(p, stream);

@@ -51,3 +51,22 @@ def test_pairs_of_length_zero(a_k, b_k, M, N, K, dtype):
         torch.cuda.synchronize()
         want = (ref if K else 0.0 * ref) + (C0 if acc else 0)
         assert rc == 0 and rel_err(to_np(C), want) < (2e-6 if dtype == "f32" else 6e-3)
+
+
+@pytest.mark.parametrize("a_k,b_k", [(True, False), (False, False), (True, True)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K,shift", [(1664, 1668, 16, 8), (1537, 1792, 40, 4), (1700, 1669, 33, 8), (1664, 1664, 65, 2)])
+def test_tiles_leave_whole(a_k, b_k, M, N, K, shift, dtype):
+    # 182 .. 196 tiles of 128x128 whose rows leave in pieces of four (N and the output's alignment allow it, or not), edge
+    # tiles among them, into a column slice of a wider buffer whose other columns stay untouched
+    import paper_2503_01066_amd as A_
+    A, B, ref = operands(np.random.default_rng(M + N), M, N, K, a_k, b_k, dtype)
+    C0 = synth.quantize(np.random.default_rng(1).standard_normal((M, N)).astype(np.float32), dtype)
+    for acc in (False, True):
+        wide = torch.full((M, (N + 2 * shift + 3) // 4 * 4), 7.0, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+        C = wide[:, shift:shift + N]
+        C.copy_(to_dev(C0, dtype))
+        A_.alch_gemm(M, N, [(to_dev(A, dtype), to_dev(B, dtype), K)], a_k, b_k, out=C, accumulate=acc)
+        torch.cuda.synchronize()
+        assert rel_err(to_np(C), ref + C0 if acc else ref) < (2e-6 if dtype == "f32" else 6e-3)
+        assert bool((wide[:, :shift] == 7).all()) and bool((wide[:, shift + N:] == 7).all())
