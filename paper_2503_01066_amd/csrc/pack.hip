@@ -137,7 +137,8 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_scan(const uint8_t* __res
                                                             const int* __restrict__ cu_seqlens, int n_bounds,
                                                             int* __restrict__ kept_index, int* __restrict__ cu_kept,
                                                             int* __restrict__ n_kept_and_status, long long capacity) {
-    __shared__ int prefix[kScanThreads];  // kept tokens before each thread's sixteen
+    __shared__ int prefix[kScanThreads];            // kept tokens before each thread's sixteen
+    __shared__ unsigned short kept_bits[kScanThreads];  // and which of these are kept
     const int tid = threadIdx.x, block0 = blockIdx.x * kTokPerBlock, t0 = block0 + tid * kTokPerThread;
     int count = 0;
 #pragma unroll 4
@@ -151,6 +152,7 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_scan(const uint8_t* __res
     block_exclusive_scan(count, before);
     int ex = before + block_exclusive_scan(own, total);
     prefix[tid] = ex;
+    kept_bits[tid] = (unsigned short)bits;
     if (tid == 0 && blockIdx.x == gridDim.x - 1) {
         n_kept_and_status[0] = before + total;
         n_kept_and_status[1] = (long long)(before + total) > capacity ? 1 : 0;
@@ -163,8 +165,7 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_scan(const uint8_t* __res
         int c = before + total;
         if (end < block0 + kTokPerBlock) {
             const int owner = (end - block0) / kTokPerThread;
-            c = prefix[owner];
-            for (int t = block0 + owner * kTokPerThread; t < end; ++t) c += mask[t] != 0;
+            c = prefix[owner] + __popc(kept_bits[owner] & ((1u << ((end - block0) % kTokPerThread)) - 1u));
         }
         cu_kept[s] = c;
     }
@@ -233,17 +234,21 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_small(GatherArgs a, const
                                                              int* __restrict__ n_kept_and_status, long long capacity) {
     __shared__ int token;
     __shared__ int prefix[kScanThreads];
+    __shared__ unsigned short kept_bits[kScanThreads];
     uint32_t bits;
     const int tid = threadIdx.x, c = nonzero_bytes16(mask, tid * kTokPerThread, T, bits);
     int total;
     const int ex = block_exclusive_scan(c, total), r = blockIdx.x;
+    const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+    if (first) {
+        prefix[tid] = ex;
+        kept_bits[tid] = (unsigned short)bits;
+    }
     if (r >= ex && r < ex + c) {
         for (int i = ex; i < r; ++i) bits &= bits - 1;
         token = tid * kTokPerThread + __ffs(bits) - 1;
         if (blockIdx.y == 0 && r < capacity) kept_index[r] = token;
     }
-    const bool first = blockIdx.x == 0 && blockIdx.y == 0;
-    if (first) prefix[tid] = ex;
     __syncthreads();
     if (first) {
         if (tid == 0) {
@@ -253,10 +258,7 @@ __global__ __launch_bounds__(kScanThreads) void k_pack_small(GatherArgs a, const
         for (int s = tid; s < n_bounds; s += kScanThreads) {
             const int end = cu_seqlens[s], owner = end / kTokPerThread;
             int n = total;
-            if (owner < kScanThreads) {
-                n = prefix[owner];
-                for (int t = owner * kTokPerThread; t < end; ++t) n += mask[t] != 0;
-            }
+            if (owner < kScanThreads) n = prefix[owner] + __popc(kept_bits[owner] & ((1u << (end % kTokPerThread)) - 1u));
             cu_kept[s] = n;
         }
     }

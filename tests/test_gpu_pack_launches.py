@@ -28,3 +28,19 @@ def test_scan_and_gather(lens, keep, part):
         assert np.array_equal(cu_kept, ocu) and np.array_equal(kept[:n], ok[:n])
         for d, o in zip(dsts, opacked):
             assert np.array_equal(d[:n], o[:n].view(d.dtype))
+
+
+@pytest.mark.parametrize("lens", [[1] * 3967, [3, 0, 14, 16, 1] * 200, [1, 2] * 3000])
+@pytest.mark.parametrize("n_streams", [1, 20])
+def test_many_boundaries(lens, n_streams):
+    # more boundaries than threads, at every place inside the sixteen tokens of a thread, in either scan
+    cu = synth.ragged_cu(lens)
+    T = int(cu[-1])
+    rng = np.random.default_rng(T)
+    mask = (rng.random(T) < 0.4).astype(np.uint8)
+    srcs = streams_for(T, rng, widths=(8,) * n_streams)
+    kept, cu_kept, status, dsts = run_pack(cu, mask, srcs, capacity=T)
+    ok, ocu, opacked = gather_pack(mask, cu, srcs)
+    assert status[0] == len(ok) and np.array_equal(cu_kept, ocu) and np.array_equal(kept[:len(ok)], ok)
+    for d, o in zip(dsts, opacked):
+        assert np.array_equal(d[:len(ok)], o.view(d.dtype))
