@@ -51,3 +51,24 @@ def test_sums_round_no_more_often_than_a_tree(D, Hkv, lens):
         for k, bound in (("dQ", 3.65e-7), ("dK", 3.2e-7), ("dV", 2.6e-7)):
             err = np.linalg.norm(got[k] - ref[k]) / np.linalg.norm(ref[k])
             assert err <= bound, (k, err)
+
+
+@pytest.mark.parametrize("shape_name", ["d32", "d40", "d64", "d128"])
+@pytest.mark.parametrize("prompts,responses", [([33, 64], [[20, 31], [1, 40]]), ([130, 97], [[60, 75], [200, 33, 1]])])  # (one launch; two)
+def test_shared_prompts(monkeypatch, shape_name, prompts, responses):
+    import torch
+    import paper_2503_01066_amd as A
+    from helpers import TOL, alch_shape, rel_err, to_dev, to_np
+    from oracle import WEIGHT_KEYS
+    from oracle.prefix import layer_backward_reuse_prefix
+    from test_gpu_prefix import dev_record, make
+    monkeypatch.setitem(synth.SHAPES, shape_name, SHAPES[shape_name])
+    shp, osh, b, W, _, _, _, rec, dY = make("f32", shape_name, prompts, responses, 9)
+    ref = layer_backward_reuse_prefix(osh, b["cu"], b["prefix"], f64(rec), f64(W), dY)
+    batch = A.Batch(b["cu"], positions=b["positions"], prefix=b["prefix"])
+    out = A.alch_layer_backward(alch_shape(shp, "f32"), batch, dev_record(rec, "f32"), {k: to_dev(v, "f32") for k, v in W.items()}, to_dev(dY, "f32"))
+    O, lse = A.alch_attention_forward(alch_shape(shp, "f32"), batch, *[to_dev(rec[k], "f32") for k in "QKV"])
+    torch.cuda.synchronize()
+    for k in ["dX"] + ["d" + w for w in WEIGHT_KEYS]:
+        assert rel_err(to_np(out[k]), ref[k]) <= TOL["f32"], k
+    assert rel_err(to_np(O), rec["O"]) <= 1e-5 and rel_err(to_np(lse), rec["LSE"]) <= 1e-5

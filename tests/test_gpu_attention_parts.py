@@ -30,3 +30,25 @@ def test_cut_key_blocks(monkeypatch, shape_name, lens):
     second = run_gpu(shp, "bf16", cu, W, rec, dY)
     for k in first:
         assert np.array_equal(first[k], second[k]), k  # the parts are added in a fixed order
+
+
+@pytest.mark.parametrize("shape_name", ["medium", "medium64", "group of 5", "group of 7"])
+@pytest.mark.parametrize("prompts,responses", [([300, 65], [[70, 129], [100, 200]]), ([130, 500], [[40, 75, 1], [257]])])
+def test_cut_key_blocks_of_shared_prompts(monkeypatch, shape_name, prompts, responses):
+    # the keys of a prompt meet its own queries and those of its responses: blocks long enough to be cut, in either head size
+    from helpers import alch_shape, rel_err, TOL, to_dev, to_np
+    from oracle import WEIGHT_KEYS
+    from oracle.prefix import layer_backward_reuse_prefix
+    from test_gpu_prefix import dev_record, make
+    import paper_2503_01066_amd as A
+    if shape_name in SHAPES:
+        monkeypatch.setitem(synth.SHAPES, shape_name, SHAPES[shape_name])
+    shp, osh, b, W, _, _, _, rec, dY = make("bf16", shape_name, prompts, responses, 9)
+    ref = layer_backward_reuse_prefix(osh, b["cu"], b["prefix"], f64(rec), f64(W), dY)
+    batch = A.Batch(b["cu"], positions=b["positions"], prefix=b["prefix"])
+    outs = [A.alch_layer_backward(alch_shape(shp, "bf16"), batch, dev_record(rec, "bf16"), {k: to_dev(v, "bf16") for k, v in W.items()},
+                                  to_dev(dY, "bf16")) for _ in range(2)]
+    torch.cuda.synchronize()
+    for k in ["dX"] + ["d" + w for w in WEIGHT_KEYS]:
+        assert torch.equal(outs[0][k], outs[1][k]), k
+        assert rel_err(to_np(outs[0][k]), ref[k]) <= TOL["bf16"], k

@@ -13,8 +13,8 @@ from oracle.prefix import layer_forward_prefix, layer_backward_reuse_prefix
 pytestmark = pytest.mark.gpu
 REC = ("X", "X2", "Q", "K", "V", "O", "G", "U")
 
-# (dtype, shape, prompt lengths, response lengths per prompt): f32 / head_dim 8 and bf16 / head_dim 64 take the
-# plain kernels, bf16 / head_dim 128 the matrix-core kernels (prompts and responses spanning several 64- and
+# (dtype, shape, prompt lengths, response lengths per prompt): f32 / head_dim 8 takes the fp32-arithmetic kernels,
+# bf16 / head_dim 64 and 128 the matrix-core kernels (prompts and responses spanning several 64- and
 # 128-row tiles, ragged tails, a prompt without responses, an empty response, three responses on one prompt)
 CASES = [("f32", "tiny", [4, 2, 3], [[3, 2], [1, 4], []]),
          ("f32", "tiny", [0, 3], [[2], [1, 1]]),            # an empty prompt: its response stands alone

@@ -1,4 +1,5 @@
-"""Static checks of the generated gfx950 code of the two matrix-core kernels (no GPU needed: hipcc cross-compiles).
+"""Static checks of the generated gfx950 code of the matrix-core kernels and of the cross-entropy rows (no GPU needed: hipcc
+cross-compiles).
 
 The contraction kernel feeds its pipeline with direct-to-LDS loads written as inline assembly, which the
 compiler's wait-count bookkeeping does not see.  If register allocation ever places the reload of a spilled
@@ -28,9 +29,9 @@ def _device_asm(src):
 def asm():
     if not (shutil.which(B._hipcc()) or os.path.exists(B._hipcc())):
         pytest.skip("hipcc not found")
-    with ThreadPoolExecutor(max_workers=2) as ex:
-        texts = list(ex.map(_device_asm, ["gemm_mfma.hip", "attn_mfma.hip"]))
-    return dict(zip(["gemm", "attn"], texts))
+    names = {"gemm": "gemm_mfma.hip", "attn": "attn_mfma.hip", "pair": "gemm_pair.hip", "attn64": "attn_mfma_d64.hip", "head": "lmhead.hip"}
+    with ThreadPoolExecutor(max_workers=5) as ex:
+        return dict(zip(names, ex.map(_device_asm, names.values())))
 
 
 def _functions(text, prefix):
@@ -76,3 +77,42 @@ def test_attention_kernels_do_not_spill(asm):
         for lab, txt in _blocks(body):
             if txt.count("v_mfma_") >= 16:
                 assert "scratch_" not in txt, (name, lab)
+
+
+def test_contraction_kernel_of_two_work_groups_keeps_its_registers_and_its_pipeline(asm):
+    seen = 0
+    for name, body in _functions(asm["pair"], "_ZN4alch11k_gemm_pairI"):
+        assert _meta(asm["pair"], name, "vgpr_spill_count") == 0 and _meta(asm["pair"], name, "private_segment_fixed_size") == 0, name
+        assert _meta(asm["pair"], name, "vgpr_count") <= 256 and _meta(asm["pair"], name, "group_segment_fixed_size") <= 80 * 1024, name
+        loops = [(lab, txt) for lab, txt in _blocks(body) if txt.count("v_mfma_") >= 16]
+        assert loops, name
+        for lab, txt in loops:
+            assert "scratch_" not in txt and not re.search(r"s_waitcnt [^\n]*vmcnt\(0\)", txt), (name, lab)
+        seen += 1
+    assert seen == 4  # operand layouts
+
+
+def test_attention_kernels_of_heads_of_64_do_not_spill(asm):
+    kernels = [n for n, _ in _functions(asm["attn64"], "_ZN4alch") if "k_attn_" in n or "k_dkv_" in n]
+    assert len(kernels) == 6, kernels  # dQ, dK/dV and the sum of its parts with and without prefixes, forward
+    for n in kernels:
+        assert _meta(asm["attn64"], n, "vgpr_spill_count") == 0 and _meta(asm["attn64"], n, "private_segment_fixed_size") == 0, n
+    for name, body in _functions(asm["attn64"], "_ZN4alch19k_attn_bwd_dkv_mfma"):
+        # from the first iteration's wait (five loads of a tile may be on their way) to the last matrix instruction
+        stream = body[body.index("vmcnt(5)"):body.rindex("v_mfma_")]
+        assert stream.count("v_mfma_") >= 48 and "scratch_" not in stream, name
+        if "ILi64ELb0E" in name:  # (with prefixes the search for the next sequence reads memory)
+            assert not re.search(r"s_waitcnt [^\n]*vmcnt\(0\)", stream), name
+
+
+def test_cross_entropy_rows_wait_for_no_load_between_request_and_use(asm):
+    seen = 0
+    for name, body in _functions(asm["head"], "_ZN4alch19k_ce_chunk_bf16_row"):
+        assert _meta(asm["head"], name, "vgpr_spill_count") == 0 and _meta(asm["head"], name, "private_segment_fixed_size") == 0, name
+        assert _meta(asm["head"], name, "vgpr_count") <= 128, name
+        # behind the requests of the next row (direct-to-LDS loads) nothing waits for all of them before the row's own stores
+        first = body.index("s_barrier", [m.start() for m in re.finditer(r"offen lds", body)][-1])
+        last = body.rindex("buffer_store_dwordx4")
+        assert first < last and not re.search(r"s_waitcnt [^\n]*vmcnt\(0\)", body[first:last]), name
+        seen += 1
+    assert seen == 3  # 4, 8 and 16 chunks of a row
