@@ -578,7 +578,8 @@ bool gemm_cols_together(const GemmDesc& d) {
 // Which of the two matrix-core kernels takes a product: the one whose estimated time is shorter.  Both estimates count
 // rounds of tiles over the compute units of an XCD: so many us for each k of the contraction and for what a tile costs
 // besides, with the last round on its own.  The constants are fits to measured products of 128 .. 8192 rows,
-// K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 %:
+// K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 % (both kernels on 40
+// products: profiles/contraction_kernels_both_sides.txt; the one taken is never more than 2 % behind the other):
 //   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round; a last round that is cut along K adds its two kernels
 //   128x256 tiles, two per compute unit:   0.0265 K + 2 us a round (0.0255 K + 3 weight gradient, 0.0276 K + 6 forward);
 //                                          with one per compute unit, half of that

@@ -14,7 +14,9 @@ namespace alch {
 static constexpr int kTokPerThread = 16;
 static constexpr int kScanThreads = 256;
 static constexpr int kTokPerBlock = kTokPerThread * kScanThreads;  // 4096
-static constexpr int kSmallRows = 256;  // up to so many rows a call of at most 4096 tokens has a work-group per row and stream
+// Up to so many rows a call of at most 4096 tokens has a work-group per row and stream instead of one per row.  Six streams,
+// whole call: 250 rows 19.3 against 19.5 us, 500 rows 21.1 against 19.9, 2000 rows 59.3 against 58.3.
+static constexpr int kSmallRows = 256;
 
 // 0x80 in every byte of w that is not zero
 __device__ __forceinline__ uint32_t nonzero_flags(uint32_t w) { return (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u; }
