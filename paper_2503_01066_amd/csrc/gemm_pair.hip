@@ -187,12 +187,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
             for (int s = 0; s < kU; ++s) {
                 if (kt + s < nk) {
                     const int sn = (s + 1) % kU;
-                    // k 0..15 of the tile; fragments of k 16..31
+                    // k 0..15 of the tile; fragments of k 16..31 (two products in a row share a fragment, see gemm_mfma.hip)
                     ALCH_SB();
                     f1.a[0] = frag_a(s, 1, 0); f1.b[0] = frag_b(s, 1, 0); ALCH_MM(f0, 0, 0); ALCH_MM(f0, 0, 1); ALCH_SB();
-                    f1.b[1] = frag_b(s, 1, 1); f1.a[1] = frag_a(s, 1, 1); ALCH_MM(f0, 1, 0); ALCH_MM(f0, 1, 1); ALCH_SB();
-                    f1.b[2] = frag_b(s, 1, 2); f1.b[3] = frag_b(s, 1, 3); ALCH_MM(f0, 0, 2); ALCH_MM(f0, 0, 3); ALCH_SB();
-                    ALCH_MM(f0, 1, 2); ALCH_MM(f0, 1, 3);
+                    f1.b[1] = frag_b(s, 1, 1); f1.a[1] = frag_a(s, 1, 1); ALCH_MM(f0, 1, 1); ALCH_MM(f0, 1, 0); ALCH_SB();
+                    f1.b[2] = frag_b(s, 1, 2); f1.b[3] = frag_b(s, 1, 3); ALCH_MM(f0, 1, 2); ALCH_MM(f0, 1, 3); ALCH_SB();
+                    ALCH_MM(f0, 0, 3); ALCH_MM(f0, 0, 2);
                     ALCH_SB();
                     // tile s+1 has landed (this wave's share: what may still be in flight is what step s-1 issued), and
                     // this wave's reads of tile s are done
@@ -207,11 +207,11 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
                     f0.a[0] = frag_a(sn, 0, 0); f0.b[0] = frag_b(sn, 0, 0); ALCH_MM(f1, 0, 0); ALCH_MM(f1, 0, 1); ALCH_SB();
                     if (kWide && s % 2) { load_a(s + 3, 2); load_a(s + 3, 3); }
                     if (!kWide) load_a(s, 1);
-                    f0.b[1] = frag_b(sn, 0, 1); f0.a[1] = frag_a(sn, 0, 1); ALCH_MM(f1, 1, 0); ALCH_MM(f1, 1, 1); ALCH_SB();
+                    f0.b[1] = frag_b(sn, 0, 1); f0.a[1] = frag_a(sn, 0, 1); ALCH_MM(f1, 1, 1); ALCH_MM(f1, 1, 0); ALCH_SB();
                     load_b(s, 0); load_b(s, 1);
-                    f0.b[2] = frag_b(sn, 0, 2); f0.b[3] = frag_b(sn, 0, 3); ALCH_MM(f1, 0, 2); ALCH_MM(f1, 0, 3); ALCH_SB();
+                    f0.b[2] = frag_b(sn, 0, 2); f0.b[3] = frag_b(sn, 0, 3); ALCH_MM(f1, 1, 2); ALCH_MM(f1, 1, 3); ALCH_SB();
                     load_b(s, 2); load_b(s, 3);
-                    ALCH_MM(f1, 1, 2); ALCH_MM(f1, 1, 3); ALCH_SB();
+                    ALCH_MM(f1, 0, 3); ALCH_MM(f1, 0, 2); ALCH_SB();
                 }
             }
         }
