@@ -6,6 +6,7 @@ library has not been built, loading raises.
 """
 import ctypes as C
 import os
+from array import array
 
 import numpy as np
 import torch
@@ -113,15 +114,15 @@ def lib():
     L.alch_layer_forward_workspace_bytes.argtypes = [C.POINTER(LayerShape), C.c_int32, C.c_int32]
     L.alch_stack_backward_workspace_bytes.argtypes = [C.POINTER(LayerShape), C.c_int32, C.c_int32, C.c_int32, C.c_int32]
     L.alch_capture_pack.restype = C.c_int
-    L.alch_capture_pack.argtypes = [C.POINTER(CBatch), C.c_void_p, C.c_int32, C.POINTER(CStream), C.c_int64,
+    L.alch_capture_pack.argtypes = [C.POINTER(CBatch), C.c_void_p, C.c_int32, C.c_void_p, C.c_int64,
                                     C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
     L.alch_capture_pack_static.restype = C.c_int
-    L.alch_capture_pack_static.argtypes = [C.POINTER(CBatch), C.c_void_p, C.c_int32, C.POINTER(CStream), C.c_int64,
+    L.alch_capture_pack_static.argtypes = [C.POINTER(CBatch), C.c_void_p, C.c_int32, C.c_void_p, C.c_int64,
                                            C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
     L.alch_capture_pack_static_max_tokens.restype = C.c_size_t
     L.alch_capture_pack_static_max_tokens.argtypes = []
     L.alch_capture_gather.restype = C.c_int
-    L.alch_capture_gather.argtypes = [C.POINTER(CBatch), C.c_int32, C.POINTER(CStream), C.c_int64, C.c_void_p,
+    L.alch_capture_gather.argtypes = [C.POINTER(CBatch), C.c_int32, C.c_void_p, C.c_int64, C.c_void_p,
                                       C.c_void_p, C.c_void_p]
     L.alch_layer_backward.restype = C.c_int
     L.alch_layer_backward.argtypes = [C.POINTER(LayerShape), C.POINTER(CBatch), C.POINTER(CSaved),
@@ -183,12 +184,26 @@ def _check(rc):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream_handle(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    # (the handle alone: a stream object costs 2.5 us, more than half of the launch it is for)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+
+
+def _streams(streams, dsts):
+    """The alch_stream array of a call, as the four 64-bit words of each.  Seven attributes of 14 tensors were half of the
+    host's time for a short prompt; structures filled one by one cost as much again (one prompt of 317 tokens, six
+    streams: whole call 16.6 -> 11.0 us, 5 of them the library's)."""
+    words = []
+    for s, d in zip(streams, dsts):
+        width, size, stride = s.shape[1], s.element_size(), s.stride()
+        empty = s.numel() == 0
+        assert empty or (stride[1] == 1 and d.is_contiguous())
+        words += (s.data_ptr(), d.data_ptr(), width * size, (width if empty else stride[0]) * size)
+    words += [0] * (4 * len(streams) - len(words))  # (a stream without a destination: the library refuses it)
+    return array("Q", words)
 
 
 def make_shape(hidden, n_q_heads, n_kv_heads, head_dim, ffn, rms_eps, rope_base, dtype):
@@ -233,17 +248,12 @@ def alch_capture_pack(batch, keep_mask, streams, capacity=None, dsts=None, strea
     capacity = T if capacity is None else int(capacity)
     if dsts is None:
         dsts = [torch.empty((capacity, s.shape[1]), dtype=s.dtype, device=dev) for s in streams]
-    arr = (CStream * max(len(streams), 1))()
-    for i, (s, d) in enumerate(zip(streams, dsts)):
-        assert s.numel() == 0 or (s.stride(1) == 1 and d.is_contiguous())
-        row_stride = s.stride(0) if s.numel() > 0 else s.shape[1]
-        arr[i] = CStream(s.data_ptr(), d.data_ptr(), s.shape[1] * s.element_size(), row_stride * s.element_size())
+    arr = _streams(streams, dsts)
     kept_index = torch.empty(max(capacity, 1), dtype=torch.int32, device=dev)
     cu_kept = torch.empty(batch.n_seqs + 1, dtype=torch.int32, device=dev)
     status = torch.empty(2, dtype=torch.int32, device=dev)
-    need = L.alch_capture_pack_workspace_bytes(T)
-    ws = workspace if workspace is not None else _workspace(need, dev)
-    _check(L.alch_capture_pack(C.byref(batch.c), _ptr(keep_mask), len(streams), arr, capacity, _ptr(kept_index),
+    ws = workspace if workspace is not None else _workspace(L.alch_capture_pack_workspace_bytes(T), dev)
+    _check(L.alch_capture_pack(C.byref(batch.c), _ptr(keep_mask), len(streams), arr.buffer_info()[0], capacity, _ptr(kept_index),
                                _ptr(cu_kept), _ptr(status), _ptr(ws), ws.numel(), _stream_handle(stream)))
     return kept_index, cu_kept, status, dsts
 
@@ -252,13 +262,9 @@ def alch_capture_pack_static(batch, keep_mask, streams, dsts, kept_index, cu_kep
     """alch_capture_pack on the library's built-in scratch: every buffer, outputs included, comes from the
     caller, and neither this wrapper nor the library allocates device memory."""
     L = lib()
-    arr = (CStream * max(len(streams), 1))()
-    for i, (s, d) in enumerate(zip(streams, dsts)):
-        assert s.numel() == 0 or (s.stride(1) == 1 and d.is_contiguous())
-        row_stride = s.stride(0) if s.numel() > 0 else s.shape[1]
-        arr[i] = CStream(s.data_ptr(), d.data_ptr(), s.shape[1] * s.element_size(), row_stride * s.element_size())
+    arr = _streams(streams, dsts)
     capacity = min([int(kept_index.numel())] + [int(d.shape[0]) for d in dsts])
-    _check(L.alch_capture_pack_static(C.byref(batch.c), _ptr(keep_mask), len(streams), arr, capacity,
+    _check(L.alch_capture_pack_static(C.byref(batch.c), _ptr(keep_mask), len(streams), arr.buffer_info()[0], capacity,
                                       _ptr(kept_index), _ptr(cu_kept), _ptr(status), _stream_handle(stream)))
     return capacity
 
@@ -271,12 +277,8 @@ def alch_capture_gather(batch, kept_index, status, streams, capacity=None, dsts=
     capacity = batch.total_tokens if capacity is None else int(capacity)
     if dsts is None:
         dsts = [torch.empty((capacity, s.shape[1]), dtype=s.dtype, device=dev) for s in streams]
-    arr = (CStream * max(len(streams), 1))()
-    for i, (s, d) in enumerate(zip(streams, dsts)):
-        assert s.numel() == 0 or (s.stride(1) == 1 and d.is_contiguous())
-        row_stride = s.stride(0) if s.numel() > 0 else s.shape[1]
-        arr[i] = CStream(s.data_ptr(), d.data_ptr(), s.shape[1] * s.element_size(), row_stride * s.element_size())
-    _check(L.alch_capture_gather(C.byref(batch.c), len(streams), arr, capacity, _ptr(kept_index), _ptr(status),
+    arr = _streams(streams, dsts)
+    _check(L.alch_capture_gather(C.byref(batch.c), len(streams), arr.buffer_info()[0], capacity, _ptr(kept_index), _ptr(status),
                                  _stream_handle(stream)))
     return dsts
 
