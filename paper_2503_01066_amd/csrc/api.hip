@@ -467,34 +467,33 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         d.act_out = (g.dWd || wants(ALCH_PROJ_D)) ? p.Act : nullptr;
         ALCH_TRY(launch_gemm(d, st));
     }
-    if (g.dWd) {  // dWd = dY^T Act
-        GemmDesc d = gemm_ws(dt, H, F, false, false);
-        d.k_dev = ndev;
-        add_seg(d, mY, H, p.Act, F, T);
-        add_out(d, g.dWd, 0, F);
-        d.accumulate = acc;
-        ALCH_TRY(launch_gemm(d, st));
+    GemmDesc dWd = gemm_ws(dt, H, F, false, false);  // dWd = dY^T Act
+    if (g.dWd) {
+        dWd.k_dev = ndev;
+        add_seg(dWd, mY, H, p.Act, F, T);
+        add_out(dWd, g.dWd, 0, F);
+        dWd.accumulate = acc;
     }
+    GemmDesc dH2 = gemm_ws(dt, T, H, true, false);  // dH2 = dG Wg + dU Wu
+    const bool lora_gu = has(ALCH_PROJ_G) || has(ALCH_PROJ_U);
+    dH2.m_dev = ndev;
+    add_seg(dH2, p.dGU, 2 * (long long)F, w.Wg, H, F);
+    add_seg(dH2, at(p.dGU, F, E), 2 * (long long)F, w.Wu, H, F);
+    if (lora_gu) add_seg(dH2, p.T2, ldt2, p.Ap_gu, H, 2 * kLoraSlot);
+    add_out(dH2, p.dHn, 0, H);
+    const bool dwd_beside = g.dWd && gemm_together(dH2, dWd);
+    if (g.dWd && !dwd_beside) ALCH_TRY(launch_gemm(dWd, st));
     {
         const void* dys[1] = {mY};
         const int outs1[1] = {H};
         ALCH_TRY(adapter_grads(ALCH_PROJ_D, 1, p.Act, F, F, dys, H, outs1));
     }
-    const bool lora_gu = has(ALCH_PROJ_G) || has(ALCH_PROJ_U);
     if (lora_gu) {
         const void* dys[2] = {p.dGU, at(p.dGU, F, E)};
         const int outs2[2] = {F, F};
         ALCH_TRY(down_t2(ALCH_PROJ_G, 2, dys, 2 * (long long)F, outs2));
     }
-    {  // dH2 = dG Wg + dU Wu
-        GemmDesc d = gemm_ws(dt, T, H, true, false);
-        d.m_dev = ndev;
-        add_seg(d, p.dGU, 2 * (long long)F, w.Wg, H, F);
-        add_seg(d, at(p.dGU, F, E), 2 * (long long)F, w.Wu, H, F);
-        if (lora_gu) add_seg(d, p.T2, ldt2, p.Ap_gu, H, 2 * kLoraSlot);
-        add_out(d, p.dHn, 0, H);
-        ALCH_TRY(launch_gemm(d, st));
-    }
+    ALCH_TRY(dwd_beside ? launch_gemm_together(dH2, dWd, st) : launch_gemm(dH2, st));
     // dX2 = dY + RMSNorm-2 backward(dH2); dg2.  The same pass over X2 leaves H2 for the weight and adapter gradients
     // of the gate and up projections (unless the record completion above already formed it).
     {
@@ -507,16 +506,24 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         const int outs2[2] = {F, F};
         ALCH_TRY(adapter_grads(ALCH_PROJ_G, 2, p.Hn, H, H, dys, 2 * (long long)F, outs2));
     }
-    if (g.dWg || g.dWu) {  // [dWg; dWu] = [dG | dU]^T H2
+    GemmDesc dO = gemm_ws(dt, T, QD, true, false);  // dO = dX2 Wo
+    dO.m_dev = ndev;
+    add_seg(dO, mdX2, H, w.Wo, QD, H);
+    if (has(ALCH_PROJ_O)) add_seg(dO, p.T2, ldt2, p.Ap_o, QD, kLoraSlot);
+    add_out(dO, mdO, 0, QD);
+    GemmDesc dWgu = gemm_ws(dt, 2 * F, H, false, false);  // [dWg; dWu] = [dG | dU]^T H2
+    bool dwgu_beside = false;
+    if (g.dWg || g.dWu) {
         if (g.dWg && g.dWu) {
-            GemmDesc d = gemm_ws(dt, 2 * F, H, false, false);
+            GemmDesc& d = dWgu;
             d.k_dev = ndev;
             add_seg(d, p.dGU, 2 * (long long)F, p.Hn, H, T);
             add_out(d, g.dWg, 0, H);
             add_out(d, g.dWu, F, H);
             d.accumulate = acc;
             if (F % 256 == 0) {
-                ALCH_TRY(launch_gemm(d, st));
+                dwgu_beside = gemm_together(dO, d);
+                if (!dwgu_beside) ALCH_TRY(launch_gemm(d, st));
             } else {
                 d.M = F; d.n_out = 1;
                 ALCH_TRY(launch_gemm(d, st));
@@ -538,27 +545,28 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         const int outs1[1] = {H};
         ALCH_TRY(down_t2(ALCH_PROJ_O, 1, dys, H, outs1));
     }
-    {  // dO = dX2 Wo
-        GemmDesc d = gemm_ws(dt, T, QD, true, false);
-        d.m_dev = ndev;
-        add_seg(d, mdX2, H, w.Wo, QD, H);
-        if (has(ALCH_PROJ_O)) add_seg(d, p.T2, ldt2, p.Ap_o, QD, kLoraSlot);
-        add_out(d, mdO, 0, QD);
-        ALCH_TRY(launch_gemm(d, st));
-    }
+    ALCH_TRY(dwgu_beside ? launch_gemm_together(dO, dWgu, st) : launch_gemm(dO, st));
     {
         const void* dys[1] = {mdX2};
         const int outs1[1] = {H};
         ALCH_TRY(adapter_grads(ALCH_PROJ_O, 1, mO, QD, QD, dys, H, outs1));
     }
-    if (g.dWo) {  // dWo = dX2^T O
-        GemmDesc d = gemm_ws(dt, H, QD, false, false);
-        d.k_dev = ndev;
-        add_seg(d, mdX2, H, mO, QD, T);
-        add_out(d, g.dWo, 0, QD);
-        d.accumulate = acc;
-        ALCH_TRY(launch_gemm(d, st));
+    const bool lora_qkv = has(ALCH_PROJ_Q) || has(ALCH_PROJ_K) || has(ALCH_PROJ_V);
+    GemmDesc dH1 = gemm_ws(dt, T, H, true, false);  // dH1 = dQ Wq + dK Wk + dV Wv
+    add_seg(dH1, p.dQKV, QKV, w.Wq, H, QD);
+    add_seg(dH1, at(p.dQKV, QD, E), QKV, w.Wk, H, KD);
+    add_seg(dH1, at(p.dQKV, QD + KD, E), QKV, w.Wv, H, KD);
+    if (lora_qkv) add_seg(dH1, p.T2, ldt2, p.Ap_qkv, H, 3 * kLoraSlot);
+    add_out(dH1, p.dHn, 0, H);
+    GemmDesc dWo = gemm_ws(dt, H, QD, false, false);  // dWo = dX2^T O
+    if (g.dWo) {
+        dWo.k_dev = ndev;
+        add_seg(dWo, mdX2, H, mO, QD, T);
+        add_out(dWo, g.dWo, 0, QD);
+        dWo.accumulate = acc;
     }
+    const bool dwo_beside = g.dWo && gemm_together(dH1, dWo);
+    if (g.dWo && !dwo_beside) ALCH_TRY(launch_gemm(dWo, st));
 
     if (compact) {  // back to [T, width]: zeros in the masked rows
         ALCH_TRY(launch_scatter_rows(p.c_dO, p.c_inv, p.dO, T, (size_t)QD * E, st));
@@ -580,21 +588,12 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         ALCH_TRY(launch_attn_bwd(a, st));
     }
 
-    const bool lora_qkv = has(ALCH_PROJ_Q) || has(ALCH_PROJ_K) || has(ALCH_PROJ_V);
     if (lora_qkv) {
         const void* dys[3] = {p.dQKV, at(p.dQKV, QD, E), at(p.dQKV, QD + KD, E)};
         const int outs3[3] = {QD, KD, KD};
         ALCH_TRY(down_t2(ALCH_PROJ_Q, 3, dys, QKV, outs3));
     }
-    {  // dH1 = dQ Wq + dK Wk + dV Wv
-        GemmDesc d = gemm_ws(dt, T, H, true, false);
-        add_seg(d, p.dQKV, QKV, w.Wq, H, QD);
-        add_seg(d, at(p.dQKV, QD, E), QKV, w.Wk, H, KD);
-        add_seg(d, at(p.dQKV, QD + KD, E), QKV, w.Wv, H, KD);
-        if (lora_qkv) add_seg(d, p.T2, ldt2, p.Ap_qkv, H, 3 * kLoraSlot);
-        add_out(d, p.dHn, 0, H);
-        ALCH_TRY(launch_gemm(d, st));
-    }
+    ALCH_TRY(dwo_beside ? launch_gemm_together(dH1, dWo, st) : launch_gemm(dH1, st));
     // dX = dX2 + RMSNorm-1 backward(dH1); dg1.  The same pass over X leaves H1 for the weight and adapter gradients of
     // the q, k, v projections.
     {

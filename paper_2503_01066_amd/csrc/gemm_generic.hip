@@ -113,12 +113,13 @@ template <> struct F32Tile<16> {
 // loads of four elements: no load then depends on a condition, so that all of a batch are requested before the first is
 // waited for (the eight products of a layer backward of 256 tokens, hidden 256, ffn 1024: 77 us with the conditions, 63 us
 // without); -1 = everything else.
+// `wave` of the kWaves that form tile `tile`; `red` holds their sums.  Every wavefront of the work-group takes part in the
+// one barrier; whether the tile is written may differ.
 template <typename T, int kTile, int kWaves, int kForm>
-__global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_slices(GenericGemmParams p) {
+__device__ __forceinline__ void slices_tile(const GenericGemmParams& p, int tile, int wave, float (*red)[kTile * kTile / 64][64], bool written) {
     constexpr int kElems = kTile * kTile / 64, kChunk = 256 / kTile;
-    __shared__ float red[kWaves][kElems][64];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = lane / kTile;
-    const int m0 = (int)(blockIdx.x / p.tiles_n) * kTile, n0 = (int)(blockIdx.x % p.tiles_n) * kTile;
+    const int lane = threadIdx.x & 63, part = lane / kTile;
+    const int m0 = tile / p.tiles_n * kTile, n0 = tile % p.tiles_n * kTile;
     const int m = min(m0 + lane % kTile, p.M - 1), n = min(n0 + lane % kTile, p.N - 1);
     constexpr bool kPlain = kForm >= 0;
     const bool ak = kPlain ? (kForm & 1) != 0 : p.a_kmajor != 0, bk = kPlain ? (kForm & 2) != 0 : p.b_kmajor != 0;
@@ -162,13 +163,51 @@ __global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_slices(GenericGemmPara
 #pragma unroll
     for (int e = 0; e < kElems; ++e) red[wave][e][lane] = acc[e];
     __syncthreads();
-    for (int q = threadIdx.x; q < kElems * 64; q += kWaves * 64) {
+    if (!written) return;
+    for (int q = wave * 64 + lane; q < kElems * 64; q += kWaves * 64) {
         const int e = q >> 6, l = q & 63;
         float v = red[0][e][l];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) v += red[w][e][l];
         store_element<T>(p, m0 + F32Tile<kTile>::row(e, l), n0 + l % kTile, v);
     }
+}
+
+template <typename T, int kTile, int kWaves, int kForm>
+__global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_slices(GenericGemmParams p) {
+    __shared__ float red[kWaves][kTile * kTile / 64][64];
+    slices_tile<T, kTile, kWaves, kForm>(p, (int)blockIdx.x, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), red, true);
+}
+
+// A data gradient (form 1) and, in the work-groups from n_data on, a weight gradient (form 0) that does not depend on it:
+// either is a chain of latencies on part of the chip (layer of 2 x 128 tokens, hidden 256: dO 4.5 us and [dWg; dWu] 10, now
+// 11.7 together; dH1 10.2 and dWo 3.9, now 12.3; the layer 94 -> 92 us).  Each takes its own tile size and wavefronts per tile
+// (kWaves at most); a work-group holds as many tiles as fit.  Work-groups of 16 wavefronts are left out: one fills a compute
+// unit's registers, so that the second product's wait for the first one's to end (dH2 15.5 and dWd 5.5 us, together 28).
+struct SlicesJob { GenericGemmParams p; int tiles, tile, waves; };
+template <int kTile, int kWaves, int kPer, int kForm>
+__device__ __forceinline__ void slices_tiles(const SlicesJob& job, int block, float* red) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), sub = wave / kPer;
+    constexpr int kEach = kTile * kTile / 64 * 64;
+    const int t = block * (kWaves / kPer) + sub;
+    slices_tile<float, kTile, kPer, kForm>(job.p, min(t, job.tiles - 1), wave % kPer,
+                                           reinterpret_cast<float (*)[kTile * kTile / 64][64]>(red + sub * kPer * kEach), t < job.tiles);
+}
+template <int kWaves, int kForm>
+__device__ __forceinline__ void slices_job(const SlicesJob& job, int block, float* red) {
+    if (job.tile == 32) {
+        if (job.waves == kWaves) slices_tiles<32, kWaves, kWaves, kForm>(job, block, red);
+        else slices_tiles<32, kWaves, 4, kForm>(job, block, red);
+    } else {
+        if (job.waves == kWaves) slices_tiles<16, kWaves, kWaves, kForm>(job, block, red);
+        else slices_tiles<16, kWaves, 4, kForm>(job, block, red);
+    }
+}
+template <int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_two(SlicesJob data, SlicesJob weight, int n_data) {
+    __shared__ float red[kWaves * 16 * 64];
+    if ((int)blockIdx.x < n_data) slices_job<kWaves, 1>(data, (int)blockIdx.x, red);
+    else slices_job<kWaves, 0>(weight, (int)blockIdx.x - n_data, red);
 }
 
 template <typename T>
@@ -297,22 +336,28 @@ static constexpr int kTiledFrom = 160;
 // (256 x 256 x 2048, 64 tiles of 32x32: 24 against 12.4 us; 192 tiles, K 256: equal; 512^3, 256 tiles: 10.6 against 13.7 us).
 static constexpr int kWideFrom = 128;
 
+// Wavefronts per tile: slices of at least 64 k.
+static int slices_waves(int k_total) { return k_total >= 1024 ? 16 : k_total >= 512 ? 8 : 4; }
+// Contractions of whole chunks and, for k-major operands, rows that allow loads of four elements (kForm >= 0).
+static bool slices_plain(const GenericGemmParams& p, int tile) {
+    bool plain = true;
+    for (int s = 0; s < p.n_seg; ++s)
+        plain = plain && p.K[s] > 0 && p.K[s] % (256 / tile) == 0 && (!p.a_kmajor || p.a_vec[s]) && (!p.b_kmajor || p.b_vec[s]);
+    return plain;
+}
+
 template <typename T, int kTile, int kForm>
 static void gemm_slices_form(GenericGemmParams& p, int k_total, hipStream_t stream) {
     p.tiles_n = ceil_div(p.N, kTile);
-    const int grid = ceil_div(p.M, kTile) * p.tiles_n;
-    // slices of at least 64 k
-    if (k_total >= 1024) k_gemm_f32_slices<T, kTile, 16, kForm><<<grid, 1024, 0, stream>>>(p);
-    else if (k_total >= 512) k_gemm_f32_slices<T, kTile, 8, kForm><<<grid, 512, 0, stream>>>(p);
+    const int grid = ceil_div(p.M, kTile) * p.tiles_n, waves = slices_waves(k_total);
+    if (waves == 16) k_gemm_f32_slices<T, kTile, 16, kForm><<<grid, 1024, 0, stream>>>(p);
+    else if (waves == 8) k_gemm_f32_slices<T, kTile, 8, kForm><<<grid, 512, 0, stream>>>(p);
     else k_gemm_f32_slices<T, kTile, 4, kForm><<<grid, 256, 0, stream>>>(p);
 }
 template <typename T, int kTile>
 static void gemm_slices_t(GenericGemmParams& p, int k_total, hipStream_t stream) {
     if constexpr (std::is_same<T, float>::value) {
-        bool plain = true;
-        for (int s = 0; s < p.n_seg; ++s)
-            plain = plain && p.K[s] > 0 && p.K[s] % (256 / kTile) == 0 && (!p.a_kmajor || p.a_vec[s]) && (!p.b_kmajor || p.b_vec[s]);
-        if (plain) {
+        if (slices_plain(p, kTile)) {
             if (p.a_kmajor && p.b_kmajor) return gemm_slices_form<T, kTile, 3>(p, k_total, stream);
             if (p.b_kmajor) return gemm_slices_form<T, kTile, 2>(p, k_total, stream);
             if (p.a_kmajor) return gemm_slices_form<T, kTile, 1>(p, k_total, stream);
@@ -322,23 +367,31 @@ static void gemm_slices_t(GenericGemmParams& p, int k_total, hipStream_t stream)
     gemm_slices_form<T, kTile, -1>(p, k_total, stream);
 }
 
+static int total_k(const GenericGemmParams& p) {
+    int k = 0;
+    for (int s = 0; s < p.n_seg; ++s) k += p.K[s];
+    return k;
+}
+// Rows and columns of a tile: 128 (tiled kernel), 32 or 16 (slices).
+static int generic_tile(const GenericGemmParams& p) {
+    if ((long long)ceil_div(p.M, 128) * ceil_div(p.N, 128) >= kTiledFrom) return 128;
+    return (long long)ceil_div(p.M, 32) * ceil_div(p.N, 32) >= kWideFrom ? 32 : 16;
+}
+
 template <typename T>
 static void gemm_generic_t(GenericGemmParams& p, hipStream_t stream) {
-    int k_total = 0;
-    for (int s = 0; s < p.n_seg; ++s) k_total += p.K[s];
-    const long long tiles128 = (long long)ceil_div(p.M, 128) * ceil_div(p.N, 128);
-    const long long tiles32 = (long long)ceil_div(p.M, 32) * ceil_div(p.N, 32);
-    if (tiles128 >= kTiledFrom) {
+    const int tile = generic_tile(p);
+    if (tile == 128) {
         p.tiles_n = ceil_div(p.N, 128);
-        k_gemm_f32_tiled<T><<<(int)tiles128, 256, 0, stream>>>(p);
-    } else if (tiles32 >= kWideFrom) {
-        gemm_slices_t<T, 32>(p, k_total, stream);
+        k_gemm_f32_tiled<T><<<ceil_div(p.M, 128) * p.tiles_n, 256, 0, stream>>>(p);
+    } else if (tile == 32) {
+        gemm_slices_t<T, 32>(p, total_k(p), stream);
     } else {
-        gemm_slices_t<T, 16>(p, k_total, stream);
+        gemm_slices_t<T, 16>(p, total_k(p), stream);
     }
 }
 
-int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
+static GenericGemmParams generic_params(const GemmDesc& d) {
     GenericGemmParams p;
     p.M = d.M; p.N = d.N; p.n_seg = d.n_seg; p.n_out = d.n_out; p.accumulate = d.accumulate;
     p.a_kmajor = d.a_kmajor; p.b_kmajor = d.b_kmajor;
@@ -362,11 +415,40 @@ int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
         p.c_vec[s] = oo && vec_ok(d.out[s].C, d.out[s].ldc);
     }
     p.epilogue = d.epilogue; p.G = d.G; p.U = d.U; p.ldgu = d.ldgu; p.act_out = d.act_out;
+    return p;
+}
+
+int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
+    GenericGemmParams p = generic_params(d);
     if (d.dtype == ALCH_BF16) gemm_generic_t<__bf16>(p, stream);
     else gemm_generic_t<float>(p, stream);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
+
+static bool slices_job_of(const GemmDesc& d, SlicesJob& job) {
+    job.p = generic_params(d);
+    job.tile = generic_tile(job.p);
+    if (job.tile == 128 || !slices_plain(job.p, job.tile)) return false;
+    job.p.tiles_n = ceil_div(d.N, job.tile);
+    job.tiles = ceil_div(d.M, job.tile) * job.p.tiles_n;
+    job.waves = slices_waves(total_k(job.p));
+    return true;
+}
+static bool slices_jobs(const GemmDesc& data, const GemmDesc& weight, SlicesJob& a, SlicesJob& b) {
+    if (data.dtype != ALCH_F32 || weight.dtype != ALCH_F32 || data.m_dev || weight.k_dev || data.by_cols || weight.by_cols) return false;
+    if (!data.a_kmajor || data.b_kmajor || weight.a_kmajor || weight.b_kmajor) return false;
+    return slices_job_of(data, a) && slices_job_of(weight, b) && std::max(a.waves, b.waves) < 16;
+}
+static int launch_slices_jobs(const SlicesJob& a, const SlicesJob& b, hipStream_t stream) {
+    const int waves = std::max(a.waves, b.waves), n_data = ceil_div(a.tiles, waves / a.waves);
+    const int grid = n_data + ceil_div(b.tiles, waves / b.waves);
+    if (waves == 8) k_gemm_f32_two<8><<<grid, 512, 0, stream>>>(a, b, n_data);
+    else k_gemm_f32_two<4><<<grid, 256, 0, stream>>>(a, b, n_data);
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
+}
+
 
 // The matrix-core kernel addresses an operand through one buffer descriptor and refuses operands of 2 GiB or more.
 // The operands that grow with the batch are indexed by tokens: the rows of a k-major A (data gradients, forward)
@@ -457,6 +539,27 @@ int launch_gemm(const GemmDesc& d, hipStream_t stream) {
     if (launch_gemm_in_bands(d, stream, rc)) return rc;
     TraceScope ts(kTraceGemmGeneric, flops, bytes, stream);
     return launch_gemm_generic(d, stream);
+}
+
+bool gemm_together(const GemmDesc& data, const GemmDesc& weight) {
+    if (data.M <= 0 || data.N <= 0 || weight.M <= 0 || weight.N <= 0) return false;
+    SlicesJob a, b;
+    return data.dtype == ALCH_F32 ? slices_jobs(data, weight, a, b) : gemm_mfma_together(data, weight);
+}
+
+int launch_gemm_together(const GemmDesc& data, const GemmDesc& weight, hipStream_t stream) {
+    double flops = 0, bytes = 0;
+    for (const GemmDesc* d : {&data, &weight}) {
+        double k_total = 0;
+        for (int s = 0; s < d->n_seg; ++s) k_total += d->seg[s].K;
+        flops += 2.0 * d->M * d->N * k_total;
+        bytes += ((double)d->M * k_total + (double)d->N * k_total + (double)d->M * d->N) * dtype_size(d->dtype);
+    }
+    TraceScope ts(data.dtype == ALCH_F32 ? kTraceGemmGeneric : kTraceGemmMfma, flops, bytes, stream);
+    if (data.dtype != ALCH_F32) return launch_gemm_mfma_together(data, weight, stream);
+    SlicesJob a, b;
+    if (!slices_jobs(data, weight, a, b)) return fail(ALCH_ERR_UNSUPPORTED, "products that do not run together");
+    return launch_slices_jobs(a, b, stream);
 }
 
 }  // namespace alch

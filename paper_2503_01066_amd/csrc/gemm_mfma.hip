@@ -630,8 +630,17 @@ int compute_units(int* n_cu) {
     return ALCH_OK;
 }
 
-int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
+// A product as either kernel would run it, and which of them does.
+struct MfmaProduct {
     MfmaGemmParams p;
+    int n_cu, pair_tiles_m;
+    float* split_ws;
+    BigPlan big;
+    PairPlan pair;
+    bool as_pair;
+};
+static int plan_product(const GemmDesc& d, MfmaProduct& out) {
+    MfmaGemmParams& p = out.p;
     p.M = d.M;
     p.N = d.N;
     p.n_seg = d.n_seg;
@@ -669,15 +678,26 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     p.ldgu = d.ldgu;
     p.act_out = static_cast<__bf16*>(d.act_out);
     const int nt = p.tiles_m * p.tiles_n;
-    int n_cu = 0;
-    ALCH_TRY(compute_units(&n_cu));
-    float* split_ws = aligned16(d.split_ws) ? static_cast<float*>(d.split_ws) : nullptr;
-    const BigPlan plan = big_plan(p, d.a_kmajor, n_cu, split_ws ? d.split_ws_bytes : 0);
+    ALCH_TRY(compute_units(&out.n_cu));
+    out.split_ws = aligned16(d.split_ws) ? static_cast<float*>(d.split_ws) : nullptr;
+    const size_t ws_bytes = out.split_ws ? d.split_ws_bytes : 0;
+    out.big = big_plan(p, d.a_kmajor, out.n_cu, ws_bytes);
     // (a 256x256 tile is two tiles of the other kernel, numbered in the same order)
-    const PairPlan pair = d.keep_parts ? PairPlan{2 * ceil_div(nt, 8), 2 * plan.q_end, plan.parts, plan.per}
-                                       : pair_plan(p, d.a_kmajor, n_cu, split_ws ? d.split_ws_bytes : 0);
-    if (pair_is_better(p, plan, pair, d.a_kmajor, d.b_kmajor, n_cu))
-        return launch_gemm_pair(p, d.a_kmajor, d.b_kmajor, d.keep_parts ? 2 * p.tiles_m : ceil_div(p.M, BM / 2), pair, split_ws, stream);
+    out.pair = d.keep_parts ? PairPlan{2 * ceil_div(nt, 8), 2 * out.big.q_end, out.big.parts, out.big.per}
+                            : pair_plan(p, d.a_kmajor, out.n_cu, ws_bytes);
+    out.pair_tiles_m = d.keep_parts ? 2 * p.tiles_m : ceil_div(p.M, BM / 2);
+    out.as_pair = pair_is_better(p, out.big, out.pair, d.a_kmajor, d.b_kmajor, out.n_cu);
+    return ALCH_OK;
+}
+
+int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
+    MfmaProduct m;
+    ALCH_TRY(plan_product(d, m));
+    if (m.as_pair) return launch_gemm_pair(m.p, d.a_kmajor, d.b_kmajor, m.pair_tiles_m, m.pair, m.split_ws, stream);
+    MfmaGemmParams& p = m.p;
+    const BigPlan& plan = m.big;
+    float* split_ws = m.split_ws;
+    const int n_cu = m.n_cu, nt = p.tiles_m * p.tiles_n;
     const int grid = ceil_div(nt, 8) * 8 < n_cu ? ceil_div(nt, 8) * 8 : n_cu;
     const int per_xcd = ceil_div(nt, 8), rem = per_xcd - plan.q_end;
     p.q_end = plan.q_end;
@@ -701,6 +721,23 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     if (p.split_s > 1) k_gemm_split_finish<<<dim3(8 * rem, BM / 16), 256, 0, stream>>>(p, per_xcd, nt);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
+}
+
+// Whether a data gradient and a weight gradient run as one launch.
+static bool plan_together(const GemmDesc& data, const GemmDesc& weight, MfmaProduct& a, MfmaProduct& b) {
+    if (data.split_ws != weight.split_ws || !gemm_mfma_supported(data) || !gemm_mfma_supported(weight)) return false;
+    if (!data.a_kmajor || data.b_kmajor || weight.a_kmajor || weight.b_kmajor) return false;
+    if (plan_product(data, a) != ALCH_OK || plan_product(weight, b) != ALCH_OK) return false;
+    return a.as_pair && b.as_pair && pair_split_bytes(a.pair) + pair_split_bytes(b.pair) <= std::min(data.split_ws_bytes, weight.split_ws_bytes);
+}
+bool gemm_mfma_together(const GemmDesc& data, const GemmDesc& weight) {
+    MfmaProduct a, b;
+    return plan_together(data, weight, a, b);
+}
+int launch_gemm_mfma_together(const GemmDesc& data, const GemmDesc& weight, hipStream_t stream) {
+    MfmaProduct a, b;
+    if (!plan_together(data, weight, a, b)) return fail(ALCH_ERR_UNSUPPORTED, "products that do not run together");
+    return launch_gemm_two_pairs(a.p, a.pair_tiles_m, a.pair, b.p, b.pair_tiles_m, b.pair, a.split_ws, stream);
 }
 
 }  // namespace alch

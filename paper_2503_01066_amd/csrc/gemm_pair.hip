@@ -21,12 +21,14 @@ static constexpr int kPairGroupM = 8;  // tile rows per raster band
 // Epilogue of 64 x 128 results in the accumulators of a wavefront: block (i, j) holds the transposed 32x32 result, this
 // lane owns output row i*32 + (lane&31) and, in registers 4b..4b+3, columns j*32 + 8b + 4*(lane>>5) + 0..3.  The results
 // pass through 16 KB of LDS of the wavefront's own so that they leave as 16-byte pieces of 256-byte row segments.
+static constexpr int kSuper = 16384, kAStage = 8192, kBStage = 16384;
+template <bool kWide> static constexpr int kPairLds = kWide ? 2 * kSuper + 3 * kBStage : 3 * (kAStage + kBStage);
+
+// Work-group `block` of the product's grid.
 template <bool AK, bool BKM>
-__global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
+__device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, char* smem) {
     constexpr bool kWide = AK;
-    constexpr int kSuper = 16384, kAStage = 8192, kBStage = 16384;
     constexpr int kU = kWide ? 12 : 3;  // steps after which every ring is back at its first stage
-    __shared__ __attribute__((aligned(1024))) char smem[kWide ? 2 * kSuper + 3 * kBStage : 3 * (kAStage + kBStage)];
     const uint32_t lds0 = (uint32_t)(uintptr_t)ALCH_LDS(smem);
     auto a_off = [](int st) -> uint32_t { return kWide ? (uint32_t)((st / 2) % 2) * kSuper : (uint32_t)(st % 3) * (kAStage + kBStage); };
     auto b_off = [](int st) -> uint32_t {
@@ -38,12 +40,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
 
     // ---- work-group -> tile (and part of its contraction): every XCD owns per_xcd consecutive tiles
     const int Mv = p.M, tiles_m = p.tiles_m, nt = tiles_m * p.tiles_n, per_xcd = p.per_xcd;
-    const int in_xcd = (int)(blockIdx.x / 8);
+    const int in_xcd = block / 8;
     const bool whole = in_xcd < p.q_end;
     const int rem = per_xcd - p.q_end;
     const int q = whole ? in_xcd : p.q_end + (in_xcd - p.q_end) % rem;
     const int ks = whole ? 0 : (in_xcd - p.q_end) / rem;
-    const int t = (int)(blockIdx.x % 8) * per_xcd + q;
+    const int t = (block % 8) * per_xcd + q;
     if (q >= per_xcd || t >= nt) return;
     const int band_tiles = kPairGroupM * p.tiles_n;
     const int band = t / band_tiles, in_band = t % band_tiles;
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
 
     const int half = lane >> 5;
     if (!whole) {
-        float* ws = p.split_ws + ((size_t)(((blockIdx.x % 8) * rem + (q - p.q_end)) * p.split_s + ks)) * (PM * PN) +
+        float* ws = p.split_ws + ((size_t)(((block % 8) * rem + (q - p.q_end)) * p.split_s + ks)) * (PM * PN) +
                     (wm * 64 + (lane & 31)) * PN + wn * 128 + 4 * half;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -334,6 +336,23 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
     }
 }
 
+template <bool AK, bool BKM>
+__global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[kPairLds<AK>];
+    pair_tile<AK, BKM>(p, (int)blockIdx.x, smem);
+}
+
+// A data gradient and, in the work-groups from n_data on, a weight gradient that does not depend on it.  Of a short batch the
+// one has a work-group per compute unit, or fewer, that read cold weights, the other many short ones that write cold
+// gradients: they fill each other's gaps, and neither waits for the other's last round.  Every tile and part of a tile is
+// the one of a launch of its own: the same bits.  Layer of 107 tokens with heads of 64 235 -> 208 us a backward, 487 tokens
+// of the 8B shape 650 -> 643 us, 4099 tokens with heads of 64 1224 -> 1214 us.
+__global__ __launch_bounds__(256, 2) void k_gemm_two_pairs(MfmaGemmParams data, MfmaGemmParams weight, int n_data) {
+    __shared__ __attribute__((aligned(1024))) char smem[kPairLds<true>];
+    if ((int)blockIdx.x < n_data) pair_tile<true, false>(data, (int)blockIdx.x, smem);
+    else pair_tile<false, false>(weight, (int)blockIdx.x - n_data, smem);
+}
+
 // Sum of the partial tiles -> output.  blockIdx.x % 8: XCD of the tile, blockIdx.x / 8: split tile of its share,
 // blockIdx.y: slab of 16 rows; a thread handles eight consecutive columns of two rows.
 __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
@@ -391,21 +410,44 @@ __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
     }
 }
 
-int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream) {
-    const int per_xcd = plan.per_xcd, q_end = plan.q_end, parts = plan.parts;
+static void set_pair_plan(MfmaGemmParams& p, int tiles_m, const PairPlan& plan, float* split_ws) {
     p.tiles_m = tiles_m;
     p.tiles_n = ceil_div(p.N, PN);
-    p.per_xcd = per_xcd;
-    p.q_end = q_end;
-    p.split_s = parts;
+    p.per_xcd = plan.per_xcd;
+    p.q_end = plan.q_end;
+    p.split_s = plan.parts;
     p.split_per = plan.per;
     p.split_ws = split_ws;
-    const int grid = 8 * (q_end + (per_xcd - q_end) * parts);
+}
+static int pair_grid(const PairPlan& plan) { return 8 * (plan.q_end + (plan.per_xcd - plan.q_end) * plan.parts); }
+static void finish_pair(const MfmaGemmParams& p, hipStream_t stream) {
+    if (p.split_s > 1) k_gemm_pair_finish<<<dim3(8 * (p.per_xcd - p.q_end), PM / 16), 256, 0, stream>>>(p);
+}
+
+int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream) {
+    set_pair_plan(p, tiles_m, plan, split_ws);
+    const int grid = pair_grid(plan);
     if (a_kmajor && b_kmajor) k_gemm_pair<true, true><<<grid, 256, 0, stream>>>(p);
     else if (a_kmajor) k_gemm_pair<true, false><<<grid, 256, 0, stream>>>(p);
     else if (b_kmajor) k_gemm_pair<false, true><<<grid, 256, 0, stream>>>(p);
     else k_gemm_pair<false, false><<<grid, 256, 0, stream>>>(p);
-    if (parts > 1) k_gemm_pair_finish<<<dim3(8 * (per_xcd - q_end), PM / 16), 256, 0, stream>>>(p);
+    finish_pair(p, stream);
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
+}
+
+size_t pair_split_bytes(const PairPlan& plan) {
+    return plan.parts > 1 ? (size_t)8 * (plan.per_xcd - plan.q_end) * plan.parts * PM * PN * sizeof(float) : 0;
+}
+
+int launch_gemm_two_pairs(MfmaGemmParams data, int data_tiles_m, const PairPlan& data_plan, MfmaGemmParams weight, int weight_tiles_m,
+                          const PairPlan& weight_plan, float* split_ws, hipStream_t stream) {
+    set_pair_plan(data, data_tiles_m, data_plan, split_ws);
+    set_pair_plan(weight, weight_tiles_m, weight_plan, split_ws + pair_split_bytes(data_plan) / sizeof(float));
+    const int n_data = pair_grid(data_plan);
+    k_gemm_two_pairs<<<n_data + pair_grid(weight_plan), 256, 0, stream>>>(data, weight, n_data);
+    finish_pair(data, stream);
+    finish_pair(weight, stream);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }

@@ -71,10 +71,15 @@ struct GemmDesc {
 };
 static constexpr size_t kGemmSplitWsBytes = (size_t)64 << 20;
 int launch_gemm(const GemmDesc& d, hipStream_t stream);
+// A data gradient and a weight gradient that do not depend on one another: whether they run as one launch, and that launch.
+bool gemm_together(const GemmDesc& data, const GemmDesc& weight);
+int launch_gemm_together(const GemmDesc& data, const GemmDesc& weight, hipStream_t stream);
 // used by launch_gemm
 bool gemm_mfma_supported(const GemmDesc& d);
 bool gemm_cols_together(const GemmDesc& d);
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream);
+bool gemm_mfma_together(const GemmDesc& data, const GemmDesc& weight);
+int launch_gemm_mfma_together(const GemmDesc& data, const GemmDesc& weight, hipStream_t stream);
 int launch_gemm_generic(const GemmDesc& d, hipStream_t stream);
 
 // ---- row-wise kernels --------------------------------------------------------------------
