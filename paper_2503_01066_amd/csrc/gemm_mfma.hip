@@ -288,15 +288,19 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
                     ALCH_RA(f1, st, 1, 2); ALCH_RA(f1, st, 1, 3); ALCH_MFMA(f0, 0, 2); ALCH_MFMA(f0, 0, 3); ALCH_SB();
                     ALCH_RB(f1, st, 1, 0); ALCH_RB(f1, st, 1, 1); ALCH_MFMA(f0, 1, 3); ALCH_MFMA(f0, 1, 2); ALCH_SB();
                     ALCH_RB(f1, st, 1, 2); ALCH_RB(f1, st, 1, 3); ALCH_MFMA(f0, 1, 1); ALCH_MFMA(f0, 1, 0); ALCH_SB();
-                    ALCH_MFMA(f0, 2, 0); ALCH_MFMA(f0, 2, 1); ALCH_MFMA(f0, 2, 2); ALCH_MFMA(f0, 2, 3);
+                    ALCH_MFMA(f0, 2, 0); ALCH_MFMA(f0, 2, 1); ALCH_SB();
+                    if constexpr (kWide) open_a();
+                    else open_next();
+                    ALCH_SB();
+                    ALCH_MFMA(f0, 2, 2); ALCH_MFMA(f0, 2, 3); ALCH_SB();
+                    if constexpr (kWide) open_b();
+                    ALCH_SB();
                     ALCH_MFMA(f0, 3, 3); ALCH_MFMA(f0, 3, 2); ALCH_MFMA(f0, 3, 1); ALCH_MFMA(f0, 3, 0);
                     ALCH_SB();
                     // k-tile kt+s+1 has landed (this wave's share), and this wave's reads of stage s are done
                     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kLoadsPerTile * (kDepth - 2)) : "memory");
                     __syncthreads();
                     // ---- second half: MFMAs on k 16..31, refill of stage s, fragment reads of the next stage
-                    if constexpr (kWide) { open_a(); open_b(); }
-                    else open_next();
                     ALCH_SB();
                     ALCH_DMA_A(s, 0); ALCH_RA(f0, stn, 0, 0); ALCH_RA(f0, stn, 0, 1); ALCH_MFMA(f1, 0, 0); ALCH_MFMA(f1, 0, 1); ALCH_SB();
                     ALCH_DMA_A(s, 1); ALCH_RA(f0, stn, 0, 2); ALCH_RA(f0, stn, 0, 3); ALCH_MFMA(f1, 0, 2); ALCH_MFMA(f1, 0, 3); ALCH_SB();

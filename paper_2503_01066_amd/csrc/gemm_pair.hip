@@ -194,15 +194,18 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
                     f1.a[0] = frag_a(s, 1, 0); f1.b[0] = frag_b(s, 1, 0); ALCH_MM(f0, 0, 0); ALCH_MM(f0, 0, 1); ALCH_SB();
                     f1.b[1] = frag_b(s, 1, 1); f1.a[1] = frag_a(s, 1, 1); ALCH_MM(f0, 1, 1); ALCH_MM(f0, 1, 0); ALCH_SB();
                     f1.b[2] = frag_b(s, 1, 2); f1.b[3] = frag_b(s, 1, 3); ALCH_MM(f0, 1, 2); ALCH_MM(f0, 1, 3); ALCH_SB();
-                    ALCH_MM(f0, 0, 3); ALCH_MM(f0, 0, 2);
+                    if (!kWide || s % 2) open_a();
+                    ALCH_SB();
+                    ALCH_MM(f0, 0, 3); ALCH_SB();
+                    open_b();
+                    ALCH_SB();
+                    ALCH_MM(f0, 0, 2);
                     ALCH_SB();
                     // tile s+1 has landed (this wave's share: what may still be in flight is what step s-1 issued), and
                     // this wave's reads of tile s are done
                     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kWide ? (s % 2 ? 4 : 8) : 6) : "memory");
                     __syncthreads();
                     // k 16..31; loads of tile s+3 into the stage of tile s, fragments of tile s+1
-                    if (!kWide || s % 2) open_a();
-                    open_b();
                     ALCH_SB();
                     if (kWide && s % 2) { load_a(s + 3, 0); load_a(s + 3, 1); }
                     if (!kWide) load_a(s, 0);
