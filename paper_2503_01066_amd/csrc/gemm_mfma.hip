@@ -104,6 +104,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
+    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)wave * 4096u);
     // kSplit: one tile per work-group; work-group w of an XCD takes part w / rem of tile q_end + w % rem
     const int rem = per_xcd - p.q_end;
     const int ks = kSplit ? (int)(blockIdx.x / 8) / rem : 0;
@@ -127,6 +128,9 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
+    // (seen anew for every tile: addresses formed from it are not kept, and spilled, across the tiles' ends)
+    int flane = lane;
+    asm volatile("" : "+v"(flane));
     int seg_kt0 = 0;  // kSplit: k-tiles of the operand pairs before this one
     for (int seg = 0; seg < p.n_seg; ++seg) {
         const long long lda = p.lda[seg], ldb = p.ldb[seg];
@@ -162,9 +166,9 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
             pb += (long long)lo * stepb;
         }
         uint32_t va[kWide ? 8 : 4], vb[4];
-        if constexpr (kWide) tile_offsets_wide(va, wave, lane, lda, Mv - m0);
-        else tile_offsets<AK>(va, wave, lane, lda, Mv - m0);
-        tile_offsets<BKM>(vb, wave, lane, ldb, p.N - n0);
+        if constexpr (kWide) tile_offsets_wide(va, wave, flane, lda, Mv - m0);
+        else tile_offsets<AK>(va, wave, flane, lda, Mv - m0);
+        tile_offsets<BKM>(vb, wave, flane, ldb, p.N - n0);
 
         // Loads of the next k-tile go out one instruction at a time between MFMAs (a burst of
         // eight would hold the wave at the issue stage while the texture path drains).  Past the
@@ -188,60 +192,49 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
         const int sa_step = __builtin_amdgcn_readfirstlane((int)stepa);
         const int sb_step = __builtin_amdgcn_readfirstlane((int)stepb);
         i32x4 ra, rb;
-        auto open_next = [&]() {
-            // resources of the next k-tile (an exhausted stream gets an empty buffer), then advance
-            int na, nbb;
-            asm volatile("s_cmp_gt_i32 %2, 0\n\ts_cselect_b32 %0, %3, 0\n\ts_cselect_b32 %1, %4, 0"
-                         : "=&s"(na), "=&s"(nbb)
-                         : "s"(tiles_left), "s"(a_rem), "s"(b_rem)
-                         : "scc");
-            ra[0] = (int)a_lo; ra[1] = (int)a_hi; ra[2] = na; ra[3] = 0x00020000;
-            rb[0] = (int)b_lo; rb[1] = (int)b_hi; rb[2] = nbb; rb[3] = 0x00020000;
-            asm volatile("s_add_u32 %0, %0, %7\n\ts_addc_u32 %1, %1, 0\n\ts_sub_i32 %2, %2, %7\n\ts_max_i32 %2, %2, 0\n\t"
-                         "s_add_u32 %3, %3, %8\n\ts_addc_u32 %4, %4, 0\n\ts_sub_i32 %5, %5, %8\n\ts_max_i32 %5, %5, 0\n\t"
-                         "s_sub_i32 %6, %6, 1"
-                         : "+s"(a_lo), "+s"(a_hi), "+s"(a_rem), "+s"(b_lo), "+s"(b_hi), "+s"(b_rem), "+s"(tiles_left)
-                         : "s"(sa_step), "s"(sb_step)
-                         : "scc");
+        // The loads of a step read through the descriptors ra, rb; an exhausted stream gets an empty buffer.  kWide: A's
+        // stream moves by 128 bytes (64 k) after every second batch (a_inc alternates 0, 128).
+        int a_left = kWide ? (nk + 1) & ~1 : nk, a_inc = kWide ? 0 : sa_step;
+        auto select = [](i32x4& r, uint32_t lo, uint32_t hi, int bytes, int left) {
+            int n;
+            asm volatile("s_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=&s"(n) : "s"(left), "s"(bytes) : "scc");
+            r[0] = (int)lo; r[1] = (int)hi; r[2] = n; r[3] = 0x00020000;
         };
-        // kWide: the two streams advance separately.  A moves by 128 bytes (64 k) after every second batch
-        // (a_inc alternates 0, 128); its batches are counted in a_left, B's k-tiles in tiles_left.
-        int a_left = (nk + 1) & ~1, a_inc = 0;
-        auto open_a = [&]() {
-            int na;
-            asm volatile("s_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=&s"(na) : "s"(a_left), "s"(a_rem) : "scc");
-            ra[0] = (int)a_lo; ra[1] = (int)a_hi; ra[2] = na; ra[3] = 0x00020000;
-            asm volatile("s_add_u32 %0, %0, %4\n\ts_addc_u32 %1, %1, 0\n\ts_sub_i32 %2, %2, %4\n\ts_max_i32 %2, %2, 0\n\t"
-                         "s_sub_i32 %4, 128, %4\n\ts_sub_i32 %3, %3, 1"
-                         : "+s"(a_lo), "+s"(a_hi), "+s"(a_rem), "+s"(a_left), "+s"(a_inc)
-                         :
-                         : "scc");
-        };
-        auto open_b = [&]() {
-            int nbb;
-            asm volatile("s_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=&s"(nbb) : "s"(tiles_left), "s"(b_rem) : "scc");
-            rb[0] = (int)b_lo; rb[1] = (int)b_hi; rb[2] = nbb; rb[3] = 0x00020000;
+        auto advance = [](uint32_t& lo, uint32_t& hi, int& bytes, int& left, int step) {
             asm volatile("s_add_u32 %0, %0, %4\n\ts_addc_u32 %1, %1, 0\n\ts_sub_i32 %2, %2, %4\n\ts_max_i32 %2, %2, 0\n\t"
                          "s_sub_i32 %3, %3, 1"
-                         : "+s"(b_lo), "+s"(b_hi), "+s"(b_rem), "+s"(tiles_left)
-                         : "s"(sb_step)
+                         : "+s"(lo), "+s"(hi), "+s"(bytes), "+s"(left)
+                         : "s"(step)
                          : "scc");
         };
+        // in four pieces, each short enough to hide behind a matrix product
+        auto open_step = [&](auto piece) {
+            constexpr int q = decltype(piece)::value;
+            if constexpr (q == 0) select(ra, a_lo, a_hi, a_rem, a_left);
+            if constexpr (q == 1) {
+                advance(a_lo, a_hi, a_rem, a_left, a_inc);
+                if constexpr (kWide) asm volatile("s_sub_i32 %0, 128, %0" : "+s"(a_inc) : : "scc");
+            }
+            if constexpr (q == 2) select(rb, b_lo, b_hi, b_rem, tiles_left);
+            if constexpr (q == 3) advance(b_lo, b_hi, b_rem, tiles_left, sb_step);
+        };
+        auto open_a = [&]() { open_step(IntC<0>{}); open_step(IntC<1>{}); };
+        auto open_b = [&]() { open_step(IntC<2>{}); open_step(IntC<3>{}); };
         // Refill issued in step `st`: !kWide: k-tile st + kStages of both operands into the stage of k-tile st.
         // kWide: A batch st + 5 = half (st+5)&1 of super-tile (st+5)/2, B k-tile st + 4 into the stage of k-tile st.
 #define ALCH_DMA_A(st, j)                                                                                              \
-    dma16(ra, lds0 + (kWide ? a_off((st) + 5) + (uint32_t)(((st) + 5) & 1) * kOperandStageBytes : a_off(st)) +          \
-                  (uint32_t)(wave * 4 + (j)) * 1024u, va[kWide ? (((st) + 5) & 1) * 4 + (j) : (j)])
-#define ALCH_DMA_B(st, j) dma16(rb, lds0 + b_off(st) + (uint32_t)(wave * 4 + (j)) * 1024u, vb[j])
+    dma16(ra, lds_wave, (kWide ? a_off((st) + 5) + (uint32_t)(((st) + 5) & 1) * kOperandStageBytes : a_off(st)) +       \
+                            (uint32_t)(j) * 1024u, va[kWide ? (((st) + 5) & 1) * 4 + (j) : (j)])
+#define ALCH_DMA_B(st, j) dma16(rb, lds_wave, b_off(st) + (uint32_t)(j) * 1024u, vb[j])
 #define ALCH_MFMA(F, i, j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[j], F.a[i], acc[i][j], 0, 0, 0)
 #define ALCH_SB() __builtin_amdgcn_sched_barrier(0)
         // fragment reads of k-tile step `st`
         auto frag_a = [&](int st, int kk, int i) -> bf16x8 {
-            if constexpr (kWide) return read_frag_wide(smem + a_off(st), st & 1, wm * 128 + i * 32, kk, lane);
-            else return read_frag<AK>(smem + a_off(st), wm * 128 + i * 32, kk, lane);
+            if constexpr (kWide) return read_frag_wide(smem + a_off(st), st & 1, wm * 128 + i * 32, kk, flane);
+            else return read_frag<AK>(smem + a_off(st), wm * 128 + i * 32, kk, flane);
         };
 #define ALCH_RA(F, st, kk, i) F.a[i] = frag_a(st, kk, i)
-#define ALCH_RB(F, st, kk, i) F.b[i] = read_frag<BKM>(smem + b_off(st), wn * 128 + (i) * 32, kk, lane)
+#define ALCH_RB(F, st, kk, i) F.b[i] = read_frag<BKM>(smem + b_off(st), wn * 128 + (i) * 32, kk, flane)
 
         // all waves are done with the previous segment's stages before they are refilled
         __syncthreads();
@@ -263,7 +256,8 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
         } else {
 #pragma unroll
             for (int s = 0; s < kStages; ++s) {
-                open_next();
+                open_a();
+                open_b();
 #pragma unroll
                 for (int j = 0; j < 4; ++j) { ALCH_DMA_A(s, j); ALCH_DMA_B(s, j); }
             }
@@ -273,46 +267,49 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
         Frags f0, f1;
 #pragma unroll
         for (int i = 0; i < 4; ++i) { ALCH_RA(f0, 0, 0, i); ALCH_RB(f0, 0, 0, i); }
-        for (int kt = 0; kt < nk; kt += kU) {
+        // One wavefront to a SIMD: whatever stands between two matrix products and takes longer than one of them is time in
+        // which the matrix cores idle (on operands of zeros, which the power cap lets run, a k-tile took 1262 cycles of 1024).
+        // So a step ends in a branch out of the loop alone, in straight line with the next one, where the compiler knows
+        // which fragments are on their way and waits for those that a product needs instead of for all; the descriptors
+        // of the next loads are formed in pieces between products of the first half; and LDS addresses are constants added
+        // to one base.  Before, with 22 scalar instructions behind the barrier and a wait for all fragments: step 8b 6400,
+        // now 6245 us; layer backward over 2 x 3001 tokens 6687 -> 6486 us; layer forward of 5003 tokens 2066 -> 2015 us.
+        for (int kt = 0;; kt += kU) {
 #pragma unroll
             for (int s = 0; s < kU; ++s) {
-                if (kt + s < nk) {
-                    const int st = s, stn = (s + 1) % kU;
-                    // ---- first half: MFMAs on k 0..15 of this stage, fragment reads for k 16..31.  Their order goes to
-                    // and fro over the columns, so that two in a row always share a fragment: the power cap sets the
-                    // clock, and an operand that stays draws less (registers alone, random operands: both operands
-                    // new 1770, rows of four in one direction 1793, to and fro 1808 TFLOP/s; layer forward of 5003
-                    // tokens 2022 -> 2013 us, preference step 8371 -> 8346 us).
-                    ALCH_SB();
-                    ALCH_RA(f1, st, 1, 0); ALCH_RA(f1, st, 1, 1); ALCH_MFMA(f0, 0, 0); ALCH_MFMA(f0, 0, 1); ALCH_SB();
-                    ALCH_RA(f1, st, 1, 2); ALCH_RA(f1, st, 1, 3); ALCH_MFMA(f0, 0, 2); ALCH_MFMA(f0, 0, 3); ALCH_SB();
-                    ALCH_RB(f1, st, 1, 0); ALCH_RB(f1, st, 1, 1); ALCH_MFMA(f0, 1, 3); ALCH_MFMA(f0, 1, 2); ALCH_SB();
-                    ALCH_RB(f1, st, 1, 2); ALCH_RB(f1, st, 1, 3); ALCH_MFMA(f0, 1, 1); ALCH_MFMA(f0, 1, 0); ALCH_SB();
-                    ALCH_MFMA(f0, 2, 0); ALCH_MFMA(f0, 2, 1); ALCH_SB();
-                    if constexpr (kWide) open_a();
-                    else open_next();
-                    ALCH_SB();
-                    ALCH_MFMA(f0, 2, 2); ALCH_MFMA(f0, 2, 3); ALCH_SB();
-                    if constexpr (kWide) open_b();
-                    ALCH_SB();
-                    ALCH_MFMA(f0, 3, 3); ALCH_MFMA(f0, 3, 2); ALCH_MFMA(f0, 3, 1); ALCH_MFMA(f0, 3, 0);
-                    ALCH_SB();
-                    // k-tile kt+s+1 has landed (this wave's share), and this wave's reads of stage s are done
-                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kLoadsPerTile * (kDepth - 2)) : "memory");
-                    __syncthreads();
-                    // ---- second half: MFMAs on k 16..31, refill of stage s, fragment reads of the next stage
-                    ALCH_SB();
-                    ALCH_DMA_A(s, 0); ALCH_RA(f0, stn, 0, 0); ALCH_RA(f0, stn, 0, 1); ALCH_MFMA(f1, 0, 0); ALCH_MFMA(f1, 0, 1); ALCH_SB();
-                    ALCH_DMA_A(s, 1); ALCH_RA(f0, stn, 0, 2); ALCH_RA(f0, stn, 0, 3); ALCH_MFMA(f1, 0, 2); ALCH_MFMA(f1, 0, 3); ALCH_SB();
-                    ALCH_DMA_A(s, 2); ALCH_RB(f0, stn, 0, 0); ALCH_MFMA(f1, 1, 3); ALCH_MFMA(f1, 1, 2); ALCH_SB();
-                    ALCH_DMA_A(s, 3); ALCH_RB(f0, stn, 0, 1); ALCH_MFMA(f1, 1, 1); ALCH_MFMA(f1, 1, 0); ALCH_SB();
-                    ALCH_DMA_B(s, 0); ALCH_RB(f0, stn, 0, 2); ALCH_MFMA(f1, 2, 0); ALCH_MFMA(f1, 2, 1); ALCH_SB();
-                    ALCH_DMA_B(s, 1); ALCH_RB(f0, stn, 0, 3); ALCH_MFMA(f1, 2, 2); ALCH_MFMA(f1, 2, 3); ALCH_SB();
-                    ALCH_DMA_B(s, 2); ALCH_MFMA(f1, 3, 3); ALCH_MFMA(f1, 3, 2); ALCH_SB();
-                    ALCH_DMA_B(s, 3); ALCH_MFMA(f1, 3, 1); ALCH_MFMA(f1, 3, 0); ALCH_SB();
-                }
+                if (kt + s >= nk) goto steps_done;
+                const int st = s, stn = (s + 1) % kU;
+                // ---- first half: MFMAs on k 0..15 of this stage, fragment reads for k 16..31.  Their order goes to
+                // and fro over the columns, so that two in a row always share a fragment: the power cap sets the
+                // clock, and an operand that stays draws less (registers alone, random operands: both operands
+                // new 1770, rows of four in one direction 1793, to and fro 1808 TFLOP/s; layer forward of 5003
+                // tokens 2022 -> 2013 us, preference step 8371 -> 8346 us).
+                ALCH_SB();
+                ALCH_RA(f1, st, 1, 0); ALCH_RA(f1, st, 1, 1); ALCH_MFMA(f0, 0, 0); ALCH_MFMA(f0, 0, 1); ALCH_SB();
+                ALCH_RA(f1, st, 1, 2); ALCH_RA(f1, st, 1, 3); ALCH_MFMA(f0, 0, 2); ALCH_MFMA(f0, 0, 3); ALCH_SB();
+                ALCH_RB(f1, st, 1, 0); ALCH_RB(f1, st, 1, 1); ALCH_MFMA(f0, 1, 3); ALCH_MFMA(f0, 1, 2); ALCH_SB();
+                ALCH_RB(f1, st, 1, 2); ALCH_RB(f1, st, 1, 3); ALCH_MFMA(f0, 1, 1); ALCH_MFMA(f0, 1, 0); ALCH_SB();
+                ALCH_MFMA(f0, 2, 0); ALCH_SB(); open_step(IntC<0>{}); ALCH_SB();
+                ALCH_MFMA(f0, 2, 1); ALCH_SB(); open_step(IntC<1>{}); ALCH_SB();
+                ALCH_MFMA(f0, 2, 2); ALCH_SB(); open_step(IntC<2>{}); ALCH_SB();
+                ALCH_MFMA(f0, 2, 3); ALCH_SB(); open_step(IntC<3>{}); ALCH_SB();
+                ALCH_MFMA(f0, 3, 3); ALCH_MFMA(f0, 3, 2); ALCH_MFMA(f0, 3, 1); ALCH_MFMA(f0, 3, 0);
+                ALCH_SB();
+                // k-tile kt+s+1 has landed (this wave's share), and this wave's reads of stage s are done
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kLoadsPerTile * (kDepth - 2)) : "memory");
+                // ---- second half: MFMAs on k 16..31, refill of stage s, fragment reads of the next stage
+                ALCH_SB();
+                ALCH_DMA_A(s, 0); ALCH_RA(f0, stn, 0, 0); ALCH_RA(f0, stn, 0, 1); ALCH_MFMA(f1, 0, 0); ALCH_MFMA(f1, 0, 1); ALCH_SB();
+                ALCH_DMA_A(s, 1); ALCH_RA(f0, stn, 0, 2); ALCH_RA(f0, stn, 0, 3); ALCH_MFMA(f1, 0, 2); ALCH_MFMA(f1, 0, 3); ALCH_SB();
+                ALCH_DMA_A(s, 2); ALCH_RB(f0, stn, 0, 0); ALCH_MFMA(f1, 1, 3); ALCH_MFMA(f1, 1, 2); ALCH_SB();
+                ALCH_DMA_A(s, 3); ALCH_RB(f0, stn, 0, 1); ALCH_MFMA(f1, 1, 1); ALCH_MFMA(f1, 1, 0); ALCH_SB();
+                ALCH_DMA_B(s, 0); ALCH_RB(f0, stn, 0, 2); ALCH_MFMA(f1, 2, 0); ALCH_MFMA(f1, 2, 1); ALCH_SB();
+                ALCH_DMA_B(s, 1); ALCH_RB(f0, stn, 0, 3); ALCH_MFMA(f1, 2, 2); ALCH_MFMA(f1, 2, 3); ALCH_SB();
+                ALCH_DMA_B(s, 2); ALCH_MFMA(f1, 3, 3); ALCH_MFMA(f1, 3, 2); ALCH_SB();
+                ALCH_DMA_B(s, 3); ALCH_MFMA(f1, 3, 1); ALCH_MFMA(f1, 3, 0); ALCH_SB();
             }
         }
+    steps_done:
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #undef ALCH_DMA_A
 #undef ALCH_DMA_B

@@ -60,11 +60,13 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;
 // 16 bytes per lane from buffer `r` at byte offset `voff` straight into LDS at
 // lds_addr + lane*16.  Written as assembly so that the compiler does not order later LDS
 // reads of the other pipeline stage behind it; completion is awaited with vmcnt.
-__device__ __forceinline__ void dma16(i32x4 r, uint32_t lds_addr, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+// lds_off: a constant once the loop around it is unrolled (as an operand of the addition it takes no scalar register: the
+// addresses of a whole ring were more of them than there are).
+__device__ __forceinline__ void dma16(i32x4 r, uint32_t lds_addr, uint32_t lds_off, uint32_t voff) {
+    asm volatile("s_add_u32 m0, %0, %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :
-                 : "s"(lds_addr), "v"(voff), "s"(r)
-                 : "memory", "m0");
+                 : "s"(lds_addr), "v"(voff), "s"(r), "i"(lds_off)
+                 : "memory", "m0", "scc");
 }
 
 // Per-lane byte offsets (relative to the tile origin) of the 4 direct-to-LDS loads a wave

@@ -37,6 +37,8 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
+    const uint32_t lds_a = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)wave * 2048u);
+    const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)wave * 4096u);
 
     // ---- work-group -> tile (and part of its contraction): every XCD owns per_xcd consecutive tiles
     const int Mv = p.M, tiles_m = p.tiles_m, nt = tiles_m * p.tiles_n, per_xcd = p.per_xcd;
@@ -124,21 +126,27 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
         int a_left = kWide ? (nk + 1) / 2 : nk, b_left = nk;
         const int sa_step = __builtin_amdgcn_readfirstlane(kWide ? 128 : (int)stepa), sb_step = __builtin_amdgcn_readfirstlane((int)stepb);
         i32x4 ra, rb;
-        auto open = [](i32x4& r, uint32_t& lo, uint32_t& hi, int& left_bytes, int& left, int step) {
+        auto select = [](i32x4& r, uint32_t lo, uint32_t hi, int left_bytes, int left) {
             int n;
             asm volatile("s_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=&s"(n) : "s"(left), "s"(left_bytes) : "scc");
             r[0] = (int)lo; r[1] = (int)hi; r[2] = n; r[3] = 0x00020000;
+        };
+        auto advance = [](uint32_t& lo, uint32_t& hi, int& left_bytes, int& left, int step) {
             asm volatile("s_add_u32 %0, %0, %4\n\ts_addc_u32 %1, %1, 0\n\ts_sub_i32 %2, %2, %4\n\ts_max_i32 %2, %2, 0\n\t"
                          "s_sub_i32 %3, %3, 1"
                          : "+s"(lo), "+s"(hi), "+s"(left_bytes), "+s"(left)
                          : "s"(step)
                          : "scc");
         };
-        auto open_a = [&]() { open(ra, a_lo, a_hi, a_rem, a_left, sa_step); };
-        auto open_b = [&]() { open(rb, b_lo, b_hi, b_rem, b_left, sb_step); };
+        auto select_a = [&]() { select(ra, a_lo, a_hi, a_rem, a_left); };
+        auto select_b = [&]() { select(rb, b_lo, b_hi, b_rem, b_left); };
+        auto advance_a = [&]() { advance(a_lo, a_hi, a_rem, a_left, sa_step); };
+        auto advance_b = [&]() { advance(b_lo, b_hi, b_rem, b_left, sb_step); };
+        auto open_a = [&]() { select_a(); advance_a(); };
+        auto open_b = [&]() { select_b(); advance_b(); };
         // the loads of tile `st` (A: of the super-stage that holds it)
-        auto load_a = [&](int st, int j) { dma16(ra, lds0 + a_off(st) + (uint32_t)(wave * (kWide ? 4 : 2) + j) * 1024u, va[j]); };
-        auto load_b = [&](int st, int j) { dma16(rb, lds0 + b_off(st) + (uint32_t)(wave * 4 + j) * 1024u, vb[j]); };
+        auto load_a = [&](int st, int j) { dma16(ra, kWide ? lds_b : lds_a, a_off(st) + (uint32_t)j * 1024u, va[j]); };
+        auto load_b = [&](int st, int j) { dma16(rb, lds_b, b_off(st) + (uint32_t)j * 1024u, vb[j]); };
         auto frag_a = [&](int st, int kk, int i) -> bf16x8 {
             if constexpr (kWide) {
                 const int row = wm * 64 + i * 32 + (lane & 31), c = ((st & 1) * 4 + kk * 2 + (lane >> 5)) ^ ((row >> 1) & 7);
@@ -184,42 +192,41 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
         for (int i = 0; i < 2; ++i) f0.a[i] = frag_a(0, 0, i);
 #pragma unroll
         for (int j = 0; j < 4; ++j) f0.b[j] = frag_b(0, 0, j);
-        for (int kt = 0; kt < nk; kt += kU) {
+        for (int kt = 0;; kt += kU) {
 #pragma unroll
             for (int s = 0; s < kU; ++s) {
-                if (kt + s < nk) {
-                    const int sn = (s + 1) % kU;
-                    // k 0..15 of the tile; fragments of k 16..31 (two products in a row share a fragment, see gemm_mfma.hip)
-                    ALCH_SB();
-                    f1.a[0] = frag_a(s, 1, 0); f1.b[0] = frag_b(s, 1, 0); ALCH_MM(f0, 0, 0); ALCH_MM(f0, 0, 1); ALCH_SB();
-                    f1.b[1] = frag_b(s, 1, 1); f1.a[1] = frag_a(s, 1, 1); ALCH_MM(f0, 1, 1); ALCH_MM(f0, 1, 0); ALCH_SB();
-                    f1.b[2] = frag_b(s, 1, 2); f1.b[3] = frag_b(s, 1, 3); ALCH_MM(f0, 1, 2); ALCH_MM(f0, 1, 3); ALCH_SB();
-                    if (!kWide || s % 2) open_a();
-                    ALCH_SB();
-                    ALCH_MM(f0, 0, 3); ALCH_SB();
-                    open_b();
-                    ALCH_SB();
-                    ALCH_MM(f0, 0, 2);
-                    ALCH_SB();
-                    // tile s+1 has landed (this wave's share: what may still be in flight is what step s-1 issued), and
-                    // this wave's reads of tile s are done
-                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kWide ? (s % 2 ? 4 : 8) : 6) : "memory");
-                    __syncthreads();
-                    // k 16..31; loads of tile s+3 into the stage of tile s, fragments of tile s+1
-                    ALCH_SB();
-                    if (kWide && s % 2) { load_a(s + 3, 0); load_a(s + 3, 1); }
-                    if (!kWide) load_a(s, 0);
-                    f0.a[0] = frag_a(sn, 0, 0); f0.b[0] = frag_b(sn, 0, 0); ALCH_MM(f1, 0, 0); ALCH_MM(f1, 0, 1); ALCH_SB();
-                    if (kWide && s % 2) { load_a(s + 3, 2); load_a(s + 3, 3); }
-                    if (!kWide) load_a(s, 1);
-                    f0.b[1] = frag_b(sn, 0, 1); f0.a[1] = frag_a(sn, 0, 1); ALCH_MM(f1, 1, 1); ALCH_MM(f1, 1, 0); ALCH_SB();
-                    load_b(s, 0); load_b(s, 1);
-                    f0.b[2] = frag_b(sn, 0, 2); f0.b[3] = frag_b(sn, 0, 3); ALCH_MM(f1, 1, 2); ALCH_MM(f1, 1, 3); ALCH_SB();
-                    load_b(s, 2); load_b(s, 3);
-                    ALCH_MM(f1, 0, 3); ALCH_MM(f1, 0, 2); ALCH_SB();
-                }
+                if (kt + s >= nk) goto steps_done;
+                const int sn = (s + 1) % kU;
+                // k 0..15 of the tile; fragments of k 16..31 (two products in a row share a fragment, see gemm_mfma.hip)
+                ALCH_SB();
+                f1.a[0] = frag_a(s, 1, 0); f1.b[0] = frag_b(s, 1, 0); ALCH_MM(f0, 0, 0); ALCH_MM(f0, 0, 1); ALCH_SB();
+                f1.b[1] = frag_b(s, 1, 1); f1.a[1] = frag_a(s, 1, 1); ALCH_MM(f0, 1, 1); ALCH_MM(f0, 1, 0); ALCH_SB();
+                f1.b[2] = frag_b(s, 1, 2); f1.b[3] = frag_b(s, 1, 3); ALCH_MM(f0, 1, 2); ALCH_SB();
+                if (!kWide || s % 2) select_a();
+                ALCH_SB(); ALCH_MM(f0, 1, 3); ALCH_SB();
+                if (!kWide || s % 2) advance_a();
+                ALCH_SB(); ALCH_MM(f0, 0, 3); ALCH_SB();
+                select_b();
+                ALCH_SB(); ALCH_MM(f0, 0, 2); ALCH_SB();
+                advance_b();
+                // tile s+1 has landed (this wave's share: what may still be in flight is what step s-1 issued), and
+                // this wave's reads of tile s are done
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kWide ? (s % 2 ? 4 : 8) : 6) : "memory");
+                // k 16..31; loads of tile s+3 into the stage of tile s, fragments of tile s+1
+                ALCH_SB();
+                if (kWide && s % 2) { load_a(s + 3, 0); load_a(s + 3, 1); }
+                if (!kWide) load_a(s, 0);
+                f0.a[0] = frag_a(sn, 0, 0); f0.b[0] = frag_b(sn, 0, 0); ALCH_MM(f1, 0, 0); ALCH_MM(f1, 0, 1); ALCH_SB();
+                if (kWide && s % 2) { load_a(s + 3, 2); load_a(s + 3, 3); }
+                if (!kWide) load_a(s, 1);
+                f0.b[1] = frag_b(sn, 0, 1); f0.a[1] = frag_a(sn, 0, 1); ALCH_MM(f1, 1, 1); ALCH_MM(f1, 1, 0); ALCH_SB();
+                load_b(s, 0); load_b(s, 1);
+                f0.b[2] = frag_b(sn, 0, 2); f0.b[3] = frag_b(sn, 0, 3); ALCH_MM(f1, 1, 2); ALCH_MM(f1, 1, 3); ALCH_SB();
+                load_b(s, 2); load_b(s, 3);
+                ALCH_MM(f1, 0, 3); ALCH_MM(f1, 0, 2); ALCH_SB();
             }
         }
+    steps_done:
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #undef ALCH_SB
 #undef ALCH_MM
