@@ -89,9 +89,9 @@ __global__ __launch_bounds__(256) void k_lora_down(const T* __restrict__ X, long
 //
 // A problem = one streamed X [Trows, K] and up to four groups of eight columns of the output, each with its
 // own [rows <= 8, K] matrix S and its own destination (problems that share X are merged by the host: the t1
-// of q, k, v, or of gate and up, cost one pass).  A work-group owns 32 rows; its four wavefronts split K in
-// chunks of 64 and fold their sums through LDS in a fixed order.  Every wavefront runs a private ring of
-// stages [X 32 rows x 128 B | S 8 rows x 128 B per group]: no barrier inside the loop.  16-byte piece c of
+// of q, k, v, or of gate and up, cost one pass).  A work-group owns kRows rows (32, fewer in a short batch); its kWaves
+// wavefronts split K in chunks of 64 and fold their sums through LDS in a fixed order.  Every wavefront runs a private ring of
+// stages [X kRows rows x 128 B | S 8 rows x 128 B per group]: no barrier inside the loop.  16-byte piece c of
 // row r sits at position c ^ ((r >> 1) & 7) of the row, which makes the operand reads conflict-free.
 typedef __attribute__((ext_vector_type(16))) float f32x16_l;
 typedef __attribute__((ext_vector_type(4))) int i32x4_l;
@@ -109,9 +109,9 @@ struct LoraDownParams {
     __bf16* slot[3]; int slot_r[3]; int nslots;  // output slots: columns slot_r .. slot_cols-1 are zero-filled
     int Trows; long long ldy; float alpha; int slot_cols;
 };
-template <int kG> struct DownCfg {
-    static constexpr int kStageBytes = 4096 + kG * 1024;
-    static constexpr int kStages = kG == 1 ? 7 : kG == 2 ? 6 : kG == 3 ? 5 : 4;  // at most 36 KB per wavefront
+template <int kG, int kRows, int kWaves> struct DownCfg {
+    static constexpr int kStageBytes = kRows * 128 + kG * 1024;
+    static constexpr int kStages = 144 * 1024 / kWaves / kStageBytes < 2 ? 2 : 144 * 1024 / kWaves / kStageBytes;  // 36 KB per wavefront of four
 };
 __device__ __forceinline__ void lora_dma16(i32x4_l r, uint32_t lds_addr, uint32_t voff) {
     asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(r)
@@ -127,20 +127,23 @@ __device__ __forceinline__ i32x4_l lora_rsrc(const void* p, long long bytes) {
     r[3] = 0x00020000;
     return r;
 }
-template <int kG>
-__global__ __launch_bounds__(256) void k_lora_down_mfma(LoraDownParams p) {
-    constexpr int kStageBytes = DownCfg<kG>::kStageBytes, kStages = DownCfg<kG>::kStages;
-    __shared__ __attribute__((aligned(1024))) char smem[4 * kStages * kStageBytes];
-    __shared__ float red[3][64][17];
+template <int kG, int kRows, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void k_lora_down_mfma(LoraDownParams p) {
+    constexpr int kStageBytes = DownCfg<kG, kRows, kWaves>::kStageBytes, kStages = DownCfg<kG, kRows, kWaves>::kStages;
+    constexpr int kLoadsX = kRows / 8, kElems = kRows / 2;  // (accumulator elements whose row is one of kRows)
+    constexpr uint32_t kS = kRows * 128;  // S behind X in a stage
+    __shared__ __attribute__((aligned(1024))) char smem[kWaves * kStages * kStageBytes];
+    float (*red)[64][kElems + 1] = reinterpret_cast<float (*)[64][kElems + 1]>(smem);  // the stages have been read by then
+    static_assert(sizeof(float) * (kWaves - 1) * 64 * (kElems + 1) <= sizeof(smem), "");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 31, kh = lane >> 5;
-    const long long t0 = (long long)blockIdx.x * 32;
-    const int rows_valid = (int)(p.Trows - t0 < 32 ? p.Trows - t0 : 32);
+    const long long t0 = (long long)blockIdx.x * kRows;
+    const int rows_valid = (int)(p.Trows - t0 < kRows ? p.Trows - t0 : kRows);
     if (blockIdx.y == 0) {  // the columns past the rank of every output slot
         const int pieces = p.slot_cols >> 3;
         const bf16x8_l z = {(__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
         for (int sl = 0; sl < p.nslots; ++sl)
-            for (int idx = threadIdx.x; idx < 32 * pieces; idx += 256) {
+            for (int idx = threadIdx.x; idx < kRows * pieces; idx += kWaves * 64) {
                 const int row = idx / pieces, piece = idx % pieces;
                 if (row < rows_valid && piece * 8 >= p.slot_r[sl])
                     *reinterpret_cast<bf16x8_l*>(p.slot[sl] + (t0 + row) * p.ldy + piece * 8) = z;
@@ -149,14 +152,14 @@ __global__ __launch_bounds__(256) void k_lora_down_mfma(LoraDownParams p) {
     const LoraDownProblem& pb = p.pr[blockIdx.y];
     if (pb.ngroups == 0) return;
     const int nc = pb.K >> 6;
-    const int c_lo = wave * nc / 4, n = (wave + 1) * nc / 4 - c_lo;  // this wavefront's chunks of 64 k
+    const int c_lo = wave * nc / kWaves, n = (wave + 1) * nc / kWaves - c_lo;  // this wavefront's chunks of 64 k
     char* wbase = smem + wave * (kStages * kStageBytes);
     const uint32_t lds_w = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) void*)wbase);
     // per-lane source offsets of the loads: lane -> (row 8j + lane/8, piece (lane & 7) ^ swizzle of the LDS row)
     const int row8 = lane >> 3, q = lane & 7;
-    uint32_t voff_x[4], voff_s[kG];
+    uint32_t voff_x[kLoadsX], voff_s[kG];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < kLoadsX; ++j) {
         const int row = 8 * j + row8;
         voff_x[j] = (uint32_t)(row * pb.ldx * 2 + ((q ^ ((row >> 1) & 7)) << 4));
     }
@@ -169,32 +172,32 @@ __global__ __launch_bounds__(256) void k_lora_down_mfma(LoraDownParams p) {
         const bool live = i < n;
         const i32x4_l rx = lora_rsrc(xb + (long long)i * 64, live ? x_bytes : 0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) lora_dma16(rx, st + (uint32_t)j * 1024u, voff_x[j]);
+        for (int j = 0; j < kLoadsX; ++j) lora_dma16(rx, st + (uint32_t)j * 1024u, voff_x[j]);
 #pragma unroll
         for (int g = 0; g < kG; ++g) {
             const LoraDownGroup& gr = pb.g[g];
             const i32x4_l rs = lora_rsrc(gr.S + (long long)(c_lo + i) * 64,
                                          live && gr.rows > 0 ? ((long long)(gr.rows - 1) * gr.lds + 64) * 2 : 0);
-            lora_dma16(rs, st + 4096u + (uint32_t)g * 1024u, voff_s[g]);
+            lora_dma16(rs, st + kS + (uint32_t)g * 1024u, voff_s[g]);
         }
     };
     f32x16_l acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    // operand read offsets inside a stage: X row c, S row c (columns past the groups read a row that exists;
-    // their results are never stored)
-    const int cs = c < 8 * kG ? c : (c & 7);
+    // operand read offsets inside a stage: X row c, S row c (rows and columns past those of the stage read one that
+    // exists; their results are never stored)
+    const int cs = c < 8 * kG ? c : (c & 7), cx = c & (kRows - 1);
     uint32_t off_a[4], off_b[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        off_a[u] = (uint32_t)(c * 128 + (((2 * u + kh) ^ ((c >> 1) & 7)) << 4));
-        off_b[u] = (uint32_t)(4096 + cs * 128 + (((2 * u + kh) ^ ((cs >> 1) & 7)) << 4));
+        off_a[u] = (uint32_t)(cx * 128 + (((2 * u + kh) ^ ((cx >> 1) & 7)) << 4));
+        off_b[u] = (uint32_t)(kS + cs * 128 + (((2 * u + kh) ^ ((cs >> 1) & 7)) << 4));
     }
 #pragma unroll
     for (int s = 0; s < kStages - 1; ++s) issue(s);
     for (int i = 0; i < n; ++i) {
         issue(i + kStages - 1);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 1) * (4 + kG)) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 1) * (kLoadsX + kG)) : "memory");
         const char* st = wbase + (i % kStages) * kStageBytes;
         bf16x8_l a[4], b[4];
 #pragma unroll
@@ -206,9 +209,10 @@ __global__ __launch_bounds__(256) void k_lora_down_mfma(LoraDownParams p) {
         for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[u], acc, 0, 0, 0);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     if (wave > 0) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) red[wave - 1][lane][e] = acc[e];
+        for (int e = 0; e < kElems; ++e) red[wave - 1][lane][e] = acc[e];
     }
     __syncthreads();
     if (wave == 0) {
@@ -219,8 +223,10 @@ __global__ __launch_bounds__(256) void k_lora_down_mfma(LoraDownParams p) {
             if ((c >> 3) == g && g < pb.ngroups) { yp = pb.g[g].Y; yrows = pb.g[g].rows; }
         // accumulator element e: row 8*(e>>2) + 4*kh + (e&3), column c
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float v = ((acc[e] + red[0][lane][e]) + red[1][lane][e]) + red[2][lane][e];
+        for (int e = 0; e < kElems; ++e) {
+            float v = acc[e];
+#pragma unroll
+            for (int w = 0; w < kWaves - 1; ++w) v += red[w][lane][e];
             const int row = 8 * (e >> 2) + 4 * kh + (e & 3);
             if (row < rows_valid && (c & 7) < yrows) yp[(t0 + row) * p.ldy + (c & 7)] = (__bf16)(p.alpha * v);
         }
@@ -405,6 +411,15 @@ static int lora_down_valu(const LoraDown& j, int Trows, float alpha, long long l
     return ALCH_OK;
 }
 
+template <int kRows, int kWaves>
+static void launch_down(const LoraDownParams& p, int groups, int Trows, int problems, hipStream_t stream) {
+    const dim3 grid(ceil_div(Trows, kRows), std::max(problems, 1));
+    if (groups <= 1) k_lora_down_mfma<1, kRows, kWaves><<<grid, kWaves * 64, 0, stream>>>(p);
+    else if (groups == 2) k_lora_down_mfma<2, kRows, kWaves><<<grid, kWaves * 64, 0, stream>>>(p);
+    else if (groups == 3) k_lora_down_mfma<3, kRows, kWaves><<<grid, kWaves * 64, 0, stream>>>(p);
+    else k_lora_down_mfma<4, kRows, kWaves><<<grid, kWaves * 64, 0, stream>>>(p);
+}
+
 int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows, float alpha, long long ldy,
                      int slot_cols, hipStream_t stream) {
     if (n_jobs < 1 || n_jobs > 3) return fail(ALCH_ERR_INVALID_ARG, "adapter product: 1..3 problems per launch");
@@ -444,11 +459,16 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
         bytes = 0;
         for (int i = 0; i < np; ++i) bytes += (double)Trows * p.pr[i].K * dtype_size(dt);
         TraceScope ts(kTraceLora, flops, bytes, stream);
-        const dim3 grid(ceil_div(Trows, 32), std::max(np, 1));
-        if (most <= 1) k_lora_down_mfma<1><<<grid, 256, 0, stream>>>(p);
-        else if (most == 2) k_lora_down_mfma<2><<<grid, 256, 0, stream>>>(p);
-        else if (most == 3) k_lora_down_mfma<3><<<grid, 256, 0, stream>>>(p);
-        else k_lora_down_mfma<4><<<grid, 256, 0, stream>>>(p);
+        // Few rows leave compute units without a work-group, and a wavefront alone on its SIMD takes 0.37 us for a chunk (load,
+        // read, four dependent products, one after the other): work-groups of fewer rows and more wavefronts, as long as
+        // each finds a compute unit.  8B shape, us a launch of 32 rows by 4 / 16 rows by 8 / 8 rows by 16 wavefronts: 200
+        // tokens, K 14336 21.5 / 13.6 / 10.2, K 4096 10.3 / 7.4 / 6.2; 900 tokens, two of K 14336 23.4 / 17.9 / 14.8; 2000
+        // tokens, one 29.2 / 22.4 / 17.3 and two (500 work-groups of 8 rows) 34.7 / 25.2 / 30.6; 5120 tokens 40.9 / 46.3 / 44.0.
+        int n_cu = 0;
+        ALCH_TRY(compute_units(&n_cu));
+        if (ceil_div(Trows, 8) * np <= n_cu) launch_down<8, 16>(p, most, Trows, np, stream);
+        else if (ceil_div(Trows, 16) * np <= n_cu) launch_down<16, 8>(p, most, Trows, np, stream);
+        else launch_down<32, 4>(p, most, Trows, np, stream);
     } else {
         TraceScope ts(kTraceLora, flops, bytes, stream);
         for (int i = 0; i < n_jobs; ++i) {
