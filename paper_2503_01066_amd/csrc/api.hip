@@ -122,6 +122,7 @@ struct LayerBwdPlan {
     void *Ap_d = nullptr, *Ap_gu = nullptr, *Ap_o = nullptr, *Ap_qkv = nullptr;  // [64,F] [128,H] [64,QD] [192,H]
     void* Bt[ALCH_N_PROJ] = {};                                                  // B_p transposed: [rank, out_p]
     float* up_scratch = nullptr;
+    size_t up_scratch_bytes = 0;
     void* gemm_ws = nullptr;  // fp32 partial tiles of a weight-gradient product whose last round of tiles is split
     size_t bytes;
 };
@@ -166,7 +167,8 @@ static LayerBwdPlan plan_layer_bwd(const alch_layer_shape& s, int T, void* ws, s
         // the widest group of adapter gradients formed by one launch: gate + up (dA on H twice, dB on F twice) or
         // q + k + v (dA on H three times, dB on QD + 2 KD)
         const size_t n_sum = std::max(2 * (H + F), std::max(3 * H + QD + 2 * KD, std::max(F + H, QD + H)));
-        p.up_scratch = static_cast<float*>(a.take(lora_up_scratch_bytes(lora_rank, (int)n_sum)));
+        p.up_scratch_bytes = lora_up_scratch_bytes(lora_rank, (int)n_sum);
+        p.up_scratch = static_cast<float*>(a.take(p.up_scratch_bytes));
     }
     p.bytes = round_up(a.used, 256);
     return p;
@@ -387,6 +389,10 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
             if (has(pj)) pp.job[nj++] = LoraPrepJob{lo->B[pj], p.Bt[pj], r, outs[pj], r, 1};
         ALCH_TRY(launch_lora_prep(dt, pp, nj, st));
     }
+    LoraUpSums adapter_sums;
+    adapter_sums.p.Trows = T; adapter_sums.p.r = r; adapter_sums.p.alpha = 1.f; adapter_sums.p.accumulate = lacc;
+    adapter_sums.p.scratch = p.up_scratch;
+    adapter_sums.capacity = (long long)(p.up_scratch_bytes / sizeof(float));
     // Adapter gradients of the n <= 3 projections pj0, pj0+1, .. that share the input x [T, in_p]; dy[i] [T, out_p[i]]
     // with row stride lddy; t2 of projection pj0+i sits in slot i.  One launch forms the t1 of all of them, one pair
     // of launches all their dA and dB.
@@ -407,7 +413,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
             if (lg->dA[pj]) uj[nu++] = LoraUp{at(p.T2, (size_t)i * kLoraSlot, E), ldt2, x, ldx, in_p, lg->dA[pj], in_p, 0};
         }
         if (nd) ALCH_TRY(launch_lora_down(dt, dj, nd, T, lo->scale, ldt1, kLoraSlot, st));
-        if (nu) ALCH_TRY(launch_lora_up(dt, uj, nu, T, r, 1.f, lacc, p.up_scratch, st));
+        if (nu) ALCH_TRY(launch_lora_up(dt, uj, nu, adapter_sums, st));
         return ALCH_OK;
     };
 
@@ -606,6 +612,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         const int outs3[3] = {QD, KD, KD};
         ALCH_TRY(adapter_grads(ALCH_PROJ_Q, 3, p.Hn, H, H, dys, QKV, outs3));
     }
+    ALCH_TRY(launch_lora_up_sums(dt, adapter_sums, st));
     if (g.dWq || g.dWk || g.dWv) {  // dW{q,k,v} = d{Q,K,V}^T H1
         if (g.dWq && g.dWk && g.dWv && QD % 256 == 0 && KD % 256 == 0) {
             GemmDesc d = gemm_ws(dt, QKV, H, false, false);

@@ -122,7 +122,7 @@ struct LoraDown {
 int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows, float alpha, long long ldy,
                      int slot_cols, hipStream_t stream);
 // C(j, n) (+)= alpha * sum_t S[t*lds + j] * X[t*ldx + n], j < r, n < N; stored C[j*ldc + n], or C[n*ldc + j]
-// when transposed.  Up to kLoraUpJobs problems per launch pair, all with Trows rows, the same r, alpha and
+// when transposed.  Up to kLoraUpJobs problems per launch, all with Trows rows, the same r, alpha and
 // accumulate.  scratch: lora_up_scratch_bytes(r, sum of the N of the jobs) bytes of fp32 partial sums.
 static constexpr int kLoraUpJobs = 6;
 struct LoraUp {
@@ -133,8 +133,30 @@ struct LoraUp {
     int transposed;
 };
 size_t lora_up_scratch_bytes(int rank, int n_sum);
-int launch_lora_up(alch_dtype dt, const LoraUp* jobs, int n_jobs, int Trows, int r, float alpha, int accumulate,
-                   float* scratch, hipStream_t stream);
+// The sums over the splits of several such launches may be left to one launch: LoraUpSums holds them until
+// launch_lora_up_sums.  launch_lora_up makes room first where the scratch, or the list, would not take its problems.
+struct LoraUpJob {
+    const void* S; long long lds;
+    const void* X; long long ldx;
+    int N, nsplit, rows_per_split;
+    void* C; long long ldc;
+    int transposed;
+    int first_group;        // work-groups of the jobs before this one in the launch that adds the splits
+    long long scratch_off;  // floats
+};
+static constexpr int kLoraUpSums = 14;  // A and B of seven projections
+struct LoraUpParams {
+    LoraUpJob job[kLoraUpSums];
+    int n_jobs, Trows, r, accumulate;
+    float alpha;
+    float* scratch;
+};
+struct LoraUpSums {
+    LoraUpParams p = {};
+    long long floats = 0, capacity = 0;  // of the scratch: taken, all
+};
+int launch_lora_up(alch_dtype dt, const LoraUp* jobs, int n_jobs, LoraUpSums& sums, hipStream_t stream);
+int launch_lora_up_sums(alch_dtype dt, LoraUpSums& sums, hipStream_t stream);
 // Operand preparation: job i writes dst [rows_out, cols] = src [r, cols] (or, transpose, src [cols, r]
 // transposed) followed by zero rows; src null: all zeros.
 struct LoraPrepJob {

@@ -276,28 +276,13 @@ __device__ __forceinline__ void up_step(const __bf16* xr, const __bf16* sr, long
 template <typename T> struct UpStep { static constexpr int kTokens = 1; };
 template <> struct UpStep<__bf16> { static constexpr int kTokens = 2; };
 
-struct LoraUpJob {
-    const void* S; long long lds;
-    const void* X; long long ldx;
-    int N, nsplit, rows_per_split;
-    void* C; long long ldc;
-    int transposed;
-    long long scratch_off;  // floats
-};
-struct LoraUpParams {
-    LoraUpJob job[kLoraUpJobs];
-    int Trows, r, accumulate;
-    float alpha;
-    float* scratch;
-};
-
-// blockIdx.z = job * (r / 8) + chunk of eight rank rows; work-groups beyond a job's column slabs or row splits exit
+// blockIdx.z = (job - first) * (r / 8) + chunk of eight rank rows; work-groups beyond a job's column slabs or row splits exit
 template <typename T>
-__global__ __launch_bounds__(256) void k_lora_up_partial(LoraUpParams p) {
+__global__ __launch_bounds__(256) void k_lora_up_partial(LoraUpParams p, int first) {
     __shared__ float red[3][64][65];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int chunks = p.r >> 3;
-    const LoraUpJob jb = p.job[blockIdx.z / chunks];
+    const LoraUpJob jb = p.job[first + blockIdx.z / chunks];
     const int jc = blockIdx.z % chunks;
     const int N = jb.N, nsplit = jb.nsplit, split = blockIdx.y;
     if ((int)blockIdx.x * 512 >= N || split >= nsplit) return;
@@ -344,33 +329,38 @@ __global__ __launch_bounds__(256) void k_lora_up_partial(LoraUpParams p) {
 }
 
 // ---- up, pass 2: C(j, n) (+)= alpha * sum over splits, written as C[j*ldc + n] or transposed C[n*ldc + j].
-// Eight lanes share one output: lane q adds splits q, q+8, ... and the eight sums are folded in a fixed order.
+// Eight lanes share four neighbouring outputs: lane q adds splits q, q+8, ... and the eight sums are folded in a fixed order.
+// The sums of all adapters of a layer are one launch (with one for every group of projections, of single outputs, a layer
+// of 900 tokens spent 32 us in four of them).
+static constexpr int kSumsPerGroup = 128;  // outputs of a work-group
 template <typename T>
 __global__ __launch_bounds__(256) void k_lora_up_finish(LoraUpParams p) {
-    const LoraUpJob jb = p.job[blockIdx.y];
-    const int N = jb.N, nsplit = jb.nsplit, r = p.r, transposed = jb.transposed, accumulate = p.accumulate;
-    const float alpha = p.alpha;
-    const float* __restrict__ partial = p.scratch + jb.scratch_off;
-    T* __restrict__ C = static_cast<T*>(jb.C);
-    const long long ldc = jb.ldc;
-    const long long idx = ((long long)blockIdx.x * 256 + threadIdx.x) >> 3;
+    int at = 0;
+    for (int i = 1; i < p.n_jobs; ++i)
+        if ((int)blockIdx.x >= p.job[i].first_group) at = i;
+    const LoraUpJob jb = p.job[at];
+    const int N = jb.N, nsplit = jb.nsplit;
+    const long long idx = (long long)((int)blockIdx.x - jb.first_group) * kSumsPerGroup + (threadIdx.x >> 3) * 4;
     const int q = threadIdx.x & 7;
-    const bool live = idx < (long long)N * r;
-    // consecutive outputs walk n: the partial sums are read in order (C itself is small)
+    const bool live = idx < (long long)N * p.r;
+    // consecutive outputs walk n: the partial sums are read in order (C itself is small; N is a multiple of 8)
     const int jj = !live ? 0 : (int)(idx / N);
     const int n = !live ? 0 : (int)(idx % N);
-    const float* src = partial + ((long long)(jj >> 3) * nsplit * 8 + (jj & 7)) * N + n;
-    float s = 0.f;
+    const float* src = p.scratch + jb.scratch_off + ((long long)(jj >> 3) * nsplit * 8 + (jj & 7)) * N + n;
+    f32x4_l s = {0.f, 0.f, 0.f, 0.f};
     if (live)
-        for (int k = q; k < nsplit; k += 8) s += src[(long long)k * 8 * N];
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    s += __shfl_xor(s, 4, 64);
-    if (live && q == 0) {
-        T* dst = transposed ? C + (long long)n * ldc + jj : C + (long long)jj * ldc + n;
-        s *= alpha;
-        if (accumulate) s += (float)*dst;
-        *dst = (T)s;
+        for (int k = q; k < nsplit; k += 8) s += *reinterpret_cast<const f32x4_l*>(src + (long long)k * 8 * N);
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += __shfl_xor(s[e], d, 64);
+    if (live && q < 4) {  // lane e writes output e
+        const float v = q == 0 ? s[0] : q == 1 ? s[1] : q == 2 ? s[2] : s[3];
+        T* C = static_cast<T*>(jb.C);
+        T* dst = jb.transposed ? C + (long long)(n + q) * jb.ldc + jj : C + (long long)jj * jb.ldc + n + q;
+        float o = v * p.alpha;
+        if (p.accumulate) o += (float)*dst;
+        *dst = (T)o;
     }
 }
 
@@ -480,39 +470,57 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
     return ALCH_OK;
 }
 
-int launch_lora_up(alch_dtype dt, const LoraUp* jobs, int n_jobs, int Trows, int r, float alpha, int accumulate,
-                   float* scratch, hipStream_t stream) {
+int launch_lora_up(alch_dtype dt, const LoraUp* jobs, int n_jobs, LoraUpSums& sums, hipStream_t stream) {
+    LoraUpParams& p = sums.p;
+    const int r = p.r, Trows = p.Trows;
     if (n_jobs < 1 || n_jobs > kLoraUpJobs) return fail(ALCH_ERR_INVALID_ARG, "adapter gradient: 1..%d problems per launch", kLoraUpJobs);
     if (r % 8 || r <= 0) return fail(ALCH_ERR_UNSUPPORTED, "adapter gradient: rank must be a positive multiple of 8");
-    LoraUpParams p;
-    p.Trows = Trows; p.r = r; p.accumulate = accumulate; p.alpha = alpha; p.scratch = scratch;
-    double flops = 0, bytes = 0;
-    long long off = 0;
-    int max_slabs = 1, max_split = 0, max_n = 1;
-    for (int i = 0; i < kLoraUpJobs; ++i) {
-        const LoraUp& j = jobs[i < n_jobs ? i : 0];
-        if (i < n_jobs && (j.N % 8 || j.ldx % 8 || j.lds % 8))
+    long long need = 0;
+    for (int i = 0; i < n_jobs; ++i) {
+        const LoraUp& j = jobs[i];
+        if (j.N % 8 || j.ldx % 8 || j.lds % 8)
             return fail(ALCH_ERR_UNSUPPORTED, "adapter gradient: widths and strides must be multiples of 8");
+        need += (long long)r * (Trows > 0 ? up_splits(Trows, j.N) : 0) * j.N;
+    }
+    if (p.n_jobs + n_jobs > kLoraUpSums || sums.floats + need > sums.capacity) ALCH_TRY(launch_lora_up_sums(dt, sums, stream));
+    double flops = 0, bytes = 0;
+    int max_slabs = 1, max_split = 0;
+    const int first = p.n_jobs;
+    for (int i = 0; i < n_jobs; ++i) {
+        const LoraUp& j = jobs[i];
         const int nsplit = Trows > 0 ? up_splits(Trows, j.N) : 0;
-        p.job[i] = LoraUpJob{j.S, j.lds, j.X, j.ldx, j.N, nsplit, nsplit > 0 ? ceil_div(Trows, nsplit) : 0, j.C, j.ldc, j.transposed, off};
-        if (i < n_jobs) {
-            off += (long long)(r / 8) * kLoraMaxSplits * 8 * j.N;  // the job's share of the scratch
-            flops += 2.0 * Trows * j.N * r;
-            bytes += (double)Trows * j.N * dtype_size(dt);
-            max_slabs = std::max(max_slabs, ceil_div(j.N, 512));
-            max_split = std::max(max_split, nsplit);
-            max_n = std::max(max_n, j.N);
-        }
+        const LoraUpJob* before = p.n_jobs > 0 ? &p.job[p.n_jobs - 1] : nullptr;
+        const int first_group = before ? before->first_group + ceil_div((long long)before->N * r, (long long)kSumsPerGroup) : 0;
+        p.job[p.n_jobs++] = LoraUpJob{j.S, j.lds, j.X, j.ldx, j.N, nsplit, nsplit > 0 ? ceil_div(Trows, nsplit) : 0, j.C, j.ldc,
+                                      j.transposed, first_group, sums.floats};
+        sums.floats += (long long)r * nsplit * j.N;
+        flops += 2.0 * Trows * j.N * r;
+        bytes += (double)Trows * j.N * dtype_size(dt);
+        max_slabs = std::max(max_slabs, ceil_div(j.N, 512));
+        max_split = std::max(max_split, nsplit);
     }
     TraceScope ts(kTraceLora, flops, bytes, stream);
-    const dim3 grid_f(ceil_div((long long)max_n * r * 8, 256LL), n_jobs);
-    if (dt == ALCH_BF16) {
-        if (max_split > 0) k_lora_up_partial<__bf16><<<dim3(max_slabs, max_split, n_jobs * (r / 8)), 256, 0, stream>>>(p);
-        k_lora_up_finish<__bf16><<<grid_f, 256, 0, stream>>>(p);
-    } else {
-        if (max_split > 0) k_lora_up_partial<float><<<dim3(max_slabs, max_split, n_jobs * (r / 8)), 256, 0, stream>>>(p);
-        k_lora_up_finish<float><<<grid_f, 256, 0, stream>>>(p);
+    const dim3 grid(max_slabs, max_split, n_jobs * (r / 8));
+    if (max_split > 0) {
+        if (dt == ALCH_BF16) k_lora_up_partial<__bf16><<<grid, 256, 0, stream>>>(p, first);
+        else k_lora_up_partial<float><<<grid, 256, 0, stream>>>(p, first);
     }
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
+}
+
+int launch_lora_up_sums(alch_dtype dt, LoraUpSums& sums, hipStream_t stream) {
+    LoraUpParams& p = sums.p;
+    if (p.n_jobs == 0) return ALCH_OK;
+    const LoraUpJob& last = p.job[p.n_jobs - 1];
+    const int groups = last.first_group + ceil_div((long long)last.N * p.r, (long long)kSumsPerGroup);
+    {
+        TraceScope ts(kTraceLora, 0.0, 0.0, stream);
+        if (dt == ALCH_BF16) k_lora_up_finish<__bf16><<<groups, 256, 0, stream>>>(p);
+        else k_lora_up_finish<float><<<groups, 256, 0, stream>>>(p);
+    }
+    p.n_jobs = 0;
+    sums.floats = 0;
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
