@@ -502,10 +502,14 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     ALCH_TRY(dwd_beside ? launch_gemm_together(dH2, dWd, st) : launch_gemm(dH2, st));
     // dX2 = dY + RMSNorm-2 backward(dH2); dg2.  The same pass over X2 leaves H2 for the weight and adapter gradients
     // of the gate and up projections (unless the record completion above already formed it).
+    // Act has had its last reader: where it has the room, it keeps the partial rows of dg2 until those of dg1 are there too.
+    const bool gains_together = (size_t)T * F * E >= (size_t)rmsnorm_bwd_blocks(T) * H * sizeof(float);
+    GainSums gains;
     {
         const bool need_h2 = !hn_ready && (g.dWg || g.dWu || wants(ALCH_PROJ_G) || wants(ALCH_PROJ_U));
-        ALCH_TRY(launch_rmsnorm_bwd(dt, p.dHn, mX2, w.g2, mY, nullptr, mdX2, g.dg2, acc, p.partial, T, H, s.rms_eps, st, ndev,
-                                    need_h2 ? p.Hn : nullptr));
+        ALCH_TRY(launch_rmsnorm_bwd(dt, p.dHn, mX2, w.g2, mY, nullptr, mdX2, g.dg2, acc,
+                                    gains_together ? static_cast<float*>(p.Act) : p.partial, T, H, s.rms_eps, st, ndev,
+                                    need_h2 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
     }
     {
         const void* dys[2] = {p.dGU, at(p.dGU, F, E)};
@@ -605,7 +609,8 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     {
         const bool need_h1 = g.dWq || g.dWk || g.dWv || wants(ALCH_PROJ_Q) || wants(ALCH_PROJ_K) || wants(ALCH_PROJ_V);
         ALCH_TRY(launch_rmsnorm_bwd(dt, p.dHn, sv.X, w.g1, p.dX2, nullptr, dX, g.dg1, acc, p.partial, T, H, s.rms_eps, st, nullptr,
-                                    need_h1 ? p.Hn : nullptr));
+                                    need_h1 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
+        if (gains_together) ALCH_TRY(launch_gain_sums(dt, gains, H, acc, st));
     }
     {
         const void* dys[3] = {p.dQKV, at(p.dQKV, QD, E), at(p.dQKV, QD + KD, E)};
@@ -1242,8 +1247,7 @@ static int layer_forward_impl(const alch_layer_shape* shape, const alch_batch* b
         add_seg(d, p.Hn, H, Ws[0], H, H);
         ALCH_TRY(launch_gemm(d, st));
     }
-    ALCH_TRY(launch_rope(dt, rQ, QD, T, s.n_q_heads, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, st));
-    ALCH_TRY(launch_rope(dt, rK, KD, T, s.n_kv_heads, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, st));
+    ALCH_TRY(launch_rope(dt, rQ, s.n_q_heads, rK, s.n_kv_heads, T, D, pos, batch->cu_seqlens, batch->n_seqs, s.rope_base, st));
     // attention indexes whole-batch rows: the keys and values of a prefix sequence lie before r0
     ALCH_TRY(launch_attn_fwd(dt, rec->Q, rec->K, rec->V, rec->O, rec->LSE, batch->total_tokens, batch->n_seqs,
                              batch->max_seqlen, batch->cu_seqlens, batch->cu_seqlens_host, batch->seq_prefix,

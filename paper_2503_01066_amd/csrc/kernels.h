@@ -92,17 +92,25 @@ int launch_rmsnorm_fwd(alch_dtype dt, const void* X, const void* g, void* H, int
 // hn_out (may be NULL): also writes the normalised rows X*r*g themselves, the operand of the weight gradients
 // that follow, so that X is read once for both.
 int rmsnorm_bwd_blocks(int T);
+// sums (may be NULL): dg is left to a later launch_gain_sums, which adds the partial rows of up to two such calls at once;
+// `partial` of the first has to stay until then.
+struct GainSums {
+    struct { const float* partial; void* dg; int rows; } of[2];
+    int n = 0;
+};
+int launch_gain_sums(alch_dtype dt, const GainSums& sums, int width, int accumulate, hipStream_t stream);
 int launch_rmsnorm_bwd(alch_dtype dt, const void* dH, const void* X, const void* g, const void* resid,
                        const uint8_t* resid_mask, void* dX, void* dg, int accumulate, float* partial, int T,
-                       int width, float eps, hipStream_t stream, const int* rows_dev = nullptr, void* hn_out = nullptr);
+                       int width, float eps, hipStream_t stream, const int* rows_dev = nullptr, void* hn_out = nullptr,
+                       GainSums* sums = nullptr);
 // inv[t] = rank of token t among the first *n_rows entries of index (the kept tokens), -1 if absent
 int launch_rank_of_kept(const int* index, const int* n_rows, int* inv, int T, hipStream_t stream);
 // out [T, row_bytes] = src[inv[t], :] where inv[t] >= 0, zeros elsewhere
 int launch_scatter_rows(const void* src, const int* inv, void* out, int T, size_t row_bytes, hipStream_t stream);
 // Act = silu(G) * U
 int launch_swiglu_act(alch_dtype dt, const void* G, const void* U, void* Act, long long n, hipStream_t stream);
-// In-place rotary rotation of x [T, n_heads, D] (row stride ld elements).
-int launch_rope(alch_dtype dt, void* x, long long ld, int T, int n_heads, int D, const int* positions,
+// In-place rotary rotation of q [T, n_q, D] and k [T, n_kv, D].
+int launch_rope(alch_dtype dt, void* q, int n_q, void* k, int n_kv, int T, int D, const int* positions,
                 const int* cu_seqlens, int n_seqs, float base, hipStream_t stream);
 // out = a with rows zeroed where mask == 0 (mask may be NULL: plain copy)
 int launch_masked_copy(alch_dtype dt, const void* a, const uint8_t* mask, void* out, int T, int width,

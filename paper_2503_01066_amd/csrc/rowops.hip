@@ -271,11 +271,14 @@ __global__ __launch_bounds__(256) void k_rmsnorm_bwd_bf16(const __bf16* __restri
         }
 }
 
-// dg[c] (+)= sum over nblk partial rows; 64 columns per block, 16 row groups folded through LDS
+// dg[c] (+)= sum over nblk partial rows; 64 columns per block, 16 row groups folded through LDS.  blockIdx.y: which of the
+// gains (a layer's two in one launch: 5 us less of a backward).
 template <typename T>
-__global__ __launch_bounds__(1024) void k_colsum_finish_wide(const float* __restrict__ partial, int nblk, int width,
-                                                             T* __restrict__ dg, int accumulate) {
+__global__ __launch_bounds__(1024) void k_colsum_finish_wide(GainSums sums, int width, int accumulate) {
     __shared__ float red[16][64];
+    const float* __restrict__ partial = sums.of[blockIdx.y].partial;
+    T* __restrict__ dg = static_cast<T*>(sums.of[blockIdx.y].dg);
+    const int nblk = sums.of[blockIdx.y].rows;
     const int c = blockIdx.x * 64 + (threadIdx.x & 63), rg = threadIdx.x >> 6;
     float s = 0.f;
     if (c < width) {
@@ -302,6 +305,15 @@ __global__ __launch_bounds__(1024) void k_colsum_finish_wide(const float* __rest
     }
 }
 
+int launch_gain_sums(alch_dtype dt, const GainSums& sums, int width, int accumulate, hipStream_t stream) {
+    if (sums.n == 0) return ALCH_OK;
+    const dim3 grid(ceil_div(width, 64), sums.n);
+    if (dt == ALCH_BF16) k_colsum_finish_wide<__bf16><<<grid, 1024, 0, stream>>>(sums, width, accumulate);
+    else k_colsum_finish_wide<float><<<grid, 1024, 0, stream>>>(sums, width, accumulate);
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
+}
+
 int rmsnorm_bwd_blocks(int T) {
     const int n = T < kNormBwdBlocks ? (T > 0 ? T : 1) : kNormBwdBlocks;
     return n > kNormFastBlocks ? n : kNormFastBlocks;  // scratch rows: enough for either kernel
@@ -309,12 +321,10 @@ int rmsnorm_bwd_blocks(int T) {
 
 template <typename T>
 static int rmsnorm_bwd_t(const void* dH, const void* X, const void* g, const void* resid, const uint8_t* resid_mask,
-                         void* dX, void* dg, int accumulate, float* partial, int T_, int width, float eps,
-                         hipStream_t stream, void* hn_out) {
-    const int nblk = T_ < kNormBwdBlocks ? T_ : kNormBwdBlocks;
+                         void* dX, float* partial, int T_, int width, float eps, hipStream_t stream, void* hn_out, int& nblk) {
+    nblk = T_ < kNormBwdBlocks ? T_ : kNormBwdBlocks;
     k_rmsnorm_bwd<T><<<nblk, 256, 0, stream>>>((const T*)dH, (const T*)X, (const T*)g, (const T*)resid, resid_mask,
-                                                (T*)dX, dg ? partial : nullptr, T_, width, eps, (T*)hn_out);
-    if (dg) k_colsum_finish_wide<T><<<ceil_div(width, 64), 1024, 0, stream>>>(partial, nblk, width, (T*)dg, accumulate);
+                                                (T*)dX, partial, T_, width, eps, (T*)hn_out);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
@@ -429,13 +439,12 @@ __global__ __launch_bounds__(256) void k_rmsnorm_bwd_bf16_split(const __bf16* __
 }
 
 static int rmsnorm_bwd_bf16_fast(const void* dH, const void* X, const void* g, const void* resid,
-                                 const uint8_t* resid_mask, void* dX, void* dg, int accumulate, float* partial, int T_,
-                                 int width, float eps, hipStream_t stream, const int* rows_dev, void* hn_out) {
+                                 const uint8_t* resid_mask, void* dX, float* part, int T_,
+                                 int width, float eps, hipStream_t stream, const int* rows_dev, void* hn_out, int& nblk) {
     // A work-group takes 4, 2 or 1 rows at a time.  Four rows each, but fewer where that leaves compute units without one
     // (487 rows of 4096: 122 work-groups 11 us, 244 of them 9 us).
     const int rows_at_once = width <= 2048 ? 4 : width <= 4096 ? 2 : 1;
-    const int nblk = std::max(std::min(ceil_div(T_, rows_at_once), kNormFastBlocks / 2), std::min(ceil_div(T_, 4), kNormFastBlocks));
-    float* part = dg ? partial : nullptr;
+    nblk = std::max(std::min(ceil_div(T_, rows_at_once), kNormFastBlocks / 2), std::min(ceil_div(T_, 4), kNormFastBlocks));
 #define ALCH_NORM_BWD(NC)                                                                                          \
     k_rmsnorm_bwd_bf16<NC><<<nblk, 256, 0, stream>>>((const __bf16*)dH, (const __bf16*)X, (const __bf16*)g,         \
                                                      (const __bf16*)resid, resid_mask, (__bf16*)dX, part, T_, width, eps, rows_dev, (__bf16*)hn_out)
@@ -448,33 +457,30 @@ static int rmsnorm_bwd_bf16_fast(const void* dH, const void* X, const void* g, c
     else ALCH_NORM_BWD_SPLIT(4);
 #undef ALCH_NORM_BWD
 #undef ALCH_NORM_BWD_SPLIT
-    if (dg) k_colsum_finish_wide<__bf16><<<ceil_div(width, 64), 1024, 0, stream>>>(partial, nblk, width, (__bf16*)dg, accumulate);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
 
 int launch_rmsnorm_bwd(alch_dtype dt, const void* dH, const void* X, const void* g, const void* resid,
                        const uint8_t* resid_mask, void* dX, void* dg, int accumulate, float* partial, int T,
-                       int width, float eps, hipStream_t stream, const int* rows_dev, void* hn_out) {
+                       int width, float eps, hipStream_t stream, const int* rows_dev, void* hn_out, GainSums* sums) {
     if (width > 256 * kNormMaxCols) return fail(ALCH_ERR_UNSUPPORTED, "hidden %d > %d", width, 256 * kNormMaxCols);
-    if (T <= 0) {
-        // no rows: the gain gradient is zero (or unchanged when accumulating)
-        if (dg) {
-            if (dt == ALCH_BF16)
-                k_colsum_finish_wide<__bf16><<<ceil_div(width, 64), 1024, 0, stream>>>(partial, 0, width, (__bf16*)dg, accumulate);
-            else
-                k_colsum_finish_wide<float><<<ceil_div(width, 64), 1024, 0, stream>>>(partial, 0, width, (float*)dg, accumulate);
-            ALCH_HIP_TRY(hipGetLastError());
-        }
-        return ALCH_OK;
+    int nblk = 0;  // (no rows: the gain gradient is zero, or unchanged when accumulating)
+    float* part = dg ? partial : nullptr;
+    if (T > 0) {
+        if (dt == ALCH_BF16 && width % 8 == 0 && aligned16(dH) && aligned16(X) && aligned16(g) && aligned16(dX) &&
+            (!resid || aligned16(resid)) && (!hn_out || (aligned16(hn_out) && hn_out != dX)))
+            ALCH_TRY(rmsnorm_bwd_bf16_fast(dH, X, g, resid, resid_mask, dX, part, T, width, eps, stream, rows_dev, hn_out, nblk));
+        else if (rows_dev) return fail(ALCH_ERR_UNSUPPORTED, "device-side row count needs the bf16 row kernel");
+        else if (dt == ALCH_BF16) ALCH_TRY(rmsnorm_bwd_t<__bf16>(dH, X, g, resid, resid_mask, dX, part, T, width, eps, stream, hn_out, nblk));
+        else ALCH_TRY(rmsnorm_bwd_t<float>(dH, X, g, resid, resid_mask, dX, part, T, width, eps, stream, hn_out, nblk));
     }
-    if (dt == ALCH_BF16 && width % 8 == 0 && aligned16(dH) && aligned16(X) && aligned16(g) && aligned16(dX) &&
-        (!resid || aligned16(resid)) && (!hn_out || (aligned16(hn_out) && hn_out != dX)))
-        return rmsnorm_bwd_bf16_fast(dH, X, g, resid, resid_mask, dX, dg, accumulate, partial, T, width, eps, stream, rows_dev, hn_out);
-    if (rows_dev) return fail(ALCH_ERR_UNSUPPORTED, "device-side row count needs the bf16 row kernel");
-    return dt == ALCH_BF16
-               ? rmsnorm_bwd_t<__bf16>(dH, X, g, resid, resid_mask, dX, dg, accumulate, partial, T, width, eps, stream, hn_out)
-               : rmsnorm_bwd_t<float>(dH, X, g, resid, resid_mask, dX, dg, accumulate, partial, T, width, eps, stream, hn_out);
+    if (!dg) return ALCH_OK;
+    GainSums own, &to = sums ? *sums : own;
+    to.of[to.n].partial = partial;
+    to.of[to.n].dg = dg;
+    to.of[to.n++].rows = nblk;
+    return sums ? ALCH_OK : launch_gain_sums(dt, own, width, accumulate, stream);
 }
 
 // ---- SwiGLU
@@ -557,7 +563,7 @@ __global__ __launch_bounds__(256) void k_rope(T* __restrict__ x, long long ld, i
 // bf16, head_dim a multiple of 16: a thread owns 8 consecutive pairs of one token, computes their sines and
 // cosines once and applies them to every kHeadLanes-th head (all heads of a token share the angles).
 static constexpr int kHeadLanes = 8;
-__global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ x, long long ld, int Trows, int n_heads, int D,
+__global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ q, int n_q, __bf16* __restrict__ k, int n_kv, int Trows, int D,
                                                      const int* __restrict__ positions, const int* __restrict__ cu_seqlens,
                                                      int n_seqs, float log2_base) {
     const int half = D >> 1, kc = half >> 3;  // 8-pair chunks per head
@@ -567,7 +573,7 @@ __global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ x, lon
         const long long t = i / per_tok;
         const int rem = (int)(i - t * per_tok);
         const int hl = rem / kc, k0 = (rem - hl * kc) * 8;
-        if (hl >= n_heads) continue;
+        if (hl >= n_q + n_kv) continue;
         int pos;
         if (positions) {
             pos = positions[t];
@@ -585,8 +591,8 @@ __global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ x, lon
             const float theta = exp2f(-2.f * (float)(k0 + e) / (float)D * log2_base);
             sincosf((float)pos * theta, &sn[e], &cs[e]);
         }
-        for (int h = hl; h < n_heads; h += kHeadLanes) {
-            __bf16* p = x + t * ld + (long long)h * D + k0;
+        for (int h = hl; h < n_q + n_kv; h += kHeadLanes) {
+            __bf16* p = (h < n_q ? q + (t * n_q + h) * (long long)D : k + (t * n_kv + (h - n_q)) * (long long)D) + k0;
             const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(p), b = *reinterpret_cast<const bf16x8_t*>(p + half);
             bf16x8_t ra, rb;
 #pragma unroll
@@ -601,23 +607,30 @@ __global__ __launch_bounds__(256) void k_rope_bf16x8(__bf16* __restrict__ x, lon
     }
 }
 
-int launch_rope(alch_dtype dt, void* x, long long ld, int T, int n_heads, int D, const int* positions,
+template <typename T>
+static void rope_one(void* x, int T_, int n_heads, int D, const int* positions, const int* cu_seqlens, int n_seqs, float l2, hipStream_t stream) {
+    const long long n = (long long)T_ * n_heads * (D / 2);
+    if (n <= 0) return;
+    const int grid = (int)((n + 255) / 256 < 256 * 16 ? (n + 255) / 256 : 256 * 16);
+    k_rope<T><<<grid, 256, 0, stream>>>((T*)x, (long long)n_heads * D, T_, n_heads, D, positions, cu_seqlens, n_seqs, l2);
+}
+
+int launch_rope(alch_dtype dt, void* q, int n_q, void* k, int n_kv, int T, int D, const int* positions,
                 const int* cu_seqlens, int n_seqs, float base, hipStream_t stream) {
-    const long long n = (long long)T * n_heads * (D / 2);
-    if (n <= 0) return ALCH_OK;
-    if (dt == ALCH_BF16 && D % 16 == 0 && ld % 8 == 0 && aligned16(x)) {
+    if (T <= 0) return ALCH_OK;
+    const float l2 = log2f(base);
+    if (dt == ALCH_BF16 && D % 16 == 0 && aligned16(q) && aligned16(k)) {
+        // (q and k turn by the same angles: 5003 tokens 17.8 and 8.8 us on their own)
         const long long nt = (long long)T * (D / 16) * kHeadLanes;
         const int g = (int)((nt + 255) / 256 < 256 * 32 ? (nt + 255) / 256 : 256 * 32);
-        k_rope_bf16x8<<<g, 256, 0, stream>>>((__bf16*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, log2f(base));
-        ALCH_HIP_TRY(hipGetLastError());
-        return ALCH_OK;
+        k_rope_bf16x8<<<g, 256, 0, stream>>>((__bf16*)q, n_q, (__bf16*)k, n_kv, T, D, positions, cu_seqlens, n_seqs, l2);
+    } else if (dt == ALCH_BF16) {
+        rope_one<__bf16>(q, T, n_q, D, positions, cu_seqlens, n_seqs, l2, stream);
+        rope_one<__bf16>(k, T, n_kv, D, positions, cu_seqlens, n_seqs, l2, stream);
+    } else {
+        rope_one<float>(q, T, n_q, D, positions, cu_seqlens, n_seqs, l2, stream);
+        rope_one<float>(k, T, n_kv, D, positions, cu_seqlens, n_seqs, l2, stream);
     }
-    const int grid = (int)((n + 255) / 256 < 256 * 16 ? (n + 255) / 256 : 256 * 16);
-    const float l2 = log2f(base);
-    if (dt == ALCH_BF16)
-        k_rope<__bf16><<<grid, 256, 0, stream>>>((__bf16*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, l2);
-    else
-        k_rope<float><<<grid, 256, 0, stream>>>((float*)x, ld, T, n_heads, D, positions, cu_seqlens, n_seqs, l2);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
