@@ -76,6 +76,7 @@ struct AttnMfmaParams {
     // [part][T][Hkv][dK | dV] in `partial` (max_parts 1: none is)
     int T, n_blocks, max_parts, part_len;
     float* partial;
+    int prefix_ranks;  // dQ: blockIdx.z counts the blocks of a prefix too
 };
 
 // Work-groups that share a key block whose query stream has `tiles` tiles per head, and how many heads each takes.
@@ -721,9 +722,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
     const uint32_t lds0 = (uint32_t)(uintptr_t)ALCH_LDS(smem);
     const int seq = blockIdx.y, h = blockIdx.x;
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
-    // heaviest (last) query blocks of every sequence and head first: blockIdx.z is the slowest index
-    const int qb = (int)gridDim.z - 1 - (int)blockIdx.z;
-    if (qb * 128 >= len || len <= p.short_upto) return;
+    // heaviest query blocks of every sequence and head first: blockIdx.z is the slowest index
+    const int pre = p.prefix ? p.prefix[seq] : -1;
+    const int pre_start = pre >= 0 ? p.cu[pre] : 0, pre_len = pre >= 0 ? p.cu[pre + 1] - pre_start : 0;
+    const int qb = (int)gridDim.z - 1 - (int)blockIdx.z - (p.prefix_ranks ? (pre_len + 127) / 128 : 0);
+    if (qb < 0 || qb * 128 >= len || len <= p.short_upto) return;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kv = h / (p.Hq / p.Hkv);
@@ -734,8 +737,6 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
     tile_voffsets<kD>(voff, p.ldk, wave, lane);
     // key tiles: all tiles of the prefix sequence (if any), then own tiles 0 .. the last one that holds a
     // key <= the work-group's last query
-    const int pre = p.prefix ? p.prefix[seq] : -1;
-    const int pre_start = pre >= 0 ? p.cu[pre] : 0, pre_len = pre >= 0 ? p.cu[pre + 1] - pre_start : 0;
     const int npt = (pre_len + kTileRows - 1) / kTileRows;
     const int last_q = min(qb * 128 + 127, len - 1);
     const int n_it = npt + last_q / kTileRows + 1;
@@ -1121,6 +1122,24 @@ inline int plan_dkv_parts(const AttnArgs& a, AttnMfmaParams& p, int& longest) {
     return ALCH_OK;
 }
 
+// The third dimension of dQ's grid.  Work-groups go out by it, the last first, so it ranks a query block by the keys it meets:
+// its own blocks up to the diagonal and those of its prefix.  By its own blocks alone the responses on a long prompt, the
+// heaviest of all, started last (two responses to each prompt, 32/8 heads of 128, us: 4 prompts of 1024 tokens, responses of
+// 128 138 -> 120; 2 of 1024, 64 84 -> 61; 2 of 2048, 128 190 -> 144; 4 of 2048, 64 300 -> 265; 6 of 300, 128 66 -> 66).
+inline int plan_dq_ranks(const AttnArgs& a, AttnMfmaParams& p) {
+    p.prefix_ranks = 0;
+    long long ranks = p.n_blocks;
+    if (!a.prefix_host) return p.n_blocks;
+    const int* cu = a.cu_seqlens_host;
+    for (int s = 0; s < a.n_seqs; ++s) {
+        const int pre = a.prefix_host[s];
+        if (pre >= 0) ranks = std::max<long long>(ranks, (long long)ceil_div(cu[s + 1] - cu[s], 128) + ceil_div(cu[pre + 1] - cu[pre], 128));
+    }
+    if (ranks > kMaxGridBlocks) return p.n_blocks;
+    p.prefix_ranks = 1;
+    return (int)ranks;
+}
+
 template <int kD>
 int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     AttnMfmaParams p{};
@@ -1140,7 +1159,7 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     int longest = 0;
     ALCH_TRY(plan_dkv_parts(a, p, longest));
     const bool cut = p.max_parts > 1;
-    k_attn_bwd_dq_mfma<kD><<<dim3(a.Hq, a.n_seqs, nb), 256, 0, stream>>>(p);   // also writes delta
+    k_attn_bwd_dq_mfma<kD><<<dim3(a.Hq, a.n_seqs, plan_dq_ranks(a, p)), 256, 0, stream>>>(p);   // also writes delta
     const dim3 grid(a.Hkv, a.n_seqs, nb * p.max_parts), grid_finish(a.Hkv, a.n_seqs, ceil_div(longest, 32));
     if (a.prefix) {
         k_attn_bwd_dkv_mfma<kD, true><<<grid, 256, 0, stream>>>(p);
