@@ -85,11 +85,16 @@ __device__ __forceinline__ int dkv_parts(const AttnMfmaParams& p, int G, int til
     heads = (G + max(want, 1) - 1) / max(want, 1);
     return (G + heads - 1) / heads;
 }
-// 64-query tiles per head of the sequences that name `seq` as their prefix
-__device__ __forceinline__ int prefix_child_tiles(const AttnMfmaParams& p, int seq) {
+// 64-query tiles per head of the sequences that name `seq` as their prefix, and how many of them are not whole
+__device__ __forceinline__ int prefix_child_tiles(const AttnMfmaParams& p, int seq, int& tails) {
     int n = 0;
+    tails = 0;
     for (int c = seq + 1; c < p.n_seqs; ++c)
-        if (p.prefix[c] == seq) n += (p.cu[c + 1] - p.cu[c] + kTileRows - 1) / kTileRows;
+        if (p.prefix[c] == seq) {
+            const int rows = p.cu[c + 1] - p.cu[c];
+            n += (rows + kTileRows - 1) / kTileRows;
+            tails += rows % kTileRows != 0;
+        }
     return n;
 }
 
@@ -242,7 +247,7 @@ __device__ __forceinline__ bf16x8 global_frag_d(const __bf16* base, long long ld
 // dK / dV
 // kPrefix: sequences may name an earlier sequence as their prefix.  The key block then also meets, after the
 // queries of its own sequence (causal), every query of every sequence that names this one (no mask but the
-// ends of the sequences): the tile stream is the concatenation of those, sequence by sequence.
+// ends of the sequences).
 template <int kD, bool kPrefix>
 __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     constexpr int kTileBytes = AttnTile<kD>::kBytes, kStageBytes = AttnTile<kD>::kStageBytes, kRowBytes = AttnTile<kD>::kRowBytes;
@@ -263,7 +268,13 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     const int nqt = (len + kTileRows - 1) / kTileRows - qt0;
     const int G = p.Hq / p.Hkv;
     int head_tiles = nqt;
-    if constexpr (kPrefix) head_tiles += prefix_child_tiles(p, seq);
+    int child_tails = 0;
+    unsigned long long children = 0;  // bit i: sequence seq + 1 + i names this one and has a row
+    if constexpr (kPrefix) {
+        head_tiles += prefix_child_tiles(p, seq, child_tails);
+        const int c = seq + 1 + (int)(threadIdx.x & 63);
+        children = __ballot(c < p.n_seqs && p.prefix[c] == seq && p.cu[c + 1] > p.cu[c]);
+    }
     int part_heads;
     const int parts = dkv_parts(p, G, head_tiles, part_heads);
     if (part >= parts) return;
@@ -295,16 +306,21 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
 
     // The tile stream: for the key block's own sequence and then (kPrefix) every sequence that names it as
     // prefix, for every query head of the group, the 64-query tiles qt_first .. qt_end-1 of that sequence.
-    // Without prefixes the stream is ordered in two passes over the heads of the group: first the (at most two)
-    // tiles of every head that meet the diagonal of the key block, which need the causal mask, then all the
-    // others, which need none -- rows and keys past the end of the sequence are zero-filled by the loads, so
-    // they contribute exactly nothing to rows that are stored.  n_mask iterations take the masked code.
-    const int n_diag = kPrefix ? nqt : min(2, nqt);
-    const int n_mask = kPrefix ? n_it : (h_end - h_first) * n_diag;
+    // The stream is ordered in passes over the heads of the group: first the (at most two) tiles of every head that
+    // meet the diagonal of the key block, which need the causal mask, last the others, which need none -- rows and
+    // keys past the end of the sequence are zero-filled by the loads, so they contribute exactly nothing to rows that
+    // are stored.  kPrefix: between the two, still masked, the last tiles past the diagonal that are not whole.
+    // n_mask iterations take the masked code.  (Prefix batches, with the mask on all tiles -> so, 32/8 heads of 128, two
+    // responses to a prompt, us: 4 prompts of 1024 tokens, responses of 128 190 -> 162; 4 of 2048, 64 355 -> 306; 6 of
+    // 2048, 250 828 -> 708; one of 500, 40 34 -> 36.)
+    const int n_diag = min(2, nqt);
+    const int n_tail = kPrefix ? child_tails + (nqt > n_diag && len % kTileRows != 0 ? 1 : 0) : 0;
+    const int n_mask = (h_end - h_first) * (n_diag + n_tail);
     struct Cursor {
         int c, row0, n;         // sequence of the queries, its first row in the batch, its length
         int qt_first, qt_end;   // its tiles that this key block meets in the current pass
         int h, qt;              // query head and tile of the current position
+        int pass;               // kPrefix: 0 the diagonal, 1 tiles that are not whole, 2 all others
     };
     auto advance = [&](Cursor& q) {
         if (++q.qt < q.qt_end) return;
@@ -318,11 +334,27 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
             }
         }
         if constexpr (kPrefix) {
-            int c = q.c + 1;
-            while (c < p.n_seqs && !(p.prefix[c] == seq && p.cu[c + 1] > p.cu[c])) ++c;
-            if (c < p.n_seqs) {
-                q.c = c; q.row0 = p.cu[c]; q.n = p.cu[c + 1] - q.row0;
-                q.qt_first = q.qt = 0; q.qt_end = (q.n + kTileRows - 1) / kTileRows;
+            int c = q.c, pass = q.pass;
+            for (;;) {
+                const unsigned long long more = c - seq < 64 ? children >> (c - seq) : 0;
+                if (pass == 0) c = p.n_seqs;  // (of the diagonal the sequence itself is all)
+                else if (more) c += 1 + __builtin_ctzll(more);
+                else
+                    for (c = max(c + 1, seq + 65); c < p.n_seqs && !(p.prefix[c] == seq && p.cu[c + 1] > p.cu[c]);) ++c;
+                if (c >= p.n_seqs) {
+                    if (pass == 2) break;
+                    pass = pass == 0 && n_tail > 0 ? 1 : 2;
+                    c = seq;
+                }
+                const int row0 = p.cu[c], n = p.cu[c + 1] - row0;
+                const int lo = c == seq ? qt0 + n_diag : 0, hi = (n + kTileRows - 1) / kTileRows;
+                const int whole = hi > lo && n % kTileRows != 0 ? hi - 1 : hi;
+                const int first = pass == 1 ? whole : lo, end = pass == 1 ? hi : whole;
+                if (first < end) {
+                    q.c = c; q.row0 = row0; q.n = n; q.pass = pass;
+                    q.qt_first = q.qt = first; q.qt_end = end;
+                    break;
+                }
             }
         }
         // (past the end of the stream the cursor wraps; its tiles are then loaded with zero extent)
@@ -407,7 +439,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
         dma4(d.sc, st + sc_lds, sc_voff);
     };
     // Four LDS stages, tile t in stage t & 3; iteration `it` works on tiles it and it+1 and loads tile it+3.
-    Cursor q_ld{seq, seq_start, len, qt0, qt0 + n_diag, h_first, qt0};
+    Cursor q_ld{seq, seq_start, len, qt0, qt0 + n_diag, h_first, qt0, 0};
     Meta m_cur = meta_of(q_ld);
     issue_tile(desc_of(q_ld, 0 < n_it), lds0);
     advance(q_ld);
@@ -671,7 +703,8 @@ __global__ __launch_bounds__(256) void k_dkv_finish(AttnMfmaParams p) {
     const int row0 = (int)blockIdx.z * 32, kb = row0 / 128;
     if (row0 >= len) return;
     int tiles = (len + kTileRows - 1) / kTileRows - 2 * kb;
-    if constexpr (kPrefix) tiles += prefix_child_tiles(p, seq);
+    int tails;
+    if constexpr (kPrefix) tiles += prefix_child_tiles(p, seq, tails);
     int heads;
     const int parts = dkv_parts(p, p.Hq / p.Hkv, tiles, heads);
     if (parts < 2) return;

@@ -1,5 +1,6 @@
 """Query blocks on a shared prompt are handed out by the keys they meet: every block of every sequence has to come up once,
-also where the prompt is empty, where its blocks are whole, and where one rank is reached by a single sequence."""
+also where the prompt is empty, where its blocks are whole, and where one rank is reached by a single sequence.  A prompt's
+key blocks meet the tiles that need a mask first: whole and ragged tiles, own and of responses, more than 64 sequences on."""
 import pytest
 import torch
 
@@ -15,8 +16,10 @@ pytestmark = pytest.mark.gpu
     ("medium", [128, 256], [[128, 129], [256]]),       # whole blocks
     ("medium", [1, 385], [[400], [1]]),                # a response longer than its prompt; the last rank has one row
     ("medium64", [257, 1], [[1, 1], [130]]),
+    ("medium", [333, 320], [[64, 128, 0], [65, 192]]),  # ragged and whole tiles past the diagonal
+    ("medium", [130, 70], [[33] * 66, [64, 65]]),
 ])
-def test_dq_of_every_block(shape_name, prompts, responses):
+def test_every_query_and_key_block(shape_name, prompts, responses):
     import paper_2503_01066_amd as A
     shp, osh, b, W, X, _, _, rec, dY = make("bf16", shape_name, prompts, responses, 11)
     ref = layer_backward_reuse_prefix(osh, b["cu"], b["prefix"], f64(rec), f64(W), dY)
