@@ -150,12 +150,13 @@ __device__ __forceinline__ i32x4 rsrc_of(const void* p, long long bytes) {
     r[3] = 0x00020000;
     return r;
 }
+// (s_nop: a load into LDS takes one wait state after a scalar write of m0, which the compiler does not see to in assembly)
 __device__ __forceinline__ void dma16(i32x4 r, uint32_t lds_addr, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(r)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(r)
                  : "memory", "m0");
 }
 __device__ __forceinline__ void dma4(i32x4 r, uint32_t lds_addr, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(r)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(r)
                  : "memory", "m0");
 }
 

@@ -62,8 +62,10 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;
 // reads of the other pipeline stage behind it; completion is awaited with vmcnt.
 // lds_off: a constant once the loop around it is unrolled (as an operand of the addition it takes no scalar register: the
 // addresses of a whole ring were more of them than there are).
+// s_nop: a load into LDS takes one wait state after a scalar write of m0.  The compiler puts it there for its own loads
+// of this kind and does not look into assembly.
 __device__ __forceinline__ void dma16(i32x4 r, uint32_t lds_addr, uint32_t lds_off, uint32_t voff) {
-    asm volatile("s_add_u32 m0, %0, %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :
                  : "s"(lds_addr), "v"(voff), "s"(r), "i"(lds_off)
                  : "memory", "m0", "scc");

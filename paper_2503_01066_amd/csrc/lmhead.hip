@@ -128,8 +128,8 @@ __global__ __launch_bounds__(kCeThreads) void k_ce_chunk_bf16_row(__bf16* __rest
         uint32_t at = (uint32_t)tid * 16u;
         asm volatile("" : "+v"(at));  // (one register, not one per chunk kept across the loop)
 #pragma unroll
-        for (int k = 0; k < kLds; ++k)
-            asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds0 + k * kCeThreads * 16),
+        for (int k = 0; k < kLds; ++k)  // (s_nop: a load into LDS takes one wait state after a scalar write of m0)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds0 + k * kCeThreads * 16),
                          "v"(at + k * kCeThreads * 16), "s"(src)
                          : "memory", "m0");
 #pragma unroll

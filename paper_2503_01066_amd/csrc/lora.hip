@@ -113,8 +113,9 @@ template <int kG, int kRows, int kWaves> struct DownCfg {
     static constexpr int kStageBytes = kRows * 128 + kG * 1024;
     static constexpr int kStages = 144 * 1024 / kWaves / kStageBytes < 2 ? 2 : 144 * 1024 / kWaves / kStageBytes;  // 36 KB per wavefront of four
 };
+// (s_nop: a load into LDS takes one wait state after a scalar write of m0, which the compiler does not see to in assembly)
 __device__ __forceinline__ void lora_dma16(i32x4_l r, uint32_t lds_addr, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(r)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(r)
                  : "memory", "m0");
 }
 __device__ __forceinline__ i32x4_l lora_rsrc(const void* p, long long bytes) {

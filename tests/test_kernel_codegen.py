@@ -29,8 +29,9 @@ def _device_asm(src):
 def asm():
     if not (shutil.which(B._hipcc()) or os.path.exists(B._hipcc())):
         pytest.skip("hipcc not found")
-    names = {"gemm": "gemm_mfma.hip", "attn": "attn_mfma.hip", "pair": "gemm_pair.hip", "attn64": "attn_mfma_d64.hip", "head": "lmhead.hip"}
-    with ThreadPoolExecutor(max_workers=5) as ex:
+    names = {"gemm": "gemm_mfma.hip", "attn": "attn_mfma.hip", "pair": "gemm_pair.hip", "attn64": "attn_mfma_d64.hip", "head": "lmhead.hip",
+             "lora": "lora.hip"}
+    with ThreadPoolExecutor(max_workers=6) as ex:
         return dict(zip(names, ex.map(_device_asm, names.values())))
 
 
@@ -116,3 +117,56 @@ def test_cross_entropy_rows_wait_for_no_load_between_request_and_use(asm):
         assert first < last and not re.search(r"s_waitcnt [^\n]*vmcnt\(0\)", body[first:last]), name
         seen += 1
     assert seen == 3  # 4, 8 and 16 chunks of a row
+
+
+class _Code:
+    """Instructions (opcode, operands) of a function and, of each, those that may have run just before it."""
+    def __init__(self, body):
+        self.ins, labels = [], {}
+        for line in body.split("\n"):
+            line = line.split(";")[0].strip()
+            label = re.match(r"(\.LBB\w+):", line)
+            if label:
+                labels[label.group(1)] = len(self.ins)
+            elif line and not line.startswith(".") and not line.endswith(":"):
+                op, _, rest = line.replace("\t", " ", 1).partition(" ")
+                self.ins.append((op, rest.strip()))
+        self.before = [[i - 1] if i and self.ins[i - 1][0] not in ("s_branch", "s_endpgm") else [] for i in range(len(self.ins))]
+        for i, (op, rest) in enumerate(self.ins):
+            if op.startswith("s_cbranch") or op == "s_branch":
+                self.before[labels[rest.split()[0]]].append(i)
+
+    def loads_into_lds(self):
+        return [i for i, (op, rest) in enumerate(self.ins) if op.startswith("buffer_load") and rest.split()[-1] == "lds"]
+
+    def within(self, i, states, found):
+        """Whether some path to instruction i meets one that is `found` with fewer than `states` wait states between."""
+        for j in self.before[i]:
+            op, rest = self.ins[j]
+            left = states - (int(rest, 0) + 1 if op == "s_nop" else 1)
+            if found(op, rest) or (left > 0 and self.within(j, left, found)):
+                return True
+        return False
+
+
+def _scalars(operands):
+    out = set()
+    for lo, hi, one in re.findall(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b", operands):
+        out |= {int(one)} if one else set(range(int(lo), int(hi) + 1))
+    return out
+
+
+def test_loads_into_lds_wait_for_their_scalars(asm):
+    """A buffer load into LDS takes one wait state after a scalar write of m0 and five after a vector instruction's write of
+    its descriptor.  The compiler keeps both for loads of its own and looks into no assembly."""
+    seen = 0
+    for text in asm.values():
+        for name, body in _functions(text, "_ZN4alch"):
+            code = _Code(body)
+            for i in code.loads_into_lds():
+                assert not code.within(i, 1, lambda op, rest: op.startswith("s_") and rest.split(",")[0] == "m0"), (name, code.ins[i])
+                src = _scalars(code.ins[i][1].partition(",")[2])
+                assert not code.within(i, 5, lambda op, rest: op.startswith(("v_readfirstlane", "v_readlane", "v_cmp")) and
+                                       _scalars(rest.split(",")[0]) & src), (name, code.ins[i])
+                seen += 1
+    assert seen > 1000
