@@ -208,6 +208,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_lora_down_mfma(LoraDownParams p
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[u], acc, 0, 0, 0);
+        // this stage has been read before the next loads overwrite it (the products have waited for it, but may move)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();

@@ -170,3 +170,23 @@ def test_loads_into_lds_wait_for_their_scalars(asm):
                                        _scalars(rest.split(",")[0]) & src), (name, code.ins[i])
                 seen += 1
     assert seen > 1000
+
+
+def test_adapter_rings_are_read_before_they_are_refilled(asm):
+    """No read of a wavefront's ring may be on its way when a load into LDS is issued, by a wait that is written there and not
+    by one that the compiler places for the products, which it may move."""
+    seen = 0
+    for name, body in _functions(asm["lora"], "_ZN4alch16k_lora_down_mfma"):
+        code = _Code(body)
+        assert re.search(r";;#ASMSTART\s+s_waitcnt lgkmcnt\(0\)\s+;;#ASMEND", body), name
+        for i in code.loads_into_lds():
+            reached, todo = set(), [i]
+            while todo:
+                for j in code.before[todo.pop()]:
+                    op, rest = code.ins[j]
+                    assert not op.startswith("ds_read"), (name, code.ins[i])
+                    if j not in reached and not (op == "s_waitcnt" and "lgkmcnt(0)" in rest):
+                        reached.add(j)
+                        todo.append(j)
+        seen += 1
+    assert seen == 12  # one to four groups of columns, three sizes of work-group
