@@ -76,7 +76,6 @@ struct AttnMfmaParams {
     // [part][T][Hkv][dK | dV] in `partial` (max_parts 1: none is)
     int T, n_blocks, max_parts, part_len;
     float* partial;
-    int prefix_ranks;  // dQ: blockIdx.z counts the blocks of a prefix too
 };
 
 // Work-groups that share a key block whose query stream has `tiles` tiles per head, and how many heads each takes.
@@ -755,11 +754,21 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[2 * kStageBytes];
     const uint32_t lds0 = (uint32_t)(uintptr_t)ALCH_LDS(smem);
     const int seq = blockIdx.y, h = blockIdx.x;
-    const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
-    // heaviest query blocks of every sequence and head first: blockIdx.z is the slowest index
-    const int pre = p.prefix ? p.prefix[seq] : -1;
-    const int pre_start = pre >= 0 ? p.cu[pre] : 0, pre_len = pre >= 0 ? p.cu[pre + 1] - pre_start : 0;
-    const int qb = (int)gridDim.z - 1 - (int)blockIdx.z - (p.prefix_ranks ? (pre_len + 127) / 128 : 0);
+    // (one request for both tables: work-groups of a block or two are a chain of such requests)
+    const int* table = p.prefix ? p.prefix : p.cu;
+    const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start, named = table[seq], pre = p.prefix ? named : -1;
+    // blockIdx.z is the slowest index, so it counts down the keys that a query block meets: its own blocks up to the
+    // diagonal and those of its prefix.  By its own blocks alone the responses on a long prompt, the heaviest of all, start
+    // last.  As many ranks as the longest sequence has blocks: what lies beyond shares the last ones, and the grid
+    // holds no work-group more than without prefixes.  (32/8 heads of 128, two responses to a prompt, us by own blocks / with a
+    // rank for every count of keys / so: one prompt of 2048 tokens, responses of 40 132 / 98 / 98; 4 of 1024, 128 142 / 128 /
+    // 125; 4 of 1024, 16 137 / 134 / 124; 4 of 300, 100 57 / 56 / 47; 6 of 100, 100 39 / 44 / 41.)
+    int qb = (int)gridDim.z - 1 - (int)blockIdx.z, pre_start = 0, pre_len = 0;
+    if (pre >= 0) {
+        pre_start = p.cu[pre];
+        pre_len = p.cu[pre + 1] - pre_start;
+        qb -= min((pre_len + 127) / 128, (int)gridDim.z - (len + 127) / 128);
+    }
     if (qb < 0 || qb * 128 >= len || len <= p.short_upto) return;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1156,24 +1165,6 @@ inline int plan_dkv_parts(const AttnArgs& a, AttnMfmaParams& p, int& longest) {
     return ALCH_OK;
 }
 
-// The third dimension of dQ's grid.  Work-groups go out by it, the last first, so it ranks a query block by the keys it meets:
-// its own blocks up to the diagonal and those of its prefix.  By its own blocks alone the responses on a long prompt, the
-// heaviest of all, started last (two responses to each prompt, 32/8 heads of 128, us: 4 prompts of 1024 tokens, responses of
-// 128 138 -> 120; 2 of 1024, 64 84 -> 61; 2 of 2048, 128 190 -> 144; 4 of 2048, 64 300 -> 265; 6 of 300, 128 66 -> 66).
-inline int plan_dq_ranks(const AttnArgs& a, AttnMfmaParams& p) {
-    p.prefix_ranks = 0;
-    long long ranks = p.n_blocks;
-    if (!a.prefix_host) return p.n_blocks;
-    const int* cu = a.cu_seqlens_host;
-    for (int s = 0; s < a.n_seqs; ++s) {
-        const int pre = a.prefix_host[s];
-        if (pre >= 0) ranks = std::max<long long>(ranks, (long long)ceil_div(cu[s + 1] - cu[s], 128) + ceil_div(cu[pre + 1] - cu[pre], 128));
-    }
-    if (ranks > kMaxGridBlocks) return p.n_blocks;
-    p.prefix_ranks = 1;
-    return (int)ranks;
-}
-
 template <int kD>
 int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     AttnMfmaParams p{};
@@ -1193,7 +1184,7 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     int longest = 0;
     ALCH_TRY(plan_dkv_parts(a, p, longest));
     const bool cut = p.max_parts > 1;
-    k_attn_bwd_dq_mfma<kD><<<dim3(a.Hq, a.n_seqs, plan_dq_ranks(a, p)), 256, 0, stream>>>(p);   // also writes delta
+    k_attn_bwd_dq_mfma<kD><<<dim3(a.Hq, a.n_seqs, nb), 256, 0, stream>>>(p);   // also writes delta
     const dim3 grid(a.Hkv, a.n_seqs, nb * p.max_parts), grid_finish(a.Hkv, a.n_seqs, ceil_div(longest, 32));
     if (a.prefix) {
         k_attn_bwd_dkv_mfma<kD, true><<<grid, 256, 0, stream>>>(p);

@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     ("medium", [128, 256], [[128, 129], [256]]),       # whole blocks
     ("medium", [1, 385], [[400], [1]]),                # a response longer than its prompt; the last rank has one row
     ("medium64", [257, 1], [[1, 1], [130]]),
+    ("medium", [385, 3], [[300, 20], [129]]),          # more ranks asked for than the longest sequence has blocks
     ("medium", [333, 320], [[64, 128, 0], [65, 192]]),  # ragged and whole tiles past the diagonal
     ("medium", [130, 70], [[33] * 66, [64, 65]]),
 ])
