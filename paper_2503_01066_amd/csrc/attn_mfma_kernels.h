@@ -84,17 +84,54 @@ __device__ __forceinline__ int dkv_parts(const AttnMfmaParams& p, int G, int til
     heads = (G + max(want, 1) - 1) / max(want, 1);
     return (G + heads - 1) / heads;
 }
-// 64-query tiles per head of the sequences that name `seq` as their prefix, and how many of them are not whole
-__device__ __forceinline__ int prefix_child_tiles(const AttnMfmaParams& p, int seq, int& tails) {
-    int n = 0;
-    tails = 0;
-    for (int c = seq + 1; c < p.n_seqs; ++c)
-        if (p.prefix[c] == seq) {
-            const int rows = p.cu[c + 1] - p.cu[c];
-            n += (rows + kTileRows - 1) / kTileRows;
-            tails += rows % kTileRows != 0;
+// The sequences that name `seq` as their prefix and have a row, looked for by a wavefront, 64 candidates at a time (one at a
+// time, a key block of a batch of 600 sequences spent most of its time on this).  Every lane takes part.
+struct PrefixSeqs {
+    int first, last;     // of them (last -1: none)
+    int tiles, ragged;   // 64-query tiles per head of all, and how many of those are not whole
+    int base, row0, n;   // the 64 looked at now: lane i holds the first row and the rows of sequence base + i, 0 if it is none of them
+};
+__device__ __forceinline__ void prefix_window(const AttnMfmaParams& p, int seq, int base, int& row0, int& n) {
+    const int i = base + (int)(threadIdx.x & 63), c = min(i, p.n_seqs - 1);
+    const int named = p.prefix[c], end = p.cu[c + 1];
+    row0 = p.cu[c];
+    n = i < p.n_seqs && named == seq ? end - row0 : 0;
+}
+__device__ __forceinline__ PrefixSeqs prefix_seqs(const AttnMfmaParams& p, int seq) {
+    PrefixSeqs s{p.n_seqs, -1, 0, 0, seq + 1, 0, 0};
+    int row0, n;
+    prefix_window(p, seq, seq + 1, row0, n);
+    for (int base = seq + 1; base < p.n_seqs; base += 64) {
+        int row0_next, n_next;
+        prefix_window(p, seq, base + 64, row0_next, n_next);  // (on its way while these are counted)
+        const unsigned long long bits = __ballot(n > 0);
+        if (bits) {
+            if (s.last < 0) {
+                s.first = base + __builtin_ctzll(bits);
+                s.base = base; s.row0 = row0; s.n = n;
+            }
+            s.last = base + 63 - __builtin_clzll(bits);
+            s.ragged += __popcll(__ballot(n % kTileRows != 0));
+            s.tiles += (n + kTileRows - 1) / kTileRows;
         }
-    return n;
+        row0 = row0_next; n = n_next;
+    }
+    int sum = 0;
+    for (int b = 0; __ballot(s.tiles >> b != 0); ++b) sum += __popcll(__ballot(s.tiles >> b & 1)) << b;
+    s.tiles = sum;
+    return s;
+}
+// The next one behind sequence c that has whole tiles, or one that is not whole (n_seqs: none)
+__device__ __forceinline__ int prefix_next(const AttnMfmaParams& p, int seq, PrefixSeqs& s, int c, bool whole) {
+    for (c = max(c + 1, s.first); c <= s.last; c = s.base + 64) {
+        if (c < s.base || c >= s.base + 64) {
+            s.base = c;
+            prefix_window(p, seq, c, s.row0, s.n);
+        }
+        const unsigned long long bits = (whole ? __ballot(s.n >= kTileRows) : __ballot(s.n % kTileRows != 0)) >> (c - s.base);
+        if (bits) return c + __builtin_ctzll(bits);
+    }
+    return p.n_seqs;
 }
 
 template <int kD> __device__ __forceinline__ float rope_theta(int d, float log2_base) {
@@ -268,12 +305,10 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     const int nqt = (len + kTileRows - 1) / kTileRows - qt0;
     const int G = p.Hq / p.Hkv;
     int head_tiles = nqt;
-    int child_tails = 0;
-    unsigned long long children = 0;  // bit i: sequence seq + 1 + i names this one and has a row
+    PrefixSeqs named{};
     if constexpr (kPrefix) {
-        head_tiles += prefix_child_tiles(p, seq, child_tails);
-        const int c = seq + 1 + (int)(threadIdx.x & 63);
-        children = __ballot(c < p.n_seqs && p.prefix[c] == seq && p.cu[c + 1] > p.cu[c]);
+        named = prefix_seqs(p, seq);
+        head_tiles += named.tiles;
     }
     int part_heads;
     const int parts = dkv_parts(p, G, head_tiles, part_heads);
@@ -309,13 +344,16 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
     // The stream is ordered in passes over the heads of the group: first the (at most two) tiles of every head that
     // meet the diagonal of the key block, which need the causal mask, last the others, which need none -- rows and
     // keys past the end of the sequence are zero-filled by the loads, so they contribute exactly nothing to rows that
-    // are stored.  kPrefix: between the two, still masked, the last tiles past the diagonal that are not whole.
-    // n_mask iterations take the masked code.  (Prefix batches, with the mask on all tiles -> so, 32/8 heads of 128, two
-    // responses to a prompt, us: 4 prompts of 1024 tokens, responses of 128 190 -> 162; 4 of 2048, 64 355 -> 306; 6 of
-    // 2048, 250 828 -> 708; one of 500, 40 34 -> 36.)
+    // are stored.  kPrefix: between the two, still masked, the last tiles past the diagonal that are not whole; fewer than
+    // four that need no mask take it, too (the other loop's code has to be fetched for them).
+    // n_mask iterations take the masked code.  (Prefix batches, with the mask on all tiles and responses looked for one by one
+    // -> so, 32/8 heads of 128, two responses to a prompt, us: 4 prompts of 1024 tokens, responses of 128 194 -> 157; 4 of
+    // 2048, 64 401 -> 333; one of 500, 40 35 -> 35, sixteen of them 76 -> 74; 40 of 64, 32 148 -> 93; 200 of 40, 20 1822 -> 470.
+    // Heads of 64: 185 -> 155, 388 -> 323, 33.5 -> 34.8, 75 -> 78, 144 -> 93, 1812 -> 468.)
     const int n_diag = min(2, nqt);
-    const int n_tail = kPrefix ? child_tails + (nqt > n_diag && len % kTileRows != 0 ? 1 : 0) : 0;
-    const int n_mask = (h_end - h_first) * (n_diag + n_tail);
+    const int n_tail = kPrefix ? named.ragged + (nqt > n_diag && len % kTileRows != 0 ? 1 : 0) : 0;
+    int n_mask = (h_end - h_first) * (n_diag + n_tail);
+    if (kPrefix && n_it - n_mask < 4) n_mask = n_it;
     struct Cursor {
         int c, row0, n;         // sequence of the queries, its first row in the batch, its length
         int qt_first, qt_end;   // its tiles that this key block meets in the current pass
@@ -336,20 +374,17 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
         if constexpr (kPrefix) {
             int c = q.c, pass = q.pass;
             for (;;) {
-                const unsigned long long more = c - seq < 64 ? children >> (c - seq) : 0;
-                if (pass == 0) c = p.n_seqs;  // (of the diagonal the sequence itself is all)
-                else if (more) c += 1 + __builtin_ctzll(more);
-                else
-                    for (c = max(c + 1, seq + 65); c < p.n_seqs && !(p.prefix[c] == seq && p.cu[c + 1] > p.cu[c]);) ++c;
-                if (c >= p.n_seqs) {
+                c = pass == 0 ? p.n_seqs : prefix_next(p, seq, named, c, pass == 2);  // (of the diagonal the sequence itself is all)
+                const bool own = c >= p.n_seqs;
+                if (own) {
                     if (pass == 2) break;
                     pass = pass == 0 && n_tail > 0 ? 1 : 2;
                     c = seq;
                 }
-                const int row0 = p.cu[c], n = p.cu[c + 1] - row0;
-                const int lo = c == seq ? qt0 + n_diag : 0, hi = (n + kTileRows - 1) / kTileRows;
-                const int whole = hi > lo && n % kTileRows != 0 ? hi - 1 : hi;
-                const int first = pass == 1 ? whole : lo, end = pass == 1 ? hi : whole;
+                const int row0 = own ? seq_start : __builtin_amdgcn_readlane(named.row0, c - named.base);
+                const int n = own ? len : __builtin_amdgcn_readlane(named.n, c - named.base);
+                const int lo = own ? qt0 + n_diag : 0, whole = n / kTileRows;
+                const int first = pass == 1 ? max(whole, lo) : lo, end = pass == 1 ? whole + (n % kTileRows != 0) : whole;
                 if (first < end) {
                     q.c = c; q.row0 = row0; q.n = n; q.pass = pass;
                     q.qt_first = q.qt = first; q.qt_end = end;
@@ -703,8 +738,7 @@ __global__ __launch_bounds__(256) void k_dkv_finish(AttnMfmaParams p) {
     const int row0 = (int)blockIdx.z * 32, kb = row0 / 128;
     if (row0 >= len) return;
     int tiles = (len + kTileRows - 1) / kTileRows - 2 * kb;
-    int tails;
-    if constexpr (kPrefix) tiles += prefix_child_tiles(p, seq, tails);
+    if constexpr (kPrefix) tiles += prefix_seqs(p, seq).tiles;
     int heads;
     const int parts = dkv_parts(p, p.Hq / p.Hkv, tiles, heads);
     if (parts < 2) return;
