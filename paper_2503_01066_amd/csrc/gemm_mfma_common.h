@@ -133,6 +133,7 @@ struct PairPlan { int per_xcd, q_end, parts, per; };
 PairPlan pair_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes);
 int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream);
 size_t pair_split_bytes(const PairPlan& plan);  // scratch of its partial tiles
+int pair_grid(const PairPlan& plan);            // its work-groups
 int launch_gemm_two_pairs(MfmaGemmParams data, int data_tiles_m, const PairPlan& data_plan, MfmaGemmParams weight, int weight_tiles_m,
                           const PairPlan& weight_plan, float* split_ws, hipStream_t stream);
 

@@ -190,3 +190,15 @@ def test_adapter_rings_are_read_before_they_are_refilled(asm):
                         todo.append(j)
         seen += 1
     assert seen == 12  # one to four groups of columns, three sizes of work-group
+
+
+def test_two_contractions_in_one_kernel_keep_their_registers_and_their_pipelines(asm):
+    (name, body), = _functions(asm["pair"], "_ZN4alch16k_gemm_two_pairs")
+    assert _meta(asm["pair"], name, "vgpr_spill_count") == 0 and _meta(asm["pair"], name, "private_segment_fixed_size") == 0
+    assert _meta(asm["pair"], name, "vgpr_count") <= 256 and _meta(asm["pair"], name, "group_segment_fixed_size") <= 80 * 1024
+    loops = [txt for lab, txt in _blocks(body) if txt.count("v_mfma_") >= 16]
+    # operands with k-major A take steps in pairs, whose waits differ (4 or 8 loads on their way), the others 6
+    waits = {w for txt in loops for w in re.findall(r"s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)", txt)}
+    assert {"4", "8", "6"} <= waits, waits
+    for txt in loops:
+        assert "scratch_" not in txt and not re.search(r"s_waitcnt [^\n]*vmcnt\(0\)", txt)
