@@ -187,9 +187,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# (a private name of torch: releases without it pay 2.5 us for a stream object, more than half of a short prompt's launch)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream):
-    # (the handle alone: a stream object costs 2.5 us, more than half of the launch it is for)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _streams(streams, dsts):

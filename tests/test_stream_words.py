@@ -24,3 +24,11 @@ def test_words_are_the_structures(n_dsts):
 def test_columns_that_are_not_contiguous_are_refused(s, d):
     with pytest.raises(AssertionError):
         B._streams([s], [d])
+
+
+def test_current_stream_without_the_private_lookup(monkeypatch):
+    class Stream:
+        cuda_stream = 0x1234
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    assert B._stream_handle(None) == 0x1234 and B._stream_handle(Stream()) == 0x1234
