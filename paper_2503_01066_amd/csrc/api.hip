@@ -394,8 +394,8 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     adapter_sums.p.scratch = p.up_scratch;
     adapter_sums.capacity = (long long)(p.up_scratch_bytes / sizeof(float));
     // Adapter gradients of the n <= 3 projections pj0, pj0+1, .. that share the input x [T, in_p]; dy[i] [T, out_p[i]]
-    // with row stride lddy; t2 of projection pj0+i sits in slot i.  One launch forms the t1 of all of them, one pair
-    // of launches all their dA and dB.
+    // with row stride lddy; t2 of projection pj0+i sits in slot i.  One launch forms the t1 of all of them, one
+    // the partial sums of all their dA and dB, which adapter_sums adds at the end of the layer.
     auto adapter_grads = [&](int pj0, int n, const void* x, long long ldx, int in_p, const void* const* dy, long long lddy,
                              const int* out_p) -> int {
         LoraDown dj[3];

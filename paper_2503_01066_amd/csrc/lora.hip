@@ -479,7 +479,7 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
         TraceScope ts(kTraceLora, flops, bytes, stream);
         // Few rows leave compute units without a work-group, and a wavefront alone on its SIMD takes 0.37 us for a chunk (load,
         // read, four dependent products, one after the other): work-groups of fewer rows and more wavefronts, as long as
-        // each finds a compute unit.  8B shape, us a launch of 32 rows by 4 / 16 rows by 8 / 8 rows by 16 wavefronts: 200
+        // each finds a compute unit (the sums of a row are then folded from 8 or 16 parts of K instead of 4).  8B shape, us a launch of 32 rows by 4 / 16 rows by 8 / 8 rows by 16 wavefronts: 200
         // tokens, K 14336 21.5 / 13.6 / 10.2, K 4096 10.3 / 7.4 / 6.2; 900 tokens, two of K 14336 23.4 / 17.9 / 14.8; 2000
         // tokens, one 29.2 / 22.4 / 17.3 and two (500 work-groups of 8 rows) 34.7 / 25.2 / 30.6; 5120 tokens 40.9 / 46.3 / 44.0.
         int n_cu = 0;

@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm_bwd_bf16(const __bf16* __restri
 }
 
 // dg[c] (+)= sum over nblk partial rows; 64 columns per block, 16 row groups folded through LDS.  blockIdx.y: which of the
-// gains (a layer's two in one launch: 5 us less of a backward).
+// gains (a layer's two in one launch: fp32 layer backward of 2 x 128 tokens 91.1 -> 89.0 us).
 template <typename T>
 __global__ __launch_bounds__(1024) void k_colsum_finish_wide(GainSums sums, int width, int accumulate) {
     __shared__ float red[16][64];
