@@ -9,10 +9,9 @@
 // Design for CDNA4:
 //   * 256x256 tile per work-group, contraction in steps of 32, 4 wavefronts of 64 lanes, each owning 128x128 of the
 //     tile as 4x4 MFMA 32x32x16 bf16 accumulators (256 accumulator registers per lane).
-//   * Tiles are fetched HBM/L2 -> LDS with 16-byte direct-to-LDS buffer loads (no
-//     registers in between) into a ring of stages that fills the 160 KB LDS: five stages of
-//     [A 256x32 | B 32x256], or, when A is k-major, three 64-k-wide super-stages of A and four stages
-//     of B, so that every load of A covers whole 128-byte lines (see tile_offsets_wide).
+//   * Tiles are fetched HBM/L2 -> LDS with 16-byte direct-to-LDS buffer loads (no registers in between) into two rings of
+//     five 16 KB stages, one per operand, that fill the 160 KB LDS.  A stage holds 32 k of 256 columns, or, of a k-major
+//     operand, 64 k of 128 rows, so that every load covers whole 128-byte lines (see tile_offsets_wide).
 //     A direct-to-LDS load writes lane-linearly, so the bank-conflict swizzle is applied
 //     by permuting which global 16-byte chunk each lane fetches.
 //   * Operands whose contraction index is contiguous in memory are read from LDS with
@@ -34,19 +33,22 @@
 namespace alch {
 
 static constexpr int BM = 256, BN = 256;
-static constexpr int kStages = 5;                        // 5 x 32 KB = the whole 160 KB LDS
-static constexpr int kOperandStageBytes = 256 * BK * 2;  // 16 KB per operand per stage
+static constexpr int kStages = 5;                        // of either operand: 2 x 5 x 16 KB = the whole 160 KB LDS
+static constexpr int kOperandStageBytes = 256 * BK * 2;  // 16 KB
 static constexpr int kLoadsPerTile = 8;                  // direct-to-LDS instructions per wave per k-tile (A + B)
 static constexpr int kGroupM = 4;                        // tile rows per raster band
 
-// ---- k-major A staged 64 k wide ---------------------------------------------------------------
-// A k-major tile fetched 32 k at a time takes 64 bytes of every row: each 128-byte line then crosses the
-// L2 -> L1 path twice (once per k-tile; the 32 KB L1 has long lost it by the second time).  With AK the A
-// operand is therefore staged in super-stages of 64 k: [2 halves of 128 rows][128 bytes], 32 KB, three of
-// them, and one wave-wide load covers 8 whole lines.  A super-stage is filled by two batches (rows 0-127,
-// rows 128-255), one per k-tile step, so the loads per step stay what they are for the 32-wide layout; the
-// B operand keeps 32-wide stages, four of them, behind the three super-stages (96 + 64 = 160 KB).
-//   slot (16-byte units) inside a half = rl*8 + (c ^ ((rl>>1)&7)), rl = row & 127, c = 16-byte chunk of the
+// ---- the rings
+// Two k-tiles (64 k) are used up together: batch b of an operand, in stage b % 5, is half b & 1 of its 64 k number b / 2.
+// Of an operand whose columns are contiguous the halves are its k-tiles; of a k-major one they are rows 0-127 and 128-255,
+// all 64 k of them: a k-tile takes 64 bytes of every row, and fetched by itself every 128-byte line crosses the L2 -> L1
+// path twice (the 32 KB L1 has long lost it by the second time), which costs time and power.  Batches of 64 k free their
+// stages two at a time, so five stages hold what 2.5 x 64 k need, and one barrier in two k-tiles is enough: batch kt + 4
+// goes out in the second half of step kt and has 1.5 steps (1 us) to land if kt is odd, 2.5 if it is even.  Before, with 32 k
+// a stage for B (A in three stages of 64 k x 256 rows), four and five k-tiles ahead: 8192 x 4096 x 28672, both operands
+// k-major, 1458 -> 1301 us, 8192 x 14336 x 4096 751 -> 677, 3001 x 4096 x 14336 292 -> 266; a layer forward of 5003 tokens
+// 2029 -> 1931 us.  The other forms, whose lines were whole before, are within 1 % of what they were.
+//   slot (16-byte units) in a stage of rows = rl*8 + (c ^ ((rl>>1)&7)), rl = row & 127, c = 16-byte chunk of the
 //   row's 64 k: 16 consecutive rows at one logical chunk then cover all 64 banks once (ds_read_b128).
 __device__ __forceinline__ void tile_offsets_wide(uint32_t (&voff)[8], int wave, int lane, long long ld, int valid) {
 #pragma unroll
@@ -59,11 +61,12 @@ __device__ __forceinline__ void tile_offsets_wide(uint32_t (&voff)[8], int wave,
         }
 }
 
-// fragment of k-tile `par` (0/1) of a super-stage: rows idx0 + (lane&31), k = par*32 + kk*16 + 8*(lane>>5) ..+7
-__device__ __forceinline__ bf16x8 read_frag_wide(const char* sup, int par, int idx0, int kk, int lane) {
-    const int row = idx0 + (lane & 31), rl = row & 127;
-    const int c = (par * 4 + kk * 2 + (lane >> 5)) ^ ((rl >> 1) & 7);
-    return *reinterpret_cast<const bf16x8*>(sup + (row >> 7) * kOperandStageBytes + rl * 128 + c * 16);
+// fragment of k-tile `par` (0/1) of 64 k: rows `row` + (lane&31) of half `hi`, k = par*32 + kk*16 + 8*(lane>>5) ..+7;
+// off0, off1: stages of the halves
+__device__ __forceinline__ bf16x8 read_frag_wide(const char* ring, uint32_t off0, uint32_t off1, int hi, int par, int row, int kk, int lane) {
+    const int rl = row + (lane & 31), c = (par * 4 + kk * 2 + (lane >> 5)) ^ ((rl >> 1) & 7);
+    const uint32_t at = off1 > off0 ? off0 + (uint32_t)hi * kOperandStageBytes : hi ? off1 : off0;
+    return *reinterpret_cast<const bf16x8*>(ring + at + rl * 128 + c * 16);
 }
 
 struct Frags {
@@ -79,20 +82,11 @@ template <typename F> __device__ __forceinline__ void static_for4(F&& f) {
 
 template <bool AK, bool BKM, bool kSplit = false>
 __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
-    // kStages pipeline stages of [A tile 16 KB | B tile 16 KB]
-    __shared__ __attribute__((aligned(1024))) char smem[kStages * 2 * kOperandStageBytes];
+    __shared__ __attribute__((aligned(1024))) char smem[2 * kStages * kOperandStageBytes];  // ring of A, ring of B
     const uint32_t lds0 = (uint32_t)(uintptr_t)ALCH_LDS(smem);
-    constexpr int kStage = 2 * kOperandStageBytes;
-    // AK: A in three 64-wide super-stages, B in four 32-wide stages behind them (see tile_offsets_wide);
-    // otherwise kStages stages of [A | B].  kU = steps after which every ring is back at its first stage.
-    constexpr bool kWide = AK;
-    constexpr int kU = kWide ? 12 : kStages;
-    constexpr int kDepth = kWide ? 4 : kStages;  // k-tiles of B (and their share of A) resident at a time
-    constexpr uint32_t kWideB0 = 3 * kStage;
-    auto a_off = [](int st) -> uint32_t { return kWide ? (uint32_t)((st / 2) % 3) * kStage : (uint32_t)(st % kStages) * kStage; };
-    auto b_off = [](int st) -> uint32_t {
-        return kWide ? kWideB0 + (uint32_t)(st % 4) * kOperandStageBytes : (uint32_t)(st % kStages) * kStage + kOperandStageBytes;
-    };
+    constexpr int kU = 2 * kStages;  // steps after which the rings are back at their first stage, at an even step
+    constexpr uint32_t kRing = kStages * kOperandStageBytes;
+    auto stage_off = [](int b) -> uint32_t { return (uint32_t)(b % kStages) * kOperandStageBytes; };
 
     // ---- work-group -> output tile: XCD-contiguous chunks, banded raster inside a chunk
     // The grid is persistent (one work-group per compute unit): each work-group walks its share of
@@ -165,10 +159,11 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
             pa += (long long)lo * stepa;
             pb += (long long)lo * stepb;
         }
-        uint32_t va[kWide ? 8 : 4], vb[4];
-        if constexpr (kWide) tile_offsets_wide(va, wave, flane, lda, Mv - m0);
-        else tile_offsets<AK>(va, wave, flane, lda, Mv - m0);
-        tile_offsets<BKM>(vb, wave, flane, ldb, p.N - n0);
+        uint32_t va[AK ? 8 : 4], vb[BKM ? 8 : 4];
+        if constexpr (AK) tile_offsets_wide(va, wave, flane, lda, Mv - m0);
+        else tile_offsets<false>(va, wave, flane, lda, Mv - m0);
+        if constexpr (BKM) tile_offsets_wide(vb, wave, flane, ldb, p.N - n0);
+        else tile_offsets<false>(vb, wave, flane, ldb, p.N - n0);
 
         // Loads of the next k-tile go out one instruction at a time between MFMAs (a burst of
         // eight would hold the wave at the issue stage while the texture path drains).  Past the
@@ -176,7 +171,6 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
         // write zeros nobody reads), so the outstanding-load count is the same in every iteration.
         // The stream state (tile base address, bytes left in the operand) is kept in scalar registers
         // and advanced with scalar instructions, off the vector pipeline that feeds the MFMAs.
-        int tiles_left = nk;
         uint32_t a_lo, a_hi, b_lo, b_hi;
         int a_rem, b_rem;
         {
@@ -192,9 +186,9 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
         const int sa_step = __builtin_amdgcn_readfirstlane((int)stepa);
         const int sb_step = __builtin_amdgcn_readfirstlane((int)stepb);
         i32x4 ra, rb;
-        // The loads of a step read through the descriptors ra, rb; an exhausted stream gets an empty buffer.  kWide: A's
-        // stream moves by 128 bytes (64 k) after every second batch (a_inc alternates 0, 128).
-        int a_left = kWide ? (nk + 1) & ~1 : nk, a_inc = kWide ? 0 : sa_step;
+        // The loads of a step read through the descriptors ra, rb; an exhausted stream gets an empty buffer.  The stream of a
+        // k-major operand moves by 128 bytes (64 k) after every second batch (the increment alternates 0, 128).
+        int a_left = nk, a_inc = AK ? 0 : sa_step, b_left = nk, b_inc = BKM ? 0 : sb_step;
         auto select = [](i32x4& r, uint32_t lo, uint32_t hi, int bytes, int left) {
             int n;
             asm volatile("s_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=&s"(n) : "s"(left), "s"(bytes) : "scc");
@@ -213,56 +207,45 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
             if constexpr (q == 0) select(ra, a_lo, a_hi, a_rem, a_left);
             if constexpr (q == 1) {
                 advance(a_lo, a_hi, a_rem, a_left, a_inc);
-                if constexpr (kWide) asm volatile("s_sub_i32 %0, 128, %0" : "+s"(a_inc) : : "scc");
+                if constexpr (AK) asm volatile("s_sub_i32 %0, 128, %0" : "+s"(a_inc) : : "scc");
             }
-            if constexpr (q == 2) select(rb, b_lo, b_hi, b_rem, tiles_left);
-            if constexpr (q == 3) advance(b_lo, b_hi, b_rem, tiles_left, sb_step);
+            if constexpr (q == 2) select(rb, b_lo, b_hi, b_rem, b_left);
+            if constexpr (q == 3) {
+                advance(b_lo, b_hi, b_rem, b_left, b_inc);
+                if constexpr (BKM) asm volatile("s_sub_i32 %0, 128, %0" : "+s"(b_inc) : : "scc");
+            }
         };
         auto open_a = [&]() { open_step(IntC<0>{}); open_step(IntC<1>{}); };
         auto open_b = [&]() { open_step(IntC<2>{}); open_step(IntC<3>{}); };
-        // Refill issued in step `st`: !kWide: k-tile st + kStages of both operands into the stage of k-tile st.
-        // kWide: A batch st + 5 = half (st+5)&1 of super-tile (st+5)/2, B k-tile st + 4 into the stage of k-tile st.
-#define ALCH_DMA_A(st, j)                                                                                              \
-    dma16(ra, lds_wave, (kWide ? a_off((st) + 5) + (uint32_t)(((st) + 5) & 1) * kOperandStageBytes : a_off(st)) +       \
-                            (uint32_t)(j) * 1024u, va[kWide ? (((st) + 5) & 1) * 4 + (j) : (j)])
-#define ALCH_DMA_B(st, j) dma16(rb, lds_wave, b_off(st) + (uint32_t)(j) * 1024u, vb[j])
+        // loads of batch `b`
+#define ALCH_DMA_A(b, j) dma16(ra, lds_wave, stage_off(b) + (uint32_t)(j) * 1024u, va[(AK ? ((b) & 1) * 4 : 0) + (j)])
+#define ALCH_DMA_B(b, j) dma16(rb, lds_wave, kRing + stage_off(b) + (uint32_t)(j) * 1024u, vb[(BKM ? ((b) & 1) * 4 : 0) + (j)])
 #define ALCH_MFMA(F, i, j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[j], F.a[i], acc[i][j], 0, 0, 0)
 #define ALCH_SB() __builtin_amdgcn_sched_barrier(0)
-        // fragment reads of k-tile step `st`
+        // fragment reads of k-tile `st`
         auto frag_a = [&](int st, int kk, int i) -> bf16x8 {
-            if constexpr (kWide) return read_frag_wide(smem + a_off(st), st & 1, wm * 128 + i * 32, kk, flane);
-            else return read_frag<AK>(smem + a_off(st), wm * 128 + i * 32, kk, flane);
+            if constexpr (AK) return read_frag_wide(smem, stage_off(st / 2 * 2), stage_off(st / 2 * 2 + 1), wm, st & 1, i * 32, kk, flane);
+            else return read_frag<false>(smem + stage_off(st), wm * 128 + i * 32, kk, flane);
+        };
+        auto frag_b = [&](int st, int kk, int i) -> bf16x8 {
+            const char* ring = smem + kRing;
+            if constexpr (BKM) return read_frag_wide(ring, stage_off(st / 2 * 2), stage_off(st / 2 * 2 + 1), wn, st & 1, i * 32, kk, flane);
+            else return read_frag<false>(ring + stage_off(st), wn * 128 + i * 32, kk, flane);
         };
 #define ALCH_RA(F, st, kk, i) F.a[i] = frag_a(st, kk, i)
-#define ALCH_RB(F, st, kk, i) F.b[i] = read_frag<BKM>(smem + b_off(st), wn * 128 + (i) * 32, kk, flane)
+#define ALCH_RB(F, st, kk, i) F.b[i] = frag_b(st, kk, i)
 
         // all waves are done with the previous segment's stages before they are refilled
         __syncthreads();
-        if constexpr (kWide) {
-            // A batches 0..4 (steps -5..-1 of the refill numbering) and B k-tiles 0..3; k-tile 0 needs the
-            // first two batches and B k-tile 0: they go first, the 24 loads behind them may still be in flight
+        // batches 0..3 of both; k-tile 0 needs the first two, the 16 loads behind them may still be in flight
 #pragma unroll
-            for (int b = 0; b < 5; ++b) {
-                open_a();
+        for (int b = 0; b < 4; ++b) {
+            open_a();
+            open_b();
 #pragma unroll
-                for (int j = 0; j < 4; ++j) ALCH_DMA_A(b - 5, j);
-                if (b >= 1) {
-                    open_b();
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) ALCH_DMA_B(b - 1, j);
-                }
-            }
-            asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
-        } else {
-#pragma unroll
-            for (int s = 0; s < kStages; ++s) {
-                open_a();
-                open_b();
-#pragma unroll
-                for (int j = 0; j < 4; ++j) { ALCH_DMA_A(s, j); ALCH_DMA_B(s, j); }
-            }
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerTile * (kStages - 1)) : "memory");
+            for (int j = 0; j < 4; ++j) { ALCH_DMA_A(b, j); ALCH_DMA_B(b, j); }
         }
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerTile) : "memory");
         __syncthreads();
         Frags f0, f1;
 #pragma unroll
@@ -277,7 +260,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
         for (int kt = 0;; kt += kU) {
 #pragma unroll
             for (int s = 0; s < kU; ++s) {
-                if (kt + s >= nk) goto steps_done;
+                if ((!(AK || BKM) || s % 2 == 0) && kt + s >= nk) goto steps_done;  // (k-major operands: whole pairs of k-tiles)
                 const int st = s, stn = (s + 1) % kU;
                 // ---- first half: MFMAs on k 0..15 of this stage, fragment reads for k 16..31.  Their order goes to
                 // and fro over the columns, so that two in a row always share a fragment: the power cap sets the
@@ -295,18 +278,19 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
                 ALCH_MFMA(f0, 2, 3); ALCH_SB(); open_step(IntC<3>{}); ALCH_SB();
                 ALCH_MFMA(f0, 3, 3); ALCH_MFMA(f0, 3, 2); ALCH_MFMA(f0, 3, 1); ALCH_MFMA(f0, 3, 0);
                 ALCH_SB();
-                // k-tile kt+s+1 has landed (this wave's share), and this wave's reads of stage s are done
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kLoadsPerTile * (kDepth - 2)) : "memory");
-                // ---- second half: MFMAs on k 16..31, refill of stage s, fragment reads of the next stage
+                // odd steps: the batches of k-tiles kt+s+1 and kt+s+2 have landed (this wave's share: what may still be in
+                // flight is the batch that step s-1 issued), and this wave's reads of k-tiles kt+s-1 and kt+s are done
+                if (s % 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kLoadsPerTile) : "memory");
+                // ---- second half: MFMAs on k 16..31, loads of batch s + 4, fragment reads of the next k-tile
                 ALCH_SB();
-                ALCH_DMA_A(s, 0); ALCH_RA(f0, stn, 0, 0); ALCH_RA(f0, stn, 0, 1); ALCH_MFMA(f1, 0, 0); ALCH_MFMA(f1, 0, 1); ALCH_SB();
-                ALCH_DMA_A(s, 1); ALCH_RA(f0, stn, 0, 2); ALCH_RA(f0, stn, 0, 3); ALCH_MFMA(f1, 0, 2); ALCH_MFMA(f1, 0, 3); ALCH_SB();
-                ALCH_DMA_A(s, 2); ALCH_RB(f0, stn, 0, 0); ALCH_MFMA(f1, 1, 3); ALCH_MFMA(f1, 1, 2); ALCH_SB();
-                ALCH_DMA_A(s, 3); ALCH_RB(f0, stn, 0, 1); ALCH_MFMA(f1, 1, 1); ALCH_MFMA(f1, 1, 0); ALCH_SB();
-                ALCH_DMA_B(s, 0); ALCH_RB(f0, stn, 0, 2); ALCH_MFMA(f1, 2, 0); ALCH_MFMA(f1, 2, 1); ALCH_SB();
-                ALCH_DMA_B(s, 1); ALCH_RB(f0, stn, 0, 3); ALCH_MFMA(f1, 2, 2); ALCH_MFMA(f1, 2, 3); ALCH_SB();
-                ALCH_DMA_B(s, 2); ALCH_MFMA(f1, 3, 3); ALCH_MFMA(f1, 3, 2); ALCH_SB();
-                ALCH_DMA_B(s, 3); ALCH_MFMA(f1, 3, 1); ALCH_MFMA(f1, 3, 0); ALCH_SB();
+                ALCH_DMA_A(s + 4, 0); ALCH_RA(f0, stn, 0, 0); ALCH_RA(f0, stn, 0, 1); ALCH_MFMA(f1, 0, 0); ALCH_MFMA(f1, 0, 1); ALCH_SB();
+                ALCH_DMA_A(s + 4, 1); ALCH_RA(f0, stn, 0, 2); ALCH_RA(f0, stn, 0, 3); ALCH_MFMA(f1, 0, 2); ALCH_MFMA(f1, 0, 3); ALCH_SB();
+                ALCH_DMA_A(s + 4, 2); ALCH_RB(f0, stn, 0, 0); ALCH_MFMA(f1, 1, 3); ALCH_MFMA(f1, 1, 2); ALCH_SB();
+                ALCH_DMA_A(s + 4, 3); ALCH_RB(f0, stn, 0, 1); ALCH_MFMA(f1, 1, 1); ALCH_MFMA(f1, 1, 0); ALCH_SB();
+                ALCH_DMA_B(s + 4, 0); ALCH_RB(f0, stn, 0, 2); ALCH_MFMA(f1, 2, 0); ALCH_MFMA(f1, 2, 1); ALCH_SB();
+                ALCH_DMA_B(s + 4, 1); ALCH_RB(f0, stn, 0, 3); ALCH_MFMA(f1, 2, 2); ALCH_MFMA(f1, 2, 3); ALCH_SB();
+                ALCH_DMA_B(s + 4, 2); ALCH_MFMA(f1, 3, 3); ALCH_MFMA(f1, 3, 2); ALCH_SB();
+                ALCH_DMA_B(s + 4, 3); ALCH_MFMA(f1, 3, 1); ALCH_MFMA(f1, 3, 0); ALCH_SB();
             }
         }
     steps_done:
@@ -539,7 +523,7 @@ bool gemm_mfma_supported(const GemmDesc& d) {
 // How the 256x256 kernel walks a product: tiles q < q_end of every XCD's share whole, the rest in `parts` parts of
 // `per` k-tiles each.
 struct BigPlan { int q_end, parts, per; };
-static BigPlan big_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes) {
+static BigPlan big_plan(const MfmaGemmParams& p, bool kmajor, int n_cu, size_t ws_bytes) {
     const int per_xcd = ceil_div(ceil_div(p.M, BM) * ceil_div(p.N, BN), 8), wgx = n_cu / 8;
     const int full_q = per_xcd / wgx * wgx, rem = per_xcd - full_q;
     BigPlan b{per_xcd, 1, 0};
@@ -555,7 +539,7 @@ static BigPlan big_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t
             b.q_end = full_q;
             b.parts = s;
             b.per = ceil_div(nk_total, s);
-            if (a_kmajor) b.per += b.per & 1;  // parts start on a 64-k boundary: whole 128-byte lines of A
+            if (kmajor) b.per += b.per & 1;  // parts are whole 64 k, which the loop takes k-major operands in
         }
     }
     return b;
@@ -575,7 +559,7 @@ bool gemm_cols_together(const GemmDesc& d) {
     const size_t ws_bytes = aligned16(d.split_ws) && d.split_ws ? d.split_ws_bytes : 0;
     for (int s = -1; s < d.n_out; ++s) {
         p.N = s < 0 ? d.N : (s + 1 < d.n_out ? d.out[s + 1].m_begin : d.N) - d.out[s].m_begin;
-        if (big_plan(p, d.a_kmajor, n_cu, ws_bytes).parts > 1) return false;
+        if (big_plan(p, d.a_kmajor || d.b_kmajor, n_cu, ws_bytes).parts > 1) return false;
     }
     return true;
 }
@@ -585,7 +569,7 @@ bool gemm_cols_together(const GemmDesc& d) {
 // besides, with the last round on its own.  The constants are fits to measured products of 128 .. 8192 rows,
 // K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 % (both kernels on 40
 // products: profiles/contraction_kernels_both_sides.txt; the one taken is never more than 2 % behind the other):
-//   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round; a last round that is cut along K adds its two kernels
+//   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round (forward 0.0222 K); a last round that is cut along K adds its two kernels
 //   128x256 tiles, two per compute unit:   0.0265 K + 2 us a round (0.0255 K + 3 weight gradient, 0.0276 K + 6 forward);
 //                                          with one per compute unit, half of that
 // The second one reads 1.5 times as much from L2 per multiply-add, which the long K pays for (8192 x 4096 x 28672: 1388
@@ -602,7 +586,7 @@ static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, const Pair
     const double swiglu_split = p.epilogue == kEpiSwigluBwd ? 15.0 : 0.0;  // its finish kernel also moves G, U, dG, dU, Act
 
     const int tiles = ceil_div(ceil_div(p.M, BM) * ceil_div(p.N, BN), 8);
-    const double big_k = b_kmajor ? 0.0238 : 0.0232, big_fixed = 11.0;
+    const double big_k = b_kmajor ? 0.0222 : 0.0232, big_fixed = 11.0;
     double big = tiles / cus * (big_k * K + big_fixed);
     if (tiles % cus) big += b.parts > 1 ? big_k * K / b.parts + 33.0 + swiglu_split : 0.9 * big_k * K + big_fixed;
 
@@ -682,7 +666,7 @@ static int plan_product(const GemmDesc& d, MfmaProduct& out) {
     ALCH_TRY(compute_units(&out.n_cu));
     out.split_ws = aligned16(d.split_ws) ? static_cast<float*>(d.split_ws) : nullptr;
     const size_t ws_bytes = out.split_ws ? d.split_ws_bytes : 0;
-    out.big = big_plan(p, d.a_kmajor, out.n_cu, ws_bytes);
+    out.big = big_plan(p, d.a_kmajor || d.b_kmajor, out.n_cu, ws_bytes);
     // (a 256x256 tile is two tiles of the other kernel, numbered in the same order)
     out.pair = d.keep_parts ? PairPlan{2 * ceil_div(nt, 8), 2 * out.big.q_end, out.big.parts, out.big.per}
                             : pair_plan(p, d.a_kmajor, out.n_cu, ws_bytes);
