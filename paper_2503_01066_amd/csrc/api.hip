@@ -417,6 +417,37 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         return ALCH_OK;
     };
 
+    // bf16: what reads Act, dG and dU forms t1 or t2 and a gradient in one pass (launch_lora_pass).  t1 of gate and up has to
+    // be there by then, so H2 is formed ahead of the MLP's products.  Slots: T1 holds t1 of gate, up (then o) and d, T2 t2 of
+    // d, then of gate, up, and of o in its third slot; q, k, v come after all of them have been read.
+    auto slot = [&](void* t, int i) { return at(t, (size_t)i * kLoraSlot, E); };
+    auto wants_dB = [&](int pj) { return wants(pj) && lg->dB[pj]; };
+    auto add_up = [&](LoraPass& j, const void* q, int q_slot, void* C, long long ldc, int transposed) {
+        if (!C) return;
+        j.Q = q;
+        j.up[j.n_up++] = {q_slot * kLoraSlot, C, ldc, transposed};
+    };
+    LoraPass mlp[3] = {};  // Act, dG, dU
+    if (lo) {
+        if (has(ALCH_PROJ_D)) {
+            mlp[0].X = p.Act; mlp[0].ldx = F; mlp[0].K = F;
+            if (wants_dB(ALCH_PROJ_D)) { mlp[0].P = lo->A[ALCH_PROJ_D]; mlp[0].ldp = F; mlp[0].T = slot(p.T1, 2); }
+            if (wants(ALCH_PROJ_D)) add_up(mlp[0], p.T2, 0, lg->dA[ALCH_PROJ_D], F, 0);
+        }
+        for (int i = 0; i < 2; ++i) {
+            const int pj = ALCH_PROJ_G + i;
+            LoraPass& j = mlp[1 + i];
+            j.X = at(p.dGU, (size_t)i * F, E); j.ldx = 2 * (long long)F; j.K = F;
+            j.T = slot(p.T2, i);
+            j.pad = true;
+            j.keep_bits = true;
+            if (has(pj)) { j.P = p.Bt[pj]; j.ldp = F; }
+            if (wants_dB(pj)) add_up(j, p.T1, i, lg->dB[pj], r, 1);
+        }
+    }
+    const int t2_alone = ceil_div(r / 8, kDownGroups);  // problems of a t2 by itself
+    const bool one_pass = lo && dt == ALCH_BF16 && T > 0 && H % 64 == 0 && QD % 64 == 0 && lora_pass_fits(mlp, 3, T, adapter_sums);
+
     // Loss mask.  Rows of dY whose mask byte is 0 count as zero.  Everything from the MLP down to the
     // attention output projection is row-local, so those rows contribute nothing there and receive nothing:
     //   compact mode (bf16, matrix-core shapes, no adapters): the kept rows of dY, X2, O, G, U are gathered
@@ -456,12 +487,21 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         }
     }
 
-    // MLP down projection: dAct = dY Wd, fused with the SwiGLU gradient -> [dG | dU] and Act
-    if (has(ALCH_PROJ_D)) {
+    if (one_pass) {  // H2, t1 of gate and up, t2 of d
+        LoraDown jobs[3];
+        int n = 0;
+        for (int i = 0; i < 2; ++i)
+            if (wants_dB(ALCH_PROJ_G + i)) jobs[n++] = LoraDown{p.Hn, H, H, lo->A[ALCH_PROJ_G + i], H, r, slot(p.T1, i)};
+        if (n > 0 && !hn_ready) ALCH_TRY(launch_rmsnorm_fwd(dt, mX2, w.g2, p.Hn, T, H, s.rms_eps, st));
+        hn_ready = hn_ready || n > 0;
+        if (has(ALCH_PROJ_D)) jobs[n++] = LoraDown{mY, H, H, p.Bt[ALCH_PROJ_D], H, r, slot(p.T2, 0)};
+        if (n > 0) ALCH_TRY(launch_lora_down(dt, jobs, n, T, lo->scale, ldt2, kLoraSlot, st, t2_alone));
+    } else if (has(ALCH_PROJ_D)) {
         const void* dys[1] = {mY};
         const int outs1[1] = {H};
         ALCH_TRY(down_t2(ALCH_PROJ_D, 1, dys, H, outs1));
     }
+    // MLP down projection: dAct = dY Wd, fused with the SwiGLU gradient -> [dG | dU] and Act
     {
         GemmDesc d = gemm_ws(dt, T, F, true, false);
         d.m_dev = ndev;
@@ -489,12 +529,15 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     add_out(dH2, p.dHn, 0, H);
     const bool dwd_beside = g.dWd && gemm_together(dH2, dWd);
     if (g.dWd && !dwd_beside) ALCH_TRY(launch_gemm(dWd, st));
-    {
+    if (one_pass) {
+        ALCH_TRY(launch_lora_pass(mlp + (has(ALCH_PROJ_D) ? 0 : 1), (lora_gu ? 3 : 1) - (has(ALCH_PROJ_D) ? 0 : 1), T, ldt2, lo->scale,
+                                  adapter_sums, st));
+    } else {
         const void* dys[1] = {mY};
         const int outs1[1] = {H};
         ALCH_TRY(adapter_grads(ALCH_PROJ_D, 1, p.Act, F, F, dys, H, outs1));
     }
-    if (lora_gu) {
+    if (lora_gu && !one_pass) {
         const void* dys[2] = {p.dGU, at(p.dGU, F, E)};
         const int outs2[2] = {F, F};
         ALCH_TRY(down_t2(ALCH_PROJ_G, 2, dys, 2 * (long long)F, outs2));
@@ -511,7 +554,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
                                     gains_together ? static_cast<float*>(p.Act) : p.partial, T, H, s.rms_eps, st, ndev,
                                     need_h2 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
     }
-    {
+    if (!one_pass) {
         const void* dys[2] = {p.dGU, at(p.dGU, F, E)};
         const int outs2[2] = {F, F};
         ALCH_TRY(adapter_grads(ALCH_PROJ_G, 2, p.Hn, H, H, dys, 2 * (long long)F, outs2));
@@ -519,7 +562,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     GemmDesc dO = gemm_ws(dt, T, QD, true, false);  // dO = dX2 Wo
     dO.m_dev = ndev;
     add_seg(dO, mdX2, H, w.Wo, QD, H);
-    if (has(ALCH_PROJ_O)) add_seg(dO, p.T2, ldt2, p.Ap_o, QD, kLoraSlot);
+    if (has(ALCH_PROJ_O)) add_seg(dO, slot(p.T2, one_pass ? 2 : 0), ldt2, p.Ap_o, QD, kLoraSlot);
     add_out(dO, mdO, 0, QD);
     GemmDesc dWgu = gemm_ws(dt, 2 * F, H, false, false);  // [dWg; dWu] = [dG | dU]^T H2
     bool dwgu_beside = false;
@@ -550,13 +593,29 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         }
     }
 
-    if (has(ALCH_PROJ_O)) {
+    if (one_pass && has(ALCH_PROJ_O)) {  // t2, t1
+        LoraDown jobs[2] = {{mdX2, H, H, p.Bt[ALCH_PROJ_O], H, r, slot(p.T2, 2)}, {mO, QD, QD, lo->A[ALCH_PROJ_O], QD, r, slot(p.T1, 0)}};
+        ALCH_TRY(launch_lora_down(dt, jobs, wants_dB(ALCH_PROJ_O) ? 2 : 1, T, lo->scale, ldt2, kLoraSlot, st, t2_alone));
+    } else if (has(ALCH_PROJ_O)) {
         const void* dys[1] = {mdX2};
         const int outs1[1] = {H};
         ALCH_TRY(down_t2(ALCH_PROJ_O, 1, dys, H, outs1));
     }
     ALCH_TRY(dwgu_beside ? launch_gemm_together(dO, dWgu, st) : launch_gemm(dO, st));
-    {
+    if (one_pass) {  // the gradients that are left of d, gate, up and o
+        LoraPass rest[4] = {};
+        auto open = [&](LoraPass& j, const void* x, int K) { j.X = x; j.ldx = K; j.K = K; };
+        open(rest[0], mY, H);
+        if (wants(ALCH_PROJ_D)) add_up(rest[0], p.T1, 2, lg->dB[ALCH_PROJ_D], r, 1);
+        open(rest[1], p.Hn, H);
+        for (int i = 0; i < 2; ++i)
+            if (wants(ALCH_PROJ_G + i)) add_up(rest[1], p.T2, i, lg->dA[ALCH_PROJ_G + i], H, 0);
+        open(rest[2], mdX2, H);
+        if (wants(ALCH_PROJ_O)) add_up(rest[2], p.T1, 0, lg->dB[ALCH_PROJ_O], r, 1);
+        open(rest[3], mO, QD);
+        if (wants(ALCH_PROJ_O)) add_up(rest[3], p.T2, 2, lg->dA[ALCH_PROJ_O], QD, 0);
+        ALCH_TRY(launch_lora_pass(rest, 4, T, ldt2, lo->scale, adapter_sums, st));
+    } else {
         const void* dys[1] = {mdX2};
         const int outs1[1] = {H};
         ALCH_TRY(adapter_grads(ALCH_PROJ_O, 1, mO, QD, QD, dys, H, outs1));
@@ -612,7 +671,25 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
                                     need_h1 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
         if (gains_together) ALCH_TRY(launch_gain_sums(dt, gains, H, acc, st));
     }
-    {
+    if (one_pass) {
+        const size_t first[3] = {0, (size_t)QD, (size_t)(QD + KD)};
+        const int width[3] = {QD, KD, KD};
+        LoraDown t1[3];
+        LoraPass jobs[4] = {};
+        int n = 0;
+        jobs[3].X = p.Hn; jobs[3].ldx = H; jobs[3].K = H;
+        for (int i = 0; i < 3; ++i) {
+            const int pj = ALCH_PROJ_Q + i;
+            jobs[i].X = at(p.dQKV, first[i], E); jobs[i].ldx = QKV; jobs[i].K = width[i];
+            if (wants_dB(pj)) {
+                t1[n++] = LoraDown{p.Hn, H, H, lo->A[pj], H, r, slot(p.T1, i)};
+                add_up(jobs[i], p.T1, i, lg->dB[pj], r, 1);
+            }
+            if (wants(pj)) add_up(jobs[3], p.T2, i, lg->dA[pj], H, 0);
+        }
+        if (n) ALCH_TRY(launch_lora_down(dt, t1, n, T, lo->scale, ldt2, kLoraSlot, st));
+        ALCH_TRY(launch_lora_pass(jobs, 4, T, ldt2, lo->scale, adapter_sums, st));
+    } else {
         const void* dys[3] = {p.dQKV, at(p.dQKV, QD, E), at(p.dQKV, QD + KD, E)};
         const int outs3[3] = {QD, KD, KD};
         ALCH_TRY(adapter_grads(ALCH_PROJ_Q, 3, p.Hn, H, H, dys, QKV, outs3));

@@ -99,7 +99,7 @@ struct LoraDownGroup {
     const __bf16* S; long long lds; int rows;  // rows = 0: no such group
     __bf16* Y;                                 // first of the group's eight output columns
 };
-static constexpr int kDownProblems = 6, kDownGroups = 4;
+static constexpr int kDownProblems = 6;
 struct LoraDownProblem {
     const __bf16* X; long long ldx; int K, ngroups;
     LoraDownGroup g[kDownGroups];
@@ -438,8 +438,17 @@ static void launch_down(const LoraDownParams& p, int groups, int Trows, int prob
     else k_lora_down_mfma<4, kRows, kWaves><<<grid, kWaves * 64, 0, stream>>>(p);
 }
 
+// Few rows leave compute units without a work-group, and a wavefront alone on its SIMD takes 0.37 us for a chunk (load,
+// read, four dependent products, one after the other): work-groups of fewer rows and more wavefronts, as long as
+// each finds a compute unit (the sums of a row are then folded from 8 or 16 parts of K instead of 4).  8B shape, us a launch of
+// 32 rows by 4 / 16 rows by 8 / 8 rows by 16 wavefronts: 200 tokens, K 14336 21.5 / 13.6 / 10.2, K 4096 10.3 / 7.4 / 6.2; 900 tokens, two of K 14336 23.4 / 17.9 / 14.8; 2000
+// tokens, one 29.2 / 22.4 / 17.3 and two (500 work-groups of 8 rows) 34.7 / 25.2 / 30.6; 5120 tokens 40.9 / 46.3 / 44.0.
+int lora_down_parts(int Trows, int problems, int n_cu) {
+    return ceil_div(Trows, 8) * problems <= n_cu ? 16 : ceil_div(Trows, 16) * problems <= n_cu ? 8 : 4;
+}
+
 int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows, float alpha, long long ldy,
-                     int slot_cols, hipStream_t stream) {
+                     int slot_cols, hipStream_t stream, int as_problems) {
     if (n_jobs < 1 || n_jobs > 3) return fail(ALCH_ERR_INVALID_ARG, "adapter product: 1..3 problems per launch");
     double flops = 0, bytes = 0;
     bool fast = dt == ALCH_BF16;
@@ -477,15 +486,11 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
         bytes = 0;
         for (int i = 0; i < np; ++i) bytes += (double)Trows * p.pr[i].K * dtype_size(dt);
         TraceScope ts(kTraceLora, flops, bytes, stream);
-        // Few rows leave compute units without a work-group, and a wavefront alone on its SIMD takes 0.37 us for a chunk (load,
-        // read, four dependent products, one after the other): work-groups of fewer rows and more wavefronts, as long as
-        // each finds a compute unit (the sums of a row are then folded from 8 or 16 parts of K instead of 4).  8B shape, us a launch of 32 rows by 4 / 16 rows by 8 / 8 rows by 16 wavefronts: 200
-        // tokens, K 14336 21.5 / 13.6 / 10.2, K 4096 10.3 / 7.4 / 6.2; 900 tokens, two of K 14336 23.4 / 17.9 / 14.8; 2000
-        // tokens, one 29.2 / 22.4 / 17.3 and two (500 work-groups of 8 rows) 34.7 / 25.2 / 30.6; 5120 tokens 40.9 / 46.3 / 44.0.
         int n_cu = 0;
         ALCH_TRY(compute_units(&n_cu));
-        if (ceil_div(Trows, 8) * np <= n_cu) launch_down<8, 16>(p, most, Trows, np, stream);
-        else if (ceil_div(Trows, 16) * np <= n_cu) launch_down<16, 8>(p, most, Trows, np, stream);
+        const int parts = lora_down_parts(Trows, as_problems > 0 ? as_problems : np, n_cu);
+        if (parts == 16) launch_down<8, 16>(p, most, Trows, np, stream);
+        else if (parts == 8) launch_down<16, 8>(p, most, Trows, np, stream);
         else launch_down<32, 4>(p, most, Trows, np, stream);
     } else {
         TraceScope ts(kTraceLora, flops, bytes, stream);
@@ -496,6 +501,15 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
     }
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
+}
+
+void add_lora_up_job(LoraUpSums& sums, const LoraUp& j, int nsplit) {
+    LoraUpParams& p = sums.p;
+    const LoraUpJob* before = p.n_jobs > 0 ? &p.job[p.n_jobs - 1] : nullptr;
+    const int first_group = before ? before->first_group + ceil_div((long long)before->N * p.r, (long long)kSumsPerGroup) : 0;
+    p.job[p.n_jobs++] = LoraUpJob{j.S, j.lds, j.X, j.ldx, j.N, nsplit, nsplit > 0 ? ceil_div(p.Trows, nsplit) : 0, j.C, j.ldc,
+                                  j.transposed, first_group, sums.floats};
+    sums.floats += (long long)p.r * nsplit * j.N;
 }
 
 int launch_lora_up(alch_dtype dt, const LoraUp* jobs, int n_jobs, LoraUpSums& sums, hipStream_t stream) {
@@ -517,11 +531,7 @@ int launch_lora_up(alch_dtype dt, const LoraUp* jobs, int n_jobs, LoraUpSums& su
     for (int i = 0; i < n_jobs; ++i) {
         const LoraUp& j = jobs[i];
         const int nsplit = Trows > 0 ? up_splits(Trows, j.N) : 0;
-        const LoraUpJob* before = p.n_jobs > 0 ? &p.job[p.n_jobs - 1] : nullptr;
-        const int first_group = before ? before->first_group + ceil_div((long long)before->N * r, (long long)kSumsPerGroup) : 0;
-        p.job[p.n_jobs++] = LoraUpJob{j.S, j.lds, j.X, j.ldx, j.N, nsplit, nsplit > 0 ? ceil_div(Trows, nsplit) : 0, j.C, j.ldc,
-                                      j.transposed, first_group, sums.floats};
-        sums.floats += (long long)r * nsplit * j.N;
+        add_lora_up_job(sums, j, nsplit);
         flops += 2.0 * Trows * j.N * r;
         bytes += (double)Trows * j.N * dtype_size(dt);
         max_slabs = std::max(max_slabs, ceil_div(j.N, 512));
