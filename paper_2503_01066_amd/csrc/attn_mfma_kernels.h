@@ -1022,8 +1022,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) Ot[n][e] = 0.f;
     float m2 = -INFINITY, l = 0.f;  // running max (log2 domain) and normaliser of this lane's half of the keys
-    bool rows_again = false;
     float m_raw = -INFINITY;        // heads of 64: the running max of the raw scores (m2 is it, scaled and rounded)
+    bool rows_again = false;
 
     const uint32_t lane_d = frag_d_lane<kD>(lane), lane_r0 = frag_rows_lane<kD>(lane, 0), lane_r1 = frag_rows_lane<kD>(lane, 1);
     uint32_t voff[kLoads];
@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
         const bool in_pre = it < npt;
         const int jt = (in_pre ? it : it - npt) * kTileRows;  // first key of the tile inside its own sequence
         const int lim = in_pre ? pre_len - 1 : i;             // last key of the tile's sequence this query sees
-        // (a tile wholly above this wave's diagonal is computed and fully masked: p = 0, alpha = 1)
+        if (!in_pre && jt > i0 + 31) continue;  // wholly above this wave's diagonal
         f32x16 St[2];
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) {
@@ -1067,45 +1067,57 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_mfma(AttnFwdParams p) {
             for (int kk = 0; kk < kKK; ++kk)
                 St[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_d(tk + jb * 32 * kRowBytes, lane_d, kk), qf[kk], St[jb], 0, 0, 0);
         }
-        // scores, masked (key j = jt + jb*32 + 8b + 4*half + r must satisfy j <= lim); heads of 128 take them to the log2
-        // domain here, heads of 64 inside the exponent, where it costs no rounding
+        // scores; heads of 128 take them to the log2 domain here, heads of 64 inside the exponent, where it costs no rounding
         constexpr bool kTwo = AttnTile<kD>::kTwo;
-        const bool need_mask = jt + 63 > (in_pre ? pre_len - 1 : i0);
+        if constexpr (!kTwo) {
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) St[jb][e] *= sl2;
+        }
+        // masked: key j = jt + jb*32 + 8b + 4*half + r must satisfy j <= lim
+        if (jt + 63 > (in_pre ? pre_len - 1 : i0)) {
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (jt + jb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) > lim) St[jb][e] = -INFINITY;
+        }
         float mx = kTwo ? m_raw : m2;
+        const float m_old = mx;
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                float sv = kTwo ? St[jb][e] : St[jb][e] * sl2;
-                if (need_mask) {
-                    const int j = jt + jb * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-                    if (j > lim) sv = -INFINITY;
-                }
-                St[jb][e] = sv;
-                mx = fmaxf(mx, sv);
-            }
+            for (int e = 0; e < 16; ++e) mx = fmaxf(mx, St[jb][e]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // both halves of the wave share the query
-        if (kTwo) {
-            m_raw = mx;
-            mx *= sl2;
-            asm("" : "+v"(mx));  // (the rounded product everywhere: fused into the differences below, each tile would rescale by its rounding)
+        // The vector port bounds the kernel, so the sums are rescaled only where a maximum of the wavefront moved (with the tiles
+        // above its diagonal left out: 6 sequences of 5003 tokens, 32/8 heads of 128 82 -> 74 us, 2 of 4096 394 -> 351, heads of
+        // 64 283 -> 248, same bits).  A reference that was left behind by up to 2^8, so that hardly a tile rescales, gave another
+        // 5 %, and O 2-15 % further from 64 bits: the largest probability of a row is one here, which no rounding changes.
+        float alpha = 1.f;
+        if (__any(mx > m_old)) {
+            if (kTwo) {
+                m_raw = mx;
+                mx *= sl2;
+                asm("" : "+v"(mx));  // (the rounded product everywhere: fused into the differences below, each tile would rescale by its rounding)
+            }
+            alpha = __builtin_amdgcn_exp2f(m2 - mx);  // 0 on the first tile (m2 = -inf), keys 0.. always valid
+            m2 = mx;
+#pragma unroll
+            for (int n = 0; n < kNB; ++n)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) Ot[n][e] *= alpha;
         }
-        const float alpha = __builtin_amdgcn_exp2f(m2 - mx);  // 0 on the first tile (m2 = -inf), keys 0.. always valid
-        m2 = mx;
         float sum = 0.f;
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float pr = __builtin_amdgcn_exp2f(kTwo ? __builtin_fmaf(St[jb][e], sl2, -mx) : St[jb][e] - mx);
+                const float pr = __builtin_amdgcn_exp2f(kTwo ? __builtin_fmaf(St[jb][e], sl2, -m2) : St[jb][e] - m2);
                 St[jb][e] = pr;
                 sum += pr;
             }
         l = l * alpha + sum;
-#pragma unroll
-        for (int n = 0; n < kNB; ++n)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) Ot[n][e] *= alpha;
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
