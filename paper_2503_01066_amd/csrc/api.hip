@@ -528,7 +528,11 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     if (lora_gu) add_seg(dH2, p.T2, ldt2, p.Ap_gu, H, 2 * kLoraSlot);
     add_out(dH2, p.dHn, 0, H);
     const bool dwd_beside = g.dWd && gemm_together(dH2, dWd);
-    if (g.dWd && !dwd_beside) ALCH_TRY(launch_gemm(dWd, st));
+    // Act has had its last reader once dWd and the adapter gradients are formed: where it has the room, it keeps the partial rows of
+    // dg1, so that those of both gains are added together.
+    const bool gains_together = (size_t)T * F * E >= (size_t)rmsnorm_bwd_blocks(T) * H * sizeof(float);
+    const bool dwd_with_norm = g.dWd && !dwd_beside && gains_together && T > 0 && !ndev && gemm_beside_rows(dWd, H);
+    if (g.dWd && !dwd_beside && !dwd_with_norm) ALCH_TRY(launch_gemm(dWd, st));
     if (one_pass) {
         ALCH_TRY(launch_lora_pass(mlp + (has(ALCH_PROJ_D) ? 0 : 1), (lora_gu ? 3 : 1) - (has(ALCH_PROJ_D) ? 0 : 1), T, ldt2, lo->scale,
                                   adapter_sums, st));
@@ -545,14 +549,15 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     ALCH_TRY(dwd_beside ? launch_gemm_together(dH2, dWd, st) : launch_gemm(dH2, st));
     // dX2 = dY + RMSNorm-2 backward(dH2); dg2.  The same pass over X2 leaves H2 for the weight and adapter gradients
     // of the gate and up projections (unless the record completion above already formed it).
-    // Act has had its last reader: where it has the room, it keeps the partial rows of dg2 until those of dg1 are there too.
-    const bool gains_together = (size_t)T * F * E >= (size_t)rmsnorm_bwd_blocks(T) * H * sizeof(float);
     GainSums gains;
     {
         const bool need_h2 = !hn_ready && (g.dWg || g.dWu || wants(ALCH_PROJ_G) || wants(ALCH_PROJ_U));
-        ALCH_TRY(launch_rmsnorm_bwd(dt, p.dHn, mX2, w.g2, mY, nullptr, mdX2, g.dg2, acc,
-                                    gains_together ? static_cast<float*>(p.Act) : p.partial, T, H, s.rms_eps, st, ndev,
-                                    need_h2 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
+        if (dwd_with_norm)
+            ALCH_TRY(launch_gemm_beside_norm(dWd, NormBwdRows{p.dHn, mX2, w.g2, mY, nullptr, mdX2, p.partial, T, H, s.rms_eps,
+                                                              need_h2 ? p.Hn : nullptr}, g.dg2, gains, st));
+        else
+            ALCH_TRY(launch_rmsnorm_bwd(dt, p.dHn, mX2, w.g2, mY, nullptr, mdX2, g.dg2, acc, p.partial, T, H, s.rms_eps, st, ndev,
+                                        need_h2 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
     }
     if (!one_pass) {
         const void* dys[2] = {p.dGU, at(p.dGU, F, E)};
@@ -667,10 +672,20 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     // the q, k, v projections.
     {
         const bool need_h1 = g.dWq || g.dWk || g.dWv || wants(ALCH_PROJ_Q) || wants(ALCH_PROJ_K) || wants(ALCH_PROJ_V);
-        ALCH_TRY(launch_rmsnorm_bwd(dt, p.dHn, sv.X, w.g1, p.dX2, nullptr, dX, g.dg1, acc, p.partial, T, H, s.rms_eps, st, nullptr,
-                                    need_h1 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
-        if (gains_together) ALCH_TRY(launch_gain_sums(dt, gains, H, acc, st));
+        ALCH_TRY(launch_rmsnorm_bwd(dt, p.dHn, sv.X, w.g1, p.dX2, nullptr, dX, g.dg1, acc, gains_together ? static_cast<float*>(p.Act) : p.partial,
+                                    T, H, s.rms_eps, st, nullptr, need_h1 ? p.Hn : nullptr, gains_together ? &gains : nullptr));
     }
+    const bool qkv_together = g.dWq && g.dWk && g.dWv && QD % 256 == 0 && KD % 256 == 0;
+    GemmDesc dWqkv = gemm_ws(dt, QKV, H, false, false);  // dW{q,k,v} = d{Q,K,V}^T H1
+    if (qkv_together) {
+        add_seg(dWqkv, p.dQKV, QKV, p.Hn, H, T);
+        add_out(dWqkv, g.dWq, 0, H);
+        add_out(dWqkv, g.dWk, QD, H);
+        add_out(dWqkv, g.dWv, QD + KD, H);
+        dWqkv.accumulate = acc;
+    }
+    const bool gains_beside = qkv_together && gains.n > 0 && gemm_beside_rows(dWqkv, H);
+    if (!gains_beside) ALCH_TRY(launch_gain_sums(dt, gains, H, acc, st));
     if (one_pass) {
         const size_t first[3] = {0, (size_t)QD, (size_t)(QD + KD)};
         const int width[3] = {QD, KD, KD};
@@ -695,15 +710,9 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         ALCH_TRY(adapter_grads(ALCH_PROJ_Q, 3, p.Hn, H, H, dys, QKV, outs3));
     }
     ALCH_TRY(launch_lora_up_sums(dt, adapter_sums, st));
-    if (g.dWq || g.dWk || g.dWv) {  // dW{q,k,v} = d{Q,K,V}^T H1
-        if (g.dWq && g.dWk && g.dWv && QD % 256 == 0 && KD % 256 == 0) {
-            GemmDesc d = gemm_ws(dt, QKV, H, false, false);
-            add_seg(d, p.dQKV, QKV, p.Hn, H, T);
-            add_out(d, g.dWq, 0, H);
-            add_out(d, g.dWk, QD, H);
-            add_out(d, g.dWv, QD + KD, H);
-            d.accumulate = acc;
-            ALCH_TRY(launch_gemm(d, st));
+    if (g.dWq || g.dWk || g.dWv) {
+        if (qkv_together) {
+            ALCH_TRY(gains_beside ? launch_gemm_beside_gains(dWqkv, gains, H, acc, st) : launch_gemm(dWqkv, st));
         } else {
             void* outs[3] = {g.dWq, g.dWk, g.dWv};
             const int off[3] = {0, QD, QD + KD}, rows[3] = {QD, KD, KD};

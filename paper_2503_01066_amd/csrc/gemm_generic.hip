@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "row_sums.h"
 
 namespace alch {
 
@@ -209,6 +210,22 @@ __global__ __launch_bounds__(kWaves * 64) void k_gemm_f32_two(SlicesJob data, Sl
     __shared__ float red[kWaves * 16 * 64];
     if ((int)blockIdx.x < n_data) slices_job<kWaves, 1>(data, (int)blockIdx.x, red);
     else slices_job<kWaves, 0>(weight, (int)blockIdx.x - n_data, red);
+}
+
+// A weight gradient of four wavefronts a tile behind the rows of an RMSNorm backward, or the sums of the gain gradients, which
+// take a few latencies each on their own (layer of 2 x 128 tokens, hidden 256: dWd 5.8 us and the norm 5.0, dWqkv 6.9 and the sums
+// 3.9).  Same bits.
+template <int kCols>
+__global__ __launch_bounds__(256) void k_gemm_f32_norm(SlicesJob weight, NormBwdRows rows, int n_rows) {
+    __shared__ float red[4 * 16 * 64];
+    if ((int)blockIdx.x < n_rows) rmsnorm_bwd_rows<float, kCols>(rows, (int)blockIdx.x, n_rows, red);
+    else slices_job<4, 0>(weight, (int)blockIdx.x - n_rows, red);
+}
+__global__ __launch_bounds__(256) void k_gemm_f32_gains(SlicesJob weight, GainSums sums, int width, int accumulate, int slabs) {
+    __shared__ float red[4 * 16 * 64];
+    const int n_sums = slabs * sums.n, block = (int)blockIdx.x;
+    if (block < n_sums) gain_sums<float, 4>(sums, block / slabs, block % slabs * 64, width, accumulate, reinterpret_cast<float (*)[64]>(red));
+    else slices_job<4, 0>(weight, block - n_sums, red);
 }
 
 template <typename T>
@@ -450,6 +467,50 @@ static int launch_slices_jobs(const SlicesJob& a, const SlicesJob& b, hipStream_
     return ALCH_OK;
 }
 
+static double job_flops(const GemmDesc& d, double& bytes) {
+    double k_total = 0;
+    for (int s = 0; s < d.n_seg; ++s) k_total += d.seg[s].K;
+    bytes = ((double)d.M * k_total + (double)d.N * k_total + (double)d.M * d.N) * dtype_size(d.dtype);
+    return 2.0 * d.M * d.N * k_total;
+}
+static bool job_beside_rows(const GemmDesc& weight, SlicesJob& job) {
+    if (weight.M <= 0 || weight.N <= 0 || weight.dtype != ALCH_F32 || weight.k_dev || weight.m_dev || weight.by_cols) return false;
+    return !weight.a_kmajor && !weight.b_kmajor && slices_job_of(weight, job) && job.waves == 4;
+}
+bool gemm_beside_rows(const GemmDesc& weight, int width) {
+    SlicesJob job;
+    return width <= 1024 && job_beside_rows(weight, job);
+}
+int launch_gemm_beside_norm(const GemmDesc& weight, NormBwdRows rows, void* dg, GainSums& sums, hipStream_t stream) {
+    SlicesJob job;
+    if (!job_beside_rows(weight, job) || rows.width > 1024 || rows.Trows <= 0) return fail(ALCH_ERR_UNSUPPORTED, "a product that does not run beside rows");
+    const int n_rows = std::min(rows.Trows, kNormBwdBlocks);
+    if (dg) {
+        sums.of[sums.n].partial = rows.partial;
+        sums.of[sums.n].dg = dg;
+        sums.of[sums.n++].rows = n_rows;
+    } else {
+        rows.partial = nullptr;
+    }
+    double bytes;
+    const double flops = job_flops(weight, bytes);
+    TraceScope ts(kTraceGemmGeneric, flops, bytes, stream);
+    if (rows.width <= 256) k_gemm_f32_norm<1><<<n_rows + job.tiles, 256, 0, stream>>>(job, rows, n_rows);
+    else k_gemm_f32_norm<4><<<n_rows + job.tiles, 256, 0, stream>>>(job, rows, n_rows);
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
+}
+int launch_gemm_beside_gains(const GemmDesc& weight, const GainSums& sums, int width, int accumulate, hipStream_t stream) {
+    SlicesJob job;
+    if (!job_beside_rows(weight, job)) return fail(ALCH_ERR_UNSUPPORTED, "a product that does not run beside rows");
+    double bytes;
+    const double flops = job_flops(weight, bytes);
+    TraceScope ts(kTraceGemmGeneric, flops, bytes, stream);
+    const int slabs = ceil_div(width, 64);
+    k_gemm_f32_gains<<<slabs * sums.n + job.tiles, 256, 0, stream>>>(job, sums, width, accumulate, slabs);
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
+}
 
 // The matrix-core kernel addresses an operand through one buffer descriptor and refuses operands of 2 GiB or more.
 // The operands that grow with the batch are indexed by tokens: the rows of a k-major A (data gradients, forward)

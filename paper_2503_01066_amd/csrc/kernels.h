@@ -98,6 +98,21 @@ struct GainSums {
     struct { const float* partial; void* dg; int rows; } of[2];
     int n = 0;
 };
+// Rows of an RMSNorm backward (see launch_rmsnorm_bwd); partial null: no gain gradient.
+struct NormBwdRows {
+    const void *dH, *X, *g, *resid;
+    const uint8_t* resid_mask;
+    void* dX;
+    float* partial;
+    int Trows, width;
+    float eps;
+    void* hn_out;
+};
+// fp32: a weight gradient in one launch with the RMSNorm backward, or with the sums of the gain gradients, that do not depend on
+// it: whether it can be, and those launches (dg as launch_rmsnorm_bwd, left to `sums`).
+bool gemm_beside_rows(const GemmDesc& weight, int width);
+int launch_gemm_beside_norm(const GemmDesc& weight, NormBwdRows rows, void* dg, GainSums& sums, hipStream_t stream);
+int launch_gemm_beside_gains(const GemmDesc& weight, const GainSums& sums, int width, int accumulate, hipStream_t stream);
 int launch_gain_sums(alch_dtype dt, const GainSums& sums, int width, int accumulate, hipStream_t stream);
 int launch_rmsnorm_bwd(alch_dtype dt, const void* dH, const void* X, const void* g, const void* resid,
                        const uint8_t* resid_mask, void* dX, void* dg, int accumulate, float* partial, int T,

@@ -4,17 +4,12 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "row_sums.h"
 
 namespace alch {
 
 template <typename T> __device__ __forceinline__ float ldf(const T* p) { return (float)*p; }
 template <typename T> __device__ __forceinline__ void stf(T* p, float v) { *p = (T)v; }
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
-}
 
 // Sum over a 256-thread block (4 waves); every thread gets the result.
 __device__ __forceinline__ float block_sum(float v, float* smem /*[4]*/) {
@@ -111,63 +106,12 @@ int launch_rmsnorm_fwd(alch_dtype dt, const void* X, const void* g, void* H, int
     return ALCH_OK;
 }
 
-// ---- RMSNorm backward with residual:
-//   dX = resid + r*(g*dH) - X * r^3/width * sum(g*dH*X);   dg partial[blk] = sum over the block's rows of dH*X*r
-static constexpr int kNormBwdBlocks = 1024;
-static constexpr int kNormMaxCols = 32;  // columns per thread: width <= 8192
-
 int rmsnorm_bwd_blocks(int T);
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_rmsnorm_bwd(const T* __restrict__ dH, const T* __restrict__ X,
-                                                     const T* __restrict__ g, const T* __restrict__ resid,
-                                                     const uint8_t* __restrict__ resid_mask, T* __restrict__ dX,
-                                                     float* __restrict__ partial, int Trows, int width, float eps,
-                                                     T* __restrict__ hn_out) {
-    __shared__ float red[4];
-    float dgp[kNormMaxCols];
-    float gv[kNormMaxCols];
-#pragma unroll
-    for (int i = 0; i < kNormMaxCols; ++i) {
-        dgp[i] = 0.f;
-        const int c = threadIdx.x + 256 * i;
-        gv[i] = c < width ? ldf(g + c) : 0.f;
-    }
-    for (long long row = blockIdx.x; row < Trows; row += gridDim.x) {
-        float xv[kNormMaxCols], dv[kNormMaxCols];
-        float ss = 0.f, dot = 0.f;
-#pragma unroll
-        for (int i = 0; i < kNormMaxCols; ++i) {
-            const int c = threadIdx.x + 256 * i;
-            xv[i] = c < width ? ldf(X + row * width + c) : 0.f;
-            dv[i] = c < width ? ldf(dH + row * width + c) : 0.f;
-            ss += xv[i] * xv[i];
-            dot += gv[i] * dv[i] * xv[i];
-        }
-        ss = block_sum(ss, red);
-        dot = block_sum(dot, red);
-        const float r = rsqrtf(ss / (float)width + eps);
-        const float coef = r * r * r / (float)width * dot;
-        const bool keep = resid && !(resid_mask && resid_mask[row] == 0);
-#pragma unroll
-        for (int i = 0; i < kNormMaxCols; ++i) {
-            const int c = threadIdx.x + 256 * i;
-            if (c < width) {
-                float v = r * gv[i] * dv[i] - xv[i] * coef;
-                if (keep) v += ldf(resid + row * width + c);
-                stf(dX + row * width + c, v);
-                if (hn_out) stf(hn_out + row * width + c, xv[i] * r * gv[i]);  // the normalised row
-                dgp[i] += dv[i] * xv[i] * r;
-            }
-        }
-    }
-    if (partial) {
-#pragma unroll
-        for (int i = 0; i < kNormMaxCols; ++i) {
-            const int c = threadIdx.x + 256 * i;
-            if (c < width) partial[(long long)blockIdx.x * width + c] = dgp[i];
-        }
-    }
+template <typename T, int kCols>
+__global__ __launch_bounds__(256) void k_rmsnorm_bwd(NormBwdRows a) {
+    __shared__ float red[8];
+    rmsnorm_bwd_rows<T, kCols>(a, (int)blockIdx.x, (int)gridDim.x, red);
 }
 
 // bf16 fast path: one wavefront per row, 16-byte accesses, no barrier inside the row loop.
@@ -276,33 +220,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm_bwd_bf16(const __bf16* __restri
 template <typename T>
 __global__ __launch_bounds__(1024) void k_colsum_finish_wide(GainSums sums, int width, int accumulate) {
     __shared__ float red[16][64];
-    const float* __restrict__ partial = sums.of[blockIdx.y].partial;
-    T* __restrict__ dg = static_cast<T*>(sums.of[blockIdx.y].dg);
-    const int nblk = sums.of[blockIdx.y].rows;
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), rg = threadIdx.x >> 6;
-    float s = 0.f;
-    if (c < width) {
-        // eight rows requested before the first is added: one after the other their latencies were the kernel's time
-        // (512 x 4096: 10 us, now 5 us; 256 x 256: 6 us, now 4 us)
-        int b = rg;
-        for (; b + 7 * 16 < nblk; b += 8 * 16) {
-            float v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = partial[(long long)(b + 16 * i) * width + c];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) s += v[i];
-        }
-        for (; b < nblk; b += 16) s += partial[(long long)b * width + c];
-    }
-    red[rg][threadIdx.x & 63] = s;
-    __syncthreads();
-    if (rg == 0 && c < width) {
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) t += red[i][threadIdx.x & 63];
-        if (accumulate) t += ldf(dg + c);
-        stf(dg + c, t);
-    }
+    gain_sums<T, 16>(sums, (int)blockIdx.y, (int)blockIdx.x * 64, width, accumulate, red);
 }
 
 int launch_gain_sums(alch_dtype dt, const GainSums& sums, int width, int accumulate, hipStream_t stream) {
@@ -323,8 +241,10 @@ template <typename T>
 static int rmsnorm_bwd_t(const void* dH, const void* X, const void* g, const void* resid, const uint8_t* resid_mask,
                          void* dX, float* partial, int T_, int width, float eps, hipStream_t stream, void* hn_out, int& nblk) {
     nblk = T_ < kNormBwdBlocks ? T_ : kNormBwdBlocks;
-    k_rmsnorm_bwd<T><<<nblk, 256, 0, stream>>>((const T*)dH, (const T*)X, (const T*)g, (const T*)resid, resid_mask,
-                                                (T*)dX, partial, T_, width, eps, (T*)hn_out);
+    const NormBwdRows a{dH, X, g, resid, resid_mask, dX, partial, T_, width, eps, hn_out};
+    if (width <= 256) k_rmsnorm_bwd<T, 1><<<nblk, 256, 0, stream>>>(a);
+    else if (width <= 1024) k_rmsnorm_bwd<T, 4><<<nblk, 256, 0, stream>>>(a);
+    else k_rmsnorm_bwd<T, kNormMaxCols><<<nblk, 256, 0, stream>>>(a);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }

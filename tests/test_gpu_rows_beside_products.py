@@ -1,0 +1,36 @@
+"""fp32 layers whose RMSNorm backward and gain sums share a launch with a weight gradient: hidden sizes either side of the columns
+a thread takes, rows below, at and beyond the partial rows that are added at once, and lengths beyond those launches."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as synth
+from helpers import f64, to_np
+from oracle import WEIGHT_KEYS, layer_backward_reuse
+from test_gpu_layer import REC, compare, make_case
+from helpers import alch_shape, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hidden,T", [(256, 1), (256, 129), (256, 511), (256, 512), (260, 40), (1024, 65), (1028, 30)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_rows_beside_products(monkeypatch, hidden, T, masked):
+    import paper_2503_01066_amd as A
+    monkeypatch.setitem(synth.SHAPES, "rows", (hidden, 4, 4, 64, 512, 1e-5, 10000.0))
+    cu = synth.ragged_cu([min(50, T - a) for a in range(0, T, 50)])
+    shp, osh, W, rec, dY = make_case("rows", "f32", cu, 23, "drawn", dy_std=0.01)
+    mask = synth.keep_mask(T, 0.5, 3) if masked else None
+    ref = layer_backward_reuse(osh, cu, None, f64(rec), f64(W), dY, mask)
+    drec = {k: to_dev(rec[k], "f32") for k in REC}
+    drec["LSE"] = torch.from_numpy(rec["LSE"]).cuda()
+    run = lambda **kw: A.alch_layer_backward(alch_shape(shp, "f32"), A.Batch(cu), drec, {k: to_dev(v, "f32") for k, v in W.items()},
+                                             to_dev(dY, "f32"), loss_mask=None if mask is None else torch.from_numpy(mask).cuda(), **kw)
+    out = run(want=WEIGHT_KEYS)
+    torch.cuda.synchronize()
+    compare({k: to_np(v) for k, v in out.items()}, ref, "f32")
+    # gains without the weight gradients they ran beside: the same sums
+    alone = run(want=("g1", "g2"))
+    torch.cuda.synchronize()
+    for k in ("dg1", "dg2", "dX"):
+        assert np.array_equal(to_np(out[k]), to_np(alone[k])), k
