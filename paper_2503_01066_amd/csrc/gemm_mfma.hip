@@ -92,6 +92,11 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
     // The grid is persistent (one work-group per compute unit): each work-group walks its share of
     // the tiles, so the stores of one tile drain while the next tile's loads are already in flight.
     const int Mv = p.m_dev ? min(__builtin_amdgcn_readfirstlane(*p.m_dev), p.M) : p.M;
+    if (!kSplit && p.either) {
+        bool pair;
+        device_plan(p, Mv, pair);
+        if (pair) return;
+    }
     const int tiles_m = p.m_dev ? (Mv + BM - 1) / BM : p.tiles_m;
     const int nt = tiles_m * p.tiles_n;
     const int per_xcd = (nt + 7) / 8;
@@ -564,40 +569,6 @@ bool gemm_cols_together(const GemmDesc& d) {
     return true;
 }
 
-// Which of the two matrix-core kernels takes a product: the one whose estimated time is shorter.  Both estimates count
-// rounds of tiles over the compute units of an XCD: so many us for each k of the contraction and for what a tile costs
-// besides, with the last round on its own.  The constants are fits to measured products of 128 .. 8192 rows,
-// K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 % (both kernels on 40
-// products: profiles/contraction_kernels_both_sides.txt; the one taken is never more than 2 % behind the other):
-//   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round (forward 0.0222 K); a last round that is cut along K adds its two kernels
-//   128x256 tiles, two per compute unit:   0.0265 K + 2 us a round (0.0255 K + 3 weight gradient, 0.0276 K + 6 forward);
-//                                          with one per compute unit, half of that
-// The second one reads 1.5 times as much from L2 per multiply-add, which the long K pays for (8192 x 4096 x 28672: 1388
-// against 1574 us), and has no idle start and end of tile, nor as coarse a last round (4096 x 14336 x 487: 86 against
-// 60 us; 6144 x 4096 x 1024: 82 against 49; 487 x 4096 x 4096: 47 against 31; 6001 x 4096 x 6144: 262 against 239 us).
-// Whole tiles of the second one fill rounds of two work-groups per compute unit, or a last one of at most one each; the
-// tiles cut along K run beside that.  4099 x 2048 x 16384 is 17 tiles for the 32 compute units of an XCD, or 32 whole tiles
-// of half the size and one in 16 parts: 410 -> 290 us.
-static bool pair_is_better(const MfmaGemmParams& p, const BigPlan& b, const PairPlan& plan, bool a_kmajor, bool b_kmajor, int n_cu) {
-    if (p.m_dev || p.k_dev) return false;  // sizes that only the device knows
-    double K = 0;
-    for (int s = 0; s < p.n_seg; ++s) K += p.K[s];
-    const int cus = n_cu / 8;  // compute units of an XCD
-    const double swiglu_split = p.epilogue == kEpiSwigluBwd ? 15.0 : 0.0;  // its finish kernel also moves G, U, dG, dU, Act
-
-    const int tiles = ceil_div(ceil_div(p.M, BM) * ceil_div(p.N, BN), 8);
-    const double big_k = b_kmajor ? 0.0222 : 0.0232, big_fixed = 11.0;
-    double big = tiles / cus * (big_k * K + big_fixed);
-    if (tiles % cus) big += b.parts > 1 ? big_k * K / b.parts + 33.0 + swiglu_split : 0.9 * big_k * K + big_fixed;
-
-    const double pair_k = b_kmajor ? 0.0276 : a_kmajor ? 0.0265 : 0.0255, pair_fixed = b_kmajor ? 6.0 : a_kmajor ? 2.0 : 3.0;
-    double pair = plan.q_end / (2 * cus) * (pair_k * K + pair_fixed);
-    const int rest = plan.q_end % (2 * cus), cut = plan.per_xcd - plan.q_end, s = plan.parts;
-    if (rest > 0) pair += rest <= cus ? 0.52 * pair_k * K + 4.0 : 0.9 * pair_k * K + pair_fixed;
-    if (cut > 0) pair += (cut * s > cus ? pair_k * K / s + 27.0 : 0.52 * pair_k * K / s + 17.0) + swiglu_split;
-    return pair < big;
-}
-
 int compute_units(int* n_cu) {
     static constexpr int kDevices = 64;
     static std::atomic<int> known[kDevices] = {};  // by device: those of a process need not be alike (partitions)
@@ -619,6 +590,7 @@ int compute_units(int* n_cu) {
 struct MfmaProduct {
     MfmaGemmParams p;
     int n_cu, pair_tiles_m;
+    size_t ws_bytes;
     float* split_ws;
     BigPlan big;
     PairPlan pair;
@@ -665,19 +637,79 @@ static int plan_product(const GemmDesc& d, MfmaProduct& out) {
     const int nt = p.tiles_m * p.tiles_n;
     ALCH_TRY(compute_units(&out.n_cu));
     out.split_ws = aligned16(d.split_ws) ? static_cast<float*>(d.split_ws) : nullptr;
-    const size_t ws_bytes = out.split_ws ? d.split_ws_bytes : 0;
+    const size_t ws_bytes = out.ws_bytes = out.split_ws ? d.split_ws_bytes : 0;
     out.big = big_plan(p, d.a_kmajor || d.b_kmajor, out.n_cu, ws_bytes);
+    int nk_total = 0;
+    long long K = 0;
+    for (int s = 0; s < p.n_seg; ++s) {
+        nk_total += ceil_div(p.K[s], BK);
+        K += p.K[s];
+    }
+    p.either = 0;
+    p.plan_cu = out.n_cu;
+    p.a_kmajor = d.a_kmajor;
+    p.b_kmajor = d.b_kmajor;
+    p.plan_ws = d.keep_parts ? 0 : (long long)ws_bytes;
+    const bool swiglu = p.epilogue == kEpiSwigluBwd;
+    // m_dev: launch_device_rows.  k_dev: whole tiles, of the kernel that is the faster one with half of the tokens kept (its
+    // tiles are the same for any count, and the lengths where the choice turns lie close together)
+    if (p.m_dev || p.k_dev) {
+        out.pair = pair_plan(p.M, p.N, nk_total, d.a_kmajor, out.n_cu, 0);
+        out.pair_tiles_m = ceil_div(p.M, BM / 2);
+        out.as_pair = !p.m_dev && !d.a_kmajor && !d.b_kmajor && pair_is_better(p.M, p.N, K / 2, d.a_kmajor, d.b_kmajor, swiglu, out.n_cu, 1, out.pair);
+        return ALCH_OK;
+    }
     // (a 256x256 tile is two tiles of the other kernel, numbered in the same order)
     out.pair = d.keep_parts ? PairPlan{2 * ceil_div(nt, 8), 2 * out.big.q_end, out.big.parts, out.big.per}
-                            : pair_plan(p, d.a_kmajor, out.n_cu, ws_bytes);
+                            : pair_plan(p.M, p.N, nk_total, d.a_kmajor, out.n_cu, (long long)ws_bytes);
     out.pair_tiles_m = d.keep_parts ? 2 * p.tiles_m : ceil_div(p.M, BM / 2);
-    out.as_pair = pair_is_better(p, out.big, out.pair, d.a_kmajor, d.b_kmajor, out.n_cu);
+    out.as_pair = pair_is_better(p.M, p.N, K, d.a_kmajor, d.b_kmajor, swiglu, out.n_cu, out.big.parts, out.pair);
+    return ALCH_OK;
+}
+
+static void launch_big(const MfmaGemmParams& p, int grid, hipStream_t stream) {
+    if (p.a_kmajor && p.b_kmajor) k_gemm_mfma<true, true><<<grid, 256, 0, stream>>>(p);
+    else if (p.a_kmajor) k_gemm_mfma<true, false><<<grid, 256, 0, stream>>>(p);
+    else if (!p.b_kmajor) k_gemm_mfma<false, false><<<grid, 256, 0, stream>>>(p);
+    else k_gemm_mfma<false, true><<<grid, 256, 0, stream>>>(p);
+}
+
+// A product whose row count lies on the device (the rows that a loss mask keeps): every kernel that some count of rows up to M
+// calls for is launched, and reads the count.  With 256x256 tiles alone, whole, a few hundred kept rows left most compute
+// units without work and the others with all of a long contraction: the gradient of H2 of 175 kept rows (4096 columns, K 28672)
+// was 474 us on 16 busy compute units.  Layers with a quarter of the rows kept: 700 tokens 1038 -> 526 us, 1500 tokens 1202 -> 751,
+// 5003 tokens and a tenth of them 1751 -> 1257; where the 256x256 tiles stay (hidden 8192, 8192 tokens) 8989 and 8988.
+static int launch_device_rows(MfmaProduct& m, hipStream_t stream) {
+    MfmaGemmParams& p = m.p;
+    int pair_most = 0, cut_most = 0;
+    bool any_big = false;
+    for (int rows = PM; rows < p.M + PM; rows += PM) {
+        bool pair;
+        const PairPlan plan = device_plan(p, std::min(rows, p.M), pair);
+        if (!pair || !p.a_kmajor) {
+            any_big = true;
+            continue;
+        }
+        pair_most = std::max(pair_most, pair_grid(plan));
+        if (plan.parts > 1) cut_most = std::max(cut_most, plan.per_xcd - plan.q_end);
+    }
+    p.either = any_big && pair_most > 0;
+    if (any_big) {
+        const int nt = p.tiles_m * p.tiles_n;
+        p.q_end = ceil_div(nt, 8);
+        p.split_ws = nullptr;
+        p.split_s = 1;
+        launch_big(p, std::min(ceil_div(nt, 8) * 8, m.n_cu), stream);
+    }
+    if (pair_most > 0) ALCH_TRY(launch_gemm_pair_rows(p, pair_most, cut_most, m.split_ws, stream));
+    ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
 
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     MfmaProduct m;
     ALCH_TRY(plan_product(d, m));
+    if (d.m_dev) return launch_device_rows(m, stream);
     if (m.as_pair) return launch_gemm_pair(m.p, d.a_kmajor, d.b_kmajor, m.pair_tiles_m, m.pair, m.split_ws, stream);
     MfmaGemmParams& p = m.p;
     const BigPlan& plan = m.big;
@@ -690,18 +722,12 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     p.split_s = plan.parts;
     p.split_per = plan.per;
     const int grid_split = 8 * rem * p.split_s;
-    if (d.a_kmajor && d.b_kmajor) {
-        if (p.q_end > 0) k_gemm_mfma<true, true><<<grid, 256, 0, stream>>>(p);
-        if (p.split_s > 1) k_gemm_mfma<true, true, true><<<grid_split, 256, 0, stream>>>(p);
-    } else if (d.a_kmajor && !d.b_kmajor) {
-        if (p.q_end > 0) k_gemm_mfma<true, false><<<grid, 256, 0, stream>>>(p);
-        if (p.split_s > 1) k_gemm_mfma<true, false, true><<<grid_split, 256, 0, stream>>>(p);
-    } else if (!d.a_kmajor && !d.b_kmajor) {
-        if (p.q_end > 0) k_gemm_mfma<false, false><<<grid, 256, 0, stream>>>(p);
-        if (p.split_s > 1) k_gemm_mfma<false, false, true><<<grid_split, 256, 0, stream>>>(p);
-    } else {
-        if (p.q_end > 0) k_gemm_mfma<false, true><<<grid, 256, 0, stream>>>(p);
-        if (p.split_s > 1) k_gemm_mfma<false, true, true><<<grid_split, 256, 0, stream>>>(p);
+    if (p.q_end > 0) launch_big(p, grid, stream);
+    if (p.split_s > 1) {
+        if (d.a_kmajor && d.b_kmajor) k_gemm_mfma<true, true, true><<<grid_split, 256, 0, stream>>>(p);
+        else if (d.a_kmajor) k_gemm_mfma<true, false, true><<<grid_split, 256, 0, stream>>>(p);
+        else if (!d.b_kmajor) k_gemm_mfma<false, false, true><<<grid_split, 256, 0, stream>>>(p);
+        else k_gemm_mfma<false, true, true><<<grid_split, 256, 0, stream>>>(p);
     }
     if (p.split_s > 1) k_gemm_split_finish<<<dim3(8 * rem, BM / 16), 256, 0, stream>>>(p, per_xcd, nt);
     ALCH_HIP_TRY(hipGetLastError());

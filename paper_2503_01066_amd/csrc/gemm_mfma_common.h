@@ -44,6 +44,10 @@ struct MfmaGemmParams {
     float* split_ws;
     int split_s, split_per;  // parts per tile; k-tiles per part (counted over all operand pairs in order)
     int per_xcd;             // k_gemm_pair: tiles of an XCD's share
+    // m_dev: k_gemm_pair plans on the device, for plan_cu compute units and plan_ws bytes of scratch (0: no tile is cut);
+    // either: both kernels are launched, and the one that the estimate does not choose leaves at once.
+    int either, plan_cu, a_kmajor, b_kmajor;
+    long long plan_ws;
 };
 
 // output range that row (or column) x of the product belongs to
@@ -127,11 +131,82 @@ __device__ __forceinline__ void swiglu_gradient(const V& dv, const V& gv, const 
     }
 }
 
-// The kernel of 128x256 tiles.  A share of per_xcd tiles per XCD (of tiles_m tile rows, the last may be empty), whole up
-// to q_end, the others in `parts` parts of `per` k-tiles each, with their partial tiles in split_ws.
+// ---- how the kernel of 128x256 tiles walks a product, and which of the two kernels takes it.  In whole numbers: products whose
+// row count only the device knows are planned there, and every kernel of theirs has to come to the same answer.
+static constexpr int PM = 128, PN = 256;
+__host__ __device__ inline int up_div(int a, int b) { return (a + b - 1) / b; }
+__host__ __device__ inline int least(int a, int b) { return a < b ? a : b; }
+
+// A share of per_xcd tiles per XCD (of tiles_m tile rows, the last may be empty), whole up to q_end, the others in `parts` parts
+// of `per` k-tiles each, with their partial tiles in split_ws.
 struct PairPlan { int per_xcd, q_end, parts, per; };
-PairPlan pair_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes);
+// The rest of a share is cut for one work-group per compute unit (a second one
+// would halve the length of the parts again and double the partial tiles: 487 x 4096 x 4096 41 us with 8 parts, 31 us with
+// 4).  Tiles that leave some compute units with two work-groups and the others with one are cut as well, once every
+// compute unit has a whole one: 4099 rows by 2048 are 33 tiles for the 32 units of an XCD.
+__host__ __device__ inline PairPlan pair_plan(int M, int N, int nk_total, bool a_kmajor, int n_cu, long long ws_bytes) {
+    const int per_xcd = up_div(up_div(M, PM) * up_div(N, PN), 8), cus = n_cu / 8;
+    PairPlan plan{per_xcd, per_xcd, 1, 0};
+    if (ws_bytes == 0) return plan;
+    const int rem = per_xcd % cus;
+    if (rem == 0) return plan;
+    const int s = least(least(cus / rem, 16), nk_total / 16);
+    if (s < 2 || (long long)8 * rem * s * PM * PN * (int)sizeof(float) > ws_bytes) return plan;
+    plan.q_end = per_xcd - rem;
+    plan.parts = s;
+    plan.per = up_div(nk_total, s);
+    if (a_kmajor) plan.per += plan.per & 1;  // parts start on a 64-k boundary: whole 128-byte lines of A
+    return plan;
+}
+
+// The kernel whose estimated time is shorter.  Both estimates count rounds of tiles over the compute units of an XCD: so many
+// us (here in units of 1e-4) for each k of the contraction and for what a tile costs
+// besides, with the last round on its own.  The constants are fits to measured products of 128 .. 8192 rows,
+// K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 % (both kernels on 40
+// products: profiles/contraction_kernels_both_sides.txt; the one taken is never more than 2 % behind the other):
+//   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round (forward 0.0222 K); a last round that is cut along K (big_parts
+//                                          > 1) adds its two kernels
+//   128x256 tiles, two per compute unit:   0.0265 K + 2 us a round (0.0255 K + 3 weight gradient, 0.0276 K + 6 forward);
+//                                          with one per compute unit, half of that
+// The second one reads 1.5 times as much from L2 per multiply-add, which the long K pays for (8192 x 4096 x 28672: 1388
+// against 1574 us), and has no idle start and end of tile, nor as coarse a last round (4096 x 14336 x 487: 86 against
+// 60 us; 6144 x 4096 x 1024: 82 against 49; 487 x 4096 x 4096: 47 against 31; 6001 x 4096 x 6144: 262 against 239 us).
+// Whole tiles of the second one fill rounds of two work-groups per compute unit, or a last one of at most one each; the
+// tiles cut along K run beside that.  4099 x 2048 x 16384 is 17 tiles for the 32 compute units of an XCD, or 32 whole tiles
+// of half the size and one in 16 parts: 410 -> 290 us.
+__host__ __device__ inline bool pair_is_better(int M, int N, long long K, bool a_kmajor, bool b_kmajor, bool swiglu, int n_cu, int big_parts,
+                                               const PairPlan& plan) {
+    const int cus = n_cu / 8;                             // compute units of an XCD
+    const long long swiglu_split = swiglu ? 150000 : 0;  // its finish kernel also moves G, U, dG, dU, Act
+    const int tiles = up_div(up_div(M, 256) * up_div(N, 256), 8);
+    const long long big_k = (b_kmajor ? 222 : 232) * K;
+    long long big = tiles / cus * (big_k + 110000);
+    if (tiles % cus) big += big_parts > 1 ? big_k / big_parts + 330000 + swiglu_split : big_k * 9 / 10 + 110000;
+    const long long pair_k = (b_kmajor ? 276 : a_kmajor ? 265 : 255) * K, pair_fixed = b_kmajor ? 60000 : a_kmajor ? 20000 : 30000;
+    long long pair = plan.q_end / (2 * cus) * (pair_k + pair_fixed);
+    const int rest = plan.q_end % (2 * cus), cut = plan.per_xcd - plan.q_end, s = plan.parts;
+    if (rest > 0) pair += rest <= cus ? pair_k * 52 / 100 + 40000 : pair_k * 9 / 10 + pair_fixed;
+    if (cut > 0) pair += (cut * s > cus ? pair_k / s + 270000 : pair_k * 52 / 100 / s + 170000) + swiglu_split;
+    return pair < big;
+}
+// Plan and choice of a product whose row count lies on the device, for Mv rows of it.  Two rounds of 128x256 tiles at most:
+// beyond that the two kernels differ by little, and the grid that leaves when the others are chosen stays at 1024
+// work-groups (5 us in a profile, 2 between products).
+__host__ __device__ inline PairPlan device_plan(const MfmaGemmParams& p, int Mv, bool& pair) {
+    int nk = 0;
+    long long K = 0;
+    for (int s = 0; s < p.n_seg; ++s) {
+        nk += up_div(p.K[s], BK);
+        K += p.K[s];
+    }
+    const PairPlan plan = pair_plan(Mv, p.N, nk, p.a_kmajor != 0, p.plan_cu, p.plan_ws);
+    pair = plan.per_xcd <= 4 * (p.plan_cu / 8) &&
+           pair_is_better(Mv, p.N, K, p.a_kmajor != 0, p.b_kmajor != 0, p.epilogue == kEpiSwigluBwd, p.plan_cu, 1, plan);
+    return plan;
+}
+
 int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream);
+int launch_gemm_pair_rows(MfmaGemmParams p, int grid, int cut, float* split_ws, hipStream_t stream);  // m_dev, k-major A: most work-groups, cut tiles of an XCD
 size_t pair_split_bytes(const PairPlan& plan);  // scratch of its partial tiles
 int pair_grid(const PairPlan& plan);            // its work-groups
 int launch_gemm_two_pairs(MfmaGemmParams data, int data_tiles_m, const PairPlan& data_plan, MfmaGemmParams weight, int weight_tiles_m,

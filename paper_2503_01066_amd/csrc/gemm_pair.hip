@@ -1,6 +1,6 @@
 // bf16 GEMM on the gfx950 matrix cores, two work-groups per compute unit: the kernel for products whose tiles are short
-// or few.  Same contract as k_gemm_mfma (gemm_mfma.hip), but for sizes that
-// only the device knows.
+// or few.  Same contract as k_gemm_mfma (gemm_mfma.hip).  A row count that only the
+// device knows is planned there: every work-group, and the finish kernel, forms the same plan from it.
 //
 //   * 128x256 tile per work-group, 4 wavefronts of 64x128 each (128 accumulator registers), at most 256 registers and
 //     80 KB of LDS, so that two work-groups share a compute unit: while one waits for its first loads, writes its tile or
@@ -15,7 +15,6 @@
 
 namespace alch {
 
-static constexpr int PM = 128, PN = 256;
 static constexpr int kPairGroupM = 8;  // tile rows per raster band
 
 // Epilogue of 64 x 128 results in the accumulators of a wavefront: block (i, j) holds the transposed 32x32 result, this
@@ -24,8 +23,24 @@ static constexpr int kPairGroupM = 8;  // tile rows per raster band
 static constexpr int kSuper = 16384, kAStage = 8192, kBStage = 16384;
 template <bool kWide> static constexpr int kPairLds = kWide ? 2 * kSuper + 3 * kBStage : 3 * (kAStage + kBStage);
 
+// Plan and row count of a product; kRows: from the row count on the device (false: nothing to do).
+template <bool kRows>
+__device__ __forceinline__ bool the_plan(const MfmaGemmParams& p, PairPlan& plan, int& Mv, int& tiles_m) {
+    plan = PairPlan{p.per_xcd, p.q_end, p.split_s, p.split_per};
+    Mv = p.M;
+    tiles_m = p.tiles_m;
+    if constexpr (kRows) {
+        bool pair;
+        Mv = min(__builtin_amdgcn_readfirstlane(*p.m_dev), p.M);
+        plan = device_plan(p, Mv, pair);
+        tiles_m = up_div(Mv, PM);
+        return Mv > 0 && (!p.either || pair);
+    }
+    return true;
+}
+
 // Work-group `block` of the product's grid.
-template <bool AK, bool BKM>
+template <bool AK, bool BKM, bool kRows = false>
 __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, char* smem) {
     constexpr bool kWide = AK;
     constexpr int kU = kWide ? 12 : 3;  // steps after which every ring is back at its first stage
@@ -41,12 +56,16 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
     const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)wave * 4096u);
 
     // ---- work-group -> tile (and part of its contraction): every XCD owns per_xcd consecutive tiles
-    const int Mv = p.M, tiles_m = p.tiles_m, nt = tiles_m * p.tiles_n, per_xcd = p.per_xcd;
+    PairPlan plan;
+    int Mv, tiles_m;
+    if (!the_plan<kRows>(p, plan, Mv, tiles_m)) return;
+    const int nt = tiles_m * p.tiles_n, per_xcd = plan.per_xcd;
     const int in_xcd = block / 8;
-    const bool whole = in_xcd < p.q_end;
-    const int rem = per_xcd - p.q_end;
-    const int q = whole ? in_xcd : p.q_end + (in_xcd - p.q_end) % rem;
-    const int ks = whole ? 0 : (in_xcd - p.q_end) / rem;
+    const bool whole = in_xcd < plan.q_end;
+    const int rem = per_xcd - plan.q_end;
+    if (kRows && !whole && (rem == 0 || in_xcd >= plan.q_end + rem * plan.parts)) return;  // (grids for any number of rows)
+    const int q = whole ? in_xcd : plan.q_end + (in_xcd - plan.q_end) % rem;
+    const int ks = whole ? 0 : (in_xcd - plan.q_end) / rem;
     const int t = (block % 8) * per_xcd + q;
     if (q >= per_xcd || t >= nt) return;
     const int band_tiles = kPairGroupM * p.tiles_n;
@@ -66,7 +85,9 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
     int seg_kt0 = 0;  // k-tiles of the operand pairs before this one
     for (int seg = 0; seg < p.n_seg; ++seg) {
         const long long lda = p.lda[seg], ldb = p.ldb[seg];
-        const int K = p.K[seg];
+        int K = p.K[seg];
+        if constexpr (!AK && !BKM)  // (weight gradients)
+            if (p.k_dev) K = min(__builtin_amdgcn_readfirstlane(*p.k_dev), K);
         int nk = (K + BK - 1) / BK;
         const char *pa, *pb, *enda, *endb;
         long long stepa, stepb;
@@ -90,7 +111,7 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
             stepb = (long long)BK * ldb * 2;
         }
         if (!whole) {  // this work-group's share [ks*per, (ks+1)*per) of the k-tiles of all pairs, cut to this pair
-            const int lo = min(max(ks * p.split_per - seg_kt0, 0), nk), hi = min(max((ks + 1) * p.split_per - seg_kt0, 0), nk);
+            const int lo = min(max(ks * plan.per - seg_kt0, 0), nk), hi = min(max((ks + 1) * plan.per - seg_kt0, 0), nk);
             seg_kt0 += nk;
             if (hi <= lo) continue;
             nk = hi - lo;
@@ -234,7 +255,7 @@ __device__ __forceinline__ void pair_tile(const MfmaGemmParams& p, int block, ch
 
     const int half = lane >> 5;
     if (!whole) {
-        float* ws = p.split_ws + ((size_t)(((block % 8) * rem + (q - p.q_end)) * p.split_s + ks)) * (PM * PN) +
+        float* ws = p.split_ws + ((size_t)(((block % 8) * rem + (q - plan.q_end)) * plan.parts + ks)) * (PM * PN) +
                     (wm * 64 + (lane & 31)) * PN + wn * 128 + 4 * half;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -352,6 +373,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pair(MfmaGemmParams p) {
     pair_tile<AK, BKM>(p, (int)blockIdx.x, smem);
 }
 
+// With the row count on the device: kernels of their own, since a plan to be formed first, or looked at and left, is 0.4 us a
+// launch (801 tokens of hidden 2048, 8 launches: 359 / 362 us).
+template <bool BKM>
+__global__ __launch_bounds__(256, 2) void k_gemm_pair_rows(MfmaGemmParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[kPairLds<true>];
+    pair_tile<true, BKM, true>(p, (int)blockIdx.x, smem);
+}
+
 // A data gradient and a weight gradient that does not depend on it, the one with the longer tiles in the first n_first
 // work-groups.  Of a short batch the one has a work-group per compute unit, or fewer, that read cold weights, the other many
 // short ones that write cold gradients: they fill each other's gaps, and neither waits for the other's last round.  Every tile
@@ -370,23 +399,27 @@ __global__ __launch_bounds__(256, 2) void k_gemm_two_pairs(MfmaGemmParams data, 
 
 // Sum of the partial tiles -> output.  blockIdx.x % 8: XCD of the tile, blockIdx.x / 8: split tile of its share,
 // blockIdx.y: slab of 16 rows; a thread handles eight consecutive columns of two rows.
+template <bool kRows>
 __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
-    const int per_xcd = p.per_xcd, nt = p.tiles_m * p.tiles_n;
-    const int rem = per_xcd - p.q_end;
+    PairPlan plan;
+    int Mv, tiles_m;
+    if (!the_plan<kRows>(p, plan, Mv, tiles_m)) return;
+    const int per_xcd = plan.per_xcd, nt = tiles_m * p.tiles_n;
+    const int rem = per_xcd - plan.q_end;
     const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
-    const int t = xcd * per_xcd + p.q_end + j;
-    if (t >= nt) return;
+    const int t = xcd * per_xcd + plan.q_end + j;
+    if (j >= rem || t >= nt) return;
     const int band_tiles = kPairGroupM * p.tiles_n;
     const int band = t / band_tiles, in_band = t % band_tiles;
-    const int band_rows = min(kPairGroupM, p.tiles_m - band * kPairGroupM);
+    const int band_rows = min(kPairGroupM, tiles_m - band * kPairGroupM);
     const int m0 = (band * kPairGroupM + in_band % band_rows) * PM, n0 = (in_band / band_rows) * PN;
     const bool cols = p.by_cols;
     const int oseg = range_of(p, cols ? n0 : m0);
     __bf16* __restrict__ C = p.C[oseg];
     const long long ldc = p.ldc[oseg];
     const int mrel0 = cols ? m0 : m0 - p.m_begin[oseg];
-    const int m_end = (!cols && oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], p.M) : p.M);
-    const float* ws = p.split_ws + (size_t)(xcd * rem + j) * p.split_s * (PM * PN);
+    const int m_end = (!cols && oseg + 1 < p.n_out ? min(p.m_begin[oseg + 1], Mv) : Mv);
+    const float* ws = p.split_ws + (size_t)(xcd * rem + j) * plan.parts * (PM * PN);
     const int col = 8 * (threadIdx.x & 31), n = n0 + col;
     if (n >= p.N) return;  // (N is a multiple of 8)
 #pragma unroll
@@ -395,7 +428,7 @@ __global__ __launch_bounds__(256) void k_gemm_pair_finish(MfmaGemmParams p) {
         if (m >= m_end) continue;
         f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll 4
-        for (int k = 0; k < p.split_s; ++k) {
+        for (int k = 0; k < plan.parts; ++k) {
             const float* w = ws + (size_t)k * (PM * PN) + r * PN + col;
             lo += *reinterpret_cast<const f32x4*>(w);
             hi += *reinterpret_cast<const f32x4*>(w + 4);
@@ -442,7 +475,7 @@ static int pair_steps(const MfmaGemmParams& p, const PairPlan& plan) {
 }
 int pair_grid(const PairPlan& plan) { return 8 * (plan.q_end + (plan.per_xcd - plan.q_end) * plan.parts); }
 static void finish_pair(const MfmaGemmParams& p, hipStream_t stream) {
-    if (p.split_s > 1) k_gemm_pair_finish<<<dim3(8 * (p.per_xcd - p.q_end), PM / 16), 256, 0, stream>>>(p);
+    if (p.split_s > 1) k_gemm_pair_finish<false><<<dim3(8 * (p.per_xcd - p.q_end), PM / 16), 256, 0, stream>>>(p);
 }
 
 int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream) {
@@ -474,25 +507,14 @@ int launch_gemm_two_pairs(MfmaGemmParams data, int data_tiles_m, const PairPlan&
     return ALCH_OK;
 }
 
-// How the tiles of a share run: whole up to q_end, the rest in parts for one work-group per compute unit (a second one
-// would halve the length of the parts again and double the partial tiles: 487 x 4096 x 4096 41 us with 8 parts, 31 us with
-// 4).  Tiles that leave some compute units with two work-groups and the others with one are cut as well, once every
-// compute unit has a whole one: 4099 rows by 2048 are 33 tiles for the 32 units of an XCD.
-PairPlan pair_plan(const MfmaGemmParams& p, bool a_kmajor, int n_cu, size_t ws_bytes) {
-    const int per_xcd = ceil_div(ceil_div(p.M, PM) * ceil_div(p.N, PN), 8), cus = n_cu / 8;
-    PairPlan plan{per_xcd, per_xcd, 1, 0};
-    if (ws_bytes == 0) return plan;
-    const int rem = per_xcd % cus;
-    if (rem == 0) return plan;
-    int nk_total = 0;
-    for (int s = 0; s < p.n_seg; ++s) nk_total += ceil_div(p.K[s], BK);
-    const int s = std::min(std::min(cus / rem, 16), nk_total / 16);
-    if (s < 2 || (size_t)8 * rem * s * PM * PN * sizeof(float) > ws_bytes) return plan;
-    plan.q_end = per_xcd - rem;
-    plan.parts = s;
-    plan.per = ceil_div(nk_total, s);
-    if (a_kmajor) plan.per += plan.per & 1;  // parts start on a 64-k boundary: whole 128-byte lines of A
-    return plan;
+int launch_gemm_pair_rows(MfmaGemmParams p, int grid, int cut, float* split_ws, hipStream_t stream) {
+    p.tiles_n = ceil_div(p.N, PN);
+    p.split_ws = split_ws;
+    if (p.b_kmajor) k_gemm_pair_rows<true><<<grid, 256, 0, stream>>>(p);
+    else k_gemm_pair_rows<false><<<grid, 256, 0, stream>>>(p);
+    if (cut > 0) k_gemm_pair_finish<true><<<dim3(8 * cut, PM / 16), 256, 0, stream>>>(p);
+    ALCH_HIP_TRY(hipGetLastError());
+    return ALCH_OK;
 }
 
 }  // namespace alch

@@ -1,0 +1,42 @@
+"""Products sized by the number of rows that a loss mask keeps: which kernel takes them, and whether their tiles are cut along
+the contraction, is settled on the device.  Kept counts at edges of the 128- and 256-row tiles, none, one and all, in a batch where
+the counts reach whole and cut tiles of either kernel, against the dense call on a dY whose masked rows are zero."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as synth
+from helpers import alch_shape, to_dev
+from oracle import WEIGHT_KEYS
+from test_gpu_layer import REC, make_case
+
+pytestmark = pytest.mark.gpu
+COUNTS = (0, 1, 128, 129, 257, 700, 1025, 1281, 2049, 2305, 4159, 4160)
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_kept_counts(monkeypatch, accumulate):
+    import paper_2503_01066_amd as A
+    monkeypatch.setitem(synth.SHAPES, "kept", (2048, 16, 4, 128, 8192, 1e-5, 10000.0))
+    cu = synth.uniform_cu(65, 64)
+    T = int(cu[-1])
+    shp, _, W, rec, dY = make_case("kept", "bf16", cu, 29, "drawn", dy_std=0.01)
+    d = {k: to_dev(rec[k], "bf16") for k in REC}
+    d["LSE"] = torch.from_numpy(rec["LSE"]).cuda()
+    Wd, dYd, old = {k: to_dev(v, "bf16") for k, v in W.items()}, to_dev(dY, "bf16"), 0.001
+    start = lambda: {"d" + k: torch.full_like(Wd[k], old) for k in WEIGHT_KEYS}
+    order = np.random.default_rng(7).permutation(T)
+    for kept in COUNTS:
+        mask = np.zeros(T, np.uint8)
+        mask[order[:kept]] = 1
+        m = torch.from_numpy(mask).cuda()
+        run = lambda dy, lm: A.alch_layer_backward(alch_shape(shp, "bf16"), A.Batch(cu), d, Wd, dy, loss_mask=lm, grads=start(),
+                                                   accumulate=accumulate)
+        got, want = run(dYd, m), run(dYd * m[:, None].to(dYd.dtype), None)
+        torch.cuda.synchronize()
+        for k in want:
+            a, b = got[k].float(), want[k].float()
+            assert torch.isfinite(a).all(), (kept, k)
+            # the two differ in the order of fp32 sums, and so in where a bf16 rounding falls: at most four roundings, one
+            # behind the other (dG/dU, dH2, dX2, the output), each 2^-9 of the norm
+            assert float((a - b).norm()) <= 2 ** -7 * float(b.norm()), (kept, k, float((a - b).norm() / b.norm()))
