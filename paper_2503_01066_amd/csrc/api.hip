@@ -470,7 +470,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         if (sv.U) rows[n_rows++] = alch_stream{sv.U, p.c_U, (size_t)F * E, (size_t)F * E};
         // (per-sequence counts are not needed: zero sequences asked for, one boundary written)
         ALCH_TRY(launch_pack(loss_mask, T, b.cu_seqlens, 0, n_rows, rows, T, p.c_index, p.c_cu, p.c_n, p.c_packws, st, false));
-        ALCH_TRY(launch_rank_of_kept(p.c_index, p.c_n, p.c_inv, T, st));
+        ALCH_TRY(launch_kept_rows(p.c_index, p.c_n, p.c_inv, T, st));
         mY = p.c_dY; mX2 = p.c_X2; mO = p.c_O; mG = p.c_G; mU = p.c_U;
         mdX2 = p.c_dX2; mdO = p.c_dO;
         ndev = p.c_n;
@@ -642,10 +642,8 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     const bool dwo_beside = g.dWo && gemm_together(dH1, dWo);
     if (g.dWo && !dwo_beside) ALCH_TRY(launch_gemm(dWo, st));
 
-    if (compact) {  // back to [T, width]: zeros in the masked rows
-        ALCH_TRY(launch_scatter_rows(p.c_dO, p.c_inv, p.dO, T, (size_t)QD * E, st));
-        ALCH_TRY(launch_scatter_rows(p.c_dX2, p.c_inv, p.dX2, T, (size_t)H * E, st));
-    }
+    if (compact)  // back to [T, width]: zeros in the masked rows
+        ALCH_TRY(launch_scatter_rows(p.c_dO, p.c_inv, p.dO, T, (size_t)QD * E, st, p.c_dX2, p.dX2, (size_t)H * E));
 
     // attention backward from saved Q, K, V, O, LSE -> [dQ | dK | dV] with RoPE backward applied to dQ, dK
     {
@@ -1124,19 +1122,18 @@ static int stack_backward_impl(const alch_layer_shape* shape, int32_t n_layers, 
         // take their row counts from device memory, and dHf is scattered back into a zero-filled [T, H].
         compact_head = loss_mask && T > 0 && dt == ALCH_BF16 && H % 64 == 0 && vocab % 64 == 0 &&
                        (long long)kHeadChunkRows * vocab * (long long)E < (1LL << 31);
-        ALCH_TRY(launch_count_labels(labels, loss_mask, T, vocab, p.n_counted, p.row_loss, st));
+        ALCH_TRY(launch_count_labels(labels, loss_mask, T, vocab, p.n_counted, p.row_loss,
+                                     compact_head ? p.h_counted : nullptr, st));
         ALCH_TRY(launch_rmsnorm_fwd(dt, X_final, g_final, p.Hf, T, H, s.rms_eps, st));
         const void* head_in = p.Hf;
         void* head_out = p.dHf;
         const int* head_labels = labels;
         const uint8_t* head_mask = loss_mask;
         if (compact_head) {
-            ALCH_TRY(launch_counted_mask(labels, loss_mask, T, vocab, p.h_counted, st));
             const alch_stream rows1[1] = {{p.Hf, p.h_Hf, (size_t)H * E, (size_t)H * E}};
             ALCH_TRY(launch_pack(p.h_counted, T, batch->cu_seqlens, 0, 1, rows1, T, p.h_index, p.h_cu, p.h_n, p.h_packws, st, false));
-            ALCH_TRY(launch_gather_int(labels, p.h_index, p.h_n, p.h_labels, T, st));
-            ALCH_TRY(launch_rank_of_kept(p.h_index, p.h_n, p.h_inv, T, st));
-            ALCH_TRY(launch_chunk_rows(p.h_n, ceil_div(T, kHeadChunkRows), kHeadChunkRows, p.h_chunk_rows, st));
+            ALCH_TRY(launch_kept_rows(p.h_index, p.h_n, p.h_inv, T, st, labels, p.h_labels, ceil_div(T, kHeadChunkRows), kHeadChunkRows,
+                                      p.h_chunk_rows));
             head_in = p.h_Hf; head_out = p.h_dHf; head_labels = p.h_labels; head_mask = nullptr;
         }
         bool first = true;

@@ -118,10 +118,13 @@ int launch_rmsnorm_bwd(alch_dtype dt, const void* dH, const void* X, const void*
                        const uint8_t* resid_mask, void* dX, void* dg, int accumulate, float* partial, int T,
                        int width, float eps, hipStream_t stream, const int* rows_dev = nullptr, void* hn_out = nullptr,
                        GainSums* sums = nullptr);
-// inv[t] = rank of token t among the first *n_rows entries of index (the kept tokens), -1 if absent
-int launch_rank_of_kept(const int* index, const int* n_rows, int* inv, int T, hipStream_t stream);
-// out [T, row_bytes] = src[inv[t], :] where inv[t] >= 0, zeros elsewhere
-int launch_scatter_rows(const void* src, const int* inv, void* out, int T, size_t row_bytes, hipStream_t stream);
+// inv[t] = rank of token t among the first *n_rows entries of index (the kept tokens, ascending), -1 if absent; of a head also
+// kept_labels[r] = labels[index[r]] and chunk_rows[c] = rows of chunk c among the kept ones
+int launch_kept_rows(const int* index, const int* n_rows, int* inv, int T, hipStream_t stream, const int* labels = nullptr,
+                     int* kept_labels = nullptr, int n_chunks = 0, int chunk = 0, int* chunk_rows = nullptr);
+// out [T, row_bytes] = src[inv[t], :] where inv[t] >= 0, zeros elsewhere; a second pair of tensors likewise
+int launch_scatter_rows(const void* src, const int* inv, void* out, int T, size_t row_bytes, hipStream_t stream, const void* src2 = nullptr,
+                        void* out2 = nullptr, size_t row_bytes2 = 0);
 // Act = silu(G) * U
 int launch_swiglu_act(alch_dtype dt, const void* G, const void* U, void* Act, long long n, hipStream_t stream);
 // In-place rotary rotation of q [T, n_q, D] and k [T, n_kv, D].
@@ -269,19 +272,14 @@ int launch_attn_fwd(alch_dtype dt, const void* Q, const void* K, const void* V, 
                     const int* prefix_host, int seq_begin, int Hq, int Hkv, int D, hipStream_t stream);
 
 // ---- LM head + cross-entropy ---------------------------------------------------------------
-// n_counted[0] = #{t : labels[t] >= 0 and (mask == NULL or mask[t] != 0)}; row_loss[0..T) = 0
-int launch_count_labels(const int* labels, const uint8_t* loss_mask, int T, int vocab, int* n_counted, float* row_loss,
+// n_counted[0] = #{t : labels[t] >= 0 and (mask == NULL or mask[t] != 0)}; row_loss[0..T) = 0; counted[t] (or NULL): that predicate
+int launch_count_labels(const int* labels, const uint8_t* loss_mask, int T, int vocab, int* n_counted, float* row_loss, uint8_t* counted,
                         hipStream_t stream);
 // One chunk of logits rows [rows, vocab] (row stride ld), in place: logits -> dlogits =
 // (softmax - onehot(label)) / N for counted rows, 0 otherwise; row_loss[r] = -log softmax[label].
 int launch_ce_chunk(alch_dtype dt, void* logits, long long ld, int rows, int vocab, const int* labels,
                     const uint8_t* loss_mask, const int* n_counted, float* row_loss, hipStream_t stream,
                     const int* rows_dev = nullptr);
-// counted[t] = label >= 0 and loss-mask byte nonzero; chunk_rows[c] = rows of chunk c among the first *n_rows rows
-int launch_counted_mask(const int* labels, const uint8_t* loss_mask, int T, int vocab, uint8_t* counted, hipStream_t stream);
-int launch_chunk_rows(const int* n_rows, int n_chunks, int chunk, int* chunk_rows, hipStream_t stream);
-// dst[r] = src[index[r]] for r < min(*n_rows, T)
-int launch_gather_int(const int* src, const int* index, const int* n_rows, int* dst, int T, hipStream_t stream);
 // ---- DPO head on scored tokens (items) -----------------------------------------------------
 // logp[m], logz[m] of a chunk of item logits rows
 int launch_dpo_logp(alch_dtype dt, const void* logits, long long ld, int rows, int vocab, const int* labels, float* logp,

@@ -26,12 +26,14 @@ __device__ __forceinline__ bool label_counts(int label, int vocab) { return (uns
 
 __global__ __launch_bounds__(256) void k_count_labels(const int* __restrict__ labels, const uint8_t* __restrict__ mask,
                                                       int T, int vocab, int* __restrict__ n_counted,
-                                                      float* __restrict__ row_loss) {
+                                                      float* __restrict__ row_loss, uint8_t* __restrict__ counted) {
     // single block: deterministic count
     __shared__ int part[4];
     int c = 0;
     for (int t = threadIdx.x; t < T; t += 256) {
-        c += (label_counts(labels[t], vocab) && (!mask || mask[t] != 0)) ? 1 : 0;
+        const int one = (label_counts(labels[t], vocab) && (!mask || mask[t] != 0)) ? 1 : 0;
+        c += one;
+        if (counted) counted[t] = (uint8_t)one;
         row_loss[t] = 0.f;
     }
 #pragma unroll
@@ -253,47 +255,9 @@ __global__ __launch_bounds__(256) void k_finish_loss(const float* __restrict__ r
 }
 
 // counted[t] = 1 where the token contributes to the loss (0 <= label < vocab and loss-mask byte nonzero)
-__global__ __launch_bounds__(256) void k_counted_mask(const int* __restrict__ labels, const uint8_t* __restrict__ mask,
-                                                      int T, int vocab, uint8_t* __restrict__ counted) {
-    for (int t = blockIdx.x * 256 + threadIdx.x; t < T; t += gridDim.x * 256)
-        counted[t] = (label_counts(labels[t], vocab) && (!mask || mask[t] != 0)) ? 1 : 0;
-}
-// chunk_rows[c] = number of the n compacted rows that fall into row chunk c
-__global__ void k_chunk_rows(const int* __restrict__ n_rows, int n_chunks, int chunk, int* __restrict__ chunk_rows) {
-    const int n = n_rows[0];
-    for (int c = threadIdx.x; c < n_chunks; c += blockDim.x) {
-        const int left = n - c * chunk;
-        chunk_rows[c] = left < 0 ? 0 : (left > chunk ? chunk : left);
-    }
-}
-// dst[r] = src[index[r]] for r < *n_rows
-__global__ __launch_bounds__(256) void k_gather_int(const int* __restrict__ src, const int* __restrict__ index,
-                                                    const int* __restrict__ n_rows, int* __restrict__ dst, int T) {
-    const int n = min(n_rows[0], T);
-    for (int r = blockIdx.x * 256 + threadIdx.x; r < n; r += gridDim.x * 256) dst[r] = src[index[r]];
-}
-int launch_gather_int(const int* src, const int* index, const int* n_rows, int* dst, int T, hipStream_t stream) {
-    if (T <= 0) return ALCH_OK;
-    k_gather_int<<<ceil_div(T, 256) < 1024 ? ceil_div(T, 256) : 1024, 256, 0, stream>>>(src, index, n_rows, dst, T);
-    ALCH_HIP_TRY(hipGetLastError());
-    return ALCH_OK;
-}
-int launch_counted_mask(const int* labels, const uint8_t* loss_mask, int T, int vocab, uint8_t* counted, hipStream_t stream) {
-    if (T <= 0) return ALCH_OK;
-    k_counted_mask<<<ceil_div(T, 256) < 1024 ? ceil_div(T, 256) : 1024, 256, 0, stream>>>(labels, loss_mask, T, vocab, counted);
-    ALCH_HIP_TRY(hipGetLastError());
-    return ALCH_OK;
-}
-int launch_chunk_rows(const int* n_rows, int n_chunks, int chunk, int* chunk_rows, hipStream_t stream) {
-    if (n_chunks <= 0) return ALCH_OK;
-    k_chunk_rows<<<1, 64, 0, stream>>>(n_rows, n_chunks, chunk, chunk_rows);
-    ALCH_HIP_TRY(hipGetLastError());
-    return ALCH_OK;
-}
-
-int launch_count_labels(const int* labels, const uint8_t* loss_mask, int T, int vocab, int* n_counted, float* row_loss,
+int launch_count_labels(const int* labels, const uint8_t* loss_mask, int T, int vocab, int* n_counted, float* row_loss, uint8_t* counted,
                         hipStream_t stream) {
-    k_count_labels<<<1, 256, 0, stream>>>(labels, loss_mask, T, vocab, n_counted, row_loss);
+    k_count_labels<<<1, 256, 0, stream>>>(labels, loss_mask, T, vocab, n_counted, row_loss, counted);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }

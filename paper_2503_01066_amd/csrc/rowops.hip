@@ -598,19 +598,38 @@ int launch_masked_copy(alch_dtype dt, const void* a, const uint8_t* mask, void* 
 }
 
 // ---- row scatter: out [T, width] = src[rank of t among the kept rows, :] for kept t, zeros elsewhere.
-// inv[t] = that rank or -1 is built first (two launches: clear, then fill from the kept-row index), so the
-// scatter writes every row of `out` exactly once, 16 bytes per lane.
-__global__ __launch_bounds__(256) void k_rank_clear(int* __restrict__ inv, int T_) {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < T_; i += gridDim.x * 256) inv[i] = -1;
-}
-__global__ __launch_bounds__(256) void k_rank_fill(const int* __restrict__ index, const int* __restrict__ n_rows,
-                                                   int* __restrict__ inv, int T_) {
+// What else is to be known of the kept rows, in one launch: inv[t] = that rank or -1, found in the sorted index of the kept
+// tokens (every entry is written, so nothing is cleared first), and for a head the kept tokens' labels and the rows of its
+// chunks.  Launches of a few microseconds, and nothing but launch: two for inv, four for a head before; as one, and
+// both scatters of a layer as one, masked layers of 700 tokens 275 -> 271 us (hidden 2048), of 1500 tokens 711 -> 707.
+__global__ __launch_bounds__(256) void k_kept_rows(const int* __restrict__ index, const int* __restrict__ n_rows, int* __restrict__ inv,
+                                                   int T_, const int* __restrict__ labels, int* __restrict__ kept_labels, int n_chunks,
+                                                   int chunk, int* __restrict__ chunk_rows) {
     const int n = min(*n_rows, T_);
-    for (int r = blockIdx.x * 256 + threadIdx.x; r < n; r += gridDim.x * 256) inv[index[r]] = r;
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < T_; t += gridDim.x * 256) {
+        int lo = 0, hi = n;  // first entry >= t
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (index[mid] < t) lo = mid + 1;
+            else hi = mid;
+        }
+        const bool kept = lo < n && index[lo] == t;
+        inv[t] = kept ? lo : -1;
+        if (kept && labels) kept_labels[lo] = labels[t];
+    }
+    if (blockIdx.x == 0)
+        for (int c = threadIdx.x; c < n_chunks; c += 256) chunk_rows[c] = min(max(n - c * chunk, 0), chunk);
 }
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
-__global__ __launch_bounds__(256) void k_scatter_rows(const u32x4_t* __restrict__ src, const int* __restrict__ inv,
-                                                      u32x4_t* __restrict__ out, int T_, int pieces) {
+struct ScatterArgs {
+    const u32x4_t* src[2];
+    u32x4_t* out[2];
+    int pieces[2];
+};
+__global__ __launch_bounds__(256) void k_scatter_rows(ScatterArgs a, const int* __restrict__ inv, int T_) {
+    const u32x4_t* __restrict__ src = a.src[blockIdx.y];
+    u32x4_t* __restrict__ out = a.out[blockIdx.y];
+    const int pieces = a.pieces[blockIdx.y];
     for (int t = blockIdx.x; t < T_; t += gridDim.x) {
         const int r = inv[t];
         for (int c = threadIdx.x; c < pieces; c += 256) {
@@ -621,19 +640,22 @@ __global__ __launch_bounds__(256) void k_scatter_rows(const u32x4_t* __restrict_
     }
 }
 
-int launch_rank_of_kept(const int* index, const int* n_rows, int* inv, int T_, hipStream_t stream) {
+int launch_kept_rows(const int* index, const int* n_rows, int* inv, int T_, hipStream_t stream, const int* labels, int* kept_labels,
+                     int n_chunks, int chunk, int* chunk_rows) {
     if (T_ <= 0) return ALCH_OK;
-    const int nb = ceil_div(T_, 256) < 1024 ? ceil_div(T_, 256) : 1024;
-    k_rank_clear<<<nb, 256, 0, stream>>>(inv, T_);
-    k_rank_fill<<<nb, 256, 0, stream>>>(index, n_rows, inv, T_);
+    k_kept_rows<<<ceil_div(T_, 256) < 1024 ? ceil_div(T_, 256) : 1024, 256, 0, stream>>>(index, n_rows, inv, T_, labels, kept_labels, n_chunks,
+                                                                                       chunk, chunk_rows);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
 
-int launch_scatter_rows(const void* src, const int* inv, void* out, int T_, size_t row_bytes, hipStream_t stream) {
+int launch_scatter_rows(const void* src, const int* inv, void* out, int T_, size_t row_bytes, hipStream_t stream, const void* src2, void* out2,
+                        size_t row_bytes2) {
     if (T_ <= 0) return ALCH_OK;
-    if (row_bytes % 16 || !aligned16(src) || !aligned16(out)) return fail(ALCH_ERR_UNSUPPORTED, "scatter: rows must be 16-byte multiples");
-    k_scatter_rows<<<T_ < 65536 ? T_ : 65536, 256, 0, stream>>>((const u32x4_t*)src, inv, (u32x4_t*)out, T_, (int)(row_bytes / 16));
+    if ((row_bytes | row_bytes2) % 16 || !aligned16(src) || !aligned16(out) || !aligned16(src2) || !aligned16(out2))
+        return fail(ALCH_ERR_UNSUPPORTED, "scatter: rows must be 16-byte multiples");
+    const ScatterArgs a{{(const u32x4_t*)src, (const u32x4_t*)src2}, {(u32x4_t*)out, (u32x4_t*)out2}, {(int)(row_bytes / 16), (int)(row_bytes2 / 16)}};
+    k_scatter_rows<<<dim3(T_ < 65536 ? T_ : 65536, src2 ? 2 : 1), 256, 0, stream>>>(a, inv, T_);
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }
