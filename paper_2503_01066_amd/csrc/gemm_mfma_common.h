@@ -163,7 +163,8 @@ __host__ __device__ inline PairPlan pair_plan(int M, int N, int nk_total, bool a
 // us (here in units of 1e-4) for each k of the contraction and for what a tile costs
 // besides, with the last round on its own.  The constants are fits to measured products of 128 .. 8192 rows,
 // K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 % (both kernels on 40
-// products: profiles/contraction_kernels_both_sides.txt; the one taken is never more than 2 % behind the other):
+// products: profiles/contraction_kernels_both_sides.txt; the one taken is never more than 2 % behind the other, but for
+// 487 x 4096 x 28672, a tie by the estimates: 126 and 118 us):
 //   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round (forward 0.0222 K); a last round that is cut along K (big_parts
 //                                          > 1) adds its two kernels
 //   128x256 tiles, two per compute unit:   0.0265 K + 2 us a round (0.0255 K + 3 weight gradient, 0.0276 K + 6 forward);
