@@ -612,6 +612,7 @@ bool gemm_together(const GemmDesc& data, const GemmDesc& weight) {
 int launch_gemm_together(const GemmDesc& data, const GemmDesc& weight, hipStream_t stream) {
     double flops = 0, bytes = 0;
     for (const GemmDesc* d : {&data, &weight}) {
+        if (d->m_dev || d->k_dev) continue;  // (as in launch_gemm)
         double k_total = 0;
         for (int s = 0; s < d->n_seg; ++s) k_total += d->seg[s].K;
         flops += 2.0 * d->M * d->N * k_total;

@@ -40,3 +40,26 @@ def test_kept_counts(monkeypatch, accumulate):
             # the two differ in the order of fp32 sums, and so in where a bf16 rounding falls: at most four roundings, one
             # behind the other (dG/dU, dH2, dX2, the output), each 2^-9 of the norm
             assert float((a - b).norm()) <= 2 ** -7 * float(b.norm()), (kept, k, float((a - b).norm() / b.norm()))
+
+
+def test_products_of_kept_rows_are_traced_without_work(monkeypatch):
+    """A record of the launch trace counts the operations of products whose sizes the host knows: with a mask those behind the
+    attention, dH1 and d[Wq; Wk; Wv], and not dWo, which contracts the kept rows, where it shares the launch of dH1."""
+    import paper_2503_01066_amd as A
+    H, QKV = 2048, 3072
+    monkeypatch.setitem(synth.SHAPES, "kept", (H, 16, 4, 128, 8192, 1e-5, 10000.0))
+    cu = synth.uniform_cu(65, 64)
+    T = int(cu[-1])
+    shp, _, W, rec, dY = make_case("kept", "bf16", cu, 29, "drawn", dy_std=0.01)
+    d = {k: to_dev(rec[k], "bf16") for k in REC}
+    d["LSE"] = torch.from_numpy(rec["LSE"]).cuda()
+    mask = torch.from_numpy(synth.keep_mask(T, 0.25, 3)).cuda()
+    A.alch_trace_enable(True)
+    A.alch_layer_backward(alch_shape(shp, "bf16"), A.Batch(cu), d, {k: to_dev(v, "bf16") for k, v in W.items()}, to_dev(dY, "bf16"),
+                          loss_mask=mask, want=WEIGHT_KEYS)
+    torch.cuda.synchronize()
+    A.alch_trace_enable(False)
+    work = [(flops, nbytes) for kind, flops, nbytes, ms in A.alch_trace_collect() if kind == "gemm_mfma"]
+    known = (2.0 * T * H * QKV, 2.0 * (T * QKV + QKV * H + T * H))  # of either: the three matrices are the same sizes
+    assert sorted(w for w in work if w != (0.0, 0.0)) == [known, known], work
+    assert len(work) == 7, work  # dAct, dWd, dH2, [dWg; dWu], dO without work; dH1 with dWo, d[Wq; Wk; Wv]
