@@ -504,7 +504,7 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     for (int s = 0; s < d.n_seg; ++s) {
         const GemmSeg& g = d.seg[s];
         if (g.K <= 0 || !aligned16(g.A) || !aligned16(g.B) || g.lda % 8 || g.ldb % 8) return false;
-        if ((d.a_kmajor || d.b_kmajor) && g.K % 64) return false;  // no k tail on k-major operands
+        if ((d.a_kmajor || d.b_kmajor) && (g.K % 64 || d.k_dev)) return false;  // no k tail on k-major operands
         if (!d.a_kmajor && d.M % 8) return false;
         if (!d.b_kmajor && d.N % 8) return false;
         if (d.N % 8) return false;  // 16-byte output stores

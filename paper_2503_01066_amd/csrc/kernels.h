@@ -57,7 +57,8 @@ struct GemmDesc {
     long long ldgu = 0;
     void* act_out = nullptr;
     // optional device-resident sizes (matrix-core kernel only): effective M = min(*m_dev, M); effective K of
-    // every operand pair = min(*k_dev, K).  Rows / contraction steps beyond them are neither read nor written.
+    // every operand pair = min(*k_dev, K), token-major operands only.  Rows / contraction steps beyond them are neither read
+    // nor written.
     const int* m_dev = nullptr;
     const int* k_dev = nullptr;
     // optional scratch (matrix-core kernel only): when the last round of tiles would leave at least half of the
