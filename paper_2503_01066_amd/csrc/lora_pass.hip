@@ -352,10 +352,12 @@ static int plan_pass(const LoraPass* jobs, int n_jobs, int Trows, const LoraUpSu
     p.need_up = width * r * p.splits;
     return ALCH_OK;
 }
+// What k_lora_both takes: K is cut in chunks of 64, and the rows of a block lie within 1 GiB (offsets in 32 bits).
+static bool both_takes(const LoraPass& j) { return j.K % 64 == 0 && j.ldx % 8 == 0 && j.ldp % 8 == 0 && kBothRows * j.ldx < (1LL << 29); }
 bool lora_pass_fits(const LoraPass* jobs, int n_jobs, int Trows, const LoraUpSums& sums) {
     PassPlan p;
     for (int i = 0; i < n_jobs; ++i)
-        if (jobs[i].K % 64 || (jobs[i].P && jobs[i].ldp % 8)) return false;
+        if (!both_takes(jobs[i])) return false;
     return plan_pass(jobs, n_jobs, Trows, sums, p) == ALCH_OK && p.need_up + p.need_t <= sums.capacity && p.splits <= kLoraMaxSplits;
 }
 
@@ -363,11 +365,11 @@ int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq,
     if (Trows <= 0 || n_jobs <= 0) return ALCH_OK;
     const int r = sums.p.r, groups = r / 8;
     if (r % 8 || r <= 0 || ldq % 8) return fail(ALCH_ERR_UNSUPPORTED, "adapter product: rank must be a positive multiple of 8");
-    for (int i = 0; i < n_jobs; ++i)
-        if (jobs[i].K % 8 || jobs[i].ldx % 8 || jobs[i].ldp % 8 || kBothRows * jobs[i].ldx >= (1LL << 29))
-            return fail(ALCH_ERR_UNSUPPORTED, "adapter product: widths and strides must be multiples of 8");
     PassPlan plan;
     ALCH_TRY(plan_pass(jobs, n_jobs, Trows, sums, plan));
+    for (int i = 0; i < n_jobs; ++i)
+        if (jobs[i].K % 8 || jobs[i].ldx % 8 || (plan.both && !both_takes(jobs[i])))
+            return fail(ALCH_ERR_UNSUPPORTED, "adapter product: widths and strides must be multiples of 8, of a shared pass of 64");
     if (sums.p.n_jobs + plan.n_up > kLoraUpSums || sums.floats + plan.need_up + plan.need_t > sums.capacity)
         ALCH_TRY(launch_lora_up_sums(ALCH_BF16, sums, stream));
     if (plan.need_up + plan.need_t > sums.capacity) return fail(ALCH_ERR_UNSUPPORTED, "adapter product: more partial sums than scratch");

@@ -37,3 +37,10 @@ def test_contraction_length_on_the_device_needs_token_major_operands(ask):
     assert known == [(1,)] * 4
     dev = ask(*[("supported", 512, 512, 256, a, b, True) for a, b in forms])
     assert dev == [(1,), (0,), (0,), (0,)]
+
+
+def test_adapter_pass_takes_no_rows_that_its_launch_refuses(ask):
+    """[dG | dU] rows of 2^22 elements and more: beyond the offsets of the pass (128 rows below 2^29 elements), so the layer takes the
+    separate kernels; a layer that found this out at the launch had failed half way."""
+    last = (1 << 21) - 64  # [dG | dU] has two of them to a row
+    assert ask(("one_pass", 8, last, 8), ("one_pass", 8, last + 64, 8), ("one_pass", 8, 1 << 22, 8)) == [(1,), (0,), (0,)]
