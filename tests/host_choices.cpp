@@ -33,9 +33,22 @@ int main() {
             GemmDesc d = product(M, N, K, a, b);
             if (dev) d.k_dev = static_cast<const int*>(kSome);
             std::cout << gemm_mfma_supported(d) << "\n";
-        } else if (what == "one_pass") {  // T F rank: the pass over Act, dG and dU of a layer with all adapters and gradients, hidden 64
-            int T, F, r;
-            std::cin >> T >> F >> r;
+        } else if (what == "kernel") {  // M N K a_kmajor b_kmajor, whole tiles: 1 for 128x256, 0 for 256x256
+            int M, N, K, a, b;
+            std::cin >> M >> N >> K >> a >> b;
+            std::cout << pair_is_better(M, N, K, a, b, false, 256, 1, pair_plan(M, N, up_div(K, BK), a, 256, 0)) << "\n";
+        } else if (what == "rows_beside") {  // hidden ffn T qkv of an fp32 layer: the norm beside dWd, the gain sums beside d[Wq; Wk; Wv]
+            int H, F, T, qkv;
+            std::cin >> H >> F >> T >> qkv;
+            GemmDesc dWd = product(H, F, T, false, false), dH2 = product(T, H, F, true, false), dWqkv = product(qkv, H, T, false, false);
+            dH2.n_seg = 2;
+            dH2.seg[1] = dH2.seg[0];
+            dWd.dtype = dH2.dtype = dWqkv.dtype = ALCH_F32;
+            const bool together = (size_t)T * F >= (size_t)rmsnorm_bwd_blocks(T) * H;
+            std::cout << (together && !gemm_together(dH2, dWd) && gemm_beside_rows(dWd, H)) << " " << (together && gemm_beside_rows(dWqkv, H)) << "\n";
+        } else if (what == "one_pass") {  // T hidden ffn rank: the pass over Act, dG and dU, all adapters and gradients
+            int T, H, F, r;
+            std::cin >> T >> H >> F >> r;
             LoraPass jobs[3] = {};
             for (int i = 0; i < 3; ++i) {
                 jobs[i].X = kSome; jobs[i].ldx = i ? 2 * (long long)F : F; jobs[i].K = F;
@@ -46,8 +59,12 @@ int main() {
             }
             LoraUpSums sums;
             sums.p.Trows = T; sums.p.r = r; sums.p.scratch = static_cast<float*>(kSome);
-            sums.capacity = (long long)(lora_up_scratch_bytes(r, 2 * (64 + F)) / sizeof(float));
+            sums.capacity = (long long)(lora_up_scratch_bytes(r, 2 * (H + F)) / sizeof(float));
             std::cout << lora_pass_fits(jobs, 3, T, sums) << "\n";
+        } else if (what == "t_parts") {  // T problems: parts of the contraction of t2
+            int T, problems;
+            std::cin >> T >> problems;
+            std::cout << lora_down_parts(T, problems, 256) << "\n";
         } else {
             return 1;
         }

@@ -1,6 +1,8 @@
 """Products sized by the number of rows that a loss mask keeps: which kernel takes them, and whether their tiles are cut along
 the contraction, is settled on the device.  Kept counts at edges of the 128- and 256-row tiles, none, one and all, in a batch where
-the counts reach whole and cut tiles of either kernel, against the dense call on a dY whose masked rows are zero."""
+the counts reach whole and cut tiles of the 128x256 kernel and whole ones of the 256x256 kernel (which cuts none of these), against
+the dense call on a dY whose masked rows are zero.  Weight gradients that contract the kept rows choose for half of the tokens: short
+ones run on the 128x256 kernel, those of the long batch on the other."""
 import numpy as np
 import pytest
 import torch
@@ -12,13 +14,24 @@ from test_gpu_layer import REC, make_case
 
 pytestmark = pytest.mark.gpu
 COUNTS = (0, 1, 128, 129, 257, 700, 1025, 1281, 2049, 2305, 4159, 4160)
+LONG, LONG_T = (4096, 4, 2, 64, 2048, 1e-5, 10000.0), 7040
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_kept_counts(monkeypatch, accumulate):
-    import paper_2503_01066_amd as A
     monkeypatch.setitem(synth.SHAPES, "kept", (2048, 16, 4, 128, 8192, 1e-5, 10000.0))
-    cu = synth.uniform_cu(65, 64)
+    compare_kept_counts(synth.uniform_cu(65, 64), COUNTS, accumulate)
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_kept_counts_of_a_long_batch(monkeypatch, accumulate):
+    # [dWg; dWu] of 4096 x 4096: counts beside a k-tile, odd numbers of them, ragged ends, other remainders by the ten of the rings
+    monkeypatch.setitem(synth.SHAPES, "kept", LONG)
+    compare_kept_counts(synth.uniform_cu(LONG_T // 64, 64), (0, 1, 31, 32, 33, 159, 161, 3525, 7039, 7040), accumulate)
+
+
+def compare_kept_counts(cu, counts, accumulate):
+    import paper_2503_01066_amd as A
     T = int(cu[-1])
     shp, _, W, rec, dY = make_case("kept", "bf16", cu, 29, "drawn", dy_std=0.01)
     d = {k: to_dev(rec[k], "bf16") for k in REC}
@@ -26,7 +39,7 @@ def test_kept_counts(monkeypatch, accumulate):
     Wd, dYd, old = {k: to_dev(v, "bf16") for k, v in W.items()}, to_dev(dY, "bf16"), 0.001
     start = lambda: {"d" + k: torch.full_like(Wd[k], old) for k in WEIGHT_KEYS}
     order = np.random.default_rng(7).permutation(T)
-    for kept in COUNTS:
+    for kept in counts:
         mask = np.zeros(T, np.uint8)
         mask[order[:kept]] = 1
         m = torch.from_numpy(mask).cuda()

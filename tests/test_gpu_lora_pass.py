@@ -42,3 +42,21 @@ def test_gradients_that_are_not_asked_for(monkeypatch, wanted, projections):
     gpu = run_gpu(shp, "bf16", cu, W, lora, 16, scale, rec, dY, lora_grads=bufs)
     assert sorted(gpu) == sorted(list(bufs) + ["dX"])
     compare(gpu, ref, "bf16")
+
+
+# Tokens in one pass and tokens for whose partial sums the scratch has no room, the parts of t2 16, 8 and 4
+BITS_SHAPE = (64, 2, 2, 64, 320, 1e-5, 10000.0)
+BITS = [(8, 880, 1000), (8, 1480, 1600), (8, 2480, 2600)]
+
+
+@pytest.mark.parametrize("rank,in_one,apart", BITS)
+def test_data_gradient_keeps_its_bits_in_one_pass(monkeypatch, rank, in_one, apart):
+    """The tokens of a batch that takes one pass, alone and at the front of one that takes two: t2, and so dX, is the same sum (no
+    product of this shape is long enough to be cut, and no sequence depends on another)."""
+    import paper_2503_01066_amd as A
+    monkeypatch.setitem(synth.SHAPES, "pass", BITS_SHAPE)
+    cu = synth.uniform_cu(apart // 40, 40)
+    shp, osh, W, lora, lora64, rec, dY, scale = make_case("pass", "bf16", cu, 31, rank, synth.PROJECTIONS, record="drawn", dy_std=0.01)
+    both = run_gpu(shp, "bf16", cu, W, lora, rank, scale, rec, dY)["dX"]
+    front = run_gpu(shp, "bf16", synth.uniform_cu(in_one // 40, 40), W, lora, rank, scale, {k: v[:in_one] for k, v in rec.items()}, dY[:in_one])["dX"]
+    assert np.array_equal(front, both[:in_one])

@@ -1,5 +1,6 @@
 """fp32 layers whose RMSNorm backward and gain sums share a launch with a weight gradient: hidden sizes either side of the columns
-a thread takes, rows below, at and beyond the partial rows that are added at once, and lengths beyond those launches."""
+a thread takes, rows below, at and beyond the 64 partial rows that are added at once; and layers whose launches stay apart: tokens that
+are no whole chunks or too many, too few for the partial rows of both gains to find room, rows too wide (test_host_choices.py holds both lists to that)."""
 import numpy as np
 import pytest
 import torch
@@ -13,11 +14,18 @@ from helpers import alch_shape, to_dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("hidden,T", [(256, 1), (256, 129), (256, 511), (256, 512), (260, 40), (1024, 65), (1028, 30)])
+BESIDE = [(256, 8192, 16), (256, 8192, 64), (256, 8192, 72), (256, 8192, 496), (256, 512, 256), (260, 6400, 24), (260, 6400, 136),
+          (1024, 2048, 256), (1024, 2048, 264)]
+APART = [(256, 8192, 65), (256, 8192, 512), (256, 512, 1), (256, 512, 129), (256, 512, 511), (256, 512, 512), (260, 512, 40), (1024, 512, 65),
+         (1028, 512, 30), (1028, 2048, 264)]
+QKV = 3 * 4 * 64
+
+
+@pytest.mark.parametrize("hidden,ffn,T", BESIDE + APART)
 @pytest.mark.parametrize("masked", [False, True])
-def test_rows_beside_products(monkeypatch, hidden, T, masked):
+def test_rows_beside_products(monkeypatch, hidden, ffn, T, masked):
     import paper_2503_01066_amd as A
-    monkeypatch.setitem(synth.SHAPES, "rows", (hidden, 4, 4, 64, 512, 1e-5, 10000.0))
+    monkeypatch.setitem(synth.SHAPES, "rows", (hidden, 4, 4, 64, ffn, 1e-5, 10000.0))
     cu = synth.ragged_cu([min(50, T - a) for a in range(0, T, 50)])
     shp, osh, W, rec, dY = make_case("rows", "f32", cu, 23, "drawn", dy_std=0.01)
     mask = synth.keep_mask(T, 0.5, 3) if masked else None

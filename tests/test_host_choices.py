@@ -43,4 +43,40 @@ def test_adapter_pass_takes_no_rows_that_its_launch_refuses(ask):
     """[dG | dU] rows of 2^22 elements and more: beyond the offsets of the pass (128 rows below 2^29 elements), so the layer takes the
     separate kernels; a layer that found this out at the launch had failed half way."""
     last = (1 << 21) - 64  # [dG | dU] has two of them to a row
-    assert ask(("one_pass", 8, last, 8), ("one_pass", 8, last + 64, 8), ("one_pass", 8, 1 << 22, 8)) == [(1,), (0,), (0,)]
+    assert ask(*[("one_pass", 8, 64, ffn, 8) for ffn in (last, last + 64, 1 << 22)]) == [(1,), (0,), (0,)]
+
+
+# ---- the GPU tests that are about one kernel reach it (256 compute units)
+def test_ring_lengths_run_on_the_kernel_with_the_rings(ask):
+    from test_gpu_gemm_rings import CASES, M, N, OTHER_KERNEL
+    for a_k, b_k, lengths in CASES:
+        assert ask(*[("kernel", M, N, K, a_k, b_k) for K in lengths]) == [(0,)] * len(lengths), (a_k, b_k)
+        step = 64 if a_k or b_k else 32
+        assert {K // step % (320 // step) for K in lengths} == set(range(320 // step)), (a_k, b_k)  # where the rings end
+    a_k, b_k, lengths = OTHER_KERNEL
+    assert ask(*[("kernel", M, N, K, a_k, b_k) for K in lengths]) == [(1,)] * len(lengths)
+
+
+def test_long_kept_rows_run_on_the_kernel_with_the_rings(ask):
+    from test_gpu_kept_rows_products import LONG, LONG_T
+    hidden, n_q, n_kv, head_dim, ffn = LONG[:5]
+    half = LONG_T // 2  # (the choice is that for half of the tokens)
+    assert ask(("kernel", 2 * ffn, hidden, half, False, False)) == [(0,)]
+
+
+def test_rows_beside_products_share_their_launch(ask):
+    from test_gpu_rows_beside_products import APART, BESIDE, QKV
+    beside = lambda cases: ask(*[("rows_beside", hidden, ffn, T, QKV) for hidden, ffn, T in cases])
+    assert beside(BESIDE) == [(1, 1)] * len(BESIDE)
+    assert beside(APART) == [(0, 0)] * len(APART)
+
+
+def test_pairs_of_batches_differ_in_the_pass_and_not_in_the_parts_of_t2(ask):
+    from test_gpu_lora_pass import BITS, BITS_SHAPE
+    hidden, ffn = BITS_SHAPE[0], BITS_SHAPE[4]
+    for rank, in_one, apart in BITS:
+        assert ask(("one_pass", in_one, hidden, ffn, rank), ("one_pass", apart, hidden, ffn, rank)) == [(1,), (0,)]
+        for problems in (1, 2):  # of d by itself, of gate and up
+            p = ask(("t_parts", in_one, problems), ("t_parts", apart, problems))
+            assert p[0] == p[1], (in_one, apart, problems)
+    assert {ask(("t_parts", b[1], 2))[0] for b in BITS} == {(16,), (8,), (4,)}

@@ -30,8 +30,8 @@ def asm():
     if not (shutil.which(B._hipcc()) or os.path.exists(B._hipcc())):
         pytest.skip("hipcc not found")
     names = {"gemm": "gemm_mfma.hip", "attn": "attn_mfma.hip", "pair": "gemm_pair.hip", "attn64": "attn_mfma_d64.hip", "head": "lmhead.hip",
-             "lora": "lora.hip"}
-    with ThreadPoolExecutor(max_workers=6) as ex:
+             "lora": "lora.hip", "generic": "gemm_generic.hip"}
+    with ThreadPoolExecutor(max_workers=7) as ex:
         return dict(zip(names, ex.map(_device_asm, names.values())))
 
 
@@ -80,9 +80,11 @@ def test_attention_kernels_do_not_spill(asm):
                 assert "scratch_" not in txt, (name, lab)
 
 
-def test_contraction_kernel_of_two_work_groups_keeps_its_registers_and_its_pipeline(asm):
+@pytest.mark.parametrize("prefix,count", [("_ZN4alch11k_gemm_pairI", 4),         # operand layouts
+                                          ("_ZN4alch16k_gemm_pair_rowsI", 2)])  # of the right operand, row count on the device
+def test_contraction_kernel_of_two_work_groups_keeps_its_registers_and_its_pipeline(asm, prefix, count):
     seen = 0
-    for name, body in _functions(asm["pair"], "_ZN4alch11k_gemm_pairI"):
+    for name, body in _functions(asm["pair"], prefix):
         assert _meta(asm["pair"], name, "vgpr_spill_count") == 0 and _meta(asm["pair"], name, "private_segment_fixed_size") == 0, name
         assert _meta(asm["pair"], name, "vgpr_count") <= 256 and _meta(asm["pair"], name, "group_segment_fixed_size") <= 80 * 1024, name
         loops = [(lab, txt) for lab, txt in _blocks(body) if txt.count("v_mfma_") >= 16]
@@ -90,7 +92,14 @@ def test_contraction_kernel_of_two_work_groups_keeps_its_registers_and_its_pipel
         for lab, txt in loops:
             assert "scratch_" not in txt and not re.search(r"s_waitcnt [^\n]*vmcnt\(0\)", txt), (name, lab)
         seen += 1
-    assert seen == 4  # operand layouts
+    assert seen == count
+
+
+def test_fp32_products_beside_rows_do_not_spill(asm):
+    kernels = [n for n, _ in _functions(asm["generic"], "_ZN4alch") if "k_gemm_f32_norm" in n or "k_gemm_f32_gains" in n]
+    assert len(kernels) == 3, kernels  # rows of one and of four columns a thread; gain sums
+    for n in kernels:
+        assert _meta(asm["generic"], n, "vgpr_spill_count") == 0 and _meta(asm["generic"], n, "private_segment_fixed_size") == 0, n
 
 
 def test_attention_kernels_of_heads_of_64_do_not_spill(asm):
