@@ -164,8 +164,9 @@ static LayerBwdPlan plan_layer_bwd(const alch_layer_shape& s, int T, void* ws, s
         p.Ap_qkv = a.take(3 * kLoraSlot * H * E);
         const size_t outs[ALCH_N_PROJ] = {QD, KD, KD, H, F, F, H};
         for (int i = 0; i < ALCH_N_PROJ; ++i) p.Bt[i] = a.take((size_t)lora_rank * outs[i] * E);
-        // the widest group of adapter gradients formed by one launch: gate + up (dA on H twice, dB on F twice) or
-        // q + k + v (dA on H three times, dB on QD + 2 KD)
+        // the widest group of adapter gradients formed by one launch of k_lora_up_partial: gate + up (dA on H twice, dB on F twice) or
+        // q + k + v (dA on H three times, dB on QD + 2 KD).  A shared pass over Act, dG and dU finds room in it up to 12,000 to 13,300
+        // tokens (lora_pass_fits).
         const size_t n_sum = std::max(2 * (H + F), std::max(3 * H + QD + 2 * KD, std::max(F + H, QD + H)));
         p.up_scratch_bytes = lora_up_scratch_bytes(lora_rank, (int)n_sum);
         p.up_scratch = static_cast<float*>(a.take(p.up_scratch_bytes));

@@ -677,8 +677,9 @@ static void launch_big(const MfmaGemmParams& p, int grid, hipStream_t stream) {
 // A product whose row count lies on the device (the rows that a loss mask keeps): every kernel that some count of rows up to M
 // calls for is launched, and reads the count.  With 256x256 tiles alone, whole, a few hundred kept rows left most compute
 // units without work and the others with all of a long contraction: the gradient of H2 of 175 kept rows (4096 columns, K 28672)
-// was 474 us on 16 busy compute units.  Layers with a quarter of the rows kept: 700 tokens 1038 -> 526 us, 1500 tokens 1202 -> 751,
-// 5003 tokens and a tenth of them 1751 -> 1257; where the 256x256 tiles stay (hidden 8192, 8192 tokens) 8989 and 8988.
+// was 474 us on 16 busy compute units.  Layers of 4096/14336 with a quarter of the rows kept: 700 tokens 1022 -> 509 us, 1500 tokens
+// 1210 -> 748, 5003 tokens and a tenth of them 1825 -> 1292; where the 256x256 tiles stay (hidden 8192, 8192 tokens) 8854 and 8889: the
+// launches that leave are 28 us of a profile.
 static int launch_device_rows(MfmaProduct& m, hipStream_t stream) {
     MfmaGemmParams& p = m.p;
     int pair_most = 0, cut_most = 0;

@@ -164,17 +164,19 @@ __host__ __device__ inline PairPlan pair_plan(int M, int N, int nk_total, bool a
 // besides, with the last round on its own.  The constants are fits to measured products of 128 .. 8192 rows,
 // K 128 .. 28672, each form (data gradient, weight gradient, forward), which they reproduce to about 10 % (both kernels on 40
 // products: profiles/contraction_kernels_both_sides.txt; the one taken is never more than 2 % behind the other, but for
-// 487 x 4096 x 28672, a tie by the estimates: 126 and 118 us):
+// 487 x 4096 x 28672, a tie by the estimates: 126 and 118 us).  Of the 256x256 kernel only the forward constant was fitted again
+// since its rings hold half stages; data gradients have become up to 3 % faster than theirs says:
 //   256x256 tiles, one per compute unit:   0.0232 K + 11 us a round (forward 0.0222 K); a last round that is cut along K (big_parts
 //                                          > 1) adds its two kernels
 //   128x256 tiles, two per compute unit:   0.0265 K + 2 us a round (0.0255 K + 3 weight gradient, 0.0276 K + 6 forward);
 //                                          with one per compute unit, half of that
-// The second one reads 1.5 times as much from L2 per multiply-add, which the long K pays for (8192 x 4096 x 28672: 1388
-// against 1574 us), and has no idle start and end of tile, nor as coarse a last round (4096 x 14336 x 487: 86 against
-// 60 us; 6144 x 4096 x 1024: 82 against 49; 487 x 4096 x 4096: 47 against 31; 6001 x 4096 x 6144: 262 against 239 us).
+// The second one reads 1.5 times as much from L2 per multiply-add, which the long K pays for (8192 x 4096 x 28672: 1290
+// against 1505 us), and has no idle start and end of tile, nor as coarse a last round (weight gradients 14336 x 4096 x 480: 81
+// against 59 us, 6144 x 4096 x 1024: 80 against 49; data gradients 487 x 4096 x 4096: 46 against 30, 6001 x 4096 x 6144: 241 against
+// 228 us).
 // Whole tiles of the second one fill rounds of two work-groups per compute unit, or a last one of at most one each; the
 // tiles cut along K run beside that.  4099 x 2048 x 16384 is 17 tiles for the 32 compute units of an XCD, or 32 whole tiles
-// of half the size and one in 16 parts: 410 -> 290 us.
+// of half the size and one in 16 parts: 261 against 220 us.
 __host__ __device__ inline bool pair_is_better(int M, int N, long long K, bool a_kmajor, bool b_kmajor, bool swiglu, int n_cu, int big_parts,
                                                const PairPlan& plan) {
     const int cus = n_cu / 8;                             // compute units of an XCD

@@ -254,7 +254,6 @@ __global__ __launch_bounds__(256) void k_finish_loss(const float* __restrict__ r
     }
 }
 
-// counted[t] = 1 where the token contributes to the loss (0 <= label < vocab and loss-mask byte nonzero)
 int launch_count_labels(const int* labels, const uint8_t* loss_mask, int T, int vocab, int* n_counted, float* row_loss, uint8_t* counted,
                         hipStream_t stream) {
     k_count_labels<<<1, 256, 0, stream>>>(labels, loss_mask, T, vocab, n_counted, row_loss, counted);

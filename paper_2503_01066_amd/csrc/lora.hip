@@ -1,8 +1,9 @@
 // Low-rank adapter (LoRA) kernels: the rank-r products around a projection y = x W^T + s (x A^T) B^T
 // (Section 3, assumption A1 and Section 6 of the paper: parameter-efficient fine-tuning, rank 8).
 //
-// With r = 8 every one of these products streams a [T, width] activation once and does 8 multiply-adds
-// per element, so they are HBM-bound vector-ALU kernels, not matrix-core work:
+// With r = 8 every one of these products streams a [T, width] activation once and does 8 multiply-adds per element: HBM-bound where
+// the matrix cores do them ("down" in bf16 here, "up" in bf16 and both in one pass in lora_pass.hip), near it on the vector ALU
+// (fp32, other widths, more partial sums than the scratch of a shared pass holds):
 //   down:  Y[T, r]  = alpha * X[T, K] * S         (S = A^T or B; "t1 = x A^T", "t2 = dy B")
 //   up:    C[r, N]  = alpha * S[T, r]^T * X[T, N] (adapter gradients dA = t2^T x, dB^T = t1^T dy)
 // Storage type T is float or bf16, arithmetic fp32, sums over tokens in a fixed order (deterministic).
