@@ -649,9 +649,7 @@ static int plan_product(const GemmDesc& d, MfmaProduct& out) {
     p.plan_cu = out.n_cu;
     p.a_kmajor = d.a_kmajor;
     p.b_kmajor = d.b_kmajor;
-    // A row count on the device: cut also where the bits of the parts are to stay, since no other count of rows cuts them alike
-    // anyhow.  Whole, the gradient of 136 kept rows of a head (4096 columns, K 128256) was 16 busy compute units for 1525 us.
-    p.plan_ws = d.keep_parts && !d.m_dev ? 0 : (long long)ws_bytes;
+    p.plan_ws = d.keep_parts ? 0 : (long long)ws_bytes;
     const bool swiglu = p.epilogue == kEpiSwigluBwd;
     // m_dev: launch_device_rows.  k_dev: whole tiles, of the kernel that is the faster one with half of the tokens kept (its
     // tiles are the same for any count, and the lengths where the choice turns lie close together)
