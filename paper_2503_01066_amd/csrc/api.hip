@@ -451,14 +451,19 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
 
     // Loss mask.  Rows of dY whose mask byte is 0 count as zero.  Everything from the MLP down to the
     // attention output projection is row-local, so those rows contribute nothing there and receive nothing:
-    //   compact mode (bf16, matrix-core shapes, no adapters): the kept rows of dY, X2, O, G, U are gathered
+    //   compact mode (bf16, matrix-core shapes): the kept rows of dY, X2, O, G, U are gathered
     //     into dense [n, width] tensors, the row-local part runs on n rows (n stays on the device: the
     //     products take their row or contraction count from device memory), and dX2, dO are scattered back
     //     into zero-filled [T, width] tensors for the attention backward, which is dense in the keys;
     //   otherwise dY is copied once with the masked rows zeroed and every step runs on all T rows.
     // (the compacted products take their sizes from device memory, which only the matrix-core kernel supports:
     // its 2 GiB operand limit, reached first by [dG | dU], is part of the decision, taken before anything is enqueued)
-    const bool compact = loss_mask && T > 0 && !lo && dt == ALCH_BF16 && H % 64 == 0 && F % 64 == 0 && QD % 64 == 0 &&
+    // With adapters: outside of stacks of several layers, whose layers below would carry on the other roundings, and where
+    // the rows left out are worth the launches that find, gather and scatter the others (one tile of 128 rows gets no shorter).
+    // us without / with, 0.25 or 0.6 of the rows kept: 8B shape 130 tokens 455 / 468 (all gradients), 200 489 / 494, 260 384 / 334 (frozen),
+    // 520 483 / 387, 1490 1397 / 849; hidden 2048, ffn 8192 390 tokens 322 / 334, 520 362 / 363, 1000 482 / 448; 70B shape 130 630 / 571.
+    const bool lora_pays = one_pass && !keep_parts && T > 128 && (double)T * H * F >= 15e9;
+    const bool compact = loss_mask && T > 0 && (!lo || lora_pays) && dt == ALCH_BF16 && H % 64 == 0 && F % 64 == 0 && QD % 64 == 0 &&
                          aligned16(dY) && (long long)T * 2 * F * (long long)E < (1LL << 31);
     const void *mY = dY, *mX2 = sv.X2, *mO = sv.O, *mG = sv.G, *mU = sv.U;  // inputs of the row-local part
     void *mdX2 = p.dX2, *mdO = p.dO;                                      // its outputs
@@ -493,10 +498,10 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         int n = 0;
         for (int i = 0; i < 2; ++i)
             if (wants_dB(ALCH_PROJ_G + i)) jobs[n++] = LoraDown{p.Hn, H, H, lo->A[ALCH_PROJ_G + i], H, r, slot(p.T1, i)};
-        if (n > 0 && !hn_ready) ALCH_TRY(launch_rmsnorm_fwd(dt, mX2, w.g2, p.Hn, T, H, s.rms_eps, st));
+        if (n > 0 && !hn_ready) ALCH_TRY(launch_rmsnorm_fwd(dt, mX2, w.g2, p.Hn, T, H, s.rms_eps, st, ndev));
         hn_ready = hn_ready || n > 0;
         if (has(ALCH_PROJ_D)) jobs[n++] = LoraDown{mY, H, H, p.Bt[ALCH_PROJ_D], H, r, slot(p.T2, 0)};
-        if (n > 0) ALCH_TRY(launch_lora_down(dt, jobs, n, T, lo->scale, ldt2, kLoraSlot, st, t2_alone));
+        if (n > 0) ALCH_TRY(launch_lora_down(dt, jobs, n, T, lo->scale, ldt2, kLoraSlot, st, t2_alone, ndev));
     } else if (has(ALCH_PROJ_D)) {
         const void* dys[1] = {mY};
         const int outs1[1] = {H};
@@ -536,7 +541,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     if (g.dWd && !dwd_beside && !dwd_with_norm) ALCH_TRY(launch_gemm(dWd, st));
     if (one_pass) {
         ALCH_TRY(launch_lora_pass(mlp + (has(ALCH_PROJ_D) ? 0 : 1), (lora_gu ? 3 : 1) - (has(ALCH_PROJ_D) ? 0 : 1), T, ldt2, lo->scale,
-                                  adapter_sums, st));
+                                  adapter_sums, st, ndev));
     } else {
         const void* dys[1] = {mY};
         const int outs1[1] = {H};
@@ -601,7 +606,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
 
     if (one_pass && has(ALCH_PROJ_O)) {  // t2, t1
         LoraDown jobs[2] = {{mdX2, H, H, p.Bt[ALCH_PROJ_O], H, r, slot(p.T2, 2)}, {mO, QD, QD, lo->A[ALCH_PROJ_O], QD, r, slot(p.T1, 0)}};
-        ALCH_TRY(launch_lora_down(dt, jobs, wants_dB(ALCH_PROJ_O) ? 2 : 1, T, lo->scale, ldt2, kLoraSlot, st, t2_alone));
+        ALCH_TRY(launch_lora_down(dt, jobs, wants_dB(ALCH_PROJ_O) ? 2 : 1, T, lo->scale, ldt2, kLoraSlot, st, t2_alone, ndev));
     } else if (has(ALCH_PROJ_O)) {
         const void* dys[1] = {mdX2};
         const int outs1[1] = {H};
@@ -620,7 +625,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         if (wants(ALCH_PROJ_O)) add_up(rest[2], p.T1, 0, lg->dB[ALCH_PROJ_O], r, 1);
         open(rest[3], mO, QD);
         if (wants(ALCH_PROJ_O)) add_up(rest[3], p.T2, 2, lg->dA[ALCH_PROJ_O], QD, 0);
-        ALCH_TRY(launch_lora_pass(rest, 4, T, ldt2, lo->scale, adapter_sums, st));
+        ALCH_TRY(launch_lora_pass(rest, 4, T, ldt2, lo->scale, adapter_sums, st, ndev));
     } else {
         const void* dys[1] = {mdX2};
         const int outs1[1] = {H};

@@ -147,9 +147,10 @@ struct LoraDown {
     void* Y;
 };
 // as_problems > 0: the sums over K are cut as for so many problems, whatever else the launch holds (t2 keeps its bits).
+// rows_dev (optional, matrix-core kernel only): the row count is min(*rows_dev, Trows), read on the device.
 static constexpr int kDownGroups = 4;  // groups of eight rank columns of a problem
 int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows, float alpha, long long ldy,
-                     int slot_cols, hipStream_t stream, int as_problems = 0);
+                     int slot_cols, hipStream_t stream, int as_problems = 0, const int* rows_dev = nullptr);
 int lora_down_parts(int Trows, int problems, int n_cu);  // parts that the sums over K are cut into
 // C(j, n) (+)= alpha * sum_t S[t*lds + j] * X[t*ldx + n], j < r, n < N; stored C[j*ldc + n], or C[n*ldc + j]
 // when transposed.  Up to kLoraUpJobs problems per launch, all with Trows rows, the same r, alpha and
@@ -173,6 +174,8 @@ struct LoraUpJob {
     int transposed;
     int first_group;        // work-groups of the jobs before this one in the launch that adds the splits
     long long scratch_off;  // floats
+    const int* rows_dev;    // of a row count on the device: it, and the rows of a split; splits past it were not written
+    int rows_dev_split;
 };
 static constexpr int kLoraUpSums = 14;  // A and B of seven projections
 struct LoraUpParams {
@@ -188,10 +191,11 @@ struct LoraUpSums {
 int launch_lora_up(alch_dtype dt, const LoraUp* jobs, int n_jobs, LoraUpSums& sums, hipStream_t stream);
 int launch_lora_up_sums(alch_dtype dt, LoraUpSums& sums, hipStream_t stream);
 // Adds a gradient whose partial sums [r/8][nsplit][8][N] a kernel will leave at scratch + sums.floats (before the call).
-void add_lora_up_job(LoraUpSums& sums, const LoraUp& j, int nsplit);
+void add_lora_up_job(LoraUpSums& sums, const LoraUp& j, int nsplit, const int* rows_dev = nullptr, int rows_dev_split = 0);
 // Both in one pass over X [Trows, K] (bf16; lora_pass.hip): T = alpha X P^T into an output slot (P [r, K], null: none; pad:
 // zeros in the columns past the rank, and in all of them without P), and the gradients up[i] = Q[:, q_col .. +r]^T X, whose
-// sums are left to launch_lora_up_sums.  Q and T have row stride ldq; Q holds the three slots of a row.
+// sums are left to launch_lora_up_sums.  Q and T have row stride ldq; Q holds the three slots of a row.  rows_dev: as
+// launch_lora_down.
 static constexpr int kPassUps = 3;
 struct LoraPass {
     const void* X; long long ldx; int K;
@@ -204,7 +208,8 @@ struct LoraPass {
     struct { int q_col; void* C; long long ldc; int transposed; } up[kPassUps] = {};
 };
 bool lora_pass_fits(const LoraPass* jobs, int n_jobs, int Trows, const LoraUpSums& sums);
-int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq, float alpha, LoraUpSums& sums, hipStream_t stream);
+int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq, float alpha, LoraUpSums& sums, hipStream_t stream,
+                     const int* rows_dev = nullptr);
 // Operand preparation: job i writes dst [rows_out, cols] = src [r, cols] (or, transpose, src [cols, r]
 // transposed) followed by zero rows; src null: all zeros.
 struct LoraPrepJob {

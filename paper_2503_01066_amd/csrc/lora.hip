@@ -109,6 +109,7 @@ struct LoraDownParams {
     LoraDownProblem pr[kDownProblems];
     __bf16* slot[3]; int slot_r[3]; int nslots;  // output slots: columns slot_r .. slot_cols-1 are zero-filled
     int Trows; long long ldy; float alpha; int slot_cols;
+    const int* rows_dev;
 };
 template <int kG, int kRows, int kWaves> struct DownCfg {
     static constexpr int kStageBytes = kRows * 128 + kG * 1024;
@@ -140,7 +141,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_lora_down_mfma(LoraDownParams p
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 31, kh = lane >> 5;
     const long long t0 = (long long)blockIdx.x * kRows;
-    const int rows_valid = (int)(p.Trows - t0 < kRows ? p.Trows - t0 : kRows);
+    const int Trows = p.rows_dev ? min(__builtin_amdgcn_readfirstlane(*p.rows_dev), p.Trows) : p.Trows;
+    if (t0 >= Trows) return;
+    const int rows_valid = (int)(Trows - t0 < kRows ? Trows - t0 : kRows);
     if (blockIdx.y == 0) {  // the columns past the rank of every output slot
         const int pieces = p.slot_cols >> 3;
         const bf16x8_l z = {(__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
@@ -344,6 +347,7 @@ __global__ __launch_bounds__(256) void k_lora_up_finish(LoraUpParams p) {
         if ((int)blockIdx.x >= p.job[i].first_group) at = i;
     const LoraUpJob jb = p.job[at];
     const int N = jb.N, nsplit = jb.nsplit;
+    const int live_splits = jb.rows_dev ? min((max(*jb.rows_dev, 0) + jb.rows_dev_split - 1) / jb.rows_dev_split, nsplit) : nsplit;
     const long long idx = (long long)((int)blockIdx.x - jb.first_group) * kSumsPerGroup + (threadIdx.x >> 3) * 4;
     const int q = threadIdx.x & 7;
     const bool live = idx < (long long)N * p.r;
@@ -353,7 +357,7 @@ __global__ __launch_bounds__(256) void k_lora_up_finish(LoraUpParams p) {
     const float* src = p.scratch + jb.scratch_off + ((long long)(jj >> 3) * nsplit * 8 + (jj & 7)) * N + n;
     f32x4_l s = {0.f, 0.f, 0.f, 0.f};
     if (live)
-        for (int k = q; k < nsplit; k += 8) s += *reinterpret_cast<const f32x4_l*>(src + (long long)k * 8 * N);
+        for (int k = q; k < live_splits; k += 8) s += *reinterpret_cast<const f32x4_l*>(src + (long long)k * 8 * N);
 #pragma unroll
     for (int d = 1; d < 8; d <<= 1)
 #pragma unroll
@@ -449,7 +453,7 @@ int lora_down_parts(int Trows, int problems, int n_cu) {
 }
 
 int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows, float alpha, long long ldy,
-                     int slot_cols, hipStream_t stream, int as_problems) {
+                     int slot_cols, hipStream_t stream, int as_problems, const int* rows_dev) {
     if (n_jobs < 1 || n_jobs > 3) return fail(ALCH_ERR_INVALID_ARG, "adapter product: 1..3 problems per launch");
     double flops = 0, bytes = 0;
     bool fast = dt == ALCH_BF16;
@@ -484,8 +488,10 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
             }
         }
         p.Trows = Trows; p.ldy = ldy; p.alpha = alpha; p.slot_cols = slot_cols;
+        p.rows_dev = rows_dev;
         bytes = 0;
-        for (int i = 0; i < np; ++i) bytes += (double)Trows * p.pr[i].K * dtype_size(dt);
+        if (rows_dev) flops = 0;  // (what is done only the device knows)
+        for (int i = 0; i < np && !rows_dev; ++i) bytes += (double)Trows * p.pr[i].K * dtype_size(dt);
         TraceScope ts(kTraceLora, flops, bytes, stream);
         int n_cu = 0;
         ALCH_TRY(compute_units(&n_cu));
@@ -494,6 +500,7 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
         else if (parts == 8) launch_down<16, 8>(p, most, Trows, np, stream);
         else launch_down<32, 4>(p, most, Trows, np, stream);
     } else {
+        if (rows_dev) return fail(ALCH_ERR_UNSUPPORTED, "adapter product: a row count on the device needs the matrix-core kernel");
         TraceScope ts(kTraceLora, flops, bytes, stream);
         for (int i = 0; i < n_jobs; ++i) {
             if (dt == ALCH_BF16) lora_down_valu<__bf16>(jobs[i], Trows, alpha, ldy, slot_cols, stream);
@@ -504,12 +511,12 @@ int launch_lora_down(alch_dtype dt, const LoraDown* jobs, int n_jobs, int Trows,
     return ALCH_OK;
 }
 
-void add_lora_up_job(LoraUpSums& sums, const LoraUp& j, int nsplit) {
+void add_lora_up_job(LoraUpSums& sums, const LoraUp& j, int nsplit, const int* rows_dev, int rows_dev_split) {
     LoraUpParams& p = sums.p;
     const LoraUpJob* before = p.n_jobs > 0 ? &p.job[p.n_jobs - 1] : nullptr;
     const int first_group = before ? before->first_group + ceil_div((long long)before->N * p.r, (long long)kSumsPerGroup) : 0;
     p.job[p.n_jobs++] = LoraUpJob{j.S, j.lds, j.X, j.ldx, j.N, nsplit, nsplit > 0 ? ceil_div(p.Trows, nsplit) : 0, j.C, j.ldc,
-                                  j.transposed, first_group, sums.floats};
+                                  j.transposed, first_group, sums.floats, rows_dev, rows_dev_split};
     sums.floats += (long long)p.r * nsplit * j.N;
 }
 

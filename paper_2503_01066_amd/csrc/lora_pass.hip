@@ -40,6 +40,7 @@ struct LoraPassParams {
     int n, Trows, rows_per_split, parts;
     long long ldq;
     float* scratch;
+    const int* rows_dev;  // the row count is min(*rows_dev, Trows); splits past it are not written
 };
 
 __device__ __forceinline__ i32x4 pass_rsrc(const void* p, long long bytes) {
@@ -64,6 +65,11 @@ __device__ __forceinline__ bf16x8 pass_tr(const char* first, const char* second)
     const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)first);
     const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)second);
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// Rows of the work-group's block or split that starts at r0 (none: nothing to do)
+__device__ __forceinline__ int pass_rows(const LoraPassParams& p, long long r0, int most) {
+    const int Trows = p.rows_dev ? min(__builtin_amdgcn_readfirstlane(*p.rows_dev), p.Trows) : p.Trows;
+    return (int)min((long long)most, Trows - r0);
 }
 __device__ __forceinline__ int pass_problem(const LoraPassParams& p) {
     int at = 0;
@@ -90,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void k_lora_up_mfma(LoraPassParams p) {
     const LoraPassProblem& pb = p.pr[pass_problem(p)];
     const int c0 = ((int)blockIdx.x - pb.first) * kPassCols, K = pb.K, n_up = pb.n_up;
     const long long r0 = (long long)blockIdx.y * p.rows_per_split;
-    const int rows = (int)min((long long)p.rows_per_split, p.Trows - r0);
+    const int rows = pass_rows(p, r0, p.rows_per_split);
     if (rows <= 0) return;
     const int n = (rows + kPassRows - 1) / kPassRows;
 
@@ -174,7 +180,8 @@ __global__ __launch_bounds__(256, 2) void k_lora_both(LoraPassParams p) {
     const int part = (int)blockIdx.x - pb.first, chunks = pb.K >> 6;
     const int k0 = part * chunks / p.parts * 64, cols = (part + 1) * chunks / p.parts * 64 - k0;  // this part's columns
     const long long r0 = (long long)blockIdx.y * (kM * kBothRows);
-    const int rows = (int)min((long long)(kM * kBothRows), p.Trows - r0);
+    const int rows = pass_rows(p, r0, kM * kBothRows);
+    if (rows <= 0) return;
     const int n = (cols + kBothCols - 1) / kBothCols * kM, n_down = pb.n_down, n_up = pb.n_up;
     const uint32_t q_lds = lds0 + 2 * kBothStage;
 
@@ -292,11 +299,12 @@ struct LoraTParams {
     long long ldo;
     float alpha;
     const float* scratch;
+    const int* rows_dev;
 };
 __global__ __launch_bounds__(256) void k_lora_t_finish(LoraTParams p) {
     const LoraTJob jb = p.job[blockIdx.y];
     const int row = blockIdx.x * 256 + threadIdx.x;
-    if (row >= p.Trows) return;
+    if (row >= (p.rows_dev ? min(*p.rows_dev, p.Trows) : p.Trows)) return;
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
     const float* t = p.scratch + jb.t_off + ((long long)row * jb.groups + jb.group) * 8;
 #pragma unroll 4
@@ -361,7 +369,8 @@ bool lora_pass_fits(const LoraPass* jobs, int n_jobs, int Trows, const LoraUpSum
     return plan_pass(jobs, n_jobs, Trows, sums, p) == ALCH_OK && p.need_up + p.need_t <= sums.capacity && p.splits <= kLoraMaxSplits;
 }
 
-int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq, float alpha, LoraUpSums& sums, hipStream_t stream) {
+int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq, float alpha, LoraUpSums& sums, hipStream_t stream,
+                     const int* rows_dev) {
     if (Trows <= 0 || n_jobs <= 0) return ALCH_OK;
     const int r = sums.p.r, groups = r / 8;
     if (r % 8 || r <= 0 || ldq % 8) return fail(ALCH_ERR_UNSUPPORTED, "adapter product: rank must be a positive multiple of 8");
@@ -377,6 +386,7 @@ int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq,
     LoraTParams tp = {};
     p.Trows = tp.Trows = Trows;
     p.rows_per_split = plan.rows;
+    p.rows_dev = tp.rows_dev = rows_dev;
     p.parts = plan.parts;
     p.ldq = tp.ldo = ldq;
     tp.alpha = alpha;
@@ -391,7 +401,8 @@ int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq,
         long long up_off[kPassUps];
         for (int u = 0; u < j.n_up; ++u) {
             up_off[u] = sums.floats;
-            add_lora_up_job(sums, LoraUp{nullptr, 0, j.X, j.ldx, j.K, j.up[u].C, j.up[u].ldc, j.up[u].transposed}, plan.splits);
+            add_lora_up_job(sums, LoraUp{nullptr, 0, j.X, j.ldx, j.K, j.up[u].C, j.up[u].ldc, j.up[u].transposed}, plan.splits,
+                            rows_dev, plan.rows);
         }
         for (int g0 = 0; g0 < up_groups || g0 < down_groups; g0 += kPassGroups) {
             if (p.n == kPassProblems) return fail(ALCH_ERR_UNSUPPORTED, "adapter product: too many problems");
@@ -414,8 +425,8 @@ int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq,
                     tp.job[tp.n++] = LoraTJob{t_off, plan.parts, pb.n_down, g, static_cast<__bf16*>(j.T) + (g0 + g) * 8};
                 t_off += (long long)plan.parts * Trows * pb.n_down * 8;
             }
-            flops += 2.0 * Trows * j.K * 8 * (pb.n_down + pb.n_up);
-            bytes += 2.0 * Trows * j.K;
+            flops += rows_dev ? 0.0 : 2.0 * Trows * j.K * 8 * (pb.n_down + pb.n_up);  // (what is done only the device knows)
+            bytes += rows_dev ? 0.0 : 2.0 * Trows * j.K;
         }
         for (int g = down_groups; j.pad && g < kLoraSlot / 8; ++g) tp.job[tp.n++] = LoraTJob{0, 0, 1, 0, static_cast<__bf16*>(j.T) + g * 8};
     }
