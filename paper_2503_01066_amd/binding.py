@@ -11,6 +11,11 @@ from array import array
 import numpy as np
 import torch
 
+try:
+    from . import _marshal
+except ImportError:  # (another torch than the one it was built for: the calls below are marshalled here)
+    _marshal = None
+
 RECORD_KEYS = ("X", "X2", "Q", "K", "V", "O", "G", "U")  # + LSE (fp32)
 WEIGHT_KEYS = ("Wq", "Wk", "Wv", "Wo", "Wg", "Wu", "Wd", "g1", "g2")
 STATUS = {0: "ALCH_OK", -1: "ALCH_ERR_INVALID_ARG", -2: "ALCH_ERR_SHAPE", -3: "ALCH_ERR_WORKSPACE",
@@ -92,11 +97,12 @@ def library_path():
 
 
 _LIB = None
+_PACK = 0  # address of alch_capture_pack
 
 
 def lib():
     """Loads libalch.so (built by paper_2503_01066_amd.build); raises if it is missing."""
-    global _LIB
+    global _LIB, _PACK
     if _LIB is not None:
         return _LIB
     path = library_path()
@@ -174,6 +180,7 @@ def lib():
                                          C.c_void_p, C.c_void_p, C.c_void_p]
     L.alch_trace_enable.argtypes = [C.c_int32]
     L.alch_trace_collect.argtypes = [C.POINTER(CTraceRecord), C.c_int32, C.POINTER(C.c_int32)]
+    _PACK = C.cast(L.alch_capture_pack, C.c_void_p).value
     _LIB = L
     return L
 
@@ -200,7 +207,8 @@ def _stream_handle(stream):
 def _streams(streams, dsts):
     """The alch_stream array of a call, as the four 64-bit words of each.  Seven attributes of 14 tensors were half of the
     host's time for a short prompt; structures filled one by one cost as much again (one prompt of 317 tokens, six
-    streams: whole call 16.6 -> 11.0 us, 5 of them the library's)."""
+    streams: whole call 16.6 -> 11.0 us, 5 of them the library's; alch_capture_pack has its arguments read by the
+    extension, 7 us)."""
     words = []
     for s, d in zip(streams, dsts):
         width, size, stride = s.shape[1], s.element_size(), s.stride()
@@ -253,11 +261,16 @@ def alch_capture_pack(batch, keep_mask, streams, capacity=None, dsts=None, strea
     capacity = T if capacity is None else int(capacity)
     if dsts is None:
         dsts = [torch.empty((capacity, s.shape[1]), dtype=s.dtype, device=dev) for s in streams]
+    ws = workspace if workspace is not None else _workspace(L.alch_capture_pack_workspace_bytes(T), dev)
+    if _marshal is not None:
+        out = _marshal.capture_pack(_PACK, C.addressof(batch.c), keep_mask, streams, dsts, capacity, batch.n_seqs, ws, _stream_handle(stream))
+        if out is not None:
+            _check(out[0])
+            return out[1], out[2], out[3], dsts
     arr = _streams(streams, dsts)
     kept_index = torch.empty(max(capacity, 1), dtype=torch.int32, device=dev)
     cu_kept = torch.empty(batch.n_seqs + 1, dtype=torch.int32, device=dev)
     status = torch.empty(2, dtype=torch.int32, device=dev)
-    ws = workspace if workspace is not None else _workspace(L.alch_capture_pack_workspace_bytes(T), dev)
     _check(L.alch_capture_pack(C.byref(batch.c), _ptr(keep_mask), len(streams), arr.buffer_info()[0], capacity, _ptr(kept_index),
                                _ptr(cu_kept), _ptr(status), _ptr(ws), ws.numel(), _stream_handle(stream)))
     return kept_index, cu_kept, status, dsts

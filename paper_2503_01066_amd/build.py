@@ -1,4 +1,4 @@
-"""Builds libalch.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
+"""Builds libalch.so (HIP kernels + C ABI) for gfx950 with hipcc, and _marshal.so (a Python extension) with g++, in-tree.
 
 Usage: python -m paper_2503_01066_amd.build [--force]
 Objects go to _build/ at the repo root; the library to paper_2503_01066_amd/lib/libalch.so.
@@ -12,6 +12,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "lib", "libalch.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 SOURCES = ["api.hip", "pack.hip", "gemm_mfma.hip", "gemm_pair.hip", "gemm_generic.hip", "rowops.hip", "attn_generic.hip",
            "attn_mfma.hip", "attn_mfma_d64.hip", "lmhead.hip", "lora.hip", "lora_pass.hip", "dpo.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-inline-asm", "-Wno-unused-function",
@@ -33,6 +34,22 @@ def _stale(target, deps):
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _build_marshal(verbose):
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DNDEBUG",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + os.path.join(t, "include"),
+           "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
+           "-I" + os.path.join(ROOT, "include"), os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L" + os.path.join(t, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for marshal.cpp:\n" + r.stderr)
+    if verbose:
+        print("compiled marshal.cpp", flush=True)
+
+
 def build(force=False, verbose=True):
     bdir = os.path.join(ROOT, "_build")
     os.makedirs(bdir, exist_ok=True)
@@ -47,6 +64,8 @@ def build(force=False, verbose=True):
             jobs.append((s, o))
 
     def compile_one(job):
+        if job is None:
+            return _build_marshal(verbose)
         s, o = job
         cmd = [_hipcc()] + FLAGS + ["-c", s, "-o", o]
         r = subprocess.run(cmd, capture_output=True, text=True)
@@ -56,8 +75,9 @@ def build(force=False, verbose=True):
         if verbose:
             print("compiled", os.path.basename(s), flush=True)
 
-    with ThreadPoolExecutor(max_workers=min(8, max(1, len(jobs)))) as ex:
-        list(ex.map(compile_one, jobs))
+    marshal = force or _stale(MARSHAL, [os.path.join(CSRC, "marshal.cpp"), os.path.join(ROOT, "include", "alch.h")])
+    with ThreadPoolExecutor(max_workers=min(8, len(jobs) + 1)) as ex:
+        list(ex.map(compile_one, ([None] if marshal else []) + jobs))
     objs = [os.path.join(bdir, s.replace(".hip", ".o")) for s in SOURCES]
     if force or jobs or _stale(LIB, objs):
         cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
