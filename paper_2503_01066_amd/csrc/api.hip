@@ -663,6 +663,7 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
         a.positions = b.positions; a.rope_base = s.rope_base;
         a.scratch = p.dGU;  // [dG | dU] has had its last reader
         a.scratch_bytes = (size_t)T * 2 * F * E;
+        a.keep_parts = keep_parts;
         ALCH_TRY(launch_attn_bwd(a, st));
     }
 

@@ -285,20 +285,19 @@ __device__ __forceinline__ bf16x8 global_frag_d(const __bf16* base, long long ld
 // kPrefix: sequences may name an earlier sequence as their prefix.  The key block then also meets, after the
 // queries of its own sequence (causal), every query of every sequence that names this one (no mask but the
 // ends of the sequences).
+// kv: key/value head, z: part and key block, smem: four stages.
 template <int kD, bool kPrefix>
-__global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
+__device__ __forceinline__ void attn_dkv_block(const AttnMfmaParams& p, const int kv, const int seq, const int z, char* smem) {
     constexpr int kTileBytes = AttnTile<kD>::kBytes, kStageBytes = AttnTile<kD>::kStageBytes, kRowBytes = AttnTile<kD>::kRowBytes;
     constexpr int kKK = AttnTile<kD>::kKK, kNB = AttnTile<kD>::kNB, kLoads = AttnTile<kD>::kLoads;
-    __shared__ __attribute__((aligned(1024))) char smem[4 * kStageBytes];
     const uint32_t lds0 = (uint32_t)(uintptr_t)ALCH_LDS(smem);
-    // Work-groups are handed out in order of blockIdx.z first, so z counts the work down: a key block
+    // Work-groups are handed out in order of z first, so it counts the work down: a key block
     // with `rem` blocks of queries at or after it costs rem units, and the heaviest of all sequences
     // and heads start first (longest-processing-time-first keeps the last compute units busy).
-    const int seq = blockIdx.y, kv = blockIdx.x;
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
     if (len <= p.short_upto) return;
-    const int part = (int)blockIdx.z / p.n_blocks;
-    const int rem = p.n_blocks - ((int)blockIdx.z - part * p.n_blocks), kb = (len + 127) / 128 - rem;
+    const int part = z / p.n_blocks;
+    const int rem = p.n_blocks - (z - part * p.n_blocks), kb = (len + 127) / 128 - rem;
     if (kb < 0) return;
     // this work-group's query heads h_first .. h_end-1: the group's, or a part of them
     const int qt0 = (kb * 128) / kTileRows;
@@ -728,6 +727,12 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
         }
 }
 
+template <int kD, bool kPrefix>
+__global__ __launch_bounds__(256) void k_attn_bwd_dkv_mfma(AttnMfmaParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[4 * AttnTile<kD>::kStageBytes];
+    attn_dkv_block<kD, kPrefix>(p, blockIdx.x, blockIdx.y, blockIdx.z, smem);
+}
+
 // Sum of the partial dK, dV of the key blocks that were cut (in the order of the parts), RoPE backward, one rounding.
 // blockIdx.z: 32 keys of a sequence; kD / 4 threads to a row, four columns of the lower half of dK and their partners
 // or eight of dV each.
@@ -781,27 +786,26 @@ __global__ __launch_bounds__(256) void k_dkv_finish(AttnMfmaParams p) {
 
 // ---------------------------------------------------------------------------------------------
 // dQ
-template <int kD>
-__global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
+// h: query head, z of n_z: query block, smem: two stages; kWrite: leaves delta and LSE * log2(e) for dK/dV.
+template <int kD, bool kWrite>
+__device__ __forceinline__ void attn_dq_block(const AttnMfmaParams& p, const int h, const int seq, const int z, const int n_z, char* smem) {
     constexpr int kTileBytes = AttnTile<kD>::kBytes, kStageBytes = AttnTile<kD>::kStageBytes, kRowBytes = AttnTile<kD>::kRowBytes;
     constexpr int kKK = AttnTile<kD>::kKK, kNB = AttnTile<kD>::kNB, kLoads = AttnTile<kD>::kLoads;
-    __shared__ __attribute__((aligned(1024))) char smem[2 * kStageBytes];
     const uint32_t lds0 = (uint32_t)(uintptr_t)ALCH_LDS(smem);
-    const int seq = blockIdx.y, h = blockIdx.x;
     // (one request for both tables: work-groups of a block or two are a chain of such requests)
     const int* table = p.prefix ? p.prefix : p.cu;
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start, named = table[seq], pre = p.prefix ? named : -1;
-    // blockIdx.z is the slowest index, so it counts down the keys that a query block meets: its own blocks up to the
+    // z is the slowest index, so it counts down the keys that a query block meets: its own blocks up to the
     // diagonal and those of its prefix.  By its own blocks alone the responses on a long prompt, the heaviest of all, start
     // last.  As many ranks as the longest sequence has blocks: what lies beyond shares the last ones, and the grid
     // holds no work-group more than without prefixes.  (32/8 heads of 128, two responses to a prompt, us by own blocks / with a
     // rank for every count of keys / so: one prompt of 2048 tokens, responses of 40 132 / 98 / 98; 4 of 1024, 128 142 / 128 /
     // 125; 4 of 1024, 16 137 / 134 / 124; 4 of 300, 100 57 / 56 / 47; 6 of 100, 100 39 / 44 / 41.)
-    int qb = (int)gridDim.z - 1 - (int)blockIdx.z, pre_start = 0, pre_len = 0;
+    int qb = n_z - 1 - z, pre_start = 0, pre_len = 0;
     if (pre >= 0) {
         pre_start = p.cu[pre];
         pre_len = p.cu[pre + 1] - pre_start;
-        qb -= min((pre_len + 127) / 128, (int)gridDim.z - (len + 127) / 128);
+        qb -= min((pre_len + 127) / 128, n_z - (len + 127) / 128);
     }
     if (qb < 0 || qb * 128 >= len || len <= p.short_upto) return;
     const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -867,7 +871,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
     const int i = i0 + (lane & 31);  // this lane's query (accumulator column)
     const bool i_ok = i < len;
     const float lse2 = i_ok ? p.LSE[(long long)(seq_start + i) * p.Hq + h] * kLog2e : 0.f;
-    if (i_ok && half == 0) p.lse2[(long long)(seq_start + i) * p.Hq + h] = lse2;
+    if (kWrite && i_ok && half == 0) p.lse2[(long long)(seq_start + i) * p.Hq + h] = lse2;
     // delta_i = sum_d dO[i,d] O[i,d]: each lane holds half of the elements of its query's dO row
     float del = 0.f;
     {
@@ -879,7 +883,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
             for (int e = 0; e < 8; ++e) del += (float)of[e] * (float)gf[kk][e];
         }
         del += __shfl_xor(del, 32, 64);
-        if (i_ok && half == 0) p.delta[(long long)(seq_start + i) * p.Hq + h] = del;
+        if (kWrite && i_ok && half == 0) p.delta[(long long)(seq_start + i) * p.Hq + h] = del;
     }
     const float ndel = -del;
     f32x16 dQ[kNB];
@@ -973,6 +977,49 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
             const int ii = i0 + 8 * (e >> 2) + 4 * half + (e & 3);
             if (ii < len) dQb[(long long)ii * p.ldo + nb * 32 + (lane & 31)] = (__bf16)(dQ[nb][e] * p.scale);
         }
+}
+
+template <int kD>
+__global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[2 * AttnTile<kD>::kStageBytes];
+    attn_dq_block<kD, true>(p, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, smem);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Short batches: both gradients in one launch, behind one that forms delta and LSE * log2(e).  A work-group of either is a chain of
+// latencies of 20 to 35 us, and where all of both find a compute unit the second need not wait for the first: one
+// sequence of 201 tokens, 32/8 heads of 128 57 -> 32 us, 487 tokens 71 -> 45 (dQ, dK/dV and the sums of its parts, 5 of them delta).
+// Layer backward of the 8B shape 201 tokens 423 -> 401 us, 487 619 -> 595; heads of 64 (hidden 2048) 260 tokens 236 -> 210.
+template <int kD>
+__global__ __launch_bounds__(256) void k_both_gradients_mfma(AttnMfmaParams p, int n_dkv) {
+    __shared__ __attribute__((aligned(1024))) char smem[4 * AttnTile<kD>::kStageBytes];
+    const int b = (int)blockIdx.x;
+    if (b < n_dkv) {
+        attn_dkv_block<kD, false>(p, b % p.Hkv, b / p.Hkv % p.n_seqs, b / (p.Hkv * p.n_seqs), smem);
+    } else {
+        const int q = b - n_dkv;
+        attn_dq_block<kD, false>(p, q % p.Hq, q / p.Hq % p.n_seqs, q / (p.Hq * p.n_seqs), p.n_blocks, smem);
+    }
+}
+// Two lanes to a row of a head, which add in the order of attn_dq_block: the same bits.
+template <int kD>
+__global__ __launch_bounds__(256) void k_row_delta(AttnMfmaParams p) {
+    const long long at = (long long)blockIdx.x * 128 + (threadIdx.x >> 1);  // row of the batch and head
+    const int half = threadIdx.x & 1;
+    const bool ok = at < (long long)p.T * p.Hq;
+    const long long off = (ok ? at / p.Hq * p.ldq + at % p.Hq * kD : 0) + 8 * half;
+    float del = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < AttnTile<kD>::kKK; ++kk) {
+        const bf16x8 of = *reinterpret_cast<const bf16x8*>(p.O + off + kk * 16), gf = *reinterpret_cast<const bf16x8*>(p.dO + off + kk * 16);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) del += (float)of[e] * (float)gf[e];
+    }
+    del += __shfl_xor(del, 1, 64);
+    if (ok && half == 0) {
+        p.delta[at] = del;
+        p.lse2[at] = p.LSE[at] * kLog2e;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1211,6 +1258,76 @@ inline int plan_dkv_parts(const AttnArgs& a, AttnMfmaParams& p, int& longest) {
     return ALCH_OK;
 }
 
+// Whether both gradients run as one launch (k_both_gradients_mfma): where every work-group of both finds a compute unit, and the
+// launch and those behind it come out shorter than one behind the other.  Key blocks are cut as finely as the units that are left
+// allow, into parts of four tiles at least, if eight tiles or more come off the longest.
+inline int plan_both(const AttnArgs& a, AttnMfmaParams& p, bool& both) {
+    both = false;
+    if (a.prefix) return ALCH_OK;
+    int n_cu = 0;
+    ALCH_TRY(compute_units(&n_cu));
+    const int* cu = a.cu_seqlens_host;
+    const int G = a.Hq / a.Hkv;
+    long long blocks = 0;
+    int longest = 0;
+    for (int s = 0; s < a.n_seqs; ++s) {
+        const int len = cu[s + 1] - cu[s];
+        blocks += ceil_div(len, 128);
+        if (blocks * (a.Hq + a.Hkv) > n_cu) return ALCH_OK;
+        longest = std::max(longest, len);
+    }
+    AttnMfmaParams apart = p, one = p;
+    // work-groups of both, and tiles of the longest of dK/dV (as dkv_parts)
+    struct Size { long long groups; int tiles; };
+    const auto size = [&](const AttnMfmaParams& q) {
+        Size z{blocks * a.Hq, 0};
+        for (int s = 0; s < a.n_seqs; ++s) {
+            const int len = cu[s + 1] - cu[s];
+            for (int kb = 0; kb * 128 < len; ++kb) {
+                const int tiles = ceil_div(len, kTileRows) - 2 * kb;
+                const int want = (int)std::min<long long>(q.max_parts, ((long long)G * tiles + q.part_len - 1) / q.part_len);
+                const int heads = ceil_div(G, std::max(want, 1));
+                z.groups += ceil_div(G, heads) * a.Hkv;
+                z.tiles = std::max(z.tiles, heads * tiles);
+            }
+        }
+        return z;
+    };
+    int unused = 0;
+    ALCH_TRY(plan_dkv_parts(a, apart, unused));
+    const Size before = size(apart);
+    Size now = before;
+    one.n_blocks = ceil_div(longest, 128);
+    one.max_parts = apart.max_parts; one.part_len = apart.part_len; one.partial = apart.partial;
+    if (!a.keep_parts) {
+        one.max_parts = 1;
+        one.part_len = 1 << 30;
+        now = size(one);
+        const size_t part_bytes = (size_t)a.T * a.Hkv * 2 * a.D * sizeof(float);
+        const int max_parts = a.scratch && part_bytes ? (int)std::min<size_t>(std::min(G, 8), a.scratch_bytes / part_bytes) : 1;
+        for (int part_len = 4; max_parts > 1 && part_len + 8 <= now.tiles; ++part_len) {
+            AttnMfmaParams q = one;
+            q.max_parts = max_parts;
+            q.part_len = part_len;
+            const Size z = size(q);
+            if (z.groups > n_cu) continue;
+            if (z.tiles + 8 > now.tiles) break;
+            q.partial = static_cast<float*>(a.scratch);
+            one = q;
+            now = z;
+            break;
+        }
+    }
+    // us (see plan_dkv_parts; dQ: 2.5 a tile and 10; delta: 5)
+    const int sums = 9, dq = 10 + 5 * ceil_div(longest, kTileRows) / 2;
+    const int together = 5 + std::max(dq, 11 + 2 * now.tiles) + (one.max_parts > 1 ? sums : 0);
+    const int behind = dq + 11 + 2 * before.tiles + (apart.max_parts > 1 ? sums : 0);
+    if (now.groups > n_cu || together >= behind) return ALCH_OK;
+    both = true;
+    p = one;
+    return ALCH_OK;
+}
+
 template <int kD>
 int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     AttnMfmaParams p{};
@@ -1227,6 +1344,16 @@ int attn_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
     p.T = a.T;
     p.n_blocks = nb;
     p.short_upto = a.rows.up_to;
+    bool both;
+    ALCH_TRY(plan_both(a, p, both));
+    if (both) {
+        const int n_dkv = a.Hkv * a.n_seqs * p.n_blocks * p.max_parts, n_dq = a.Hq * a.n_seqs * p.n_blocks;
+        k_row_delta<kD><<<(unsigned)ceil_div((long long)a.T * a.Hq, 128LL), 256, 0, stream>>>(p);
+        if (n_dkv + n_dq > 0) k_both_gradients_mfma<kD><<<n_dkv + n_dq, 256, 0, stream>>>(p, n_dkv);
+        if (p.max_parts > 1) k_dkv_finish<kD, false><<<dim3(a.Hkv, a.n_seqs, p.n_blocks * 4), 256, 0, stream>>>(p);
+        ALCH_HIP_TRY(hipGetLastError());
+        return ALCH_OK;
+    }
     int longest = 0;
     ALCH_TRY(plan_dkv_parts(a, p, longest));
     const bool cut = p.max_parts > 1;

@@ -244,6 +244,7 @@ struct AttnArgs {
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
     ShortRows rows;  // see rows_up_to
+    bool keep_parts = false;  // as GemmDesc: key blocks are cut as by plan_dkv_parts whatever launch they are in
 };
 // Tokens of the longest of the sequences first .. n_seqs-1.  max_seqlen is only a bound on them, and may be any number that
 // is not below it.
