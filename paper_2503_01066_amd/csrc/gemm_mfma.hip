@@ -93,9 +93,8 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(MfmaGemmParams p) {
     // the tiles, so the stores of one tile drain while the next tile's loads are already in flight.
     const int Mv = p.m_dev ? min(__builtin_amdgcn_readfirstlane(*p.m_dev), p.M) : p.M;
     if (!kSplit && p.either) {
-        bool pair;
-        device_plan(p, Mv, pair);
-        if (pair) return;
+        PairPlan plan;
+        if (device_plan(p, Mv, plan) != kRowsBig) return;
     }
     const int tiles_m = p.m_dev ? (Mv + BM - 1) / BM : p.tiles_m;
     const int nt = tiles_m * p.tiles_n;
@@ -650,6 +649,7 @@ static int plan_product(const GemmDesc& d, MfmaProduct& out) {
     p.a_kmajor = d.a_kmajor;
     p.b_kmajor = d.b_kmajor;
     p.plan_ws = d.keep_parts ? 0 : (long long)ws_bytes;
+    p.narrow = d.keep_parts && d.m_dev && d.a_kmajor && !d.b_kmajor && !d.accumulate && d.n_out == 1;
     const bool swiglu = p.epilogue == kEpiSwigluBwd;
     // m_dev: launch_device_rows.  k_dev: whole tiles, of the kernel that is the faster one with half of the tokens kept (its
     // tiles are the same for any count, and the lengths where the choice turns lie close together)
@@ -682,19 +682,24 @@ static void launch_big(const MfmaGemmParams& p, int grid, hipStream_t stream) {
 // launches that leave are 28 us of a profile.
 static int launch_device_rows(MfmaProduct& m, hipStream_t stream) {
     MfmaGemmParams& p = m.p;
-    int pair_most = 0, cut_most = 0;
+    int pair_most = 0, cut_most = 0, narrow_most = 0;
     bool any_big = false;
-    for (int rows = PM; rows < p.M + PM; rows += PM) {
-        bool pair;
-        const PairPlan plan = device_plan(p, std::min(rows, p.M), pair);
-        if (!pair || !p.a_kmajor) {
+    const int step = p.narrow ? PM / 2 : PM;  // rows of the smallest tile: the plan is the same in between
+    for (int rows = step; rows < p.M + step; rows += step) {
+        PairPlan plan;
+        const RowsKernel kernel = device_plan(p, std::min(rows, p.M), plan);
+        if (kernel == kRowsNarrow64 || kernel == kRowsNarrow128) {
+            narrow_most = std::max(narrow_most, narrow_grid(p, std::min(rows, p.M), kernel));
+            continue;
+        }
+        if (kernel == kRowsBig || !p.a_kmajor) {
             any_big = true;
             continue;
         }
         pair_most = std::max(pair_most, pair_grid(plan));
         if (plan.parts > 1) cut_most = std::max(cut_most, plan.per_xcd - plan.q_end);
     }
-    p.either = any_big && pair_most > 0;
+    p.either = (int)any_big + (pair_most > 0) + (narrow_most > 0) > 1;
     if (any_big) {
         const int nt = p.tiles_m * p.tiles_n;
         p.q_end = ceil_div(nt, 8);
@@ -703,6 +708,7 @@ static int launch_device_rows(MfmaProduct& m, hipStream_t stream) {
         launch_big(p, std::min(ceil_div(nt, 8) * 8, m.n_cu), stream);
     }
     if (pair_most > 0) ALCH_TRY(launch_gemm_pair_rows(p, pair_most, cut_most, m.split_ws, stream));
+    if (narrow_most > 0) ALCH_TRY(launch_gemm_narrow_rows(p, narrow_most, stream));
     ALCH_HIP_TRY(hipGetLastError());
     return ALCH_OK;
 }

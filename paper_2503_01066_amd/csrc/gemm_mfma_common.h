@@ -45,8 +45,8 @@ struct MfmaGemmParams {
     int split_s, split_per;  // parts per tile; k-tiles per part (counted over all operand pairs in order)
     int per_xcd;             // k_gemm_pair: tiles of an XCD's share
     // m_dev: k_gemm_pair plans on the device, for plan_cu compute units and plan_ws bytes of scratch (0: no tile is cut);
-    // either: both kernels are launched, and the one that the estimate does not choose leaves at once.
-    int either, plan_cu, a_kmajor, b_kmajor;
+    // either: several kernels are launched, and those that the estimate does not choose leave at once; narrow: k_gemm_narrow_rows may be one.
+    int either, narrow, plan_cu, a_kmajor, b_kmajor;
     long long plan_ws;
 };
 
@@ -94,6 +94,38 @@ __device__ __forceinline__ void tile_offsets(uint32_t (&voff)[4], int wave, int 
     }
 }
 
+// An operand as a run of equal steps through a buffer, in scalar registers: address and bytes left, steps left.  Past the end the
+// loads go to an empty buffer, so the number in flight is the same in every step.
+struct OperandStream {
+    uint32_t lo, hi;
+    int left_bytes, left, bytes;
+    __device__ __forceinline__ void open(const __bf16* first, const __bf16* end, int steps, int step_bytes) {
+        const uint64_t u = (uint64_t)first;
+        const long long l = (const char*)end - (const char*)first;
+        lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+        hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32) & 0xffffu);
+        left_bytes = __builtin_amdgcn_readfirstlane((int)(l < 0 ? 0 : (l > 0x7fffffffLL ? 0x7fffffffLL : l)));
+        left = __builtin_amdgcn_readfirstlane(steps);
+        bytes = __builtin_amdgcn_readfirstlane(step_bytes);
+    }
+    __device__ __forceinline__ void select(i32x4& r) const {
+        int n;
+        asm volatile("s_cmp_gt_i32 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=&s"(n) : "s"(left), "s"(left_bytes) : "scc");
+        r[0] = (int)lo; r[1] = (int)hi; r[2] = n; r[3] = 0x00020000;
+    }
+    __device__ __forceinline__ void advance() {
+        asm volatile("s_add_u32 %0, %0, %4\n\ts_addc_u32 %1, %1, 0\n\ts_sub_i32 %2, %2, %4\n\ts_max_i32 %2, %2, 0\n\t"
+                     "s_sub_i32 %3, %3, 1"
+                     : "+s"(lo), "+s"(hi), "+s"(left_bytes), "+s"(left)
+                     : "s"(bytes)
+                     : "scc");
+    }
+};
+
+// Which 16-byte piece of row k of a token-major tile lies where: rows of 512 and 256 bytes meet in the banks every second row of a
+// fragment's four, rows of 128 bytes every second one, too, half as far apart.
+template <int kCols> __device__ __forceinline__ int col_swizzle(int k) { return kCols == 64 ? 4 * ((k >> 1) & 1) : 4 * (k & 3); }
+
 // Fragment (8 consecutive-k bf16 per lane for one 32-wide block of rows/cols) from an LDS tile; kCols = columns of a
 // token-major tile.
 template <bool KMAJOR, int kCols = 256>
@@ -107,8 +139,8 @@ __device__ __forceinline__ bf16x8 read_frag(const char* stage, int idx0 /*first 
         const int col = idx0 + (g & 1) * 16 + 4 * (i & 3);
         const int krow = kk * 16 + 8 * (g >> 1) + (i >> 2);  // + 4 for the second half
         const int chunk = col >> 3, sub = (col & 7) * 2;
-        const char* p0 = stage + krow * (kCols * 2) + ((chunk ^ (4 * (krow & 3))) << 4) + sub;
-        const char* p1 = p0 + 4 * (kCols * 2);  // krow + 4 has the same (krow & 3)
+        const char* p0 = stage + krow * (kCols * 2) + ((chunk ^ col_swizzle<kCols>(krow)) << 4) + sub;
+        const char* p1 = p0 + 4 * (kCols * 2);  // krow + 4 is swizzled alike
         bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(p0));
         bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(p1));
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -195,21 +227,35 @@ __host__ __device__ inline bool pair_is_better(int M, int N, long long K, bool a
 // Plan and choice of a product whose row count lies on the device, for Mv rows of it.  Two rounds of 128x256 tiles at most:
 // beyond that the two kernels differ by little, and the grid that leaves when the others are chosen stays at 1024
 // work-groups (5 us in a profile, 2 between products).
-__host__ __device__ inline PairPlan device_plan(const MfmaGemmParams& p, int Mv, bool& pair) {
+enum RowsKernel { kRowsBig, kRowsPair, kRowsNarrow64, kRowsNarrow128 };
+// Work-groups of k_gemm_narrow_rows for Mv rows
+__host__ __device__ inline int narrow_grid(const MfmaGemmParams& p, int Mv, RowsKernel kernel) {
+    const int tile = kernel == kRowsNarrow64 ? 64 : 128;
+    return 8 * up_div(up_div(Mv, tile) * up_div(p.N, tile), 8);
+}
+__host__ __device__ inline RowsKernel device_plan(const MfmaGemmParams& p, int Mv, PairPlan& plan) {
     int nk = 0;
     long long K = 0;
     for (int s = 0; s < p.n_seg; ++s) {
         nk += up_div(p.K[s], BK);
         K += p.K[s];
     }
-    const PairPlan plan = pair_plan(Mv, p.N, nk, p.a_kmajor != 0, p.plan_cu, p.plan_ws);
-    pair = plan.per_xcd <= 4 * (p.plan_cu / 8) &&
-           pair_is_better(Mv, p.N, K, p.a_kmajor != 0, p.b_kmajor != 0, p.epilogue == kEpiSwigluBwd, p.plan_cu, 1, plan);
-    return plan;
+    plan = pair_plan(Mv, p.N, nk, p.a_kmajor != 0, p.plan_cu, p.plan_ws);
+    const bool pair = plan.per_xcd <= 4 * (p.plan_cu / 8) &&
+                      pair_is_better(Mv, p.N, K, p.a_kmajor != 0, p.b_kmajor != 0, p.epilogue == kEpiSwigluBwd, p.plan_cu, 1, plan);
+    // The smallest tile of which no compute unit has two: where that is one of 64x64 or 128x128 their contraction is as long as that of a
+    // 128x256 tile, and a step of 64 k takes 341 and 507 ns of 160 and 680 rows by 4096 against 770 (K 128256; a second round of the small
+    // ones 290 more).  Past one round of 128x128 the wide tile is the better one: 1244 rows, K 32000 388 against 512 us.
+    if (p.narrow) {
+        if (narrow_grid(p, Mv, kRowsNarrow64) <= p.plan_cu) return kRowsNarrow64;
+        if (narrow_grid(p, Mv, kRowsNarrow128) <= p.plan_cu) return kRowsNarrow128;
+    }
+    return pair ? kRowsPair : kRowsBig;
 }
 
 int launch_gemm_pair(MfmaGemmParams p, bool a_kmajor, bool b_kmajor, int tiles_m, const PairPlan& plan, float* split_ws, hipStream_t stream);
 int launch_gemm_pair_rows(MfmaGemmParams p, int grid, int cut, float* split_ws, hipStream_t stream);  // m_dev, k-major A: most work-groups, cut tiles of an XCD
+int launch_gemm_narrow_rows(const MfmaGemmParams& p, int grid, hipStream_t stream);  // m_dev, k-major A, token-major B
 size_t pair_split_bytes(const PairPlan& plan);  // scratch of its partial tiles
 int pair_grid(const PairPlan& plan);            // its work-groups
 int launch_gemm_two_pairs(MfmaGemmParams data, int data_tiles_m, const PairPlan& data_plan, MfmaGemmParams weight, int weight_tiles_m,

@@ -30,9 +30,8 @@ __device__ __forceinline__ bool the_plan(const MfmaGemmParams& p, PairPlan& plan
     Mv = p.M;
     tiles_m = p.tiles_m;
     if constexpr (kRows) {
-        bool pair;
         Mv = min(__builtin_amdgcn_readfirstlane(*p.m_dev), p.M);
-        plan = device_plan(p, Mv, pair);
+        const bool pair = device_plan(p, Mv, plan) == kRowsPair;
         tiles_m = up_div(Mv, PM);
         return Mv > 0 && (!p.either || pair);
     }
