@@ -1068,7 +1068,7 @@ static int stack_backward_impl(const alch_layer_shape* shape, int32_t n_layers, 
     // stack therefore do not depend on which of the two contraction kernels is the faster one for a product, and products of
     // kept rows run as whole tiles.  A single layer has none below that would carry it on: its products, and those of the
     // head above it, run as in a call of its own (8B shape, vocabulary 128256, a quarter of the rows counted: the head's
-    // gradient of 136 rows, 4096 columns, K 128256, 1525 us on 16 compute units, cut 230; head and layer of 543 tokens 2344 ->
+    // gradient of 136 rows, 4096 columns, K 128256, 1525 us in whole tiles of 256x256, 690 of 64x64, cut 230; head and layer of 543 tokens 2344 ->
     // 1091 us, 1379 3586 -> 2101).
     const bool keep_parts = n_layers > 1;
     auto gemm_ws = [&](alch_dtype t, int M, int N, bool a_k, bool b_k) {

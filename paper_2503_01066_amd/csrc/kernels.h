@@ -66,7 +66,7 @@ struct GemmDesc {
     // write fp32 partial tiles here; a second kernel adds them in a fixed order.  kGemmSplitWsBytes always suffices.
     void* split_ws = nullptr;
     size_t split_ws_bytes = 0;
-    // cut the contraction into the same parts whichever of the two matrix-core kernels runs (those of the 256x256 one),
+    // cut the contraction into the same parts whichever of the matrix-core kernels runs (those of the 256x256 one),
     // so that the result has the same bits: see stack_backward_impl
     bool keep_parts = false;
 };
