@@ -1260,7 +1260,9 @@ inline int plan_dkv_parts(const AttnArgs& a, AttnMfmaParams& p, int& longest) {
 
 // Whether both gradients run as one launch (k_both_gradients_mfma): where every work-group of both finds a compute unit, and the
 // launch and those behind it come out shorter than one behind the other.  Key blocks are cut as finely as the units that are left
-// allow, into parts of four tiles at least, if eight tiles or more come off the longest.
+// allow, into parts of two tiles at least, if five tiles or more come off the longest: 10 us for the 9 of the sums.  (Parts of four, if eight
+// come off -> so, layers, us: heads of 64, 100 tokens 169 -> 159, 3 sequences of 100 216 -> 210; 8B shape 128 tokens 332 -> 328, 150 362 -> 354,
+// 2 sequences of 125 405 -> 399; 201 and 256 tokens as before.)
 inline int plan_both(const AttnArgs& a, AttnMfmaParams& p, bool& both) {
     both = false;
     if (a.prefix) return ALCH_OK;
@@ -1305,13 +1307,13 @@ inline int plan_both(const AttnArgs& a, AttnMfmaParams& p, bool& both) {
         now = size(one);
         const size_t part_bytes = (size_t)a.T * a.Hkv * 2 * a.D * sizeof(float);
         const int max_parts = a.scratch && part_bytes ? (int)std::min<size_t>(std::min(G, 8), a.scratch_bytes / part_bytes) : 1;
-        for (int part_len = 4; max_parts > 1 && part_len + 8 <= now.tiles; ++part_len) {
+        for (int part_len = 2; max_parts > 1 && part_len + 5 <= now.tiles; ++part_len) {
             AttnMfmaParams q = one;
             q.max_parts = max_parts;
             q.part_len = part_len;
             const Size z = size(q);
             if (z.groups > n_cu) continue;
-            if (z.tiles + 8 > now.tiles) break;
+            if (z.tiles + 5 > now.tiles) break;
             q.partial = static_cast<float*>(a.scratch);
             one = q;
             now = z;
