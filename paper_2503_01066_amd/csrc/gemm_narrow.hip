@@ -110,6 +110,8 @@ __device__ __forceinline__ void narrow_tile(const MfmaGemmParams& p, int Mv, int
         uint32_t free_stage = kT == 1 ? 0 : (kStages - 1) * Tile::kStage;       // the stage that is loaded next
         Frags f[3];
         read(f[0], 0, 0);
+        // (in this order: of 24 reads the first step waits for twelve, and then loads into stage 0 of a 64x64 tile)
+        __builtin_amdgcn_sched_barrier(0);
         read(f[1], kT == 1 ? Tile::kStage : 0, kT == 1 ? 0 : 1);
         // A step's fragments were read two steps ago and have arrived when those of the step before are all that is on its way (12
         // reads); so the LDS has work through the barrier.  First step of a stage: what it reads has landed in every wave's share, and
