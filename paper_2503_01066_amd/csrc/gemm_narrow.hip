@@ -101,6 +101,9 @@ __device__ __forceinline__ void narrow_tile(const MfmaGemmParams& p, int Mv, int
 
         __syncthreads();  // every wave is done with the previous pair's stages
         constexpr int kAhead = kT == 1 ? kStages : kStages - 1;  // stages in flight
+        // vmcnt(0), known to the compiler, with nothing on its way yet: it holds the epilogue's loads of the other tile for pending and
+        // waited for all stages ahead of a fragment that takes one of their registers
+        __builtin_amdgcn_s_waitcnt(0x0f70);
 #pragma unroll
         for (int s = 0; s < kAhead; ++s) load_stage((uint32_t)(s * Tile::kStage));
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kAhead - 2) * 2 * kLoads) : "memory");  // stages 0 and 1 have landed

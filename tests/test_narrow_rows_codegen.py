@@ -32,6 +32,12 @@ def test_first_stage_is_read_before_the_second(asm):
     assert [o // 16384 for o in reads] == [0] * 12 + [1] * 12, reads
 
 
+def test_first_fragments_wait_for_two_stages_only(asm):
+    for landed in (28, 8):  # loads of the other stages, 64x64 and 128x128 tiles
+        first = _first_reads(_kernel(asm)[1], landed)
+        assert "ds_read_b" in first and not re.search(r"vmcnt\((?!%d\)|24\))\d+\)" % landed, first), first
+
+
 def test_narrow_rows(asm):
     name, body = _kernel(asm)
     assert _meta(asm, name, "vgpr_spill_count") == 0 and _meta(asm, name, "private_segment_fixed_size") == 0
