@@ -3,8 +3,6 @@
 
 namespace alch {
 
-static constexpr int kRowsPerCu = 16;  // see rows_up_to
-
 // Batches of heads of 64 that the grid of the matrix-core kernels cannot hold run on the fp32-arithmetic ones, which take any.
 // (Heads of 128 are refused there: they have never had another path.)
 static bool head_size_fits(int D, int n_seqs, const int* cu_host) {

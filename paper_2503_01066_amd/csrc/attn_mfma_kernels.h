@@ -54,6 +54,7 @@ template <int kD> struct AttnTile {
 };
 static constexpr float kLog2e = 1.4426950408889634f;
 static constexpr int kMinPartTiles = 8;  // tiles a part of a key block has at least
+static constexpr int kRowsPerCu = 16;    // see rows_up_to
 static constexpr int kMaxGridSeqs = 65535, kMaxGridBlocks = 65535;  // of 128 tokens: limits of a grid's second and third dimension
 
 struct AttnMfmaParams {
@@ -741,7 +742,7 @@ __global__ __launch_bounds__(256) void k_dkv_finish(AttnMfmaParams p) {
     const int seq = blockIdx.y, kv = blockIdx.x;
     const int seq_start = p.cu[seq], len = p.cu[seq + 1] - seq_start;
     const int row0 = (int)blockIdx.z * 32, kb = row0 / 128;
-    if (row0 >= len) return;
+    if (row0 >= len || len <= p.short_upto) return;
     int tiles = (len + kTileRows - 1) / kTileRows - 2 * kb;
     if constexpr (kPrefix) tiles += prefix_seqs(p, seq).tiles;
     int heads;

@@ -2,6 +2,9 @@
 #include <iostream>
 #include <string>
 
+#include <vector>
+
+#include "attn_mfma_kernels.h"
 #include "gemm_mfma_common.h"
 
 using namespace alch;
@@ -65,6 +68,27 @@ int main() {
             int T, problems;
             std::cin >> T >> problems;
             std::cout << lora_down_parts(T, problems, 256) << "\n";
+        } else if (what == "attention") {  // head size, query and key/value heads, ffn, number of lengths, lengths: the backward in bf16:
+            // longest sequence that the row kernels take, parts of a key block, whether both gradients run as one launch
+            int D, Hq, Hkv, F, n;
+            std::cin >> D >> Hq >> Hkv >> F >> n;
+            std::vector<int> cu(n + 1, 0);
+            for (int i = 0; i < n; ++i) {
+                std::cin >> cu[i + 1];
+                cu[i + 1] += cu[i];
+            }
+            AttnArgs a;
+            a.dtype = ALCH_BF16; a.T = cu[n]; a.n_seqs = n; a.Hq = Hq; a.Hkv = Hkv; a.D = D;
+            a.cu_seqlens_host = cu.data();
+            a.scratch = kSome;
+            a.scratch_bytes = (size_t)a.T * 2 * F * 2;
+            if (D == 64 && rows_up_to(D, Hq, kRowsPerCu, 0, n, cu.data(), nullptr, &a.rows) != ALCH_OK) return 1;
+            AttnMfmaParams p{};
+            p.n_blocks = up_div(longest_sequence(cu.data(), 0, n), 128);
+            bool both = false;
+            int longest = 0;
+            if (plan_both(a, p, both) != ALCH_OK || (!both && plan_dkv_parts(a, p, longest) != ALCH_OK)) return 1;
+            std::cout << a.rows.up_to << " " << p.max_parts << " " << both << "\n";
         } else {
             return 1;
         }

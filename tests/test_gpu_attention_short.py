@@ -32,3 +32,17 @@ def test_short_sequences(monkeypatch, shape_name, dtype, lens, turned):
     O, lse = A.alch_attention_forward(alch_shape(shp, dtype), A.Batch(cu), *[to_dev(rec[k], dtype) for k in "QKV"])
     want = attention_fp64(shp, cu, rec, np.zeros_like(rec["O"]))
     assert rel_err(to_np(O), want["O"]) <= (TOL["bf16"] if dtype == "bf16" else 1e-5) and rel_err(to_np(lse), want["LSE"]) <= 1e-5
+
+
+# Heads of 64 in large groups: the row kernels take the short sequences, and the key blocks of the long one are cut into parts.
+# (query heads to one key/value head, lengths, whose long sequence is first, last or between the short ones)
+CUT = [(64, [1000] + [4] * 64), (32, [4] * 128 + [1000]), (64, [3, 8] * 20 + [900] + [1, 0, 5] * 16)]
+
+
+@pytest.mark.parametrize("heads,lens", CUT)
+def test_short_sequences_beside_cut_key_blocks(monkeypatch, heads, lens):
+    monkeypatch.setitem(synth.SHAPES, "cut", (64, heads, 1, 64, 1024, 1e-5, 10000.0))
+    cu = synth.ragged_cu(lens)
+    shp, osh, W, rec, dY = make_case("cut", "bf16", cu, 31, "drawn", dy_std=0.01)
+    ref = layer_backward_reuse(osh, cu, None, f64(rec), f64(W), dY)
+    compare(run_gpu(shp, "bf16", cu, W, rec, dY), ref, "bf16")

@@ -80,3 +80,10 @@ def test_pairs_of_batches_differ_in_the_pass_and_not_in_the_parts_of_t2(ask):
             p = ask(("t_parts", in_one, problems), ("t_parts", apart, problems))
             assert p[0] == p[1], (in_one, apart, problems)
     assert {ask(("t_parts", b[1], 2))[0] for b in BITS} == {(16,), (8,), (4,)}
+
+
+def test_short_sequences_lie_beside_cut_key_blocks(ask):
+    from test_gpu_attention_short import CUT
+    for heads, lens in CUT:
+        (up_to, parts, both), = ask(("attention", 64, heads, 1, 1024, len(lens), *lens))
+        assert up_to == 8 and parts > 1 and not both, (heads, lens)
