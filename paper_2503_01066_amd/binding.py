@@ -11,10 +11,19 @@ from array import array
 import numpy as np
 import torch
 
+
+def torch_build():
+    """What the extension is bound to besides the interpreter: the layout of torch's classes is compiled into it."""
+    return "%s %s" % (torch.__version__, torch.version.git_version)
+
+
 try:
     from . import _marshal
-except ImportError:  # (another torch than the one it was built for: the calls below are marshalled here)
+    if getattr(_marshal, "torch_build", None) != torch_build():
+        _marshal = None
+except ImportError:
     _marshal = None
+# (not built, or for another torch, whose tensors it would read wrongly: all calls are marshalled here)
 
 RECORD_KEYS = ("X", "X2", "Q", "K", "V", "O", "G", "U")  # + LSE (fp32)
 WEIGHT_KEYS = ("Wq", "Wk", "Wv", "Wo", "Wg", "Wu", "Wd", "g1", "g2")

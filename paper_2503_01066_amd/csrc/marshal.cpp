@@ -67,4 +67,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }
+// The layout of at::Tensor is compiled in, and another torch may export the same names: the binding compares torch_build with its own.
+PyMODINIT_FUNC PyInit__marshal(void) {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_build", ALCH_TORCH_BUILD) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
