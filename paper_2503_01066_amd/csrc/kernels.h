@@ -210,6 +210,14 @@ struct LoraPass {
 bool lora_pass_fits(const LoraPass* jobs, int n_jobs, int Trows, const LoraUpSums& sums);
 int launch_lora_pass(const LoraPass* jobs, int n_jobs, int Trows, long long ldq, float alpha, LoraUpSums& sums, hipStream_t stream,
                      const int* rows_dev = nullptr);
+// A layer of bf16 under a loss mask, on its kept rows alone: their number is known to the device, and products whose size is there are the
+// matrix-core kernels' alone.  What these refuse of the layer's sizes (k in pieces of 64, rows of more than 2^21 elements, operands of 2 GiB) is
+// looked at ahead of anything that is enqueued; such a layer runs on all rows.
+inline bool kept_rows_fit(int T, int H, int F, int QD) {
+    const auto operand = [](long long rows, long long width) { return width <= 1 << 21 && rows * width * 2 < 1LL << 31; };
+    return H % 64 == 0 && F % 64 == 0 && QD % 64 == 0 && operand(T, 2LL * F) && operand(T, H) && operand(T, QD) && operand(H, F) &&
+           operand(F, H) && operand(H, QD);
+}
 // Operand preparation: job i writes dst [rows_out, cols] = src [r, cols] (or, transpose, src [cols, r]
 // transposed) followed by zero rows; src null: all zeros.
 struct LoraPrepJob {

@@ -68,6 +68,10 @@ int main() {
             int T, problems;
             std::cin >> T >> problems;
             std::cout << lora_down_parts(T, problems, 256) << "\n";
+        } else if (what == "kept_rows") {  // T hidden ffn, width of all query heads: a masked layer runs on its kept rows
+            int T, H, F, QD;
+            std::cin >> T >> H >> F >> QD;
+            std::cout << kept_rows_fit(T, H, F, QD) << "\n";
         } else if (what == "attention") {  // head size, query and key/value heads, ffn, number of lengths, lengths: the backward in bf16:
             // longest sequence that the row kernels take, parts of a key block, whether both gradients run as one launch
             int D, Hq, Hkv, F, n;

@@ -44,3 +44,23 @@ def test_kept_counts(monkeypatch, T, rank, hidden, ffn, frozen, accumulate):
             # the two differ in the order of fp32 sums, and so in where a bf16 rounding falls: at most four roundings, one
             # behind the other (dG/dU, dH2, dX2, the output), each 2^-9 of the norm
             assert float((a - b).norm()) <= 2 ** -7 * float(b.norm()), (kept, k, float((a - b).norm() / b.norm()))
+
+
+def test_rows_too_wide_for_device_counts_run_as_before(monkeypatch):
+    """[dG | dU] rows of more than 2^21 elements: no kernel takes such a product with its row count on the device."""
+    import paper_2503_01066_amd as A
+    T, H, F, rank, g = 256, 64, (1 << 20) + 64, 8, torch.Generator(device="cuda").manual_seed(5)
+    shape = A.make_shape(H, 1, 1, 64, F, 1e-5, 10000.0, "bf16")
+    draw = lambda *s, std=1.0: torch.randn(s, generator=g, device="cuda").mul_(std).to(torch.bfloat16)
+    d = {k: draw(T, F if k in "GU" else H) for k in REC}
+    d["LSE"] = torch.full((T, 1), 5.0, device="cuda")
+    W = {"W" + k: draw(F if k in "gu" else H, F if k == "d" else H, std=0.02) for k in "qkvogud"}
+    W["g1"], W["g2"] = draw(H), draw(H)
+    lora = {p: (draw(rank, W["W" + p].shape[1], std=0.05), draw(W["W" + p].shape[0], rank, std=0.05)) for p in synth.PROJECTIONS}
+    dY = draw(T, H, std=0.01)
+    mask = (torch.rand(T, generator=g, device="cuda") < 0.3).to(torch.uint8)
+    run = lambda dy, m: A.alch_layer_backward_lora(shape, A.Batch(np.array([0, 100, T])), d, W, lora, rank, 2.0, dy, loss_mask=m, grads={})
+    got, want = run(dY, mask), run(dY * mask[:, None].to(dY.dtype), None)
+    torch.cuda.synchronize()
+    for k in want:
+        assert torch.equal(got[k], want[k]), k

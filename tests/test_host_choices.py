@@ -87,3 +87,13 @@ def test_short_sequences_lie_beside_cut_key_blocks(ask):
     for heads, lens in CUT:
         (up_to, parts, both), = ask(("attention", 64, heads, 1, 1024, len(lens), *lens))
         assert up_to == 8 and parts > 1 and not both, (heads, lens)
+
+
+def test_kept_rows_are_products_that_the_matrix_core_kernels_take(ask):
+    """The products of a masked layer by their largest operands, beside what the kernels say of each."""
+    for T, H, F, QD in [(256, 64, 1 << 20, 256), (256, 64, (1 << 20) + 64, 256), (256, 1024, (1 << 20) - 64, 256), (256, 1024, 1 << 20, 256),
+                        (140000, 8192, 64, 256), (70000, 64, 64, 1 << 14), (8192, 8192, 28672, 8192), (300, 8192, 131072, 256), (300, 96, 256, 64)]:
+        data = ask(("supported", T, F, H, True, False, False), ("supported", T, H, F, True, False, False), ("supported", T, QD, H, True, False, False),
+                   ("supported", 2 * F, H, T, False, False, True), ("supported", H, F, T, False, False, True), ("supported", H, QD, T, False, False, True))
+        wide = 2 * F <= 1 << 21 and T * 2 * F * 2 < 1 << 31  # ([dG | dU] as the left operand of dH2)
+        assert ask(("kept_rows", T, H, F, QD)) == [(all(d == (1,) for d in data) and wide,)], (T, H, F, QD, data)
