@@ -456,11 +456,8 @@ static int layer_backward_enqueue(const alch_layer_shape& s, const alch_batch& b
     //     products take their row or contraction count from device memory), and dX2, dO are scattered back
     //     into zero-filled [T, width] tensors for the attention backward, which is dense in the keys;
     //   otherwise dY is copied once with the masked rows zeroed and every step runs on all T rows.
-    // With adapters: outside of stacks of several layers, whose layers below would carry on the other roundings, and where
-    // the rows left out are worth the launches that find, gather and scatter the others (one tile of 128 rows gets no shorter).
-    // us without / with, 0.25 or 0.6 of the rows kept: 8B shape 130 tokens 455 / 468 (all gradients), 200 489 / 494, 260 384 / 334 (frozen),
-    // 520 483 / 387, 1490 1397 / 849; hidden 2048, ffn 8192 390 tokens 322 / 334, 520 362 / 363, 1000 482 / 448; 70B shape 130 630 / 571.
-    const bool lora_pays = one_pass && !keep_parts && T > 128 && (double)T * H * F >= 15e9;
+    // With adapters: outside of stacks of several layers, whose layers below would carry on the other roundings.
+    const bool lora_pays = one_pass && !keep_parts && adapters_on_kept_rows(T, H, F);
     const bool compact = loss_mask && T > 0 && (!lo || lora_pays) && dt == ALCH_BF16 && kept_rows_fit(T, H, F, QD) && aligned16(dY);
     const void *mY = dY, *mX2 = sv.X2, *mO = sv.O, *mG = sv.G, *mU = sv.U;  // inputs of the row-local part
     void *mdX2 = p.dX2, *mdO = p.dO;                                      // its outputs

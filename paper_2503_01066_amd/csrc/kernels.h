@@ -218,6 +218,27 @@ inline bool kept_rows_fit(int T, int H, int F, int QD) {
     return H % 64 == 0 && F % 64 == 0 && QD % 64 == 0 && operand(T, 2LL * F) && operand(T, H) && operand(T, QD) && operand(H, F) &&
            operand(F, H) && operand(H, QD);
 }
+// Whether a layer with adapters does so: where the rows that are left out are worth the launches that find, gather and scatter the others
+// (one tile of 128 rows gets no shorter).  The host does not know how many are kept, and with most of them these launches, and products
+// planned on the device, cost more than the rows are worth.  us on all rows / on the kept ones, rank 8, frozen base unless stated:
+//   8B shape (4096, 14336)     0.25 of the rows kept   0.6           0.75          0.9
+//     260 tokens                382 / 315              382 / 350     384 / 359     385 / 369
+//     520                       492 / 380              498 / 450     504 / 476     506 / 494
+//     1200                      765 / 560              816 / 755     826 / 782     831 / 1006
+//     1490                      918 / 628              938 / 833     948 / 1054    959 / 1096 (all kept 951 / 1122)
+//     3000                      1455 / 909             1602 / 1355   1637 / 1498   1648 / 1717
+//     8000                      3336 / 1867            3664 / 3077   3714 / 3509   3756 / 3842
+//   hidden 2048, ffn 8192, 1000 346 / 306              353 / 349     361 / 360     358 / 393
+//     3000                      703 / 531              746 / 675     744 / 815     751 / 841
+//   5120, 17920, 1000           888 / 636              910 / 885     921 / 927     929 / 1196
+//     1500                      1218 / 807             1272 / 1301   1297 / 1409   1313 / 1515
+//   70B shape (8192, 28672) 300 843 / 628              851 / 740     860 / 760     869 / 946
+//     2000                      2750 / 1431            3016 / 2583   3087 / 2870   3111 / 3257
+// So up to two thirds kept, the masks that leave out a prompt or more, gain 1.1 to 2 times, and masks of nearly everything lose 2 to 22 %, most
+// where the kept rows by 4096 or 5120 columns are 9 to 15 bands of 128, whose tiles leave compute units idle and are not cut.  Below the
+// line (8B shape 130 tokens, all gradients 455 / 468 at a quarter, 200 489 / 494; hidden 2048 390 tokens 322 / 334, 520 362 / 363) there is
+// nothing to gain with few kept rows either.
+inline bool adapters_on_kept_rows(int T, int H, int F) { return T > 128 && (double)T * H * F >= 15e9; }
 // Operand preparation: job i writes dst [rows_out, cols] = src [r, cols] (or, transpose, src [cols, r]
 // transposed) followed by zero rows; src null: all zeros.
 struct LoraPrepJob {

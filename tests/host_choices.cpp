@@ -72,10 +72,26 @@ int main() {
             int T, H, F, QD;
             std::cin >> T >> H >> F >> QD;
             std::cout << kept_rows_fit(T, H, F, QD) << "\n";
-        } else if (what == "attention") {  // head size, query and key/value heads, ffn, number of lengths, lengths: the backward in bf16:
-            // longest sequence that the row kernels take, parts of a key block, whether both gradients run as one launch
-            int D, Hq, Hkv, F, n;
-            std::cin >> D >> Hq >> Hkv >> F >> n;
+        } else if (what == "adapters_pay") {  // T hidden ffn: with adapters, too
+            int T, H, F;
+            std::cin >> T >> H >> F;
+            std::cout << adapters_on_kept_rows(T, H, F) << "\n";
+        } else if (what == "rows") {  // rows N K swiglu, of several layers: data gradient with the row count on the device: its kernel
+            // (0: 256x256, 1: 128x256, 2: 64x64, 3: 128x128) and the parts of its cut tiles
+            int M, N, K, swiglu, several;
+            std::cin >> M >> N >> K >> swiglu >> several;
+            MfmaGemmParams p{};
+            p.n_seg = 1; p.N = N; p.K[0] = K; p.a_kmajor = 1; p.plan_cu = 256;
+            p.epilogue = swiglu ? kEpiSwigluBwd : kEpiNone;
+            p.narrow = several;
+            p.plan_ws = several ? 0 : (long long)kGemmSplitWsBytes;
+            PairPlan plan;
+            const RowsKernel kernel = device_plan(p, M, plan);
+            std::cout << (int)kernel << " " << (kernel == kRowsPair ? plan.parts : 1) << "\n";
+        } else if (what == "attention") {  // head size, query and key/value heads, ffn, stack of several layers, number of lengths, lengths:
+            // the backward in bf16: longest sequence that the row kernels take, parts of a key block, both gradients as one launch
+            int D, Hq, Hkv, F, several, n;
+            std::cin >> D >> Hq >> Hkv >> F >> several >> n;
             std::vector<int> cu(n + 1, 0);
             for (int i = 0; i < n; ++i) {
                 std::cin >> cu[i + 1];
@@ -86,6 +102,7 @@ int main() {
             a.cu_seqlens_host = cu.data();
             a.scratch = kSome;
             a.scratch_bytes = (size_t)a.T * 2 * F * 2;
+            a.keep_parts = several;
             if (D == 64 && rows_up_to(D, Hq, kRowsPerCu, 0, n, cu.data(), nullptr, &a.rows) != ALCH_OK) return 1;
             AttnMfmaParams p{};
             p.n_blocks = up_div(longest_sequence(cu.data(), 0, n), 128);

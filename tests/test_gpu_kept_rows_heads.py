@@ -9,8 +9,12 @@ from test_gpu_stack import _check_head, _head_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("kept", [1, 127, 128, 129, 300, 698])
-@pytest.mark.parametrize("hidden,V", [(256, 20032), (1088, 4160)])
+KEPT = [1, 127, 128, 129, 300, 698]
+SIZES = [(256, 20032), (1088, 4160)]
+
+
+@pytest.mark.parametrize("kept", KEPT)
+@pytest.mark.parametrize("hidden,V", SIZES)
 def test_kept_counts(monkeypatch, hidden, V, kept):
     monkeypatch.setitem(synth.SHAPES, "head", (hidden, 4, 2, 64, 512, 1e-5, 10000.0))
     shp, cu, Xf, gf, Wlm, labels = _head_case("head", V, [300, 1, 400], 41, wstd=0.05)

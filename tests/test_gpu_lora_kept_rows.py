@@ -13,9 +13,12 @@ from test_gpu_lora import REC, make_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,rank,hidden,ffn,frozen,accumulate", [(1000, 8, 2048, 8192, True, False), (4000, 24, 1088, 3904, False, True),
-                                                                 (5500, 8, 1024, 2816, True, True),  # blocks of 256 rows
-                                                                 (700, 8, 512, 1024, False, False)])  # all rows: too few to gain
+CASES = [(1000, 8, 2048, 8192, True, False), (4000, 24, 1088, 3904, False, True), (5500, 8, 1024, 2816, True, True),  # blocks of 256 rows
+         (700, 8, 512, 1024, False, False)]
+ALL_ROWS = [700]  # too few to gain
+
+
+@pytest.mark.parametrize("T,rank,hidden,ffn,frozen,accumulate", CASES)
 def test_kept_counts(monkeypatch, T, rank, hidden, ffn, frozen, accumulate):
     import paper_2503_01066_amd as A
     monkeypatch.setitem(synth.SHAPES, "kept", (hidden, 4, 2, 64, ffn, 1e-5, 10000.0))

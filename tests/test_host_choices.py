@@ -85,7 +85,7 @@ def test_pairs_of_batches_differ_in_the_pass_and_not_in_the_parts_of_t2(ask):
 def test_short_sequences_lie_beside_cut_key_blocks(ask):
     from test_gpu_attention_short import CUT
     for heads, lens in CUT:
-        (up_to, parts, both), = ask(("attention", 64, heads, 1, 1024, len(lens), *lens))
+        (up_to, parts, both), = ask(("attention", 64, heads, 1, 1024, False, len(lens), *lens))
         assert up_to == 8 and parts > 1 and not both, (heads, lens)
 
 
@@ -97,3 +97,58 @@ def test_kept_rows_are_products_that_the_matrix_core_kernels_take(ask):
                    ("supported", 2 * F, H, T, False, False, True), ("supported", H, F, T, False, False, True), ("supported", H, QD, T, False, False, True))
         wide = 2 * F <= 1 << 21 and T * 2 * F * 2 < 1 << 31  # ([dG | dU] as the left operand of dH2)
         assert ask(("kept_rows", T, H, F, QD)) == [(all(d == (1,) for d in data) and wide,)], (T, H, F, QD, data)
+
+
+BIG, PAIR, NARROW64, NARROW128 = range(4)
+
+
+def _data_gradients(hidden, ffn, qd, V, rows, several):
+    """dHf, dAct, dH2, dO of so many kept rows."""
+    return [("rows", rows, n, k, swiglu, several) for n, k, swiglu in ((hidden, V, False), (ffn, hidden, True), (hidden, 2 * ffn, False), (qd, hidden, False))]
+
+
+def test_few_kept_rows_of_several_layers_run_in_narrow_tiles(ask):
+    from test_gpu_narrow_rows import CASES, QD
+    seen = set()
+    for hidden, ffn, V, T, kept, wstd in CASES:
+        kernels = [k for k, _ in ask(*_data_gradients(hidden, ffn, QD, V, kept, True))]
+        assert set(kernels) <= {NARROW64, NARROW128}, (hidden, ffn, kept, kernels)
+        seen |= set(enumerate(kernels))
+    assert seen == {(product, k) for product in range(4) for k in (NARROW64, NARROW128)} - {(3, NARROW128)}  # (dO: 256 columns)
+
+
+def test_rows_compared_by_their_bits_run_on_different_kernels(ask):
+    from test_gpu_narrow_rows import BITS, BITS_SHAPE, BITS_V, QD
+    hidden, ffn = BITS_SHAPE[0], BITS_SHAPE[4]
+    seen = set()
+    for few, many in BITS:
+        a, b = [[k for k, _ in ask(*_data_gradients(hidden, ffn, QD, BITS_V, rows, True))[:3]] for rows in (few, many)]
+        assert set(a) <= {NARROW64, NARROW128} | ({PAIR, BIG} if few > 1024 else set()) and set(b) <= {BIG, PAIR}, (few, many, a, b)
+        assert a[0] in (NARROW64, NARROW128)
+        seen |= set(enumerate(a))
+    assert {(product, k) for product in range(3) for k in (NARROW64, NARROW128)} <= seen
+
+
+def test_head_gradients_of_few_kept_rows_are_cut(ask):
+    from test_gpu_kept_rows_heads import KEPT, SIZES
+    for hidden, V in SIZES:
+        assert all(kernel == PAIR and parts > 1 for kernel, parts in ask(*[("rows", kept, hidden, V, False, False) for kept in KEPT])), (hidden, V)
+
+
+def test_short_batches_run_both_attention_gradients_as_one(ask):
+    from test_gpu_attention_both import APART, BITS, BITS_FFN, FFN, HEADS, LENS, OTHERS, WIDE_FFN, WIDE_LENS
+    asked = lambda h, lens, ffn, several: ("attention", h[2], h[0], h[1], ffn, several, len(lens), *lens)
+    for h in HEADS:
+        for lens, (_, parts, both) in zip(LENS, ask(*[asked(h, lens, FFN, False) for lens in LENS])):
+            assert both == ((h, lens) not in APART) and (parts > 1) == (h == (32, 1, 64)), (h, lens)
+    for h in HEADS[:2]:
+        assert all(both and parts > 1 for _, parts, both in ask(*[asked(h, lens, WIDE_FFN, False) for lens in WIDE_LENS])), h
+    assert ask(*[asked(h, lens, BITS_FFN, True) for h, lens in BITS]) == [(0, 1, 1)] * len(BITS)
+    assert ask(*[asked(h, lens + OTHERS, BITS_FFN, True) for h, lens in BITS]) == [(0, 1, 0)] * len(BITS)
+
+
+def test_masked_adapter_layers_run_on_their_kept_rows(ask):
+    from test_gpu_lora_kept_rows import ALL_ROWS, CASES
+    for T, rank, hidden, ffn, frozen, accumulate in CASES:
+        on_kept_rows = all(a == (1,) for a in ask(("one_pass", T, hidden, ffn, rank), ("adapters_pay", T, hidden, ffn), ("kept_rows", T, hidden, ffn, 256)))
+        assert on_kept_rows == (T not in ALL_ROWS), T
