@@ -988,9 +988,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq_mfma(AttnMfmaParams p) {
 
 // ---------------------------------------------------------------------------------------------
 // Short batches: both gradients in one launch, behind one that forms delta and LSE * log2(e).  A work-group of either is a chain of
-// latencies of 20 to 35 us, and where all of both find a compute unit the second need not wait for the first: one
-// sequence of 201 tokens, 32/8 heads of 128 57 -> 32 us, 487 tokens 71 -> 45 (dQ, dK/dV and the sums of its parts, 5 of them delta).
-// Layer backward of the 8B shape 201 tokens 423 -> 401 us, 487 619 -> 595; heads of 64 (hidden 2048) 260 tokens 236 -> 210.
+// latencies of 12 to 35 us, and where all of both find a compute unit the second need not wait for the first.  All launches of it, with
+// delta (5 us) and the sums of cut key blocks (6 to 10): one sequence of 201 tokens, 32/8 heads of 128 57 -> 32 us, 487 tokens 68 -> 49; heads of 64
+// 260 tokens 46 -> 28, 100 tokens 39 -> 23.  Layer backward of the 8B shape 201 tokens 425 -> 395 us, 487 636 -> 614; hidden 2048 260 tokens
+// 230 -> 209, 100 181 -> 162.
 template <int kD>
 __global__ __launch_bounds__(256) void k_both_gradients_mfma(AttnMfmaParams p, int n_dkv) {
     __shared__ __attribute__((aligned(1024))) char smem[4 * AttnTile<kD>::kStageBytes];
@@ -1260,7 +1261,9 @@ inline int plan_dkv_parts(const AttnArgs& a, AttnMfmaParams& p, int& longest) {
 }
 
 // Whether both gradients run as one launch (k_both_gradients_mfma): where every work-group of both finds a compute unit, and the
-// launch and those behind it come out shorter than one behind the other.  Key blocks are cut as finely as the units that are left
+// launch and those behind it come out shorter than one behind the other.  The gain has run out where the units do: layers, 70B shape 320 tokens
+// 1524 -> 1504 us, 384 (the last) 1607 -> 1593, 5120/17920 512 880 -> 858, 640 (the last) 1026 -> 1028, 8B shape 640 706 -> 695, 768 (the last) 799 ->
+// 795, hidden 2048 640 322 -> 308, 768 (the last) 350 -> 352.  Key blocks are cut as finely as the units that are left
 // allow, into parts of two tiles at least, if five tiles or more come off the longest: 10 us for the 9 of the sums.  (Parts of four, if eight
 // come off -> so, layers, us: heads of 64, 100 tokens 169 -> 159, 3 sequences of 100 216 -> 210; 8B shape 128 tokens 332 -> 328, 150 362 -> 354,
 // 2 sequences of 125 405 -> 399; 201 and 256 tokens as before.)

@@ -679,7 +679,8 @@ static void launch_big(const MfmaGemmParams& p, int grid, hipStream_t stream) {
 // units without work and the others with all of a long contraction: the gradient of H2 of 175 kept rows (4096 columns, K 28672)
 // was 474 us on 16 busy compute units.  Layers of 4096/14336 with a quarter of the rows kept: 700 tokens 1022 -> 509 us, 1500 tokens
 // 1210 -> 748, 5003 tokens and a tenth of them 1825 -> 1292; where the 256x256 tiles stay (hidden 8192, 8192 tokens) 8854 and 8889: the
-// launches that leave are 28 us of a profile.
+// launches that leave are 28 us of a profile.  (In stacks of several layers the narrow tiles are a third one, 5 us for each of four products where
+// the rows are too many for them: two layers, 0.6 of 4000 tokens 7461 -> 7488 us, 0.25 of 8000 9782 -> 9797.)
 static int launch_device_rows(MfmaProduct& m, hipStream_t stream) {
     MfmaGemmParams& p = m.p;
     int pair_most = 0, cut_most = 0, narrow_most = 0;

@@ -245,7 +245,8 @@ __host__ __device__ inline RowsKernel device_plan(const MfmaGemmParams& p, int M
                       pair_is_better(Mv, p.N, K, p.a_kmajor != 0, p.b_kmajor != 0, p.epilogue == kEpiSwigluBwd, p.plan_cu, 1, plan);
     // The smallest tile of which no compute unit has two: where that is one of 64x64 or 128x128 their contraction is as long as that of a
     // 128x256 tile, and a step of 64 k takes 341 and 507 ns of 160 and 680 rows by 4096 against 770 (K 128256; a second round of the small
-    // ones 290 more).  Past one round of 128x128 the wide tile is the better one: 1244 rows, K 32000 388 against 512 us.
+    // ones 290 more).  Past one round of 128x128 the wide tile is the better one: 1244 rows, K 32000 388 against 512 us.  The same line for
+    // dAct, whose columns leave the narrow tiles fewer rows: 14336 columns, K 4096 60 rows 80 -> 46 us, 250 86 -> 63; 28672, K 8192 125 rows 183 -> 150.
     if (p.narrow) {
         if (narrow_grid(p, Mv, kRowsNarrow64) <= p.plan_cu) return kRowsNarrow64;
         if (narrow_grid(p, Mv, kRowsNarrow128) <= p.plan_cu) return kRowsNarrow128;

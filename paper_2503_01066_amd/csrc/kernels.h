@@ -234,9 +234,9 @@ inline bool kept_rows_fit(int T, int H, int F, int QD) {
 //     1500                      1218 / 807             1272 / 1301   1297 / 1409   1313 / 1515
 //   70B shape (8192, 28672) 300 843 / 628              851 / 740     860 / 760     869 / 946
 //     2000                      2750 / 1431            3016 / 2583   3087 / 2870   3111 / 3257
-// So up to two thirds kept, the masks that leave out a prompt or more, gain 1.1 to 2 times, and masks of nearly everything lose 2 to 22 %, most
-// where the kept rows by 4096 or 5120 columns are 9 to 15 bands of 128, whose tiles leave compute units idle and are not cut.  Below the
-// line (8B shape 130 tokens, all gradients 455 / 468 at a quarter, 200 489 / 494; hidden 2048 390 tokens 322 / 334, 520 362 / 363) there is
+// Over 32 sizes a quarter of the rows comes out 1.13 to 2.0 times as fast, 0.6 0.98 to 1.44, 0.75 0.90 to 1.17, 0.9 0.78 to 1.14: this is for masks
+// that leave out a third and more.  It loses most where the gradient of H2 has tiles of 128x256 for more than half of the compute units, which a
+// plan on the device leaves whole.  Below the line (8B shape 130 tokens, all gradients 455 / 468 at a quarter, 200 489 / 494; hidden 2048 390 tokens 322 / 334, 520 362 / 363) there is
 // nothing to gain with few kept rows either.
 inline bool adapters_on_kept_rows(int T, int H, int F) { return T > 128 && (double)T * H * F >= 15e9; }
 // Operand preparation: job i writes dst [rows_out, cols] = src [r, cols] (or, transpose, src [cols, r]
